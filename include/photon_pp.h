@@ -254,12 +254,18 @@ int pp_plan_stats(pp_plan* plan, pp_stats* out);
 int pp_plan_set_timing(pp_plan* plan, int on);
 
 /* Launch shape of the FP32 PP kernel.
- *  chunk        source-list positions per work item (multiple of 64)
+ *  chunk        source-list positions per work item (multiple of 64); with
+ *               persistent = 1 and waves_per_block = 1 an upper bound: a box
+ *               whose target blocks list fewer than 2^27 sources in all is
+ *               cut into chunks of about listed^(2/3) / 93 positions
+ *               (at least 256, or 128 below 2^17 listed)
  *  persistent   0: one workgroup per work item (when the previous call's
  *               items give at most two waves per SIMD, a build of the
  *               kernel for two resident waves; same results); 1: a fixed
  *               grid of waves_per_cu waves per CU pulling items from
- *               per-XCD queues with stealing
+ *               per-XCD queues with stealing (launched as one workgroup per
+ *               item when the last call's items were few, or shorter than
+ *               1000 positions per wave on average; same results)
  *  waves_per_cu used by the persistent form, 1..64
  *  use_graph    1: capture the persistent kernel and the reduction in a
  *               hipGraph once and replay it (needs persistent = 1)
@@ -281,7 +287,7 @@ int pp_plan_set_timing(pp_plan* plan, int on);
  *               wave sweeps every staged source; sources are pruned against
  *               four boxes around the block's runs of 16 targets first.
  * The chunk grows by itself when the lists are long enough that more than
- * 2^21 work items would be needed.  Results are reproducible for a given
+ * 2^21 work items would be needed at it.  Results are reproducible for a given
  * tuning; a different chunk or waves_per_block changes the summation order.
  * Defaults: plans {2048, 1, 20, 0, 0, 1}; batch plans {2048, 1, 20, 1, 0, 1}. */
 typedef struct pp_tuning {

@@ -189,6 +189,8 @@ struct Batch {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;   // around the PP kernel (or its graph)
     hipEvent_t ev2 = nullptr, ev3 = nullptr;   // around the whole PP stage
     DevBuf partial, pcount, counters, queues;
+    DevBuf staged, staged_mono;    // sources swept per item and wave, monopoles per block (direct launches)
+    int staged_waves = 1;
     // captured PP graph (persistent kernel + reduction)
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
@@ -199,6 +201,7 @@ struct Batch {
     // the row stride of the SoA particle arrays, a kernel argument passed by
     // value (the chunk and the counts are read on the device)
     int64_t graph_n = -1;
+    int64_t graph_grid = 0;               // its workgroups when it holds the per-item launch (else 0)
 
     ~Batch() {
         if (gexec) (void)hipGraphExecDestroy(gexec);
@@ -318,7 +321,9 @@ struct Batch {
             PP_TRY(stage_node_moments(bd, N, w, s));
             mc.mc = w.tree_mc.as<double4>();
         }
-        PP_TRY(stage_lists(bd, poff, tune.chunk, w, s, mc, active));
+        // the persistent form with one wave per block treats the chunk as an
+        // upper bound: small boxes are cut finer
+        PP_TRY(stage_lists(bd, poff, tune.chunk, tune.persistent && tune.waves_per_block == 1, w, s, mc, active));
         lists_mono = mono;
         lists_active = active != nullptr;
         return PP_OK;
@@ -400,18 +405,20 @@ struct Batch {
     }
 
     int run_pp_direct(float* acc, hipStream_t s) {
-        unsigned long long* ctr = counters.as<unsigned long long>();
-        PP_TRY(launch_reset_queues(tune.persistent ? queues.as<unsigned>() : nullptr, s, ctr));
+        // swept sources per item and wave, for the statistics
+        PP_TRY(staged.reserve(sizeof(int32_t) * (w.cap_item + 1) * tune.waves_per_block));
+        if (lists_mono) PP_TRY(staged_mono.reserve(sizeof(int32_t) * (w.cap_block + 1)));
         if (timing) PP_HIP(hipEventRecord(ev0, s));
         PP_TRY(launch_pp_f32(bd, w, tune.waves_per_block, tune.persistent ? Mode::kPersistent : Mode::kGrid,
-                             tune.waves_per_cu, tune.variant, partial.as<float>(), acc, ctr,
+                             tune.waves_per_cu, tune.variant, partial.as<float>(), acc, staged.as<int32_t>(),
                              queues.as<unsigned>(), s));
         if (timing) {
             PP_HIP(hipEventRecord(ev1, s));
             timed = true;
         }
         PP_TRY(launch_reduce_f32(bd, w, partial.as<float>(), acc, s));
-        if (lists_mono) PP_TRY(launch_monopole(bd, w, acc, ctr + 2, s));
+        if (lists_mono) PP_TRY(launch_monopole(bd, w, acc, staged_mono.as<int32_t>(), s));
+        staged_waves = tune.waves_per_block;
         evaluated_valid = true;
         return PP_OK;
     }
@@ -430,10 +437,8 @@ struct Batch {
             graph = nullptr;
         }
         PP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-        int rc = launch_reset_queues(queues.as<unsigned>(), s);
-        if (rc == PP_OK)
-            rc = launch_pp_f32(bd, w, tune.waves_per_block, Mode::kPersistent, tune.waves_per_cu, tune.variant,
-                               partial.as<float>(), acc, nullptr, queues.as<unsigned>(), s);
+        int rc = launch_pp_f32(bd, w, tune.waves_per_block, Mode::kPersistent, tune.waves_per_cu, tune.variant,
+                           partial.as<float>(), acc, nullptr, queues.as<unsigned>(), s);
         if (rc == PP_OK) rc = launch_reduce_f32(bd, w, partial.as<float>(), acc, s);
         hipError_t e = hipStreamEndCapture(s, &graph);
         if (rc != PP_OK) return rc;
@@ -444,6 +449,7 @@ struct Batch {
         graph_active = w.active;
         graph_n = w.pos_n;
         graph_variant = graph_key();
+        PP_TRY(f32_grid_groups(w, tune.waves_per_block, Mode::kPersistent, &graph_grid));
         return PP_OK;
     }
 
@@ -464,7 +470,9 @@ struct Batch {
 
     int run_f32_stage(float* acc, hipStream_t s) {
         if (tune.persistent && tune.use_graph) {
-            if (!gexec || graph_gen != alloc_generation() || graph_acc != acc ||
+            int64_t grid = 0;
+            PP_TRY(f32_grid_groups(w, tune.waves_per_block, Mode::kPersistent, &grid));
+            if (!gexec || graph_grid != grid || graph_gen != alloc_generation() || graph_acc != acc ||
                 graph_active != w.active || graph_variant != graph_key() || graph_n != w.pos_n)
                 PP_TRY(capture(acc));
             if (timing) PP_HIP(hipEventRecord(ev0, s));
@@ -497,6 +505,9 @@ struct Batch {
         st.list_reuses = list_reuses;
         if (evaluated_valid) {
             unsigned long long h[3] = {0, 0, 0};
+            PP_TRY(launch_sum_staged(bd, w, staged_waves, staged.as<int32_t>(),
+                                     lists_mono ? staged_mono.as<int32_t>() : nullptr,
+                                     counters.as<unsigned long long>(), (hipStream_t)0));
             PP_HIP(hipMemcpy(h, counters.p, sizeof(h), hipMemcpyDeviceToHost));
             st.evaluated = (int64_t)h[0];
             st.lane_pairs = (int64_t)h[1];

@@ -255,7 +255,8 @@ struct Work {
     DevBuf fent_a, fent_b, fcnt, foff, fmask;
     DevBuf lmask_e, rcnt_e, scnt_e, roff_e, soff_e, eoff;
     DevBuf roff, slen, rbeg, rpre, rcode;
-    DevBuf icount, ioff, iblock, is0;
+    DevBuf icount, ioff, iblock, is0, is1;
+    DevBuf box_chunk;  // int32 [nbox]: source-list positions per work item of each box
     DevBuf sizes;      // int64 [kSizeSlots], see SizeSlot
     DevBuf misc;       // counters and flags
 };
@@ -325,8 +326,9 @@ struct MonoCfg {
 // sized with the capacities in w (see lists_to_host).
 // active: optional device flags per input particle; target blocks without an
 // active target get no work items (their outputs are left alone).
-int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_req, Work& w,
-                hipStream_t s, const MonoCfg& mono = MonoCfg(), const uint8_t* active = nullptr);
+// adapt_chunk: small boxes get a smaller chunk than the requested one.
+int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_req, bool adapt_chunk,
+                Work& w, hipStream_t s, const MonoCfg& mono = MonoCfg(), const uint8_t* active = nullptr);
 // Work items of the current lists (after stage_lists, or on their own for a
 // call that reuses the lists): items per block for the given active flags,
 // their offsets, and the final counts.
@@ -353,9 +355,9 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved = nullptr);
 // Mass and mass-weighted position sums of every tree node (after stage_trees;
 // needs the FP32 masses in key order).
 int stage_node_moments(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
-// Adds the monopoles' forces to acc (input order), FP32 path.
-int launch_monopole(const BatchDev& bd, const Work& w, float* acc, unsigned long long* counter,
-                    hipStream_t s);
+// Adds the monopoles' forces to acc (input order), FP32 path; mcount (null:
+// not kept) gets the monopoles of each block.
+int launch_monopole(const BatchDev& bd, const Work& w, float* acc, int32_t* mcount, hipStream_t s);
 int build_canonical_pairs(const BatchDev& bd, const Work& w, int64_t W, int64_t T, DevBuf& row_cnt,
                           DevBuf& row_ptr, DevBuf& src, DevBuf& code, DevBuf& scan_ws,
                           int64_t* nentries, hipStream_t s);
@@ -365,10 +367,17 @@ enum class Mode { kGrid = 0, kPersistent = 1 };
 // variant bits: 1 = one Newton step after the hardware rsqrt, 2 = no Kahan
 // compensation, 4 = no FP64 block-origin subtraction (box-origin offsets)
 // Blocks with a single work item write acc directly; the reduction finishes
-// the others.
+// the others.  icount (null: not kept) gets the sources each wave of each
+// item swept, [cap_item][waves per block].
 int launch_pp_f32(const BatchDev& bd, const Work& w, int groups, Mode mode, int waves_per_cu,
-                  int variant, float* partial, float* acc, unsigned long long* counters,
-                  unsigned* queues, hipStream_t s);
+                  int variant, float* partial, float* acc, int32_t* icount, unsigned* queues,
+                  hipStream_t s);
+// What the last FP32 launch swept (see sum_staged_kernel), into out[0 .. 2].
+int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, const int32_t* icount,
+                      const int32_t* mcount, unsigned long long* out, hipStream_t s);
+// Workgroups of the one-workgroup-per-item launch that launch_pp_f32 would
+// make (0: the persistent one).
+int f32_grid_groups(const Work& w, int waves_per_block, Mode mode, int64_t* groups);
 int launch_reduce_f32(const BatchDev& bd, const Work& w, const float* partial, float* acc,
                       hipStream_t s);
 int launch_pp_f64(const BatchDev& bd, const Work& w, double* partial, hipStream_t s);
@@ -379,6 +388,5 @@ int launch_reduce_count(const BatchDev& bd, const Work& w, const int32_t* partia
                         unsigned long long* total, hipStream_t s);
 // Builds the interpolated split table (FP64 series, rounded to FP32).
 int launch_split_table(Work& w, hipStream_t s);
-int launch_reset_queues(unsigned* queues, hipStream_t s, unsigned long long* counters = nullptr);
 
 }  // namespace pp

@@ -33,6 +33,7 @@ namespace {
 struct ItemArgs {
     const int32_t* iblock;
     const int32_t* is0;
+    const int32_t* is1;
     const int64_t* sizes;      // the counts of the lists (SizeSlot), on the device
     const int32_t* bstart;
     const int32_t* bcount;
@@ -42,7 +43,6 @@ struct ItemArgs {
     const int32_t* rbeg;
     const int32_t* rpre;
     const uint8_t* rcode;
-    const int32_t* slen;
     const int64_t* ioff;
     const BoxDev* box;
     const int32_t* perm;       // key order -> input order
@@ -60,6 +60,7 @@ ItemArgs item_args(const BatchDev& bd, const Work& w) {
     ItemArgs ia;
     ia.iblock = w.iblock.as<int32_t>();
     ia.is0 = w.is0.as<int32_t>();
+    ia.is1 = w.is1.as<int32_t>();
     ia.sizes = w.sizes.as<int64_t>();
     ia.bstart = w.bstart.as<int32_t>();
     ia.bcount = w.bcount.as<int32_t>();
@@ -69,7 +70,6 @@ ItemArgs item_args(const BatchDev& bd, const Work& w) {
     ia.rbeg = w.rbeg.as<int32_t>();
     ia.rpre = w.rpre.as<int32_t>();
     ia.rcode = w.rcode.as<uint8_t>();
-    ia.slen = w.slen.as<int32_t>();
     ia.ioff = w.ioff.as<int64_t>();
     ia.box = bd.box;
     ia.perm = w.perm.as<int32_t>();
@@ -80,18 +80,24 @@ ItemArgs item_args(const BatchDev& bd, const Work& w) {
     return ia;
 }
 
-// Items are laid out so that the 8 XCDs (which take workgroups round-robin)
-// each see one contiguous stretch of items: neighbouring target blocks share
-// most of their sources, which then stay in that XCD's L2.  The grid is
-// sized for the item capacity, which may exceed the count: a workgroup past
-// its XCD's stretch gets -1 (mapping it into the next stretch would run
-// that item twice).
+// The item of a workgroup of the one-workgroup-per-item launches, or -1 for
+// one past the end.  The 8 XCDs take workgroups round-robin; each gets
+// stretches of kStretch consecutive items, every eighth one: neighbouring
+// target blocks share most of their sources, which then stay in that XCD's
+// L2, and dense regions are dealt out over all XCDs.  One long stretch per
+// XCD left the XCDs with the dense regions running alone at the end: 2.1 M
+// clustered particles took 6.63 ms where stretches of 16 to 256 take 6.02 to
+// 6.10 (a uniform box does not care: 2.93 to 2.96 ms).
+constexpr int64_t kStretch = 64;
+
 __device__ __forceinline__ int64_t xcd_item(int64_t bid, int64_t nitem) {
-    const int64_t per_xcd = (nitem + 7) / 8;
     const int64_t k = bid >> 3;
-    const int64_t item = (bid & 7) * per_xcd + k;
-    return k < per_xcd && item < nitem ? item : -1;
+    const int64_t item = ((k / kStretch) * 8 + (bid & 7)) * kStretch + k % kStretch;
+    return item < nitem ? item : -1;
 }
+
+// The workgroups such a launch needs for n items.
+int64_t xcd_groups(int64_t n) { return (n + 8 * kStretch - 1) / (8 * kStretch) * (8 * kStretch); }
 
 __device__ __forceinline__ int64_t find_range(const int32_t* __restrict__ rpre, int64_t lo,
                                               int64_t hi, int32_t p) {
@@ -260,8 +266,7 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
                                         const double* __restrict__ pos_s,
                                         const float* __restrict__ mass_s, int64_t N,
                                         float* __restrict__ partial,
-                                        unsigned long long& n_eval, unsigned long long& n_lane,
-                                        float4* tile_all,
+                                        int32_t* __restrict__ icount, float4* tile_all,
                                         const float4* __restrict__ tab, float4* qb_all,
                                         double* red, int* mark_all) {
     constexpr bool NEWTON = (VAR & 1) != 0;
@@ -273,14 +278,16 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
     float4* tile = tile_all + wv * 2 * kBlock;
     const int32_t b = ia.iblock[item];
     const int32_t s0 = ia.is0[item];
-    const int32_t S = ia.slen[b];
-    const int32_t chunk = (int32_t)ia.sizes[kChunk];
-    const int32_t s1 = s0 + chunk < S ? s0 + chunk : S;
+    const int32_t s1 = ia.is1[item];
     const int32_t nt = ia.bcount[b];
     const int xbox = ia.bboxid[b];
     const BoxDev& X = ia.box[xbox];
     const double L = X.L, cell = X.cell, inv_len = X.inv_len;
-    const PolyF32 P = X.poly;
+    PolyF32 P = X.poly;
+    // the pair loop's constants stay in VGPRs: with an SGPR operand an
+    // instruction issues at half the rate
+    asm("" : "+v"(P.eps2n));
+    asm("" : "+v"(P.cut2));
     // equal masses (the compensated form only): the mass joins the final scale
     const bool equal = KAHAN && ia.mass_flag[xbox] == 0;
     const float mu = equal ? mass_s[X.poff] : 1.f;
@@ -346,7 +353,7 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
     const int64_t r_lo = ia.roff[b], r_hi = ia.roff[b + 1] - 1;
     float ax = 0.f, ay = 0.f, az = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     int count = 0;                                   // staged sources (wave-uniform)
-    int64_t staged = 0;
+    int32_t staged = 0;
     const int32_t first = s0 + wv * kBlock;          // this wave's first window
     int64_t rcur = s1 > first ? find_range_wave(ia.rpre, r_lo, r_hi, first) : r_lo;
     int* mark = mark_all + wv * kBlock;
@@ -362,7 +369,8 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
         int64_t r;
         int32_t rb, rp;
         int code;
-        const int32_t end_cur = rcur < r_hi ? ia.rpre[rcur + 1] : S;
+        // the block's last range: every position of the item lies before its end
+        const int32_t end_cur = rcur < r_hi ? ia.rpre[rcur + 1] : s1;
         if (last < end_cur) {
             // the cursor's range holds the whole window: nothing to map
             r = rcur;
@@ -486,19 +494,23 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
         float tx = 0.f, ty = 0.f, tz = 0.f;
         if (KAHAN) {
             if (equal) {
+#pragma unroll 1
                 for (int q = 0; q < count; ++q) pair_f32_eq<NEWTON, TABLE>(tile[q], xi, yi, zi, tx, ty, tz, P.eps2n, tab);
             } else {
+#pragma unroll 1
                 for (int q = 0; q < count; ++q) pair_f32<NEWTON, TABLE>(tile[q], xi, yi, zi, P, tx, ty, tz, tab);
             }
             kahan_add(ax, cx, tx);
             kahan_add(ay, cy, ty);
             kahan_add(az, cz, tz);
         } else {
+#pragma unroll 1
             for (int q = 0; q < count; ++q) pair_f32<NEWTON, TABLE>(tile[q], xi, yi, zi, P, ax, ay, az, tab);
         }
     }
-    n_eval += (unsigned long long)staged * (unsigned long long)nt;
-    n_lane += (unsigned long long)staged * (unsigned long long)kBlock;
+    // the sources this wave swept, for the statistics (summed when they are
+    // asked for: an atomic per item on one counter costs 12 ns each, in turn)
+    if (icount && lane == 0) icount[item * K + wv] = staged;
     // the compensated sums, then (K > 1) the waves' sums in wave order
     double sx = (double)ax - (double)cx, sy = (double)ay - (double)cy, sz = (double)az - (double)cz;
     if (K > 1) {
@@ -552,14 +564,13 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
                                                       const TreeView* __restrict__ tvs,
                                                       const double4* __restrict__ mc,
                                                       const double* __restrict__ pos_s, int64_t N,
-                                                      int64_t nblock,
-                                                      unsigned long long* __restrict__ counter) {
+                                                      int32_t* __restrict__ mcount) {
     __shared__ float4 tile[2 * kBlock];
     const int64_t b = blockIdx.x;
     if (ia.sizes[kSkip] || b >= ia.sizes[kNBlock]) return;
-    (void)nblock;
-    if (ia.ioff[b + 1] == ia.ioff[b]) return;        // a block without active targets
     const int lane = threadIdx.x;
+    if (mcount && lane == 0) mcount[b] = 0;
+    if (ia.ioff[b + 1] == ia.ioff[b]) return;        // a block without active targets
     const int xbox = ia.bboxid[b];
     const BoxDev& X = ia.box[xbox];
     const TreeView& tv = tvs[xbox];
@@ -579,7 +590,7 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
     }
     float ax = 0.f, ay = 0.f, az = 0.f, cx = 0.f, cy = 0.f, cz = 0.f;
     int count = 0;
-    int64_t taken = 0;
+    int32_t taken = 0;
     // stage this lane's node (level, index) under shift code sc if `on`
     auto stage = [&](bool on, int lev, int64_t node, int sc) {
         bool keep = false;
@@ -654,7 +665,7 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
         ia.acc[N + i] += (float)(((double)ay - (double)cy) * X.scale);
         ia.acc[2 * N + i] += (float)(((double)az - (double)cz) * X.scale);
     }
-    if (counter && lane == 0) atomicAdd(counter, (unsigned long long)taken * (unsigned long long)nt);
+    if (mcount && lane == 0) mcount[b] = taken;
 }
 
 // One workgroup per item.
@@ -666,7 +677,7 @@ template <int VAR, int K>
 __global__ void __launch_bounds__(64 * K, K > 1 ? 5 : 6) pp_f32_kernel(ItemArgs ia, const double* __restrict__ pos_s,
                                                         const float* __restrict__ mass_s, int64_t N,
                                                         float* __restrict__ partial,
-                                                        unsigned long long* __restrict__ counters) {
+                                                        int32_t* __restrict__ icount) {
     __shared__ float4 tile[K * 2 * kBlock];
     __shared__ float4 qb[K * 8];
     __shared__ double red[K > 1 ? K * 3 * kBlock : 1];
@@ -680,12 +691,7 @@ __global__ void __launch_bounds__(64 * K, K > 1 ? 5 : 6) pp_f32_kernel(ItemArgs 
         for (int k = threadIdx.x; k < kTabN; k += 64 * K) tab[k] = ia.split_tab[k];
         __syncthreads();
     }
-    unsigned long long n_eval = 0, n_lane = 0;
-    pp_item<VAR, K>(ia, item, pos_s, mass_s, N, partial, n_eval, n_lane, tile, tab, qb, red, mark);
-    if (counters && (threadIdx.x & (kBlock - 1)) == 0) {
-        atomicAdd(counters, n_eval);
-        atomicAdd(counters + 1, n_lane);
-    }
+    pp_item<VAR, K>(ia, item, pos_s, mass_s, N, partial, icount, tile, tab, qb, red, mark);
 }
 
 // The same for launches of at most two waves per SIMD (short item lists,
@@ -697,7 +703,7 @@ template <int VAR, int K>
 __global__ void __launch_bounds__(64 * K, 2) pp_f32_kernel_few(ItemArgs ia, const double* __restrict__ pos_s,
                                                                const float* __restrict__ mass_s, int64_t N,
                                                                float* __restrict__ partial,
-                                                               unsigned long long* __restrict__ counters) {
+                                                               int32_t* __restrict__ icount) {
     __shared__ float4 tile[K * 2 * kBlock];
     __shared__ float4 qb[K * 8];
     __shared__ double red[K > 1 ? K * 3 * kBlock : 1];
@@ -711,12 +717,7 @@ __global__ void __launch_bounds__(64 * K, 2) pp_f32_kernel_few(ItemArgs ia, cons
         for (int k = threadIdx.x; k < kTabN; k += 64 * K) tab[k] = ia.split_tab[k];
         __syncthreads();
     }
-    unsigned long long n_eval = 0, n_lane = 0;
-    pp_item<VAR, K>(ia, item, pos_s, mass_s, N, partial, n_eval, n_lane, tile, tab, qb, red, mark);
-    if (counters && (threadIdx.x & (kBlock - 1)) == 0) {
-        atomicAdd(counters, n_eval);
-        atomicAdd(counters + 1, n_lane);
-    }
+    pp_item<VAR, K>(ia, item, pos_s, mass_s, N, partial, icount, tile, tab, qb, red, mark);
 }
 
 // Persistent form: a fixed grid of waves pulls items from 8 queues (one
@@ -724,12 +725,17 @@ __global__ void __launch_bounds__(64 * K, 2) pp_f32_kernel_few(ItemArgs ia, cons
 // queue of its own XCD, then steals from the others.  Every wave leaves
 // once all queues are empty.  The item count is read from device memory,
 // so the launch can be replayed from a graph while the lists change.
+//
+// Pops on one counter take about 12 ns each, in turn.  5120 waves that each
+// popped all 8 queues once to find them empty spent about 60 us at the end of
+// every launch, so a wave whose own queue ran dry reads the 8 counters with
+// one load and pops only from queues that still hold items.
 template <int VAR, int K>
 __global__ void __launch_bounds__(64 * K, K > 1 ? 5 : 6) pp_f32_persistent(ItemArgs ia,
                                                             const double* __restrict__ pos_s,
                                                             const float* __restrict__ mass_s, int64_t N,
                                                             float* __restrict__ partial,
-                                                            unsigned long long* __restrict__ counters,
+                                                            int32_t* __restrict__ icount,
                                                             unsigned* __restrict__ queues) {
     __shared__ float4 tile[K * 2 * kBlock];
     __shared__ float4 qb[K * 8];
@@ -745,14 +751,13 @@ __global__ void __launch_bounds__(64 * K, K > 1 ? 5 : 6) pp_f32_persistent(ItemA
     const int64_t nitem = ia.sizes[kNItem];
     const int64_t per = (nitem + 7) / 8;
     const int my = blockIdx.x & 7;
-    // the kernel counters, summed over this wave's items and added once
-    unsigned long long n_eval = 0, n_lane = 0;
+    unsigned todo = 0xffu;               // bit v: queue (my + v) & 7 may hold items
     for (int v = 0; v < 8; ++v) {
+        if (!(todo >> v & 1u)) continue;
         const int q = (my + v) & 7;
         const int64_t qbeg = q * per;
         const int64_t qend = qbeg + per < nitem ? qbeg + per : nitem;
-        if (qbeg >= qend) continue;
-        const unsigned qlen = (unsigned)(qend - qbeg);
+        const unsigned qlen = qend > qbeg ? (unsigned)(qend - qbeg) : 0u;
         for (;;) {
             unsigned i = 0;
             if (K == 1) {
@@ -766,20 +771,63 @@ __global__ void __launch_bounds__(64 * K, K > 1 ? 5 : 6) pp_f32_persistent(ItemA
                 i = next_item;
             }
             if (i >= qlen) break;
-            pp_item<VAR, K>(ia, qbeg + (int64_t)i, pos_s, mass_s, N, partial, n_eval, n_lane, tile, tab, qb,
-                            red, mark);
+            pp_item<VAR, K>(ia, qbeg + (int64_t)i, pos_s, mass_s, N, partial, icount, tile, tab, qb, red, mark);
         }
-    }
-    if (counters && (threadIdx.x & (kBlock - 1)) == 0 && n_lane) {
-        atomicAdd(counters, n_eval);
-        atomicAdd(counters + 1, n_lane);
+        if (v == 0) {
+            // the other queues that still hold items (read by every wave: the
+            // waves of a workgroup may differ, so the first one's word counts)
+            const int w = threadIdx.x & 7;
+            const int64_t left = nitem - ((my + w) & 7) * per;
+            const unsigned head = __hip_atomic_load(&queues[((my + w) & 7) * kQueueStride], __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+            todo = (unsigned)__ballot((int64_t)head < (left < per ? left : per)) & 0xffu;
+            if (K > 1) {
+                __syncthreads();
+                if (threadIdx.x == 0) next_item = todo;
+                __syncthreads();
+                todo = next_item;
+            }
+        }
     }
 }
 
-// Clears the work queues and (when given) the three kernel counters.
-__global__ void reset_queues_kernel(unsigned* q, unsigned long long* ctr) {
-    if (q && threadIdx.x < 8) q[threadIdx.x * kQueueStride] = 0u;
-    if (ctr && threadIdx.x < 3) ctr[threadIdx.x] = 0ull;
+// Clears the work queues.
+__global__ void reset_queues_kernel(unsigned* q) {
+    if (threadIdx.x < 8) q[threadIdx.x * kQueueStride] = 0u;
+}
+
+// Sums of the items' staged sources: out[0] times the block's targets,
+// out[1] times the lanes; with mcount, out[2]: the blocks' monopoles times
+// their targets.  (out is cleared by the caller.)
+__global__ void __launch_bounds__(256) sum_staged_kernel(ItemArgs ia, const int32_t* __restrict__ icount,
+                                                         int K, const int32_t* __restrict__ mcount,
+                                                         unsigned long long* __restrict__ out) {
+    unsigned long long ev = 0, ln = 0, mo = 0;
+    if (mcount)
+        for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < ia.sizes[kNBlock];
+             b += (int64_t)gridDim.x * blockDim.x)
+            mo += (unsigned long long)mcount[b] * (unsigned long long)ia.bcount[b];
+    for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < ia.sizes[kNItem];
+         it += (int64_t)gridDim.x * blockDim.x) {
+        unsigned long long c = 0;
+        for (int k = 0; k < K; ++k) c += (unsigned long long)icount[it * K + k];
+        ev += c * (unsigned long long)ia.bcount[ia.iblock[it]];
+        ln += c * (unsigned long long)kBlock;
+    }
+    for (int d = 32; d >= 1; d >>= 1) {
+        ev += __shfl_xor(ev, d);
+        ln += __shfl_xor(ln, d);
+        mo += __shfl_xor(mo, d);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(out, ev);
+        atomicAdd(out + 1, ln);
+        if (mcount) atomicAdd(out + 2, mo);
+    }
+}
+
+__global__ void zero_u64_kernel(unsigned long long* p, int n) {
+    if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
 }
 
 // One thread per (block, lane), grid-stride: sum the item partials of the
@@ -850,9 +898,7 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
     const int lane = threadIdx.x;
     const int32_t b = ia.iblock[item];
     const int32_t s0 = ia.is0[item];
-    const int32_t S = ia.slen[b];
-    const int32_t chunk = (int32_t)ia.sizes[kChunk];
-    const int32_t s1 = s0 + chunk < S ? s0 + chunk : S;
+    const int32_t s1 = ia.is1[item];
     const BoxDev& X = ia.box[ia.bboxid[b]];
     const double L = X.L, rs = X.rs, rcut = X.rcut, eps = X.eps, G = X.G;
     const bool active = lane < ia.bcount[b];
@@ -1018,46 +1064,70 @@ int launch_split_table(Work& w, hipStream_t s) {
     return PP_OK;
 }
 
-int launch_reset_queues(unsigned* queues, hipStream_t s, unsigned long long* counters) {
-    hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, queues, counters);
-    PP_HIP(hipGetLastError());
+// CUs of the current device.
+static int cu_count(int* cus) {
+    int dev = 0;
+    *cus = 256;
+    PP_HIP(hipGetDevice(&dev));
+    PP_HIP(hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev));
+    return PP_OK;
+}
+
+// Workgroups of the persistent launch: waves_per_cu waves per CU in
+// workgroups of K waves.
+static int64_t persistent_groups(int cus, int waves_per_cu, int K) {
+    const int wpc = waves_per_cu > 0 ? waves_per_cu : 16;
+    return (int64_t)cus * ((wpc + K - 1) / K);
+}
+
+// The persistent form is launched as one workgroup per item when the last
+// call's items were short, or fit the chip in one go: the hardware's dispatch
+// then hands them out faster than the queues, whose pops take 12 ns each, in
+// turn.  300 k clustered particles (65 k items of 512 positions): 0.86 ms
+// against 1.01 queued; 1 M uniform ones in items of 256: 1.37 against 1.65 ms,
+// of 1024 (mean 916): 1.38 against 1.42.  Long items run as fast or faster
+// queued (1.2 M at 2048 positions, mean 1600: 1.94 against 1.99 ms; 16.8 M:
+// 342.6 against 344.6).  Both forms give the same results, so the last call's
+// mean is only a hint; before the first call the room for items stands in.
+constexpr int64_t kGridFew = 8192, kGridFirst = 65536;
+constexpr int64_t kGridLength = 1000;
+
+int f32_grid_groups(const Work& w, int waves_per_block, Mode mode, int64_t* groups) {
+    const int64_t room = w.cap_item * waves_per_block;
+    const bool grid = mode == Mode::kGrid || room <= kGridFew ||
+                      (w.nitem > 0 ? w.total_src / w.nitem < kGridLength * waves_per_block : room <= kGridFirst);
+    *groups = grid ? xcd_groups(w.cap_item) : 0;
     return PP_OK;
 }
 
 template <int VAR, int K>
 static int launch_pp_f32_var(const ItemArgs& ia, const Work& w, Mode mode, int waves_per_cu,
-                             float* partial, unsigned long long* counters, unsigned* queues,
-                             hipStream_t s) {
-    if (mode == Mode::kPersistent) {
-        int dev = 0, cus = 256;
-        PP_HIP(hipGetDevice(&dev));
-        PP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        // waves_per_cu waves per CU in workgroups of K waves
-        const int wpc = waves_per_cu > 0 ? waves_per_cu : 16;
-        const unsigned grid = (unsigned)(cus * ((wpc + K - 1) / K));
-        hipLaunchKernelGGL((pp_f32_persistent<VAR, K>), dim3(grid), dim3(kBlock * K), 0, s, ia,
-                           w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, counters,
-                           queues);
+                             float* partial, int32_t* icount, unsigned* queues, hipStream_t s) {
+    if (w.cap_item == 0) return PP_OK;
+    int cus = 256;
+    int64_t grid = 0;
+    PP_TRY(cu_count(&cus));
+    PP_TRY(f32_grid_groups(w, K, mode, &grid));
+    if (grid == 0) {
+        const int64_t groups = persistent_groups(cus, waves_per_cu, K);
+        hipLaunchKernelGGL(reset_queues_kernel, dim3(1), dim3(64), 0, s, queues);
+        hipLaunchKernelGGL((pp_f32_persistent<VAR, K>), dim3((unsigned)groups), dim3(kBlock * K), 0, s, ia,
+                           w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, icount, queues);
     } else {
         // one workgroup per item, up to the item capacity (the count is on
         // the device; the workgroups past it return at once)
-        const int64_t per = (w.cap_item + 7) / 8;
-        if (per == 0) return PP_OK;
         // At most two waves per SIMD by the last call's item count (a hint
         // only: both forms give the same results), the form built for that.
         bool few = false;
         if constexpr (VAR == 0 || VAR == 8) {
-            int dev = 0, cus = 256;
-            PP_HIP(hipGetDevice(&dev));
-            PP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
             few = w.nitem > 0 && w.nitem * K <= 2 * 4 * (int64_t)cus;
             if (few)
-                hipLaunchKernelGGL((pp_f32_kernel_few<VAR, K>), dim3((unsigned)(per * 8)), dim3(kBlock * K), 0,
-                                   s, ia, w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, counters);
+                hipLaunchKernelGGL((pp_f32_kernel_few<VAR, K>), dim3((unsigned)grid), dim3(kBlock * K), 0,
+                                   s, ia, w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, icount);
         }
         if (!few)
-            hipLaunchKernelGGL((pp_f32_kernel<VAR, K>), dim3((unsigned)(per * 8)), dim3(kBlock * K), 0, s,
-                               ia, w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, counters);
+            hipLaunchKernelGGL((pp_f32_kernel<VAR, K>), dim3((unsigned)grid), dim3(kBlock * K), 0, s,
+                               ia, w.pos_s.as<double>(), w.mass_s.as<float>(), w.pos_n, partial, icount);
     }
     PP_HIP(hipGetLastError());
     return PP_OK;
@@ -1065,54 +1135,62 @@ static int launch_pp_f32_var(const ItemArgs& ia, const Work& w, Mode mode, int w
 
 template <int K>
 static int launch_pp_f32_k(const ItemArgs& ia, const Work& w, Mode mode, int waves_per_cu,
-                           int variant, float* partial, unsigned long long* counters,
+                           int variant, float* partial, int32_t* icount,
                            unsigned* queues, hipStream_t s) {
     switch (variant) {
-        case 0: return launch_pp_f32_var<0, K>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 8: return launch_pp_f32_var<8, K>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
+        case 0: return launch_pp_f32_var<0, K>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 8: return launch_pp_f32_var<8, K>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
         default: return fail(PP_EINVAL, "more than one wave per block needs variant 0 or 8");
     }
 }
 
 int launch_pp_f32(const BatchDev& bd, const Work& w, int waves_per_block, Mode mode, int waves_per_cu,
-                  int variant, float* partial, float* acc, unsigned long long* counters,
+                  int variant, float* partial, float* acc, int32_t* icount,
                   unsigned* queues, hipStream_t s) {
     ItemArgs ia = item_args(bd, w);
     ia.acc = acc;
     if (waves_per_block == 2)
-        return launch_pp_f32_k<2>(ia, w, mode, waves_per_cu, variant & 15, partial, counters, queues, s);
+        return launch_pp_f32_k<2>(ia, w, mode, waves_per_cu, variant & 15, partial, icount, queues, s);
     if (waves_per_block == 4)
-        return launch_pp_f32_k<4>(ia, w, mode, waves_per_cu, variant & 15, partial, counters, queues, s);
+        return launch_pp_f32_k<4>(ia, w, mode, waves_per_cu, variant & 15, partial, icount, queues, s);
     if (waves_per_block == 8)
-        return launch_pp_f32_k<8>(ia, w, mode, waves_per_cu, variant & 15, partial, counters, queues, s);
+        return launch_pp_f32_k<8>(ia, w, mode, waves_per_cu, variant & 15, partial, icount, queues, s);
     switch (variant & 15) {
-        case 0: return launch_pp_f32_var<0, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 1: return launch_pp_f32_var<1, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 2: return launch_pp_f32_var<2, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 3: return launch_pp_f32_var<3, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 4: return launch_pp_f32_var<4, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 5: return launch_pp_f32_var<5, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 6: return launch_pp_f32_var<6, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 7: return launch_pp_f32_var<7, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 8: return launch_pp_f32_var<8, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 9: return launch_pp_f32_var<9, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 10: return launch_pp_f32_var<10, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 11: return launch_pp_f32_var<11, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 12: return launch_pp_f32_var<12, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 13: return launch_pp_f32_var<13, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        case 14: return launch_pp_f32_var<14, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
-        default: return launch_pp_f32_var<15, 1>(ia, w, mode, waves_per_cu, partial, counters, queues, s);
+        case 0: return launch_pp_f32_var<0, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 1: return launch_pp_f32_var<1, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 2: return launch_pp_f32_var<2, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 3: return launch_pp_f32_var<3, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 4: return launch_pp_f32_var<4, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 5: return launch_pp_f32_var<5, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 6: return launch_pp_f32_var<6, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 7: return launch_pp_f32_var<7, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 8: return launch_pp_f32_var<8, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 9: return launch_pp_f32_var<9, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 10: return launch_pp_f32_var<10, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 11: return launch_pp_f32_var<11, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 12: return launch_pp_f32_var<12, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 13: return launch_pp_f32_var<13, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        case 14: return launch_pp_f32_var<14, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
+        default: return launch_pp_f32_var<15, 1>(ia, w, mode, waves_per_cu, partial, icount, queues, s);
     }
 }
 
-int launch_monopole(const BatchDev& bd, const Work& w, float* acc, unsigned long long* counter,
-                    hipStream_t s) {
+int launch_monopole(const BatchDev& bd, const Work& w, float* acc, int32_t* mcount, hipStream_t s) {
     if (w.cap_block == 0 || !w.ent_final) return PP_OK;
     ItemArgs ia = item_args(bd, w);
     ia.acc = acc;
     hipLaunchKernelGGL(monopole_kernel, dim3((unsigned)w.cap_block), dim3(kBlock), 0, s, ia, w.ent_final,
                        w.eoff.as<int64_t>(), w.mono0, w.mono1, w.tviews.as<TreeView>(),
-                       w.tree_mc.as<double4>(), w.pos_s.as<double>(), w.pos_n, w.cap_block, counter);
+                       w.tree_mc.as<double4>(), w.pos_s.as<double>(), w.pos_n, mcount);
+    PP_HIP(hipGetLastError());
+    return PP_OK;
+}
+
+int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, const int32_t* icount,
+                      const int32_t* mcount, unsigned long long* out, hipStream_t s) {
+    hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, out, 3);
+    hipLaunchKernelGGL(sum_staged_kernel, dim3(256), dim3(256), 0, s, item_args(bd, w), icount, waves_per_block,
+                       mcount, out);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
@@ -1128,10 +1206,9 @@ int launch_reduce_f32(const BatchDev& bd, const Work& w, const float* partial, f
 }
 
 int launch_pp_f64(const BatchDev& bd, const Work& w, double* partial, hipStream_t s) {
-    const int64_t per = (w.cap_item + 7) / 8;
-    if (per == 0) return PP_OK;
+    if (w.cap_item == 0) return PP_OK;
     ItemArgs ia = item_args(bd, w);
-    hipLaunchKernelGGL(pp_f64_kernel<false>, dim3((unsigned)(per * 8)), dim3(kBlock), 0, s, ia,
+    hipLaunchKernelGGL(pp_f64_kernel<false>, dim3((unsigned)xcd_groups(w.cap_item)), dim3(kBlock), 0, s, ia,
                        w.pos_s.as<double>(), w.mass_sd.as<double>(), w.pos_n, partial,
                        (int32_t*)nullptr);
     PP_HIP(hipGetLastError());
@@ -1149,10 +1226,9 @@ int launch_reduce_f64(const BatchDev& bd, const Work& w, const double* partial, 
 }
 
 int launch_count(const BatchDev& bd, const Work& w, int32_t* partial, hipStream_t s) {
-    const int64_t per = (w.cap_item + 7) / 8;
-    if (per == 0) return PP_OK;
+    if (w.cap_item == 0) return PP_OK;
     ItemArgs ia = item_args(bd, w);
-    hipLaunchKernelGGL(pp_f64_kernel<true>, dim3((unsigned)(per * 8)), dim3(kBlock), 0, s, ia,
+    hipLaunchKernelGGL(pp_f64_kernel<true>, dim3((unsigned)xcd_groups(w.cap_item)), dim3(kBlock), 0, s, ia,
                        w.pos_s.as<double>(), (const double*)nullptr, w.pos_n,
                        (double*)nullptr, partial);
     PP_HIP(hipGetLastError());

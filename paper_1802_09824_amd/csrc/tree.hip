@@ -622,6 +622,23 @@ __global__ void __launch_bounds__(64) block_split_kernel(
 // 8-child test per entry.  Leaves (or inside intervals) come in ascending order and
 // consecutive ones merge into one range of source particles.
 constexpr int kDfsLevel = 2;
+// A box that lists fewer than kSmallBox sources in all is cut into chunks of
+// kChunkScale listed^(2/3) positions: an item's fixed cost grows with the
+// number of items (listed / chunk), the wait for the last items with the
+// chunk.  Measured fastest chunks (PP stage, one wave per block): 1000
+// particles (49 k listed) 64, 28 us against 189 at 2048; 20 k (1.3 M) 128, 65
+// against 142; 32 k (2 M) 128, 85 against 155; 150 k (10 M) 256, 246 against
+// 350; 300 k (20 M) 256 to 512, 454 against 535; 1 M (70 M) 1024, 1.44 ms
+// against 1.50.  The rule stays at or above them: it sees one box, and in a
+// batch, which has no last items to wait for, shorter chunks only add items
+// (17 boxes of 6 k particles ran 9 % slower at 64 positions than at 2048).
+// The floors cost a lone box 1 to 5 us.
+constexpr int64_t kSmallBox = (int64_t)1 << 27;
+constexpr double kChunkScale = 0.01075;
+constexpr int64_t kTinyBox = (int64_t)1 << 17;
+constexpr int64_t kTinyChunk = 128, kSmallChunk = 256;
+// target blocks per box up to which the first guess of the items follows that rule
+constexpr int64_t kSmallBlocks = 65536;
 // Monopoles may be taken at every level: by the breadth-first expansion for
 // nodes of level 2 and up, by the depth-first walk for groups of 8 leaves
 // (level 1) and single leaves (level 0).
@@ -956,17 +973,41 @@ __global__ void block_entry_kernel(const FEntry* __restrict__ ent, const int64_t
 
 // Listed sources in all (sum of the block list lengths) and the effective
 // chunk: the requested one, or larger when the item partial sums (3 x 64
-// floats per item) would pass max_items items.
-__global__ void chunk_kernel(const int64_t* __restrict__ soff_e, int64_t* __restrict__ sizes,
-                             int64_t chunk_req, int64_t max_items) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// floats per item) would pass max_items items.  With `adapt` a small box gets
+// a smaller one of its own (see kSmallBox); it depends on that box alone, so a
+// box is cut the same way in a batch and by itself.
+__global__ void __launch_bounds__(256) chunk_kernel(const int64_t* __restrict__ soff_e,
+                                                    const int64_t* __restrict__ eoff,
+                                                    const int64_t* __restrict__ coff,
+                                                    const int64_t* __restrict__ choff, int nbox,
+                                                    int64_t* __restrict__ sizes, int64_t chunk_req,
+                                                    int64_t max_items, int adapt,
+                                                    int32_t* __restrict__ box_chunk) {
     const int64_t total = soff_e[sizes[kNEntry]];
-    sizes[kTotalSrc] = total;
     int64_t chunk = chunk_req;
     const int64_t need = (total + max_items - 1) / max_items;
     if (need > chunk) chunk = ((need + kBlock - 1) / kBlock) * kBlock;
     if (chunk > INT32_MAX / 2) chunk = INT32_MAX / 2;
-    sizes[kChunk] = chunk;
+    if (threadIdx.x == 0) {
+        sizes[kTotalSrc] = total;
+        sizes[kChunk] = chunk;
+    }
+    const int64_t nblock = sizes[kNBlock];
+    for (int x = threadIdx.x; x < nbox; x += blockDim.x) {
+        int64_t c = chunk;
+        if (adapt) {
+            const int64_t b0 = coff[choff[x]], b1 = coff[choff[x + 1]];
+            const int64_t own = soff_e[eoff[b1 < nblock ? b1 : nblock]] - soff_e[eoff[b0 < nblock ? b0 : nblock]];
+            if (own < kSmallBox) {
+                const double root = cbrt((double)own);
+                int64_t few = (int64_t)(kChunkScale * root * root / kBlock + 0.5) * kBlock;
+                const int64_t floor_ = own < kTinyBox ? kTinyChunk : kSmallChunk;
+                if (few < floor_) few = floor_;
+                c = few < c ? few : c;
+            }
+        }
+        box_chunk[x] = (int32_t)c;
+    }
 }
 
 // Work items per block: its list in chunks (at least one item, so that every
@@ -974,7 +1015,9 @@ __global__ void chunk_kernel(const int64_t* __restrict__ soff_e, int64_t* __rest
 // are given.
 __global__ void item_count_kernel(const int32_t* __restrict__ slen,
                                   const int32_t* __restrict__ bcount, int64_t* __restrict__ sizes,
-                                  int64_t cap_block, const uint8_t* __restrict__ active,
+                                  int64_t cap_block, const int32_t* __restrict__ bboxid,
+                                  const int32_t* __restrict__ box_chunk,
+                                  const uint8_t* __restrict__ active,
                                   const int32_t* __restrict__ perm,
                                   const int32_t* __restrict__ bstart,
                                   int32_t* __restrict__ icount) {
@@ -993,7 +1036,7 @@ __global__ void item_count_kernel(const int32_t* __restrict__ slen,
         }
     }
     const int32_t s = slen[b];
-    const int64_t chunk = sizes[kChunk];
+    const int64_t chunk = box_chunk[bboxid[b]];
     icount[b] = s <= 0 ? 1 : (int32_t)((s + chunk - 1) / chunk);
     // (target, listed source) pairs; the kernel prunes some sources further
     atomicAdd(reinterpret_cast<unsigned long long*>(sizes + kCand),
@@ -1002,16 +1045,20 @@ __global__ void item_count_kernel(const int32_t* __restrict__ slen,
 
 __global__ void item_fill_kernel(const int32_t* __restrict__ icount,
                                  const int64_t* __restrict__ ioff, const int64_t* __restrict__ sizes,
-                                 int64_t cap_item, int32_t* __restrict__ iblock,
-                                 int32_t* __restrict__ is0) {
+                                 int64_t cap_item, const int32_t* __restrict__ slen,
+                                 const int32_t* __restrict__ bboxid,
+                                 const int32_t* __restrict__ box_chunk, int32_t* __restrict__ iblock,
+                                 int32_t* __restrict__ is0, int32_t* __restrict__ is1) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= sizes[kNBlock]) return;
     const int64_t o = ioff[b];
-    const int64_t chunk = sizes[kChunk];
+    const int64_t chunk = box_chunk[bboxid[b]];
+    const int64_t len = slen[b];
     for (int32_t c = 0; c < icount[b]; ++c) {
         if (o + c >= cap_item) return;
         iblock[o + c] = (int32_t)b;
         is0[o + c] = (int32_t)(c * chunk);
+        is1[o + c] = (int32_t)((c + 1) * chunk < len ? (c + 1) * chunk : len);
     }
 }
 
@@ -1248,8 +1295,8 @@ static int64_t settle_cap(int64_t cap, int64_t need) {
     return cap > want + want / 2 ? want : cap;
 }
 
-int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_req, Work& w,
-                hipStream_t s, const MonoCfg& mcfg, const uint8_t* active) {
+int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_req, bool adapt_chunk,
+                Work& w, hipStream_t s, const MonoCfg& mcfg, const uint8_t* active) {
     const int nbox = bd.nbox;
     const int64_t N = poff[nbox];
     int64_t* sizes = w.sizes.as<int64_t>();
@@ -1401,7 +1448,12 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     w.mono0 = mono0;
     w.mono1 = mono1;
     if (w.cap_range < 1024) w.cap_range = 16 * cb;
-    if (w.cap_item < 1024) w.cap_item = 2 * cb;
+    if (w.cap_item < 1024) {
+        w.cap_item = 2 * cb;
+        // small boxes are cut finer: their items grow as the root of the blocks
+        const int64_t fine = (int64_t)(1000.0 * sqrt((double)cb * nbox));
+        if (adapt_chunk && fine > w.cap_item && cb < nbox * kSmallBlocks) w.cap_item = fine;
+    }
     hipLaunchKernelGGL(ranges_count_kernel, dim3(blocks_for(F, 128)), dim3(128), 0, s, bd, tvs, nodes, ent,
                        F, bbox, bboxid, lbegin, lcount, w.lmask_e.as<uint64_t>(), w.rcnt_e.as<int32_t>(),
                        w.scnt_e.as<int32_t>(), mono, mono0, mono1, (const int64_t*)sizes);
@@ -1416,8 +1468,11 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
                        w.slen.as<int32_t>());
     PP_HIP(hipGetLastError());
     constexpr int64_t kMaxItems = 1 << 21;
-    hipLaunchKernelGGL(chunk_kernel, dim3(1), dim3(1), 0, s, (const int64_t*)w.soff_e.as<int64_t>(), sizes,
-                       (int64_t)chunk_req, kMaxItems);
+    PP_TRY(w.box_chunk.reserve(sizeof(int32_t) * nbox));
+    hipLaunchKernelGGL(chunk_kernel, dim3(1), dim3(256), 0, s, (const int64_t*)w.soff_e.as<int64_t>(),
+                       (const int64_t*)w.eoff.as<int64_t>(), (const int64_t*)w.coff.as<int64_t>(),
+                       (const int64_t*)w.choff.as<int64_t>(), nbox, sizes, (int64_t)chunk_req, kMaxItems,
+                       adapt_chunk ? 1 : 0, w.box_chunk.as<int32_t>());
     PP_TRY(w.rbeg.reserve(sizeof(int32_t) * (w.cap_range + 1)));
     PP_TRY(w.rpre.reserve(sizeof(int32_t) * (w.cap_range + 1)));
     PP_TRY(w.rcode.reserve(sizeof(uint8_t) * (w.cap_range + 1)));
@@ -1435,15 +1490,18 @@ int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* activ
     const int64_t cb = w.cap_block;
     w.active = active;
     hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
-                       w.slen.as<int32_t>(), w.bcount.as<int32_t>(), sizes, cb, active,
+                       w.slen.as<int32_t>(), w.bcount.as<int32_t>(), sizes, cb, w.bboxid.as<int32_t>(),
+                       w.box_chunk.as<int32_t>(), active,
                        w.perm.as<int32_t>(), w.bstart.as<int32_t>(), w.icount.as<int32_t>());
     PP_HIP(hipGetLastError());
     PP_TRY(launch_scan_i32_to_i64(w.icount.as<int32_t>(), w.ioff.as<int64_t>(), cb, w.scan_ws, s, sizes));
     PP_TRY(w.iblock.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.is0.reserve(sizeof(int32_t) * (w.cap_item + 1)));
+    PP_TRY(w.is1.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     hipLaunchKernelGGL(item_fill_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
                        w.icount.as<int32_t>(), w.ioff.as<int64_t>(), (const int64_t*)sizes, w.cap_item,
-                       w.iblock.as<int32_t>(), w.is0.as<int32_t>());
+                       w.slen.as<int32_t>(), w.bboxid.as<int32_t>(), w.box_chunk.as<int32_t>(),
+                       w.iblock.as<int32_t>(), w.is0.as<int32_t>(), w.is1.as<int32_t>());
     hipLaunchKernelGGL(finish_sizes_kernel, dim3(1), dim3(1), 0, s, sizes, w.ioff.as<int64_t>(),
                        w.roff.as<int64_t>(), w.cap_item, w.cap_range, w.bad.as<int>());
     PP_HIP(hipGetLastError());

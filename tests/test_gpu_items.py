@@ -1,0 +1,73 @@
+"""GPU tests of how a box's lists are cut into work items and how the items are
+launched: the finer cut of small boxes, and the two launch forms behind
+persistent = 1 (queues, or one workgroup per item)."""
+import numpy as np
+import pytest
+
+import workloads as W
+from workloads import BoxParams
+from tests import parity
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1802_09824_amd as m
+    return m
+
+
+def dev(a, dtype):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype)
+
+
+def box(n, seed=9):
+    rng = np.random.default_rng(seed + n)
+    p = BoxParams.from_mesh(60.0, max(12, int(round(n ** (1 / 3)))))
+    return W.mixture(rng, n, p.L, 0.5, max(1, n // 500)), rng.uniform(0.5, 1.5, n).astype(np.float32), p
+
+
+@pytest.mark.parametrize("n", [1, 64, 65, 700, 1500, 6001, 20011])
+def test_small_boxes_are_cut_finer(pp, oracle_mod, n):
+    """The default tuning cuts a box that lists T sources in all into chunks
+    of 0.01075 T^(2/3) positions, rounded to 64, at least 128 (256 from 2^17
+    on) and at most the requested 2048; the results meet the oracle bars."""
+    pos, mass, p = box(n)
+    plan = pp.Plan(p, n)
+    acc = plan.accel(dev(pos, torch.float64), dev(mass, torch.float32)).cpu().numpy()
+    slen = plan.export_lists()["slen"].astype(np.int64)
+    T = int(slen.sum())
+    few = int(0.01075 * np.cbrt(float(T)) ** 2 / 64 + 0.5) * 64
+    chunk = min(2048, max(few, 128 if T < 2 ** 17 else 256))
+    assert plan.stats()["nitem"] == int(np.maximum(1, -(-slen // chunk)).sum())
+    ref = oracle_mod.accel(pos, mass.astype(np.float64), p, pair_abs=True)
+    s = parity.summary(acc, ref)
+    assert s["zero_ok"] and s["median"] <= 1e-6 and s["p999"] <= 1e-4, s
+    assert s["robust_max"] <= parity.ROBUST_MAX, s
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("k", [1, 2, 8])
+def test_queue_and_per_item_launches_agree(pp, k, graph):
+    """64 positions per wave: the first call, with room for more than 65536
+    waves of items and no mean length yet, runs from the queues; the later
+    ones, whose last items were short, one workgroup per item.  All run every
+    item once, in the same arithmetic, and count the same swept sources."""
+    pos, mass, p = box(60000)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, pos.shape[1])
+    plan.set_tuning(chunk=64 * k, waves_per_block=k, persistent=1, use_graph=graph)
+    first = plan.accel(x, m).cpu().numpy()
+    st = plan.stats()
+    assert st["nitem"] * k * 1.25 > 65536
+    for _ in range(2):
+        later = plan.accel(x, m).cpu().numpy()
+        assert np.array_equal(first.view(np.uint32), later.view(np.uint32))
+        assert plan.stats()["lane_pairs"] == st["lane_pairs"]
+        assert plan.stats()["evaluated"] == st["evaluated"]
+    plan.set_tuning(persistent=0, use_graph=0)
+    grid = plan.accel(x, m).cpu().numpy()
+    assert np.array_equal(first.view(np.uint32), grid.view(np.uint32))
