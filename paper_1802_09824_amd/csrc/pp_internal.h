@@ -257,6 +257,7 @@ struct Work {
     DevBuf roff, slen, rbeg, rpre, rcode;
     DevBuf icount, ioff, iblock, is0, is1;
     DevBuf box_chunk;  // int32 [nbox]: source-list positions per work item of each box
+    DevBuf bact;       // uint64 per block: its active lanes (calls with active flags)
     DevBuf sizes;      // int64 [kSizeSlots], see SizeSlot
     DevBuf misc;       // counters and flags
 };

@@ -1010,6 +1010,21 @@ __global__ void __launch_bounds__(256) chunk_kernel(const int64_t* __restrict__ 
     }
 }
 
+// The active lanes of every target block, one wave per block.
+__global__ void __launch_bounds__(256) block_active_kernel(const int64_t* __restrict__ sizes,
+                                                           const uint8_t* __restrict__ active,
+                                                           const int32_t* __restrict__ perm,
+                                                           const int32_t* __restrict__ bstart,
+                                                           const int32_t* __restrict__ bcount,
+                                                           uint64_t* __restrict__ bact) {
+    const int lane = threadIdx.x & (kBlock - 1);
+    const int64_t b = (int64_t)blockIdx.x * (256 / kBlock) + threadIdx.x / kBlock;
+    if (b >= sizes[kNBlock]) return;
+    const bool on = lane < bcount[b] && active[perm[(int64_t)bstart[b] + lane]] != 0;
+    const uint64_t m = __ballot(on);
+    if (lane == 0) bact[b] = m;
+}
+
 // Work items per block: its list in chunks (at least one item, so that every
 // target is written); none for a block without an active target when flags
 // are given.
@@ -1017,23 +1032,16 @@ __global__ void item_count_kernel(const int32_t* __restrict__ slen,
                                   const int32_t* __restrict__ bcount, int64_t* __restrict__ sizes,
                                   int64_t cap_block, const int32_t* __restrict__ bboxid,
                                   const int32_t* __restrict__ box_chunk,
-                                  const uint8_t* __restrict__ active,
-                                  const int32_t* __restrict__ perm,
-                                  const int32_t* __restrict__ bstart,
-                                  int32_t* __restrict__ icount) {
+                                  const uint64_t* __restrict__ bact, int32_t* __restrict__ icount) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= cap_block) return;
     if (b >= sizes[kNBlock]) {
         icount[b] = 0;
         return;
     }
-    if (active) {
-        bool on = false;
-        for (int32_t k = 0; k < bcount[b] && !on; ++k) on = active[perm[(int64_t)bstart[b] + k]] != 0;
-        if (!on) {
-            icount[b] = 0;
-            return;
-        }
+    if (bact && bact[b] == 0) {
+        icount[b] = 0;
+        return;
     }
     const int32_t s = slen[b];
     const int64_t chunk = box_chunk[bboxid[b]];
@@ -1489,10 +1497,16 @@ int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* activ
     int64_t* sizes = w.sizes.as<int64_t>();
     const int64_t cb = w.cap_block;
     w.active = active;
+    if (active) {
+        PP_TRY(w.bact.reserve(sizeof(uint64_t) * (cb + 1)));
+        hipLaunchKernelGGL(block_active_kernel, dim3(blocks_for(cb, 256 / kBlock)), dim3(256), 0, s, sizes, active,
+                           w.perm.as<int32_t>(), w.bstart.as<int32_t>(), w.bcount.as<int32_t>(),
+                           w.bact.as<uint64_t>());
+    }
     hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
                        w.slen.as<int32_t>(), w.bcount.as<int32_t>(), sizes, cb, w.bboxid.as<int32_t>(),
-                       w.box_chunk.as<int32_t>(), active,
-                       w.perm.as<int32_t>(), w.bstart.as<int32_t>(), w.icount.as<int32_t>());
+                       w.box_chunk.as<int32_t>(),
+                       active ? w.bact.as<uint64_t>() : (const uint64_t*)nullptr, w.icount.as<int32_t>());
     PP_HIP(hipGetLastError());
     PP_TRY(launch_scan_i32_to_i64(w.icount.as<int32_t>(), w.ioff.as<int64_t>(), cb, w.scan_ws, s, sizes));
     PP_TRY(w.iblock.reserve(sizeof(int32_t) * (w.cap_item + 1)));

@@ -71,3 +71,31 @@ def test_queue_and_per_item_launches_agree(pp, k, graph):
     plan.set_tuning(persistent=0, use_graph=0)
     grid = plan.accel(x, m).cpu().numpy()
     assert np.array_equal(first.view(np.uint32), grid.view(np.uint32))
+
+@pytest.mark.parametrize("k,variant,persistent", [(1, 0, 1), (1, 0, 0), (2, 0, 1), (4, 8, 1), (8, 0, 0)])
+@pytest.mark.parametrize("equal", [False, True])
+def test_few_active_targets_per_block(pp, k, variant, persistent, equal):
+    """Blocks with 0, 1, 15, 16, 17, 31, 32, 33, 63 and 64 active targets (the
+    edges between four, two and one copies of them per wave), their lists
+    ending in tiles of every remainder: the active targets get the whole
+    call's bits, the others keep what they held."""
+    pos, mass, p = box(20011)
+    n = pos.shape[1]
+    if equal:
+        mass[:] = 1.0 / n
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, n)
+    plan.set_tuning(chunk=704 * k, waves_per_block=k, persistent=persistent, variant=variant)
+    full = plan.accel(x, m).cpu().numpy()
+    lists = plan.export_lists()
+    rng = np.random.default_rng(3)
+    active = np.zeros(n, np.uint8)
+    for b, (a, c) in enumerate(zip(lists["bstart"], lists["bcount"])):
+        want = min(int(c), (0, 1, 15, 16, 17, 31, 32, 33, 63, 64)[b % 10])
+        active[lists["perm"][a + rng.permutation(int(c))[:want]]] = 1
+    out = torch.full((3, n), 7.0, dtype=torch.float32, device="cuda")
+    plan.accel_active(x, m, dev(active, torch.uint8), out)
+    got = out.cpu().numpy()
+    on = active != 0
+    assert np.array_equal(got[:, on].view(np.uint32), full[:, on].view(np.uint32))
+    assert np.all(got[:, ~on] == 7.0)
