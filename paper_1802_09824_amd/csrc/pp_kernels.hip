@@ -26,6 +26,7 @@
 
 #include "pp_internal.h"
 #include "split_poly.h"
+#include "split_poly64.h"
 
 namespace pp {
 namespace {
@@ -241,14 +242,72 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int lane) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// The ranges of the 64 list positions from `base` on (positions below s1),
+// one position per lane: its range r, that range's first particle, list
+// position and shift code.  rcur: a range at or before the one that holds
+// `base`, at most K * 64 positions before it.  A window inside the range at
+// the cursor needs no mapping; otherwise the wave reads the 64 ranges from the
+// cursor on (one per lane), marks in LDS the window positions where one of
+// them starts, and each lane takes its position's range from the count of
+// marks up to it and the range's first particle from the lane that read it;
+// only a window that runs past those 64 ranges falls back to a binary search
+// per lane.
+template <int K>
+__device__ __forceinline__ int64_t window_range(const ItemArgs& ia, int32_t base, int32_t s1, int64_t rcur,
+                                                int64_t r_hi, int* mark, int32_t& rb, int32_t& rp,
+                                                int& code) {
+    const int lane = threadIdx.x & (kBlock - 1);
+    const int32_t p = base + lane;
+    const int32_t last = s1 - 1 < base + kBlock - 1 ? s1 - 1 : base + kBlock - 1;
+    int64_t r;
+    // the block's last range: every position of the item lies before its end
+    const int32_t end_cur = rcur < r_hi ? ia.rpre[rcur + 1] : s1;
+    if (last < end_cur) {
+        // the cursor's range holds the whole window: nothing to map
+        r = rcur;
+        rb = ia.rbeg[rcur];
+        rp = ia.rpre[rcur];
+        code = ia.rcode[rcur];
+    } else {
+        // the ranges rcur .. rcur + 63, one per lane
+        const int64_t rq = rcur + lane;
+        const bool rv = rq <= r_hi;
+        const int32_t qpre = rv ? ia.rpre[rq] : INT32_MAX;
+        const int32_t qbeg = rv ? ia.rbeg[rq] : 0;
+        const int qcode = rv ? (int)ia.rcode[rq] : 13;
+        // ranges that start at or before the window's first (last) position
+        const int c0 = __popcll(__ballot(qpre <= base));
+        const int c1 = __popcll(__ballot(qpre <= last));
+        if (c1 < kBlock || rcur + (kBlock - 1) >= r_hi) {
+            // every range of the window was read: mark where they start
+            mark[lane] = 0;
+            wave_sync();
+            if (qpre > base && qpre <= last) mark[qpre - base] = 1;
+            wave_sync();
+            const uint64_t starts = __ballot(mark[lane] != 0);
+            wave_sync();
+            const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
+            const int idx = c0 - 1 + __popcll(starts & upto);
+            rb = __shfl(qbeg, idx);
+            rp = __shfl(qpre, idx);
+            code = __shfl(qcode, idx);
+            r = rcur + idx;
+        } else {
+            // more than 64 ranges in reach: the window starts at most K * 64
+            // positions (so ranges) past the cursor's
+            const int64_t top = rcur + K * kBlock < r_hi ? rcur + K * kBlock : r_hi;
+            r = p < s1 ? find_range(ia.rpre, rcur, top, p) : rcur;
+            rb = ia.rbeg[r];
+            rp = ia.rpre[r];
+            code = ia.rcode[r];
+        }
+    }
+    return r;
+}
+
 // One work item of the FP32 PP kernel on one wave (target block, chunk of
-// its source list).  Sources are fetched 64 list positions at a time.  A
-// window inside the range at the wave's range cursor needs no mapping;
-// otherwise the wave reads the 64 ranges from the cursor on (one per lane),
-// marks in LDS the window positions where one of them starts, and each lane
-// takes its position's range from the count of marks up to it and the
-// range's first particle from the lane that read it; only a window that
-// runs past those 64 ranges falls back to a binary search per lane.  Then each lane loads
+// its source list).  Sources are fetched 64 list positions at a time (their
+// ranges by window_range).  Each lane loads
 // the FP64 position and the mass; the loads of the next window are issued
 // before the current tile is swept.  A fetched source is shifted by its periodic image, made
 // relative to the FP64 block centre, scaled by 1/ell and rounded to FP32,
@@ -413,52 +472,9 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
     auto fetch = [&](int32_t base) {
         const int32_t p = base + lane;
         pv = p < s1;
-        const int32_t last = s1 - 1 < base + kBlock - 1 ? s1 - 1 : base + kBlock - 1;
-        int64_t r;
         int32_t rb, rp;
         int code;
-        // the block's last range: every position of the item lies before its end
-        const int32_t end_cur = rcur < r_hi ? ia.rpre[rcur + 1] : s1;
-        if (last < end_cur) {
-            // the cursor's range holds the whole window: nothing to map
-            r = rcur;
-            rb = ia.rbeg[rcur];
-            rp = ia.rpre[rcur];
-            code = ia.rcode[rcur];
-        } else {
-            // the ranges rcur .. rcur + 63, one per lane
-            const int64_t rq = rcur + lane;
-            const bool rv = rq <= r_hi;
-            const int32_t qpre = rv ? ia.rpre[rq] : INT32_MAX;
-            const int32_t qbeg = rv ? ia.rbeg[rq] : 0;
-            const int qcode = rv ? (int)ia.rcode[rq] : 13;
-            // ranges that start at or before the window's first (last) position
-            const int c0 = __popcll(__ballot(qpre <= base));
-            const int c1 = __popcll(__ballot(qpre <= last));
-            if (c1 < kBlock || rcur + (kBlock - 1) >= r_hi) {
-                // every range of the window was read: mark where they start
-                mark[lane] = 0;
-                wave_sync();
-                if (qpre > base && qpre <= last) mark[qpre - base] = 1;
-                wave_sync();
-                const uint64_t starts = __ballot(mark[lane] != 0);
-                wave_sync();
-                const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
-                const int idx = c0 - 1 + __popcll(starts & upto);
-                rb = __shfl(qbeg, idx);
-                rp = __shfl(qpre, idx);
-                code = __shfl(qcode, idx);
-                r = rcur + idx;
-            } else {
-                // more than 64 ranges in reach: the window starts at most K * 64
-                // positions (so ranges) past the cursor's
-                const int64_t top = rcur + K * kBlock < r_hi ? rcur + K * kBlock : r_hi;
-                r = pv ? find_range(ia.rpre, rcur, top, p) : rcur;
-                rb = ia.rbeg[r];
-                rp = ia.rpre[r];
-                code = ia.rcode[r];
-            }
-        }
+        const int64_t r = window_range<K>(ia, base, s1, rcur, r_hi, mark, rb, rp, code);
         if (pv) {
             const int64_t j = (int64_t)rb + (p - rp);
             pc = code;
@@ -962,12 +978,65 @@ __global__ void __launch_bounds__(256) reduce_f32_kernel(ItemArgs ia,
 }
 
 // ------------------------------------------------------------------ FP64 --
-#pragma clang fp contract(off)
-// The split factor (Eq. equ:split) in FP64 with the device erfc/exp.
-__device__ __forceinline__ double split_factor_f64(double x) {
-    return erfc(x) + 2.0 * x / 1.7724538509055160272981674833411 * exp(-x * x);
+// Per-box constants of the FP64 pair arithmetic.
+struct F64Const {
+    double eps2, rcut2;
+    double tx;       // t of split_poly64.h per unit of s_eps
+    double tz;       // log2(e) x^2 per unit of s_eps^2
+};
+
+// a b + c with c in scalar registers: written out because the compiler takes
+// the two-operand form, with a copy of c into vector registers before every
+// one (112 instructions per pair instead of 80).
+__device__ __forceinline__ double fma_const(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
 }
 
+// One source at separation (dx, dy, dz), G m = gm, added into (tx, ty, tz).
+// The separation and s^2 take the oracle's operation order (no contraction),
+// so the cut decides as its own test does.  With y = 1 / s_eps from the
+// hardware estimate and one third-order step, x = s_eps / 2 r_s and the split
+// factor g = 2^-n 2^-f P(x) (split_poly64.h), the pair factor G m g y^3 holds
+// about 3e-16 (relative, rms over the cut sphere), against 5e-16 with the
+// library's erfc, exp, square root and quotients.
+__device__ __forceinline__ void pair_f64(double dx, double dy, double dz, double gm, const F64Const& C,
+                                         double& tx, double& ty, double& tz) {
+#pragma clang fp contract(off)
+    const double s2 = dx * dx + dy * dy + dz * dz;
+    const bool in = s2 < C.rcut2 && s2 > 0.0;
+    const double se2 = s2 + C.eps2;
+    const double y0 = __builtin_amdgcn_rsq(se2);
+    const double e = fma(-(se2 * y0), y0, 1.0);
+    const double y = fma(y0 * e, fma(e, 0.375, 0.5), y0);
+    const double t = fma(se2 * y, C.tx, -1.0);
+    double p = SPLIT64_P[SPLIT64_DEGREE_P];
+#pragma unroll
+    for (int j = SPLIT64_DEGREE_P - 1; j >= 0; --j) p = fma_const(p, t, SPLIT64_P[j]);
+    const double z = se2 * C.tz;
+    const double n = rint(z);
+    const double f = z - n;
+    double q = SPLIT64_E[SPLIT64_DEGREE_E];
+#pragma unroll
+    for (int j = SPLIT64_DEGREE_E - 1; j >= 0; --j) q = fma_const(q, f, SPLIT64_E[j]);
+    q = ldexp(q, -(int)n);
+    double F = ((y * y) * y) * ((q * p) * gm);
+    F = in ? F : 0.0;
+    tx = fma(F, dx, tx);
+    ty = fma(F, dy, ty);
+    tz = fma(F, dz, tz);
+}
+
+// FP64 sums (or, COUNT, the number of sources with s < r_cut, j != i) of one
+// work item per wave: sources fetched, pruned against the four boxes of the
+// block's runs of 16 targets (the FP32 kernel's test, which keeps too much
+// only) and compacted into an LDS ring as in pp_item, then swept 64 at a time
+// by all lanes.  The bound is FP64 issue: about 75 instructions per lane-pair
+// at 4 clocks each.  The earlier form, library functions on every listed
+// source with a branch per pair, held all of them (both branches of erfc
+// among them) for one lane inside the cut: 262 k particles took 8.2 ms per
+// call, now 3.4.
 template <bool COUNT>
 __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* __restrict__ pos_s,
                                                     const double* __restrict__ mass_s, int64_t N,
@@ -977,69 +1046,156 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
     const int64_t nitem = ia.sizes[kNItem];
     const int64_t item = xcd_item(blockIdx.x, nitem);
     if (item < 0) return;
+    constexpr int GROUPS = 4, GW = kBlock / GROUPS;
+    __shared__ double4 tile[2 * kBlock];
+    __shared__ double shift[2 * kBlock][3];
+    __shared__ int32_t tj[COUNT ? 2 * kBlock : 1];
+    __shared__ float4 qb[2 * GROUPS];
+    __shared__ int mark[kBlock];
     const int lane = threadIdx.x;
     const int32_t b = ia.iblock[item];
     const int32_t s0 = ia.is0[item];
     const int32_t s1 = ia.is1[item];
+    const int32_t nt = ia.bcount[b];
     const BoxDev& X = ia.box[ia.bboxid[b]];
-    const double L = X.L, rs = X.rs, rcut = X.rcut, eps = X.eps, G = X.G;
-    const bool active = lane < ia.bcount[b];
-    const int64_t t = active ? (int64_t)ia.bstart[b] + lane : -2;
-    double xi = 0, yi = 0, zi = 0;
-    if (active) {
-        xi = pos_s[t];
-        yi = pos_s[N + t];
-        zi = pos_s[2 * N + t];
+    const double L = X.L, cell = X.cell, inv_len = X.inv_len, G = X.G;
+    const float keep2 = X.poly.keep2;
+    F64Const C;
+    C.eps2 = X.eps * X.eps;
+    C.rcut2 = X.rcut * X.rcut;
+    C.tx = 2.0 / SPLIT64_X_MAX / (2.0 * X.rs);
+    C.tz = 1.4426950408889634 / (4.0 * X.rs * X.rs);
+    const IBox B = ia.bbox[b];
+    const double ox = 0.5 * (double)(B.lo[0] + B.hi[0]) * cell;
+    const double oy = 0.5 * (double)(B.lo[1] + B.hi[1]) * cell;
+    const double oz = 0.5 * (double)(B.lo[2] + B.hi[2]) * cell;
+    const int64_t t = (int64_t)ia.bstart[b] + (lane < nt ? lane : 0);
+    const double xi = pos_s[t], yi = pos_s[N + t], zi = pos_s[2 * N + t];
+    {
+        // boxes around the runs of 16 targets (lanes past the last target
+        // repeat the first one), relative to the block centre in units of ell
+        const float fx = (float)((xi - ox) * inv_len), fy = (float)((yi - oy) * inv_len),
+                    fz = (float)((zi - oz) * inv_len);
+        float ax_ = fx, bx_ = fx, ay_ = fy, by_ = fy, az_ = fz, bz_ = fz;
+#pragma unroll
+        for (int m = 1; m < GW; m <<= 1) {
+            ax_ = fminf(ax_, __shfl_xor(ax_, m));
+            bx_ = fmaxf(bx_, __shfl_xor(bx_, m));
+            ay_ = fminf(ay_, __shfl_xor(ay_, m));
+            by_ = fmaxf(by_, __shfl_xor(by_, m));
+            az_ = fminf(az_, __shfl_xor(az_, m));
+            bz_ = fmaxf(bz_, __shfl_xor(bz_, m));
+        }
+        if (lane % GW == 0) {
+            const int g = lane / GW;
+            qb[2 * g] = make_float4(0.5f * (ax_ + bx_), 0.5f * (ay_ + by_), 0.5f * (az_ + bz_),
+                                    0.5f * (bx_ - ax_) * 1.0001f + 1e-6f);
+            qb[2 * g + 1] = make_float4(0.5f * (by_ - ay_) * 1.0001f + 1e-6f,
+                                        0.5f * (bz_ - az_) * 1.0001f + 1e-6f, 0.f, 0.f);
+        }
+        wave_sync();
     }
     const int64_t r_lo = ia.roff[b], r_hi = ia.roff[b + 1] - 1;
-    __shared__ double4 tile[kBlock];
-    __shared__ int64_t tj[kBlock];
-    __shared__ int tc[kBlock];
-    const double rcut2 = rcut * rcut, eps2 = eps * eps;
+    int64_t rcur = s1 > s0 ? find_range_wave(ia.rpre, r_lo, r_hi, s0) : r_lo;
     double ax = 0, ay = 0, az = 0;
     int32_t cnt = 0;
-    for (int32_t base = s0; base < s1; base += kBlock) {
+    int count = 0, shifted = 0;      // staged sources; the last shifted one's ring index + 1
+    double px = 0, py = 0, pz = 0, pm = 0;
+    int pc = 13;
+    int32_t pj = -1;
+    bool pv = false;
+    auto fetch = [&](int32_t base) {
         const int32_t p = base + lane;
-        double4 v = make_double4(0, 0, 0, 0);
-        int64_t j = -1;
-        int c = 13;
-        if (p < s1) {
-            const int64_t r = find_range(ia.rpre, r_lo, r_hi, p);
-            j = (int64_t)ia.rbeg[r] + (p - ia.rpre[r]);
-            c = ia.rcode[r];
-            v.x = pos_s[j];
-            v.y = pos_s[N + j];
-            v.z = pos_s[2 * N + j];
-            v.w = COUNT ? 0.0 : mass_s[j];
+        pv = p < s1;
+        int32_t rb, rp;
+        int code;
+        const int64_t r = window_range<1>(ia, base, s1, rcur, r_hi, mark, rb, rp, code);
+        if (pv) {
+            const int64_t j = (int64_t)rb + (p - rp);
+            pc = code;
+            pj = (int32_t)j;
+            px = pos_s[j];
+            py = pos_s[N + j];
+            pz = pos_s[2 * N + j];
+            if (!COUNT) pm = mass_s[j];
         }
-        __syncthreads();
-        tile[lane] = v;
-        tj[lane] = j;
-        tc[lane] = c;
-        __syncthreads();
-        for (int q = 0; q < kBlock; ++q) {
-            const int64_t jj = tj[q];
-            if (jj < 0 || jj == t) continue;
-            const double4 sj = tile[q];
-            const int cc = tc[q];
-            // same operation order as the minimum-image difference:
-            // (x_j - x_i), then the periodic shift
-            const double dx = (sj.x - xi) + (double)(cc / 9 - 1) * L;
-            const double dy = (sj.y - yi) + (double)((cc / 3) % 3 - 1) * L;
-            const double dz = (sj.z - zi) + (double)(cc % 3 - 1) * L;
-            const double s2 = dx * dx + dy * dy + dz * dz;
-            if (!(s2 < rcut2)) continue;
-            if (COUNT) {
-                ++cnt;
-                continue;
+        rcur = readlane64(r, kBlock - 1);
+    };
+    auto sweep = [&](int n) {
+#pragma clang fp contract(off)
+        double tx = 0, ty = 0, tz = 0;
+        if (shifted > 0) {
+            for (int q = 0; q < n; ++q) {
+                const double4 s = tile[q];
+                // (x_j - x_i), then the periodic shift: the order of the
+                // minimum-image difference
+                const double dx = (s.x - xi) + shift[q][0];
+                const double dy = (s.y - yi) + shift[q][1];
+                const double dz = (s.z - zi) + shift[q][2];
+                if (COUNT) cnt += dx * dx + dy * dy + dz * dz < C.rcut2 && tj[q] != (int32_t)t ? 1 : 0;
+                else pair_f64(dx, dy, dz, s.w, C, tx, ty, tz);
             }
-            if (!(s2 > 0)) continue;
-            const double se = sqrt(s2 + eps2);
-            const double f = G * sj.w * split_factor_f64(se / (2.0 * rs)) / (se * se * se);
-            ax += f * dx;
-            ay += f * dy;
-            az += f * dz;
+        } else {
+            for (int q = 0; q < n; ++q) {
+                const double4 s = tile[q];
+                const double dx = s.x - xi, dy = s.y - yi, dz = s.z - zi;
+                if (COUNT) cnt += dx * dx + dy * dy + dz * dz < C.rcut2 && tj[q] != (int32_t)t ? 1 : 0;
+                else pair_f64(dx, dy, dz, s.w, C, tx, ty, tz);
+            }
         }
+        ax += tx;
+        ay += ty;
+        az += tz;
+    };
+    if (s0 < s1) fetch(s0);
+    for (int32_t base = s0; base < s1; base += kBlock) {
+        bool keep = false;
+        const double sx = (double)(pc / 9 - 1) * L;
+        const double sy = (double)((pc / 3) % 3 - 1) * L;
+        const double sz = (double)(pc % 3 - 1) * L;
+        if (pv) {
+            const float vx = (float)((px + sx - ox) * inv_len);
+            const float vy = (float)((py + sy - oy) * inv_len);
+            const float vz = (float)((pz + sz - oz) * inv_len);
+#pragma unroll
+            for (int g = 0; g < GROUPS; ++g) {
+                const float4 c = qb[2 * g], h = qb[2 * g + 1];
+                const float gx = fmaxf(fabsf(vx - c.x) - c.w, 0.f);
+                const float gy = fmaxf(fabsf(vy - c.y) - h.x, 0.f);
+                const float gz = fmaxf(fabsf(vz - c.z) - h.y, 0.f);
+                keep = keep || fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < keep2;
+            }
+        }
+        const uint64_t bal = __ballot(keep), far = __ballot(keep && pc != 13);
+        const int at = count + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+        if (keep) {
+            tile[at] = make_double4(px, py, pz, G * pm);
+            shift[at][0] = sx;
+            shift[at][1] = sy;
+            shift[at][2] = sz;
+            if (COUNT) tj[at] = pj;
+        }
+        count += __popcll(bal);
+        if (far) shifted = count;
+        if (base + kBlock < s1) fetch(base + kBlock);
+        if (count >= kBlock) {
+            wave_sync();
+            sweep(kBlock);
+            wave_sync();
+            count -= kBlock;
+            shifted -= kBlock;
+            if (lane < count) {
+                tile[lane] = tile[kBlock + lane];
+                for (int k = 0; k < 3; ++k) shift[lane][k] = shift[kBlock + lane][k];
+                if (COUNT) tj[lane] = tj[kBlock + lane];
+            }
+            wave_sync();
+        }
+    }
+    if (count > 0) {
+        wave_sync();
+        sweep(count);
     }
     if (COUNT) {
         pcount[item * kBlock + lane] = cnt;
@@ -1050,7 +1206,6 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
         o[2 * kBlock + lane] = az;
     }
 }
-#pragma clang fp contract(on)
 
 __global__ void __launch_bounds__(256) reduce_f64_kernel(ItemArgs ia,
                                                          const double* __restrict__ partial,

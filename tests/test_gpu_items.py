@@ -99,3 +99,26 @@ def test_few_active_targets_per_block(pp, k, variant, persistent, equal):
     on = active != 0
     assert np.array_equal(got[:, on].view(np.uint32), full[:, on].view(np.uint32))
     assert np.all(got[:, ~on] == 7.0)
+
+
+@pytest.mark.parametrize("n,eps", [(1, None), (2, 0.0), (64, None), (65, 0.0), (129, None), (1500, 0.0), (6001, None)])
+def test_f64_pair_arithmetic(pp, oracle_mod, n, eps):
+    """FP64 sums whose lists end in every kind of remainder, with and without
+    softening, coincident particles among them, positions on the faces and
+    boxes small enough that most sources are periodic images.  Per target the
+    error is bounded by the summation (n roundings) and 32 roundings per pair
+    on both sides, relative to the sum of the pairs' magnitudes."""
+    rng = np.random.default_rng(100 + n)
+    p0 = BoxParams.from_mesh(30.0, 12 if n < 2000 else 18)
+    p = W.BoxParams(**{**p0.__dict__, "eps": p0.eps if eps is None else eps})
+    pos = W.mixture(rng, n, p.L, 0.5, max(1, n // 200)) if n > 2 else rng.random((3, n)) * 0.1
+    if n > 64:
+        pos[:, 1] = pos[:, 0]
+        pos[0, 2:6] = 0.0
+        pos[1, 4:8] = np.nextafter(p.L, 0.0)
+    mass = rng.uniform(0.5, 1.5, n)
+    acc = pp.Plan(p, n).accel_f64(dev(pos, torch.float64), dev(mass, torch.float64)).cpu().numpy()
+    ref = oracle_mod.accel(pos, mass, p, pair_abs=True)
+    tol = (64 + 2 * ref["n_inter"]) * 2.0 ** -53 * ref["pair_abs"]
+    err = np.linalg.norm(acc - ref["acc"], axis=0)
+    assert np.all(err <= tol), (float((err / np.maximum(tol, 1e-300)).max()), int(np.argmax(err - tol)))
