@@ -156,6 +156,15 @@ int validate_params(const pp_box_params* p, bool need_poly) {
     return PP_OK;
 }
 
+// One box's constants and offsets, from the kernel's arguments.
+static __global__ void set_box_kernel(BoxDev b, int64_t n, int64_t chunks, BoxDev* __restrict__ box,
+                                      int64_t* __restrict__ poff, int64_t* __restrict__ choff) {
+    box[0] = b;
+    poff[0] = choff[0] = 0;
+    poff[1] = n;
+    choff[1] = chunks;
+}
+
 // ------------------------------------------------------------------ batch --
 struct Batch {
     int nbox = 0;
@@ -213,7 +222,9 @@ struct Batch {
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
     }
 
-    int init(int nb, const pp_box_params* p, const int64_t* n, bool need_poly = true) {
+    // s: the stream the plan's first call uses, when it is known already
+    int init(int nb, const pp_box_params* p, const int64_t* n, bool need_poly = true, hipStream_t s = nullptr,
+             bool wait = true) {
         if (nb < 1) return fail(PP_EINVAL, "need at least one box");
         for (int x = 0; x < nb; ++x) {
             PP_TRY(validate_params(&p[x], need_poly));
@@ -236,8 +247,9 @@ struct Batch {
         if (N > INT32_MAX - 4096) return fail(PP_EINVAL, "too many particles (int32 indices)");
         PP_TRY(box_dev.reserve(sizeof(BoxDev) * nb));
         PP_TRY(poff_dev.reserve(sizeof(int64_t) * (nb + 1)));
-        PP_TRY(upload_boxes());
-        PP_HIP(hipMemcpy(poff_dev.p, poff.data(), sizeof(int64_t) * (nb + 1), hipMemcpyHostToDevice));
+        PP_TRY(upload_boxes(s, wait));
+        if (nb > 1)
+            PP_HIP(hipMemcpy(poff_dev.p, poff.data(), sizeof(int64_t) * (nb + 1), hipMemcpyHostToDevice));
         bd.box = box_dev.as<BoxDev>();
         bd.poff = poff_dev.as<int64_t>();
         bd.nbox = nb;
@@ -257,8 +269,21 @@ struct Batch {
         return PP_OK;
     }
 
-    // The per-box constants, with the lists' cut widened by the skin.
-    int upload_boxes() {
+    // The per-box constants, with the lists' cut widened by the skin.  Those of
+    // one box, and its particle and chunk offsets, travel as arguments of a
+    // kernel on s instead of as blocking copies; `wait` waits for it (the next
+    // call may use another stream).
+    int upload_boxes(hipStream_t s = nullptr, bool wait = true) {
+        if (nbox == 1) {
+            const int64_t chunks = (N + kBlock - 1) / kBlock;
+            PP_TRY(w.choff.reserve(sizeof(int64_t) * 2));
+            w.choff_h = {0, chunks};
+            hipLaunchKernelGGL(set_box_kernel, dim3(1), dim3(1), 0, s, make_boxdev(params[0], 0, N, skin), N, chunks,
+                               box_dev.as<BoxDev>(), poff_dev.as<int64_t>(), w.choff.as<int64_t>());
+            PP_HIP(hipGetLastError());
+            if (wait) PP_HIP(hipStreamSynchronize(s));
+            return PP_OK;
+        }
         std::vector<BoxDev> hb(nbox);
         for (int x = 0; x < nbox; ++x) hb[x] = make_boxdev(params[x], poff[x], poff[x + 1] - poff[x], skin);
         PP_HIP(hipMemcpy(box_dev.p, hb.data(), sizeof(BoxDev) * nbox, hipMemcpyHostToDevice));
@@ -294,18 +319,17 @@ struct Batch {
         reuse_ready = false;
         lists_moved = false;
         w.pos_n = N;
-        PP_TRY(reset_sizes(w, s));
-        PP_TRY(stage_keys(bd, N, pos, w, s));
+        PP_TRY(reset_sizes(nbox, w, s));
+        PP_TRY(stage_keys(bd, N, pos, mass_f, mass_d, w, s));
         PP_TRY(stage_sort(bd, N, w, s));
         if (mass_d) PP_TRY(w.mass_sd.reserve(8 * (N > 0 ? N : 1)));
-        PP_TRY(stage_gather(bd, N, pos, mass_f, mass_d, w, s));
-        if (mass_f) PP_TRY(stage_mass_flags(bd, N, w, s));
-        if (mass_f && !table_ready) {
+        PP_TRY(stage_gather(N, mass_d != nullptr, w, s));
+        if (mass_f && !table_ready && (tune.variant & 8)) {
             PP_TRY(launch_split_table(w, s));
             table_ready = true;
         }
-        PP_TRY(stage_leaves(bd, N, w.keys_s.as<uint64_t>(), w.pos_s.as<double>(), w, s));
-        PP_TRY(stage_trees(bd, N, w, s));
+        PP_TRY(stage_leaves(bd, N, w.keys_s.as<uint64_t>(), w, s));
+        PP_TRY(stage_trees(bd, N, w.pos_s.as<double>(), w, s));
         // monopoles only on the FP32 path: the FP64 yardstick and the pair
         // count keep exact lists
         MonoCfg mc;
@@ -335,10 +359,10 @@ struct Batch {
     int prepare_reuse(const double* pos, const float* mass, hipStream_t s, const uint8_t* active) {
         lists_valid = false;
         evaluated_valid = false;
-        PP_TRY(reset_sizes_reuse(w, s));
+        PP_TRY(reset_sizes_reuse(nbox, w, s));
         PP_TRY(stage_regather(bd, N, pos, mass, pos_ref.as<double>(), 0.5 * skin, w, s));
         PP_TRY(stage_mass_flags(bd, N, w, s));
-        PP_TRY(stage_items(bd, w, s, active));
+        PP_TRY(stage_items(w, s, active));
         lists_mono = false;
         lists_active = active != nullptr;
         lists_moved = true;
@@ -798,7 +822,8 @@ int pp_build_leaves(const uint64_t* sorted_keys, const double* pos_sorted, int64
     if (rc == PP_OK)
         rc = stage_wrap_copy(lv->b.bd, n, pos_sorted, lv->b.w.pos_s.as<double>(), S(stream));
     if (rc == PP_OK)
-        rc = stage_leaves(lv->b.bd, n, sorted_keys, lv->b.w.pos_s.as<double>(), lv->b.w, S(stream));
+        rc = stage_leaves(lv->b.bd, n, sorted_keys, lv->b.w, S(stream));
+    if (rc == PP_OK) rc = stage_trees(lv->b.bd, n, lv->b.w.pos_s.as<double>(), lv->b.w, S(stream));
     if (rc == PP_OK) rc = leaves_to_host(lv->b.bd, lv->b.w, S(stream));
     if (rc != PP_OK) {
         delete lv;
@@ -852,8 +877,7 @@ int pp_near_pairs(pp_leaves* lv, const pp_box_params* p, pp_pairs** out, void* s
     pp_pairs* pr = new (std::nothrow) pp_pairs;
     if (!pr) return fail(PP_ENOMEM, "host allocation failed");
     const BoxDev g = make_boxdev(*p, 0, lv->b.N);
-    int rc = stage_trees(lv->b.bd, lv->b.N, lv->b.w, S(stream));
-    if (rc == PP_OK) rc = trees_to_host(lv->b.bd, lv->b.w, S(stream));
+    int rc = trees_to_host(lv->b.bd, lv->b.w, S(stream));
     if (rc == PP_OK)
         rc = build_canonical_pairs(lv->b.bd, lv->b.w, g.W, g.T, pr->row_cnt, pr->row_ptr, pr->src,
                                    pr->code, pr->scan_ws, &pr->nentries, S(stream));
@@ -915,10 +939,9 @@ static int plan_resize(pp_plan* pl, int64_t n) {
     if (b.poff[1] == n) return PP_OK;
     b.poff[1] = n;
     b.N = n;
-    const BoxDev hb = make_boxdev(b.params[0], 0, n);
-    PP_HIP(hipMemcpy(b.box_dev.p, &hb, sizeof(BoxDev), hipMemcpyHostToDevice));
-    PP_HIP(hipMemcpy(b.poff_dev.p, b.poff.data(), sizeof(int64_t) * 2, hipMemcpyHostToDevice));
-    return PP_OK;
+    b.lists_valid = false;           // the lists were another box's
+    b.reuse_ready = false;
+    return b.upload_boxes();
 }
 
 static int check_accel_args(pp_plan* pl, const void* pos, const void* mass, int64_t n,
@@ -997,15 +1020,17 @@ int pp_accel_scratch(const pp_box_params* p, const double* pos, const float* mas
     int64_t cap_block = 0, cap_range = 0, cap_item = 0;
     int64_t cap_ent[kMaxPasses] = {};
     bool stop2 = false;
+    int start_level = -1;
     for (int attempt = 0; attempt < 32; ++attempt) {
         arena.used = 0;
         Batch b;
-        PP_TRY(b.init(1, p, &n));
+        PP_TRY(b.init(1, p, &n, true, s, false));
         b.w.cap_block = cap_block;
         b.w.cap_range = cap_range;
         b.w.cap_item = cap_item;
-        for (int k = 0; k < kMaxPasses; ++k) b.w.cap_ent[k] = cap_ent[k];
+        for (int k = 0; k < kMaxPasses; ++k) b.w.cap_ent[0][k] = cap_ent[k];
         b.w.stop_at_level2 = stop2;
+        b.w.start_level = start_level;
         PP_TRY(b.prepare(pos, mass, nullptr, s));
         PP_TRY(b.run_f32(acc, s));
         bool again = false;
@@ -1014,8 +1039,9 @@ int pp_accel_scratch(const pp_box_params* p, const double* pos, const float* mas
         cap_block = b.w.cap_block;
         cap_range = b.w.cap_range;
         cap_item = b.w.cap_item;
-        for (int k = 0; k < kMaxPasses; ++k) cap_ent[k] = b.w.cap_ent[k];
+        for (int k = 0; k < kMaxPasses; ++k) cap_ent[k] = b.w.cap_ent[0][k];
         stop2 = b.w.stop_at_level2;
+        start_level = b.w.start_level;
     }
     return fail(PP_ENOMEM, "the list buffers kept growing");
 }

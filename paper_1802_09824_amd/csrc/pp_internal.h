@@ -101,7 +101,7 @@ struct TreeView {
     int64_t cnt[kTreeMaxLevels];
     int64_t loff;
     int32_t nlev;
-    int32_t pad;
+    int32_t start;    // level the list expansion starts from
 };
 
 // FP32 constants of the PP kernel for one box, in the kernel's length unit
@@ -142,6 +142,16 @@ __device__ __forceinline__ int box_of(const int64_t* __restrict__ off, int nbox,
     return lo;
 }
 
+// Orders this wave's LDS accesses around a point.  Every caller works on
+// LDS that only its own wave touches (a workgroup of K waves gives each wave
+// its own slices), and a wave's LDS operations complete in issue order, so
+// no s_barrier is needed.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Device view of a batch shared by the kernels.
 struct BatchDev {
     const BoxDev* box;       // [nbox]
@@ -176,11 +186,11 @@ enum SizeSlot : int {
     kNEntry = 3,        // final entries of the list expansion
     kNLeaf = 4,         // leaves
     kTotalSrc = 5,      // listed sources summed over the blocks
-    kChunk = 6,         // source-list positions per work item (the effective chunk)
+    kStart = 6,         // highest start level of the list expansion over the boxes
     kSkip = 7,          // nonzero: a buffer was too small or an input not finite; the PP kernels return
     kCand = 8,          // (target, listed source) pairs
     kOverflow = 9,      // bit 0: blocks, 1: entries, 2: ranges, 3: items, 4: a list longer than int32,
-                        // 6: a single-pass scan gave up waiting
+                        // 6: a single-pass scan gave up waiting, 7: too few expansion passes
     kBad = 10,          // a non-finite position or mass
     kNeedBlock = 11,
     kNeedRange = 12,
@@ -210,10 +220,12 @@ struct HostBuf {
 struct Work {
     int64_t pos_n = 0;       // particles in the current batch (row stride of pos_s)
     // capacities the list buffers are sized with (grown when a pass reports
-    // a larger need); entries per expansion pass
+    // a larger need); entries by the level an expansion pass ends at
     int64_t cap_block = 0, cap_range = 0, cap_item = 0;
-    int64_t cap_ent[kMaxPasses] = {};
-    int npass = 0;                        // expansion passes of the current lists
+    int64_t cap_ent[2][kMaxPasses] = {};  // exact lists, lists with monopoles
+    bool mono_lists = false;              // the current lists hold monopoles
+    int npass = 0;                        // expansion passes of the current lists (the first included)
+    int start_level = -1;                 // start level of the last call's lists (-1: none yet)
     // the last pass lowers the entries from level 2 to level 1 unless that
     // would need more than kEntryBudget entries; then the depth-first walks
     // start at level 2 (64 leaves each) for the rest of the plan's life
@@ -236,21 +248,19 @@ struct Work {
     const uint8_t* active = nullptr;     // the items' target flags (null: every target)
     DevBuf sort_ws, scan_ws, sort_tmp;
     // leaves
-    DevBuf lam, pmax, smax, level_p, flag, flag_off;
     DevBuf lbegin, lcount, llevel, lprefix, loff_dev;   // leaf boxes: tree_boxes[0 .. nleaf)
     int64_t nleaf = 0;                    // host copies, valid after leaves_to_host
     std::vector<int64_t> loff;            //   or lists_to_host ([nbox + 1])
     // trees
-    DevBuf tree_boxes, tviews, lvl_prefix, tree_total;
+    DevBuf tree_boxes, tviews, lvl_prefix, group_prefix;
     std::vector<TreeView> tv;             // host copy [nbox], valid after trees_to_host
     int max_levels = 0;                   // bound on the tree levels of any box
     // blocks, lists, items (host copies, valid after lists_to_host)
     int64_t nchunk = 0, nblock = 0, nentry = 0, nrange = 0, nitem = 0;
     int64_t candidates = 0;
     int64_t total_src = 0;     // listed sources summed over the blocks
-    int chunk = 0;           // effective chunk of the current items (>= the requested one)
     std::vector<int64_t> choff_h;         // chunk offsets of the boxes (host)
-    DevBuf choff, ccount, coff;
+    DevBuf choff, ccount, cbox, coff;
     DevBuf bstart, bcount, bbox, bboxid;
     DevBuf fent_a, fent_b, fcnt, foff, fmask;
     DevBuf lmask_e, rcnt_e, scnt_e, roff_e, soff_e, eoff;
@@ -264,14 +274,18 @@ struct Work {
 
 // ------------------------------------------------------------- launches --
 // keys_sort.hip
-int stage_keys(const BatchDev& bd, int64_t N, const double* pos, Work& w, hipStream_t s);
-// per-box flag: masses not all equal (equal masses take a shorter pair loop)
+// keys, and per particle its wrapped position and mass as one record; FP32
+// masses (mass_f) also set the boxes' flags of unequal masses (equal masses
+// take a shorter pair loop), cleared by reset_sizes
+int stage_keys(const BatchDev& bd, int64_t N, const double* pos, const float* mass_f, const double* mass_d,
+               Work& w, hipStream_t s);
+// the flags from the masses in key order (a pass that reuses the lists)
 int stage_mass_flags(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
 // out = in wrapped into [0, L) per box (the form every later stage expects)
 int stage_wrap_copy(const BatchDev& bd, int64_t N, const double* in, double* out, hipStream_t s);
 int stage_sort(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
-int stage_gather(const BatchDev& bd, int64_t N, const double* pos, const float* mass_f,
-                 const double* mass_d, Work& w, hipStream_t s);
+// the records in key order: FP64 positions, masses of the type given (f64)
+int stage_gather(int64_t N, bool f64, Work& w, hipStream_t s);
 int sort_workspace(int64_t n, int nbox, int bits, size_t* bytes);
 // workspace bytes of a single-pass scan over n counts (scan.hip)
 int scan_workspace(int64_t n, size_t* bytes);
@@ -302,13 +316,13 @@ int launch_sort_raw(const uint64_t* keys, const int32_t* idx_in, uint64_t* keys_
 // tree.hip  (positions passed here are wrapped: x - L floor(x / L))
 // These stages keep their counts on the device (Work::sizes, the leaf and
 // tree offsets); nothing is read back until the *_to_host calls.
-// Leaves of every box (buffers sized for N leaves).
-int stage_leaves(const BatchDev& bd, int64_t N, const uint64_t* sorted_keys, const double* pos_s,
-                 Work& w, hipStream_t s);
+// Leaves of every box (buffers sized for N leaves), for one box its tree's
+// shape too.
+int stage_leaves(const BatchDev& bd, int64_t N, const uint64_t* sorted_keys, Work& w, hipStream_t s);
 // w.loff and w.nleaf from the device.  Synchronises the stream.
 int leaves_to_host(const BatchDev& bd, Work& w, hipStream_t s);
-// The implicit 8-ary trees over every box's leaves (levels bounded from N).
-int stage_trees(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
+// The leaf boxes and the implicit 8-ary trees over them (after stage_leaves).
+int stage_trees(const BatchDev& bd, int64_t N, const double* pos_s, Work& w, hipStream_t s);
 // w.tv from the device.  Synchronises the stream.
 int trees_to_host(const BatchDev& bd, Work& w, hipStream_t s);
 // Monopole acceptance settings of the list expansion (nodes of level >= 2):
@@ -333,12 +347,12 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
 // Work items of the current lists (after stage_lists, or on their own for a
 // call that reuses the lists): items per block for the given active flags,
 // their offsets, and the final counts.
-int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* active);
-// Zero the count slots at the start of a pass.
-int reset_sizes(Work& w, hipStream_t s);
+int stage_items(Work& w, hipStream_t s, const uint8_t* active);
+// Zero the count slots and the mass flags at the start of a pass.
+int reset_sizes(int nbox, Work& w, hipStream_t s);
 // A pass that reuses the lists: clears the per-pass slots (candidates,
 // moved, skip, bad) and keeps the list counts.
-int reset_sizes_reuse(Work& w, hipStream_t s);
+int reset_sizes_reuse(int nbox, Work& w, hipStream_t s);
 // Positions and masses of a call that reuses the lists, in the stored key
 // order: every particle moves from its reference position (ref, [3][N], the
 // positions the lists were built at) by its minimum-image displacement, so
@@ -351,7 +365,7 @@ int stage_regather(const BatchDev& bd, int64_t N, const double* pos, const float
 // then run again); sets *regrow and *moved when a pass that reused the lists
 // met a particle that moved too far (the lists must be rebuilt); PP_EINVAL
 // when an input was not finite.  Otherwise fills the host copies (nleaf,
-// nblock, nentry, nrange, nitem, candidates, chunk).
+// nblock, nentry, nrange, nitem, candidates).
 int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved = nullptr);
 // Mass and mass-weighted position sums of every tree node (after stage_trees;
 // needs the FP32 masses in key order).

@@ -222,16 +222,6 @@ __device__ __forceinline__ void kahan_add(float& s, float& c, float v) {
     s = t;
 }
 
-// Orders this wave's LDS accesses around a point.  Every caller works on
-// LDS that only its own wave touches (a workgroup of K waves gives each wave
-// its own slices), and a wave's LDS operations complete in issue order, so
-// no s_barrier is needed.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ float readlane_f(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }

@@ -10,8 +10,7 @@
 // consecutive particles (of the same box) containing k shares its top 3l
 // key bits, so
 //   level(k) = 1 + max over s in [k - M, k] of lcp(key[s], key[s + M])
-// (lcp in 3-bit digits, capped at b; 0 when no such run exists).  The
-// sliding maximum uses the van Herk / Gil-Werman block prefix/suffix maxima.
+// (lcp in 3-bit digits, capped at b; 0 when no such run exists).
 //
 // Near lists (sec. 3.3, the N-to-M leaf pairs of the dual tree traversal,
 // restricted to the short range): an implicit 8-ary tree over each box's
@@ -19,7 +18,8 @@
 // space) is walked, pruning subtrees whose integer bounding box is at least
 // r_cut away.  The leaf test is exact integer arithmetic, identical for the
 // canonical list and for the block lists.
-#include "pp_internal.h"
+#include <algorithm>
+#include "lookback.h"
 
 namespace pp {
 namespace {
@@ -48,115 +48,8 @@ __device__ __forceinline__ uint64_t key_prefix(uint64_t key, int level, int bits
     return level == 0 ? 0ull : key >> (3 * (bits - level));
 }
 
-// lamp[s + M] = lcp(key[s], key[s + M]) for s, s + M in one box, else -1.
-__global__ void lam_kernel(BatchDev bd, const uint64_t* __restrict__ keys, int64_t N,
-                           int8_t* __restrict__ lamp) {
-    const int M = bd.leaf_max;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N + M) return;
-    const int64_t s = t - M;
-    int8_t v = -1;
-    if (s >= 0 && s + M < N &&
-        (bd.nbox == 1 || box_of(bd.poff, bd.nbox, s) == box_of(bd.poff, bd.nbox, s + M)))
-        v = (int8_t)common_digits(keys[s], keys[s + M], bd.bits);
-    lamp[t] = v;
-}
-
-// Block prefix and suffix maxima over blocks of W = M + 1 entries.
-__global__ void vhgw_kernel(const int8_t* __restrict__ a, int64_t len, int W,
-                            int8_t* __restrict__ pmax, int8_t* __restrict__ smax) {
-    const int64_t blk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t b0 = blk * W;
-    if (b0 >= len) return;
-    const int64_t b1 = b0 + W < len ? b0 + W : len;
-    int8_t m = -1;
-    for (int64_t i = b0; i < b1; ++i) {
-        m = a[i] > m ? a[i] : m;
-        pmax[i] = m;
-    }
-    m = -1;
-    for (int64_t i = b1 - 1; i >= b0; --i) {
-        m = a[i] > m ? a[i] : m;
-        smax[i] = m;
-    }
-}
-
-__global__ void level_kernel(const int8_t* __restrict__ pmax, const int8_t* __restrict__ smax,
-                             int64_t N, int M, int bits, int8_t* __restrict__ lev) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    // window of lamp indices [k, k + M]
-    const int8_t a = smax[k], b = pmax[k + M];
-    const int m = a > b ? a : b;
-    lev[k] = (int8_t)(m < 0 ? 0 : (m + 1 < bits ? m + 1 : bits));
-}
-
-__global__ void flag_kernel(BatchDev bd, const uint64_t* __restrict__ keys,
-                            const int8_t* __restrict__ lev, int64_t N, int32_t* __restrict__ flag) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    int f = 1;
-    if (k > 0 && (bd.nbox == 1 || box_of(bd.poff, bd.nbox, k) == box_of(bd.poff, bd.nbox, k - 1))) {
-        const int l = lev[k - 1];
-        f = key_prefix(keys[k], l, bd.bits) != key_prefix(keys[k - 1], l, bd.bits);
-    }
-    flag[k] = f;
-}
-
-__global__ void leaf_fill_kernel(const uint64_t* __restrict__ keys, const int8_t* __restrict__ lev,
-                                 const int32_t* __restrict__ flag, const int64_t* __restrict__ off,
-                                 int64_t N, int bits, int64_t* __restrict__ begin,
-                                 int32_t* __restrict__ level, uint64_t* __restrict__ prefix) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N || !flag[k]) return;
-    const int64_t a = off[k];
-    begin[a] = k;
-    level[a] = lev[k];
-    prefix[a] = key_prefix(keys[k], lev[k], bits);
-}
-
-__global__ void leaf_box_kernel(BatchDev bd, const double* __restrict__ pos_s, int64_t N,
-                                const int64_t* __restrict__ begin, const int64_t* __restrict__ sizes,
-                                int32_t* __restrict__ count, IBox* __restrict__ box) {
-    const int64_t m = sizes[kNLeaf];
-    for (int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; a < m;
-         a += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t b0 = begin[a], b1 = a + 1 < m ? begin[a + 1] : N;
-    count[a] = (int32_t)(b1 - b0);
-    const BoxDev& X = bd.box[box_of(bd.poff, bd.nbox, b0)];
-    const uint32_t qmax = (uint32_t)(X.W - 1);
-    IBox B;
-    for (int ax = 0; ax < 3; ++ax) {
-        uint32_t lo = 0xffffffffu, hi = 0;
-        for (int64_t k = b0; k < b1; ++k) {
-            const uint32_t q = quantise_w(pos_s[ax * N + k], X.L, X.qscale, qmax);
-            lo = q < lo ? q : lo;
-            hi = q > hi ? q : hi;
-        }
-        B.lo[ax] = (int32_t)lo;
-        B.hi[ax] = (int32_t)hi + 1;
-    }
-    box[a] = B;
-    }
-}
-
-// First leaf of every box: the first leaf starting at or after poff[x].
-// First leaf of every box (and the leaf total at x = nbox): every box start
-// starts a leaf, so the leaves before box x are the leaf starts before its
-// first particle, the exclusive flag scan at that index.
-__global__ void leaf_offsets_kernel(BatchDev bd, const int64_t* __restrict__ flag_off,
-                                    int64_t* __restrict__ loff, int64_t* __restrict__ sizes) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x > bd.nbox) return;
-    loff[x] = flag_off[bd.poff[x]];
-    if (x == bd.nbox) sizes[kNLeaf] = loff[x];
-}
-
-// Tree shape of every box from its leaf count (one workgroup): level h of
-// box x has cnt_h = ceil(cnt_{h-1} / 8) nodes while cnt_{h-1} > 1.  Level h
-// of all boxes is contiguous, boxes in order: lp[h (nbox + 1) + x] is the
-// number of level-h nodes of the boxes before x, and the levels follow one
-// another; total[0] receives the node count.
+// The shape of one box's tree over c0 leaves: level h has cnt_h =
+// ceil(cnt_{h-1} / 8) nodes while cnt_{h-1} > 1.
 __device__ __forceinline__ int64_t level_count(int64_t c0, int h) {
     int64_t c = c0;
     for (int k = 0; k < h; ++k) {
@@ -166,22 +59,284 @@ __device__ __forceinline__ int64_t level_count(int64_t c0, int h) {
     return c;
 }
 
+// The level the list expansion starts from: the lowest one above the leaves
+// with at most `most` nodes (the only level of a one-leaf tree).
+__device__ __forceinline__ int start_level(int64_t c0, int64_t most) {
+    int64_t c = c0;
+    int h = 0;
+    while (c > 1 && (h == 0 || c > most)) {
+        c = (c + 7) / 8;
+        ++h;
+    }
+    return h;
+}
+
+// Leaves per workgroup of the kernel that builds levels 0 to 3.
+constexpr int kTreeGroup = 512;
+
+// Tree view, per-level prefixes and group prefix of the only box of a batch
+// of one (see tree_views_kernel, which does it for several boxes).
+__device__ void one_tree_view(int64_t c0, int64_t start_nodes, TreeView* tv, int64_t* lp, int64_t* gp,
+                              int64_t* sizes) {
+    int64_t base = 0, c = c0;
+    int nl = 0;
+    for (int h = 0; h < kTreeMaxLevels; ++h) {
+        tv->cnt[h] = c;
+        tv->off[h] = c > 0 ? base : 0;
+        lp[2 * h] = 0;
+        lp[2 * h + 1] = c;
+        if (c > 0) nl = h + 1;
+        base += c;
+        c = c <= 1 ? 0 : (c + 7) / 8;
+    }
+    tv->loff = 0;
+    tv->nlev = nl;
+    tv->start = start_level(c0, start_nodes);
+    gp[0] = 0;
+    gp[1] = (c0 + kTreeGroup - 1) / kTreeGroup;
+    sizes[kStart] = tv->start;
+}
+
+// Leaves of a tile of 256 IPT consecutive particles (key order) of all boxes:
+// lcp(key[s], key[s + M]) of the tile and the M particles before it goes to
+// LDS, its sliding maximum over M + 1 entries by doubling gives the particles'
+// leaf levels, a particle starts a leaf where its prefix at the level of the
+// particle before it differs, and the leaf numbers come from a ballot count,
+// the tile's running sums and the look-back over the earlier tiles.
+// One launch in the place of seven (lcp, block maxima, levels, flags, scan,
+// box offsets, fill): 59 us of kernels on 2.1 M particles became 41, and on
+// 32 k the launches themselves were the cost.
+template <int IPT>
+__global__ void __launch_bounds__(256) leaves_kernel(BatchDev bd, const uint64_t* __restrict__ keys, int64_t N,
+                                                     LbArgs lb, int64_t ntile, int64_t* __restrict__ begin,
+                                                     int32_t* __restrict__ level,
+                                                     uint64_t* __restrict__ prefix,
+                                                     int64_t* __restrict__ loff, int64_t* __restrict__ sizes,
+                                                     int64_t start_nodes, TreeView* __restrict__ tv,
+                                                     int64_t* __restrict__ lp, int64_t* __restrict__ gp) {
+    constexpr int TS = 256 * IPT;
+    constexpr int LEN = TS + 1 + 1024;              // leaf_max is at most 1024
+    __shared__ int8_t lam[2][LEN];
+    __shared__ unsigned s_tile;
+    __shared__ int s_seg[IPT * 4];
+    __shared__ int64_t s_pre;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int M = bd.leaf_max, W = M + 1;
+    lb_clear_other(lb);
+    if (t == 0) s_tile = (unsigned)atomicAdd(lb.cur, 1ull);
+    __syncthreads();
+    const int64_t tile = s_tile;
+    const int64_t t0 = tile * TS;
+    // lam[.][i]: run of M + 1 particles that ends at particle t0 - 1 + i
+    const int len = TS + 1 + M;
+    for (int i = t; i < len; i += 256) {
+        const int64_t e = t0 - 1 + i, s = e - M;
+        int8_t v = -1;
+        if (s >= 0 && e < N && (bd.nbox == 1 || bd.poff[box_of(bd.poff, bd.nbox, s) + 1] > e))
+            v = (int8_t)common_digits(keys[s], keys[e], bd.bits);
+        lam[0][i] = v;
+    }
+    __syncthreads();
+    int cur = 0, span = 1;
+    for (; 2 * span <= W; span *= 2) {
+        for (int i = t; i < len; i += 256) {
+            const int8_t a = lam[cur][i], b = i + span < len ? lam[cur][i + span] : (int8_t)-1;
+            lam[cur ^ 1][i] = a > b ? a : b;
+        }
+        __syncthreads();
+        cur ^= 1;
+    }
+    // level of particle t0 - 1 + i (0 <= i <= TS)
+    auto level_at = [&](int i) {
+        const int a = lam[cur][i], b = lam[cur][i + W - span];
+        const int m = a > b ? a : b;
+        return m < 0 ? 0 : (m + 1 < bd.bits ? m + 1 : bd.bits);
+    };
+    uint64_t starts[IPT];
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        const int i = j * 256 + t;
+        const int64_t k = t0 + i;
+        bool f = false;
+        if (k < N) {
+            f = true;
+            if (k > 0 && (bd.nbox == 1 || bd.poff[box_of(bd.poff, bd.nbox, k)] < k)) {
+                const int l = level_at(i);           // of the particle before
+                f = key_prefix(keys[k], l, bd.bits) != key_prefix(keys[k - 1], l, bd.bits);
+            }
+        }
+        starts[j] = __ballot(f);
+        if (lane == 0) s_seg[j * 4 + wave] = __popcll(starts[j]);
+    }
+    __syncthreads();
+    int64_t agg = 0;
+    for (int k = 0; k < IPT * 4; ++k) agg += s_seg[k];
+    if (wave == 0) {
+        const int64_t ex = lb_tile_prefix<1>(lb, tile, 0, agg, sizes, lane);
+        if (lane == 0) s_pre = ex;
+    }
+    __syncthreads();
+    const int64_t pre = s_pre;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        int64_t a = pre;
+        for (int k = 0; k < j * 4 + wave; ++k) a += s_seg[k];
+        a += __popcll(starts[j] & ((1ull << lane) - 1ull));
+        const int i = j * 256 + t;
+        const int64_t k = t0 + i;
+        if (!(starts[j] >> lane & 1ull)) continue;
+        const int l = level_at(i + 1);
+        begin[a] = k;
+        level[a] = l;
+        prefix[a] = key_prefix(keys[k], l, bd.bits);
+        // every box start starts a leaf, the first one of its box (and of the
+        // empty boxes before it)
+        int x = box_of(bd.poff, bd.nbox, k);
+        if (bd.poff[x] == k) {
+            loff[x] = a;
+            for (; x > 0 && bd.poff[x - 1] == k; --x) loff[x - 1] = a;
+        }
+    }
+    if (tile == ntile - 1 && t == 0) {
+        const int64_t total = pre + agg;
+        sizes[kNLeaf] = total;
+        for (int x = bd.nbox; x >= 0 && bd.poff[x] == N; --x) loff[x] = total;
+        if (bd.nbox == 1) one_tree_view(total, start_nodes, tv, lp, gp, sizes);
+    }
+}
+
+// No particles: no leaves.
+__global__ void no_leaves_kernel(int nbox, int64_t* __restrict__ loff, int64_t* __restrict__ sizes,
+                                 int64_t start_nodes, TreeView* __restrict__ tv, int64_t* __restrict__ lp,
+                                 int64_t* __restrict__ gp) {
+    for (int x = threadIdx.x; x <= nbox; x += blockDim.x) loff[x] = 0;
+    if (threadIdx.x != 0) return;
+    sizes[kNLeaf] = 0;
+    if (nbox == 1) one_tree_view(0, start_nodes, tv, lp, gp, sizes);
+}
+
+// Levels 0 to 3 of every box's tree, one workgroup per kTreeGroup leaves (a
+// whole level-3 node): the leaves' counts and integer boxes from their
+// particles, then the unions of up to 8 nodes, level by level, in LDS.
+// Bound by the particles' loads (48 MB at 2.1 M: 9 us) and their latency; a
+// launch for the leaves and one per level took 72 us there, these levels and
+// the rest in tree_top_kernel take 47, and a small box two launches, not 6.
+// gp: groups of the boxes before each box.
+__global__ void __launch_bounds__(kTreeGroup) leaf_tree_kernel(BatchDev bd, const double* __restrict__ pos_s,
+                                                               int64_t N, const TreeView* __restrict__ tvs,
+                                                               const int64_t* __restrict__ gp,
+                                                               const int64_t* __restrict__ begin,
+                                                               const int64_t* __restrict__ sizes,
+                                                               int32_t* __restrict__ count,
+                                                               IBox* __restrict__ nodes) {
+    __shared__ IBox s_box[kTreeGroup];
+    const int64_t g = blockIdx.x;
+    if (g >= gp[bd.nbox]) return;
+    const int x = box_of(gp, bd.nbox, g);
+    const TreeView& T = tvs[x];
+    const BoxDev& X = bd.box[x];
+    const int t = threadIdx.x;
+    int64_t i = (g - gp[x]) * kTreeGroup + t;        // leaf of the box
+    IBox B;
+    for (int ax = 0; ax < 3; ++ax) {
+        B.lo[ax] = INT32_MAX;
+        B.hi[ax] = INT32_MIN;
+    }
+    if (i < T.cnt[0]) {
+        const int64_t a = T.loff + i, m = sizes[kNLeaf];
+        const int64_t b0 = begin[a], b1 = a + 1 < m ? begin[a + 1] : N;
+        count[a] = (int32_t)(b1 - b0);
+        const uint32_t qmax = (uint32_t)(X.W - 1);
+        uint32_t lo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, hi[3] = {0, 0, 0};
+        for (int64_t k = b0; k < b1; k += 4) {       // four particles' loads in flight (the last one repeats)
+            double w[4][3];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) w[u][ax] = pos_s[ax * N + (k + u < b1 ? k + u : b1 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    const uint32_t q = quantise_w(w[u][ax], X.L, X.qscale, qmax);
+                    lo[ax] = q < lo[ax] ? q : lo[ax];
+                    hi[ax] = q > hi[ax] ? q : hi[ax];
+                }
+        }
+        for (int ax = 0; ax < 3; ++ax) {
+            B.lo[ax] = (int32_t)lo[ax];
+            B.hi[ax] = (int32_t)hi[ax] + 1;
+        }
+        nodes[T.off[0] + i] = B;
+    }
+    s_box[t] = B;
+    __syncthreads();
+    int n = kTreeGroup;
+    for (int h = 1; h <= 3; ++h) {
+        n /= 8;
+        IBox P;
+        if (t < n) {
+            P = s_box[8 * t];
+            for (int c = 1; c < 8; ++c) {
+                const IBox C = s_box[8 * t + c];     // empty past the last node
+                for (int ax = 0; ax < 3; ++ax) {
+                    P.lo[ax] = C.lo[ax] < P.lo[ax] ? C.lo[ax] : P.lo[ax];
+                    P.hi[ax] = C.hi[ax] > P.hi[ax] ? C.hi[ax] : P.hi[ax];
+                }
+            }
+            const int64_t node = (g - gp[x]) * n + t;
+            if (node < T.cnt[h]) nodes[T.off[h] + node] = P;
+        }
+        __syncthreads();
+        if (t < n) s_box[t] = P;
+        __syncthreads();
+    }
+}
+
+// Levels 4 and up, one workgroup per box.
+__global__ void __launch_bounds__(256) tree_top_kernel(const TreeView* __restrict__ tvs,
+                                                       IBox* __restrict__ nodes) {
+    const TreeView& T = tvs[blockIdx.x];
+    for (int h = 4; h < T.nlev; ++h) {
+        const int64_t n = T.cnt[h], nchild = T.cnt[h - 1];
+        const IBox* child = nodes + T.off[h - 1];
+        for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
+            IBox P = child[8 * i];
+            const int64_t e = 8 * i + 8 < nchild ? 8 * i + 8 : nchild;
+            for (int64_t c = 8 * i + 1; c < e; ++c) {
+                const IBox C = child[c];
+                for (int ax = 0; ax < 3; ++ax) {
+                    P.lo[ax] = C.lo[ax] < P.lo[ax] ? C.lo[ax] : P.lo[ax];
+                    P.hi[ax] = C.hi[ax] > P.hi[ax] ? C.hi[ax] : P.hi[ax];
+                }
+            }
+            nodes[T.off[h] + i] = P;
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
+}
+
+// Tree shapes of several boxes from their leaf counts (one workgroup).  Level
+// h of all boxes is contiguous, boxes in order: lp[h (nbox + 1) + x] is the
+// number of level-h nodes of the boxes before x, and the levels follow one
+// another; gp[x]: the kTreeGroup-leaf groups of the boxes before x.
 __global__ void __launch_bounds__(256) tree_views_kernel(const int64_t* __restrict__ loff, int nbox,
                                                          TreeView* __restrict__ tv,
                                                          int64_t* __restrict__ lp,
-                                                         int64_t* __restrict__ total) {
+                                                         int64_t* __restrict__ gp, int64_t start_nodes,
+                                                         int64_t* __restrict__ sizes) {
     __shared__ int64_t wsum[4];
+    __shared__ int s_start;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int per = (nbox + 255) / 256;
     const int x0 = t * per < nbox ? t * per : nbox;
     const int x1 = x0 + per < nbox ? x0 + per : nbox;
-    int64_t base = 0;                     // first node of level h (same in every thread)
-    int h = 0;
-    for (; h < kTreeMaxLevels; ++h) {
-        int64_t sum = 0;
-        for (int x = x0; x < x1; ++x) sum += level_count(loff[x + 1] - loff[x], h);
-        // inclusive scan of the 256 thread sums: inside each wave, then the
-        // four wave totals
+    if (t == 0) s_start = 0;
+    __syncthreads();
+    // exclusive scan of the 256 thread sums: inside each wave, then the four
+    // wave totals
+    auto scan = [&](int64_t sum, int64_t* all) {
         int64_t inc = sum;
         for (int d = 1; d < 64; d <<= 1) {
             const int64_t u = __shfl_up(inc, d);
@@ -189,13 +344,32 @@ __global__ void __launch_bounds__(256) tree_views_kernel(const int64_t* __restri
         }
         if (lane == 63) wsum[wave] = inc;
         __syncthreads();
-        int64_t before = 0, level_total = 0;
+        int64_t before = 0;
+        *all = 0;
         for (int k = 0; k < 4; ++k) {
             if (k < wave) before += wsum[k];
-            level_total += wsum[k];
+            *all += wsum[k];
         }
-        __syncthreads();                  // wsum is rewritten at the next level
-        int64_t acc = before + inc - sum;  // nodes of this level before box x0
+        __syncthreads();                  // wsum is rewritten by the next scan
+        return before + inc - sum;
+    };
+    {
+        int64_t sum = 0, all = 0;
+        for (int x = x0; x < x1; ++x) sum += (loff[x + 1] - loff[x] + kTreeGroup - 1) / kTreeGroup;
+        int64_t acc = scan(sum, &all);
+        for (int x = x0; x < x1; ++x) {
+            gp[x] = acc;
+            acc += (loff[x + 1] - loff[x] + kTreeGroup - 1) / kTreeGroup;
+        }
+        if (t == 0) gp[nbox] = all;
+    }
+    int64_t base = 0;                     // first node of level h (same in every thread)
+    int h = 0;
+    for (; h < kTreeMaxLevels; ++h) {
+        int64_t sum = 0;
+        for (int x = x0; x < x1; ++x) sum += level_count(loff[x + 1] - loff[x], h);
+        int64_t level_total = 0;
+        int64_t acc = scan(sum, &level_total);     // nodes of this level before box x0
         for (int x = x0; x < x1; ++x) {
             const int64_t c0 = loff[x + 1] - loff[x];
             const int64_t c = level_count(c0, h);
@@ -206,7 +380,8 @@ __global__ void __launch_bounds__(256) tree_views_kernel(const int64_t* __restri
                 while (nl < kTreeMaxLevels && level_count(c0, nl) > 0) ++nl;
                 T.nlev = c0 > 0 ? nl : 0;
                 T.loff = loff[x];
-                T.pad = 0;
+                T.start = start_level(c0, start_nodes);
+                atomicMax(&s_start, T.start);
             }
             T.cnt[h] = c;
             T.off[h] = c > 0 ? base + acc : 0;
@@ -225,31 +400,8 @@ __global__ void __launch_bounds__(256) tree_views_kernel(const int64_t* __restri
         }
         if (t == 0) lp[(int64_t)h * (nbox + 1) + nbox] = 0;
     }
-    if (t == 0) total[0] = base;
-}
-
-// Level h >= 1 of every box's tree: node i of box x is the union of its
-// (up to 8) children.  lp = per-box prefix of the level's node counts.
-__global__ void tree_level_kernel(const TreeView* __restrict__ tv, const int64_t* __restrict__ lp,
-                                  int nbox, int h, IBox* __restrict__ nodes) {
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < lp[nbox];
-         g += (int64_t)gridDim.x * blockDim.x) {
-    const int x = box_of(lp, nbox, g);
-    const TreeView& T = tv[x];
-    const int64_t i = g - lp[x];
-    const int64_t nchild = T.cnt[h - 1];
-    const IBox* child = nodes + T.off[h - 1];
-    IBox P = child[8 * i];
-    const int64_t e = 8 * i + 8 < nchild ? 8 * i + 8 : nchild;
-    for (int64_t c = 8 * i + 1; c < e; ++c) {
-        const IBox C = child[c];
-        for (int ax = 0; ax < 3; ++ax) {
-            P.lo[ax] = C.lo[ax] < P.lo[ax] ? C.lo[ax] : P.lo[ax];
-            P.hi[ax] = C.hi[ax] > P.hi[ax] ? C.hi[ax] : P.hi[ax];
-        }
-    }
-    nodes[T.off[h] + i] = P;
-    }
+    __syncthreads();
+    if (t == 0) sizes[kStart] = s_start;
 }
 
 // Mass and mass-weighted position sums of every tree node (x, y, z: sum of
@@ -298,22 +450,22 @@ __global__ void tree_moment_kernel(const TreeView* __restrict__ tv, const int64_
 
 // ------------------------------------------------------------ box tests --
 // Gap along one axis between target [loA, hiA) and source [loB, hiB)
-// shifted by s * W (grid units).
-__device__ __forceinline__ int64_t axis_gap(int64_t loA, int64_t hiA, int64_t loB, int64_t hiB,
-                                            int s, int64_t W) {
-    const int64_t sh = (int64_t)s * W;
-    const int64_t g1 = loB + sh - hiA, g2 = loA - hiB - sh;
-    const int64_t g = g1 > g2 ? g1 : g2;
+// shifted by s * W (grid units).  Coordinates and W are at most 2^21, so
+// gaps fit 32 bits and their squares one 32 x 32 -> 64 bit multiply-add.
+__device__ __forceinline__ int32_t axis_gap(int32_t loA, int32_t hiA, int32_t loB, int32_t hiB, int32_t sh) {
+    const int32_t g1 = loB + sh - hiA, g2 = loA - hiB - sh;
+    const int32_t g = g1 > g2 ? g1 : g2;
     return g > 0 ? g : 0;
 }
+
+__device__ __forceinline__ int64_t square_add(int32_t g, int64_t r) { return (int64_t)g * g + r; }
 
 __device__ __forceinline__ int64_t gap2_shift(const IBox& A, const IBox& B, const int s[3],
                                               int64_t W) {
     int64_t r = 0;
-    for (int ax = 0; ax < 3; ++ax) {
-        const int64_t g = axis_gap(A.lo[ax], A.hi[ax], B.lo[ax], B.hi[ax], s[ax], W);
-        r += g * g;
-    }
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax)
+        r = square_add(axis_gap(A.lo[ax], A.hi[ax], B.lo[ax], B.hi[ax], s[ax] * (int32_t)W), r);
     return r;
 }
 
@@ -322,12 +474,12 @@ __device__ __forceinline__ int64_t gap2_shift(const IBox& A, const IBox& B, cons
 __device__ __forceinline__ int64_t maxd2_shift(const IBox& A, const IBox& B, const int s[3],
                                                int64_t W) {
     int64_t r = 0;
+#pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        const int64_t sh = (int64_t)s[ax] * W;
-        const int64_t d1 = (int64_t)B.hi[ax] + sh - A.lo[ax];
-        const int64_t d2 = (int64_t)A.hi[ax] - B.lo[ax] - sh;
-        const int64_t d = d1 > d2 ? d1 : d2;
-        r += d * d;
+        const int32_t sh = s[ax] * (int32_t)W;
+        const int32_t d1 = B.hi[ax] + sh - A.lo[ax];
+        const int32_t d2 = A.hi[ax] - B.lo[ax] - sh;
+        r = square_add(d1 > d2 ? d1 : d2, r);
     }
     return r;
 }
@@ -359,7 +511,7 @@ __device__ __forceinline__ int64_t gap2_min(const IBox& A, const IBox& B, const 
         int64_t best = INT64_MAX;
         for (int s = -1; s <= 1; ++s) {
             if (!(mask[ax] >> (s + 1) & 1)) continue;
-            const int64_t g = axis_gap(A.lo[ax], A.hi[ax], B.lo[ax], B.hi[ax], s, W);
+            const int64_t g = axis_gap(A.lo[ax], A.hi[ax], B.lo[ax], B.hi[ax], s * (int32_t)W);
             best = g < best ? g : best;
         }
         r += best * best;
@@ -494,107 +646,92 @@ __global__ void canon_kernel(TreeView tv, const IBox* __restrict__ nodes, int64_
 }
 
 // -------------------------------------------------------- target blocks --
-// One wave per chunk of kBlock consecutive particles of one box.  Every
-// lane quantises its particle; if the chunk's bounding box is at most emax
-// grid units wide along every axis (the common case) the chunk is one
-// block.  Otherwise lane 0 walks the chunk and starts a new block whenever
-// adding the next particle would make the box wider than emax.
+// Minimum over the wave, in every lane: DPP steps inside the rows of 16, then
+// across the rows (lane 63 holds the whole).
 __device__ __forceinline__ int32_t wave_min_i(int32_t v) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int32_t o = __shfl_xor(v, off);
-        v = o < v ? o : v;
+#define PP_DPP_MIN(ctrl, rows)                                                             \
+    {                                                                                      \
+        const int32_t o = __builtin_amdgcn_update_dpp(INT32_MAX, v, ctrl, rows, 0xf, false); \
+        v = o < v ? o : v;                                                                 \
     }
-    return v;
-}
-__device__ __forceinline__ int32_t wave_max_i(int32_t v) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int32_t o = __shfl_xor(v, off);
-        v = o > v ? o : v;
-    }
-    return v;
+    PP_DPP_MIN(0x111, 0xf)               // row_shr:1
+    PP_DPP_MIN(0x112, 0xf)               // row_shr:2
+    PP_DPP_MIN(0x114, 0xf)               // row_shr:4
+    PP_DPP_MIN(0x118, 0xf)               // row_shr:8
+    PP_DPP_MIN(0x142, 0xa)               // row_bcast:15
+    PP_DPP_MIN(0x143, 0xc)               // row_bcast:31
+#undef PP_DPP_MIN
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
-template <bool FILL>
-__global__ void __launch_bounds__(64) block_split_kernel(
-    BatchDev bd, const double* __restrict__ pos_s, int64_t N, const int64_t* __restrict__ choff,
-    int64_t nchunk, int32_t* __restrict__ ccount, const int64_t* __restrict__ coff,
-    int32_t* __restrict__ bstart, int32_t* __restrict__ bcount, IBox* __restrict__ box,
-    int32_t* __restrict__ bboxid, int64_t cap) {
-    const int64_t c = blockIdx.x;
-    if (c >= nchunk) return;
-    const int lane = threadIdx.x;
-    const int x = box_of(choff, bd.nbox, c);
-    const BoxDev& X = bd.box[x];
-    const uint32_t qmax = (uint32_t)(X.W - 1);
-    const int64_t k0 = X.poff + (c - choff[x]) * kBlock;
+// One wave per chunk of kBlock consecutive particles of one box.  Every lane
+// quantises its particle; if the chunk's bounding box is at most emax grid
+// units wide along every axis (the common case) the chunk is one block.
+// Otherwise lane 0 walks the chunk and starts a new block whenever adding the
+// next particle would make the box wider than emax.
+struct Chunk {
+    int64_t k0, k1;                      // its particles
+    int x;                               // its box
+};
+__device__ __forceinline__ Chunk chunk_of(const BatchDev& bd, const int64_t* __restrict__ choff, int64_t c) {
+    Chunk r;
+    r.x = box_of(choff, bd.nbox, c);
+    const BoxDev& X = bd.box[r.x];
+    r.k0 = X.poff + (c - choff[r.x]) * kBlock;
     const int64_t kend = X.poff + X.n;
-    const int64_t k1 = k0 + kBlock < kend ? k0 + kBlock : kend;
-    const int64_t k = k0 + lane;
-    const bool valid = k < k1;
-    __shared__ int32_t qs[3][kBlock];
-    int32_t lo[3], hi[3];
+    r.k1 = r.k0 + kBlock < kend ? r.k0 + kBlock : kend;
+    return r;
+}
+
+// The chunk's bounding box; whether it is one block.
+__device__ __forceinline__ bool chunk_fits(const BoxDev& X, const double* __restrict__ pos_s, int64_t N,
+                                           const Chunk& ch, IBox& B) {
+    const uint32_t qmax = (uint32_t)(X.W - 1);
+    const int64_t k = ch.k0 + (threadIdx.x & (kBlock - 1));
+    const bool valid = k < ch.k1;
+    double w[3];
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) w[ax] = valid ? pos_s[ax * N + k] : 0.0;
+    bool fits = true;
+#pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
-        const int32_t q = valid ? (int32_t)quantise_w(pos_s[ax * N + k], X.L, X.qscale, qmax) : 0;
-        qs[ax][lane] = q;
-        lo[ax] = wave_min_i(valid ? q : INT32_MAX);
-        hi[ax] = wave_max_i(valid ? q + 1 : INT32_MIN);
+        const int32_t q = (int32_t)quantise_w(w[ax], X.L, X.qscale, qmax);
+        B.lo[ax] = wave_min_i(valid ? q : INT32_MAX);
+        B.hi[ax] = -wave_min_i(valid ? -q - 1 : INT32_MAX);
+        fits = fits && (int64_t)(B.hi[ax] - B.lo[ax]) <= X.emax;
     }
-    const bool fits = (int64_t)(hi[0] - lo[0]) <= X.emax && (int64_t)(hi[1] - lo[1]) <= X.emax &&
-                      (int64_t)(hi[2] - lo[2]) <= X.emax;
-    if (fits) {
-        if (lane == 0) {
-            if (FILL) {
-                const int64_t o = coff[c];
-                if (o >= cap) return;          // too many blocks: reported by the count
-                bstart[o] = (int32_t)k0;
-                bcount[o] = (int32_t)(k1 - k0);
-                IBox B;
-                for (int ax = 0; ax < 3; ++ax) {
-                    B.lo[ax] = lo[ax];
-                    B.hi[ax] = hi[ax];
-                }
-                box[o] = B;
-                bboxid[o] = x;
-            } else {
-                ccount[c] = 1;
-            }
-        }
-        return;
-    }
-    __syncthreads();
-    if (lane != 0) return;
-    int64_t o = FILL ? coff[c] : 0;
+    return fits;
+}
+
+// The walk of a wide chunk: the number of its blocks (lane 0), each handed to
+// write(number, first particle, end, box).  qs: this wave's LDS.
+template <class Write>
+__device__ __forceinline__ int32_t chunk_walk(const BoxDev& X, const double* __restrict__ pos_s, int64_t N,
+                                              const Chunk& ch, int32_t (*qs)[kBlock], Write&& write) {
+    const int lane = threadIdx.x & (kBlock - 1);
+    const uint32_t qmax = (uint32_t)(X.W - 1);
+    const bool valid = ch.k0 + lane < ch.k1;
+    wave_sync();                         // lane 0 is done with the previous chunk
+    for (int ax = 0; ax < 3; ++ax)
+        qs[ax][lane] = valid ? (int32_t)quantise_w(pos_s[ax * N + ch.k0 + lane], X.L, X.qscale, qmax) : 0;
+    wave_sync();
     int32_t nb = 0;
-    int64_t start = k0;
+    if (lane != 0) return 0;
+    int64_t start = ch.k0;
     IBox B;
-    auto emit = [&](int64_t e) {
-        if (FILL && o + nb < cap) {
-            bstart[o + nb] = (int32_t)start;
-            bcount[o + nb] = (int32_t)(e - start);
-            box[o + nb] = B;
-            bboxid[o + nb] = x;
-        }
-        ++nb;
-    };
-    for (int64_t kk = k0; kk < k1; ++kk) {
-        const int l = (int)(kk - k0);
+    for (int64_t kk = ch.k0; kk < ch.k1; ++kk) {
+        const int l = (int)(kk - ch.k0);
         const int32_t q[3] = {qs[0][l], qs[1][l], qs[2][l]};
-        if (kk == start) {
-            for (int ax = 0; ax < 3; ++ax) {
-                B.lo[ax] = q[ax];
-                B.hi[ax] = q[ax] + 1;
-            }
-            continue;
-        }
         IBox U = B;
-        bool wide = false;
-        for (int ax = 0; ax < 3; ++ax) {
-            U.lo[ax] = q[ax] < U.lo[ax] ? q[ax] : U.lo[ax];
-            U.hi[ax] = q[ax] + 1 > U.hi[ax] ? q[ax] + 1 : U.hi[ax];
-            wide |= (int64_t)(U.hi[ax] - U.lo[ax]) > X.emax;
-        }
+        bool wide = kk == ch.k0;
+        if (!wide)
+            for (int ax = 0; ax < 3; ++ax) {
+                U.lo[ax] = q[ax] < U.lo[ax] ? q[ax] : U.lo[ax];
+                U.hi[ax] = q[ax] + 1 > U.hi[ax] ? q[ax] + 1 : U.hi[ax];
+                wide |= (int64_t)(U.hi[ax] - U.lo[ax]) > X.emax;
+            }
         if (wide) {
-            emit(kk);
+            if (kk > ch.k0) write(nb++, start, kk, B);
             start = kk;
             for (int ax = 0; ax < 3; ++ax) {
                 B.lo[ax] = q[ax];
@@ -604,16 +741,130 @@ __global__ void __launch_bounds__(64) block_split_kernel(
             B = U;
         }
     }
-    emit(k1);
-    if (!FILL) ccount[c] = nb;
+    write(nb++, start, ch.k1, B);
+    return nb;
+}
+
+struct BlockOut {
+    int32_t* bstart;
+    int32_t* bcount;
+    IBox* box;
+    int32_t* bboxid;
+    int64_t cap;
+    __device__ __forceinline__ void put(int64_t at, int64_t from, int64_t to, const IBox& B, int x) const {
+        if (at >= cap) return;           // too many blocks: reported by the count
+        bstart[at] = (int32_t)from;
+        bcount[at] = (int32_t)(to - from);
+        box[at] = B;
+        bboxid[at] = x;
+    }
+};
+
+// Many chunks: a counting launch that leaves every chunk's box (in the
+// `cbox`) beside its number of blocks, a scan, and a writing launch that
+// reads positions again for the wide chunks only.  (2.1 M particles: 59 us of
+// kernels, 62 when both launches read all positions, 74 in the one-launch form
+// below, whose workgroups wait for one another.)
+template <bool FILL>
+__global__ void __launch_bounds__(256) block_split_kernel(BatchDev bd, const double* __restrict__ pos_s, int64_t N,
+                                                          const int64_t* __restrict__ choff, int64_t nchunk,
+                                                          int32_t* __restrict__ ccount,
+                                                          const int64_t* __restrict__ coff,
+                                                          IBox* __restrict__ cbox, BlockOut out) {
+    __shared__ int32_t qs[256 / kBlock][3][kBlock];
+    const int wave = threadIdx.x / kBlock;
+    const bool first = (threadIdx.x & (kBlock - 1)) == 0;
+    const int64_t c = (int64_t)blockIdx.x * (256 / kBlock) + wave;
+    if (c >= nchunk) return;
+    const Chunk ch = chunk_of(bd, choff, c);
+    const BoxDev& X = bd.box[ch.x];
+    if (!FILL) {
+        IBox B;
+        int32_t nb = 1;
+        if (!chunk_fits(X, pos_s, N, ch, B))
+            nb = chunk_walk(X, pos_s, N, ch, qs[wave], [](int32_t, int64_t, int64_t, const IBox&) {});
+        if (!first) return;
+        ccount[c] = nb;
+        cbox[c] = B;
+        return;
+    }
+    const int64_t o = coff[c];
+    if (ccount[c] == 1) {
+        if (first) out.put(o, ch.k0, ch.k1, cbox[c], ch.x);
+        return;
+    }
+    chunk_walk(X, pos_s, N, ch, qs[wave], [&](int32_t i, int64_t from, int64_t to, const IBox& B) {
+        out.put(o + i, from, to, B, ch.x);
+    });
+}
+
+// Few chunks (kFewChunks): one launch counts, scans (running sums of the workgroup and
+// look-back over the earlier ones) and writes.
+constexpr int kSplitWaves = 8;
+
+__global__ void __launch_bounds__(64 * kSplitWaves) block_split_small_kernel(
+    BatchDev bd, const double* __restrict__ pos_s, int64_t N, const int64_t* __restrict__ choff,
+    int64_t nchunk, LbArgs lb, int64_t ntile, int64_t* __restrict__ coff, int64_t* __restrict__ sizes,
+    BlockOut out) {
+    __shared__ int32_t qs[kSplitWaves][3][kBlock];
+    __shared__ int32_t s_cnt[kSplitWaves];
+    __shared__ unsigned s_tile;
+    __shared__ int64_t s_pre;
+    const int lane = threadIdx.x & (kBlock - 1), wave = threadIdx.x / kBlock;
+    lb_clear_other(lb);
+    if (threadIdx.x == 0) s_tile = (unsigned)atomicAdd(lb.cur, 1ull);
+    __syncthreads();
+    const int64_t tile = s_tile, c = tile * kSplitWaves + wave;
+    const bool any = c < nchunk;
+    Chunk ch{};
+    IBox B;
+    bool fits = false;
+    int32_t nb = 0;
+    if (any) {
+        ch = chunk_of(bd, choff, c);
+        fits = chunk_fits(bd.box[ch.x], pos_s, N, ch, B);
+        nb = fits ? 1
+                  : chunk_walk(bd.box[ch.x], pos_s, N, ch, qs[wave], [](int32_t, int64_t, int64_t, const IBox&) {});
+    }
+    if (lane == 0) s_cnt[wave] = nb;
+    __syncthreads();
+    if (wave == 0) {
+        int64_t agg = 0;
+        for (int k = 0; k < kSplitWaves; ++k) agg += s_cnt[k];
+        const int64_t ex = lb_tile_prefix<1>(lb, tile, 0, agg, sizes, lane);
+        if (lane == 0) {
+            s_pre = ex;
+            if (tile == ntile - 1) {
+                const int64_t total = ex + agg;
+                coff[nchunk] = total;
+                sizes[kNeedBlock] = total;
+                sizes[kNBlock] = total < out.cap ? total : out.cap;
+                if (total > out.cap) atomicOr(reinterpret_cast<unsigned long long*>(sizes + kOverflow), 1ull);
+            }
+        }
+    }
+    __syncthreads();
+    if (!any) return;
+    int64_t o = s_pre;
+    for (int k = 0; k < wave; ++k) o += s_cnt[k];
+    if (lane == 0) coff[c] = o;
+    if (fits) {
+        if (lane == 0) out.put(o, ch.k0, ch.k1, B, ch.x);
+        return;
+    }
+    chunk_walk(bd.box[ch.x], pos_s, N, ch, qs[wave], [&](int32_t i, int64_t from, int64_t to, const IBox& U) {
+        out.put(o + i, from, to, U, ch.x);
+    });
 }
 
 // ----------------------------------------------------------- block lists --
 // A node passes for target box A under shift s when its box is closer than
 // r_cut (gap^2 < T); it is *inside* when even its farthest point is
 // (maxdist^2 < T), and then every leaf under it passes, so the node's whole
-// leaf interval is listed without descending.  The walk is level-synchronous
-// from each box's root down to level 2 over all (block, shift, node) entries
+// leaf interval is listed without descending.  One wave per block
+// first tests the nodes of the box's start level (TreeView::start, few nodes)
+// and those above them; the walk is then level-synchronous down to level 2
+// over all (block, shift, node) entries
 // at once (one thread per entry, children written in order so entries stay
 // sorted by block, shift, node); then one thread per entry walks its
 // subtree (at most 64 leaves) depth-first, testing the 8 children of a node
@@ -665,50 +916,175 @@ __device__ __forceinline__ void expand2(const TreeView& tv, const IBox* nodes, i
     }
 }
 
-template <bool FILL>
-__global__ void bfs_root_kernel(BatchDev bd, const TreeView* __restrict__ tvs,
-                                const IBox* __restrict__ nodes, const IBox* __restrict__ bbox,
-                                const int32_t* __restrict__ bboxid, const int64_t* __restrict__ sizes,
-                                int64_t cap_in, int32_t* __restrict__ cnt,
-                                const int64_t* __restrict__ off, FEntry* __restrict__ out,
-                                int64_t cap_out, MonoDev mono) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= cap_in) return;
-    if (b >= sizes[kNBlock]) {
-        if (!FILL) cnt[b] = 0;
-        return;
-    }
-    const int x = bboxid[b];
-    const TreeView& tv = tvs[x];
-    const int64_t W = bd.box[x].W, T = bd.box[x].T;
-    const IBox A = bbox[b];
-    int mask[3];
-    allowed_shifts(A, W, T, mask);
-    const int top = tv.nlev - 1;
-    const IBox R = nodes[tv.off[top]];
-    int64_t o = FILL ? off[b] : 0;
+// The first entries of a block: for every allowed shift, the nodes of the
+// box's start level that pass, 64 at a time and in order.  A node that passes
+// has ancestors that pass, so those need no test of their own but for
+// monopoles: then they are tested from the root down, and an accepted one
+// becomes the entry itself, written by its first node of the start level.  The
+// entries are those of a walk from the root, which took two kernels and a scan
+// per level.
+//
+// One wave walks the units (allowed shift, 64 nodes) from u0 to u1 - 1 of
+// block b and returns the number of entries, which it writes from number o on
+// when `fill`.  With KEEP, the first KEEP units' ballots of the counting walk
+// stay in `keep` (LDS) for the writing one, which then visits the passing nodes
+// only.
+template <int KEEP>
+__device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& X, const IBox* __restrict__ nodes,
+                                              const IBox& A, int64_t b, const int mask[3], int u0, int u1,
+                                              bool fill, int64_t o, FEntry* __restrict__ out, int64_t cap_out,
+                                              const MonoDev& mono, uint64_t* keep) {
+    const int lane = threadIdx.x & (kBlock - 1);
+    const int64_t W = X.W, T = X.T;
+    const int top = tv.nlev - 1, start = tv.start;
+    const int64_t n0 = tv.cnt[start];
+    const int per = (int)((n0 + kBlock - 1) / kBlock);               // units per shift
+    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
     int32_t c = 0;
-    for (int sc = 0; sc < 27; ++sc) {
+    int u = 0;
+    for (int sc = 0; sc < 27 && u < u1; ++sc) {
         int s[3];
         decode_shift(sc, s);
         if (!shift_allowed(mask, s)) continue;
-        if (!(gap2_shift(A, R, s, W) < T)) continue;
-        if (FILL) {
-            FEntry e;
-            e.blk = (int32_t)b;
-            e.node = 0;
-            e.sc = (uint8_t)sc;
-            e.lev = (uint8_t)top;
-            e.inside = maxd2_shift(A, R, s, W) < T;
-            e.mono = (mono.theta2 > 0.0 || mono.alpha > 0.0) && top >= kMonoMinLevel &&
-                     accept_monopole(A, R, s, W, mono, tv.off[top], b, bd.box[x].G, bd.box[x].cell);
-            if (o < cap_out) out[o] = e;
-            ++o;
-        } else {
-            ++c;
+        if (u + per <= u0) {
+            u += per;
+            continue;
+        }
+        for (int i = 0; i < per; ++i, ++u) {
+            if (u < u0 || u >= u1) continue;
+            const bool kept = u - u0 < KEEP;
+            uint64_t known = ~0ull;
+            if (fill && kept) {
+                known = keep[u - u0];
+                if (known == 0) continue;
+            }
+            const int64_t node = (int64_t)i * kBlock + lane;
+            FEntry E{};
+            bool emit = false;
+            // the 64 nodes' common ancestor first (its box holds theirs)
+            if ((fill && kept) || start + 2 > top || gap2_shift(A, nodes[tv.off[start + 2] + i], s, W) < T)
+                for (int h = mono_on ? top : start; h >= start && node < n0 && (known >> lane & 1ull); --h) {
+                    const int64_t up = node >> (3 * (h - start));
+                    const IBox R = nodes[tv.off[h] + up];
+                    if (!(gap2_shift(A, R, s, W) < T)) break;
+                    const bool taken = mono_on && h >= kMonoMinLevel &&
+                                       accept_monopole(A, R, s, W, mono, tv.off[h] + up, b, X.G, X.cell);
+                    if (h > start && !taken) continue;
+                    E.blk = (int32_t)b;
+                    E.node = (int32_t)up;
+                    E.sc = (uint8_t)sc;
+                    E.lev = (uint8_t)h;
+                    E.inside = fill && maxd2_shift(A, R, s, W) < T;
+                    E.mono = taken;
+                    emit = up << (3 * (h - start)) == node;
+                    break;
+                }
+            const uint64_t bal = __ballot(emit);
+            if (KEEP > 0 && !fill && kept && lane == 0) keep[u - u0] = bal;
+            if (fill) {
+                const int64_t at = o + c + __popcll(bal & ((1ull << lane) - 1ull));
+                if (emit && at < cap_out) out[at] = E;
+            }
+            c += __popcll(bal);
         }
     }
-    if (!FILL) cnt[b] = c;
+    return c;
+}
+
+// A box that every lane holds alike, in scalar registers.
+__device__ __forceinline__ IBox uniform_box(const IBox& B) {
+    IBox r;
+    for (int ax = 0; ax < 3; ++ax) {
+        r.lo[ax] = __builtin_amdgcn_readfirstlane(B.lo[ax]);
+        r.hi[ax] = __builtin_amdgcn_readfirstlane(B.hi[ax]);
+    }
+    return r;
+}
+
+__device__ __forceinline__ int start_units(const TreeView& tv, const int mask[3]) {
+    return __popc(mask[0]) * __popc(mask[1]) * __popc(mask[2]) * (int)((tv.cnt[tv.start] + kBlock - 1) / kBlock);
+}
+
+// Large boxes: one wave per block, a counting and a writing launch around a
+// scan.
+template <bool FILL>
+__global__ void __launch_bounds__(256) start_kernel(BatchDev bd, const TreeView* __restrict__ tvs,
+                                                    const IBox* __restrict__ nodes,
+                                                    const IBox* __restrict__ bbox,
+                                                    const int32_t* __restrict__ bboxid,
+                                                    const int64_t* __restrict__ sizes, int64_t cap_in,
+                                                    int32_t* __restrict__ cnt, const int64_t* __restrict__ off,
+                                                    FEntry* __restrict__ out, int64_t cap_out, MonoDev mono) {
+    const int64_t b = (int64_t)blockIdx.x * (256 / kBlock) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBlock);
+    if (b >= cap_in) return;
+    const bool first = (threadIdx.x & (kBlock - 1)) == 0;
+    if (b >= sizes[kNBlock]) {
+        if (!FILL && first) cnt[b] = 0;
+        return;
+    }
+    const int x = __builtin_amdgcn_readfirstlane(bboxid[b]);
+    const IBox A = uniform_box(bbox[b]);
+    int mask[3];
+    allowed_shifts(A, bd.box[x].W, bd.box[x].T, mask);
+    const int32_t c = start_walk<0>(tvs[x], bd.box[x], nodes, A, b, mask, 0, start_units(tvs[x], mask), FILL,
+                                    FILL ? off[b] : 0, out, cap_out, mono, nullptr);
+    if (!FILL && first) cnt[b] = c;
+}
+
+// Small boxes: kStartSplit waves share a block, each a stretch of its units (a
+// small box has few blocks and many units: 32 k particles took 50 us with a
+// wave per block, 30 so), and one launch counts, scans (look-back over the
+// workgroups) and writes.  With many workgroups the look-back costs more than
+// the launches it saves (2.1 M particles: 175 us against 96).
+constexpr int kStartWaves = 8, kStartSplit = 4, kStartKeep = 48;
+
+__global__ void __launch_bounds__(64 * kStartWaves) start_small_kernel(
+    BatchDev bd, const TreeView* __restrict__ tvs, const IBox* __restrict__ nodes,
+    const IBox* __restrict__ bbox, const int32_t* __restrict__ bboxid, LbArgs lb, int64_t ntile,
+    int64_t* sizes, FEntry* __restrict__ out, int64_t cap_out, int slot2, MonoDev mono) {
+    __shared__ unsigned s_tile;
+    __shared__ int32_t s_cnt[kStartWaves];
+    __shared__ uint64_t s_keep[kStartWaves][kStartKeep];
+    __shared__ int64_t s_pre;
+    const int lane = threadIdx.x & (kBlock - 1), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kBlock);
+    lb_clear_other(lb);
+    if (threadIdx.x == 0) s_tile = (unsigned)atomicAdd(lb.cur, 1ull);
+    __syncthreads();
+    const int64_t tile = __builtin_amdgcn_readfirstlane((int)s_tile);
+    const int64_t b = tile * (kStartWaves / kStartSplit) + wave / kStartSplit;
+    const bool any = b < sizes[kNBlock];
+    const int x = any ? __builtin_amdgcn_readfirstlane(bboxid[b]) : 0;
+    IBox A{};
+    int mask[3] = {0, 0, 0};
+    if (any) {
+        A = uniform_box(bbox[b]);
+        allowed_shifts(A, bd.box[x].W, bd.box[x].T, mask);
+    }
+    const int units = start_units(tvs[x], mask), w = wave % kStartSplit;
+    const int u0 = units * w / kStartSplit, u1 = units * (w + 1) / kStartSplit;
+    const int32_t mine = start_walk<kStartKeep>(tvs[x], bd.box[x], nodes, A, b, mask, u0, u1, false, 0, out,
+                                                cap_out, mono, s_keep[wave]);
+    if (lane == 0) s_cnt[wave] = mine;
+    __syncthreads();
+    if (wave == 0) {
+        int64_t agg = 0;
+        for (int k = 0; k < kStartWaves; ++k) agg += s_cnt[k];
+        const int64_t ex = lb_tile_prefix<1>(lb, tile, 0, agg, sizes, lane);
+        if (lane == 0) {
+            s_pre = ex;
+            if (tile == ntile - 1) {
+                const int64_t total = ex + agg, kept = total < cap_out ? total : cap_out;
+                sizes[kNeedEntry0] = total;
+                sizes[kEntry0] = kept;
+                if (slot2 >= 0) sizes[slot2] = kept;
+                if (total > cap_out) atomicOr(reinterpret_cast<unsigned long long*>(sizes + kOverflow), 2ull);
+            }
+        }
+    }
+    __syncthreads();
+    int64_t o = s_pre;
+    for (int k = 0; k < wave; ++k) o += s_cnt[k];
+    start_walk<kStartKeep>(tvs[x], bd.box[x], nodes, A, b, mask, u0, u1, true, o, out, cap_out, mono, s_keep[wave]);
 }
 
 // One level down: entries above the DFS level that are not inside are
@@ -821,8 +1197,9 @@ __device__ void entry_ranges(const BatchDev& bd, const TreeView* __restrict__ tv
     int64_t last = (((int64_t)E.node + 1) << (3 * E.lev)) - 1;
     if (last > nleaf - 1) last = nleaf - 1;
     const bool walk_inside = mono.theta2 > 0.0 || mono.alpha > 0.0;   // inside nodes are opened too
-    if (E.mono) {
-        // a monopole: no source ranges
+    if (E.mono || (E.lev > kDfsLevel && (!E.inside || walk_inside))) {
+        // a monopole: no source ranges; a node above the walk's reach: the
+        // pass runs again with more expansion passes (finish_sizes)
     } else if (E.lev == 0 || (E.inside && !walk_inside)) {
         emit(first, last);
     } else {
@@ -917,17 +1294,39 @@ __global__ void ranges_count_kernel(BatchDev bd, const TreeView* __restrict__ tv
     }
 }
 
-// Per-block range offsets and list lengths; flags a list longer than int32.
-__global__ void block_sum_kernel(const int64_t* __restrict__ eoff, const int64_t* __restrict__ roff_e,
+// First entry of every block (entries are sorted by block), and from it the
+// block's first range and its list length; flags a list longer than int32.
+__global__ void block_sum_kernel(const FEntry* __restrict__ ent, const int64_t* __restrict__ roff_e,
                                  const int64_t* __restrict__ soff_e, int64_t* __restrict__ sizes,
-                                 int64_t cap_block, int64_t* __restrict__ roff,
+                                 int64_t cap_block, int64_t* __restrict__ eoff, int64_t* __restrict__ roff,
                                  int32_t* __restrict__ slen) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nblock = sizes[kNBlock];
+    const int64_t nblock = sizes[kNBlock], F = sizes[kNEntry];
     if (b > nblock || b > cap_block) return;
-    roff[b] = roff_e[eoff[b]];
+    int64_t lo = 0, hi = F;             // first e with ent[e].blk >= b
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (ent[mid].blk < b) lo = mid + 1;
+        else hi = mid;
+    }
+    eoff[b] = lo;
+    roff[b] = roff_e[lo];
     if (b == nblock) return;
-    const int64_t len = soff_e[eoff[b + 1]] - soff_e[eoff[b]];
+    // the block's end: its entries are few, so the next block is found by
+    // doubling from its first
+    int64_t step = 64, end = lo;
+    while (end + step < F && ent[end + step].blk <= b) {
+        end += step;
+        step *= 2;
+    }
+    hi = end + step < F ? end + step : F;
+    lo = end;                           // first e >= lo with ent[e].blk > b
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (ent[mid].blk <= b) lo = mid + 1;
+        else hi = mid;
+    }
+    const int64_t len = soff_e[lo] - soff_e[eoff[b]];
     if (len > INT32_MAX) atomicOr(reinterpret_cast<unsigned long long*>(sizes + kOverflow), 16ull);
     slen[b] = (int32_t)(len < INT32_MAX ? len : INT32_MAX);
 }
@@ -956,58 +1355,37 @@ __global__ void ranges_fill_kernel(BatchDev bd, const TreeView* __restrict__ tvs
                        rcode, mono, roff_e[e], soff_e[e] - soff_e[eoff[E.blk]], cap_range, nr, tot, m0, m1);
 }
 
-// First entry of every block (entries are sorted by block).
-__global__ void block_entry_kernel(const FEntry* __restrict__ ent, const int64_t* __restrict__ sizes,
-                                   int64_t cap_block, int64_t* __restrict__ eoff) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nblock = sizes[kNBlock], F = sizes[kNEntry];
-    if (b > nblock || b > cap_block) return;
-    int64_t lo = 0, hi = F;             // first e with ent[e].blk >= b
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (ent[mid].blk < b) lo = mid + 1;
-        else hi = mid;
-    }
-    eoff[b] = lo;
-}
-
-// Listed sources in all (sum of the block list lengths) and the effective
-// chunk: the requested one, or larger when the item partial sums (3 x 64
+// The chunk of a box: the requested one, or larger when the item partial sums (3 x 64
 // floats per item) would pass max_items items.  With `adapt` a small box gets
 // a smaller one of its own (see kSmallBox); it depends on that box alone, so a
 // box is cut the same way in a batch and by itself.
-__global__ void __launch_bounds__(256) chunk_kernel(const int64_t* __restrict__ soff_e,
-                                                    const int64_t* __restrict__ eoff,
-                                                    const int64_t* __restrict__ coff,
-                                                    const int64_t* __restrict__ choff, int nbox,
-                                                    int64_t* __restrict__ sizes, int64_t chunk_req,
-                                                    int64_t max_items, int adapt,
-                                                    int32_t* __restrict__ box_chunk) {
-    const int64_t total = soff_e[sizes[kNEntry]];
-    int64_t chunk = chunk_req;
-    const int64_t need = (total + max_items - 1) / max_items;
+struct ChunkArgs {
+    const int64_t* soff_e;
+    const int64_t* eoff;
+    const int64_t* coff;
+    const int64_t* choff;
+    int64_t chunk_req, max_items;
+    int adapt;
+};
+__device__ int64_t box_chunk_of(const ChunkArgs& A, const int64_t* __restrict__ sizes, int x) {
+    const int64_t total = A.soff_e[sizes[kNEntry]];
+    int64_t chunk = A.chunk_req;
+    const int64_t need = (total + A.max_items - 1) / A.max_items;
     if (need > chunk) chunk = ((need + kBlock - 1) / kBlock) * kBlock;
     if (chunk > INT32_MAX / 2) chunk = INT32_MAX / 2;
-    if (threadIdx.x == 0) {
-        sizes[kTotalSrc] = total;
-        sizes[kChunk] = chunk;
-    }
-    const int64_t nblock = sizes[kNBlock];
-    for (int x = threadIdx.x; x < nbox; x += blockDim.x) {
-        int64_t c = chunk;
-        if (adapt) {
-            const int64_t b0 = coff[choff[x]], b1 = coff[choff[x + 1]];
-            const int64_t own = soff_e[eoff[b1 < nblock ? b1 : nblock]] - soff_e[eoff[b0 < nblock ? b0 : nblock]];
-            if (own < kSmallBox) {
-                const double root = cbrt((double)own);
-                int64_t few = (int64_t)(kChunkScale * root * root / kBlock + 0.5) * kBlock;
-                const int64_t floor_ = own < kTinyBox ? kTinyChunk : kSmallChunk;
-                if (few < floor_) few = floor_;
-                c = few < c ? few : c;
-            }
+    if (A.adapt) {
+        const int64_t nblock = sizes[kNBlock];
+        const int64_t b0 = A.coff[A.choff[x]], b1 = A.coff[A.choff[x + 1]];
+        const int64_t own = A.soff_e[A.eoff[b1 < nblock ? b1 : nblock]] - A.soff_e[A.eoff[b0 < nblock ? b0 : nblock]];
+        if (own < kSmallBox) {
+            const double root = cbrt((double)own);
+            int64_t few = (int64_t)(kChunkScale * root * root / kBlock + 0.5) * kBlock;
+            const int64_t floor_ = own < kTinyBox ? kTinyChunk : kSmallChunk;
+            if (few < floor_) few = floor_;
+            chunk = few < chunk ? few : chunk;
         }
-        box_chunk[x] = (int32_t)c;
     }
+    return chunk;
 }
 
 // The active lanes of every target block, one wave per block.
@@ -1027,36 +1405,64 @@ __global__ void __launch_bounds__(256) block_active_kernel(const int64_t* __rest
 
 // Work items per block: its list in chunks (at least one item, so that every
 // target is written); none for a block without an active target when flags
-// are given.
-__global__ void item_count_kernel(const int32_t* __restrict__ slen,
+// are given.  With fresh lists (A.soff_e set) the boxes' chunks are found here too.
+__global__ void item_count_kernel(ChunkArgs A, const int32_t* __restrict__ slen,
                                   const int32_t* __restrict__ bcount, int64_t* __restrict__ sizes,
                                   int64_t cap_block, const int32_t* __restrict__ bboxid,
-                                  const int32_t* __restrict__ box_chunk,
-                                  const uint64_t* __restrict__ bact, int32_t* __restrict__ icount) {
+                                  int32_t* __restrict__ box_chunk, const uint64_t* __restrict__ bact,
+                                  int32_t* __restrict__ icount) {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= cap_block) return;
     if (b >= sizes[kNBlock]) {
         icount[b] = 0;
         return;
     }
+    const int x = bboxid[b];
+    const int64_t chunk = A.soff_e ? box_chunk_of(A, sizes, x) : box_chunk[x];
+    if (A.soff_e) {
+        if (b == 0) sizes[kTotalSrc] = A.soff_e[sizes[kNEntry]];
+        if (b == 0 || bboxid[b - 1] != x) box_chunk[x] = (int32_t)chunk;
+    }
     if (bact && bact[b] == 0) {
         icount[b] = 0;
         return;
     }
     const int32_t s = slen[b];
-    const int64_t chunk = box_chunk[bboxid[b]];
     icount[b] = s <= 0 ? 1 : (int32_t)((s + chunk - 1) / chunk);
     // (target, listed source) pairs; the kernel prunes some sources further
     atomicAdd(reinterpret_cast<unsigned long long*>(sizes + kCand),
               (unsigned long long)s * (unsigned long long)bcount[b]);
 }
 
+// Writes the items; the first workgroup also takes the item and range totals,
+// sets the flag that makes the PP kernels return, and copies the count slots
+// to the host's page-locked copy (host, when there is one), which saves a
+// copy operation behind the PP kernels.
 __global__ void item_fill_kernel(const int32_t* __restrict__ icount,
-                                 const int64_t* __restrict__ ioff, const int64_t* __restrict__ sizes,
-                                 int64_t cap_item, const int32_t* __restrict__ slen,
+                                 const int64_t* __restrict__ ioff, int64_t* __restrict__ sizes,
+                                 const int64_t* __restrict__ roff, int64_t cap_range, int npass, int stop,
+                                 const int* __restrict__ bad, int64_t* __restrict__ host, int64_t cap_item, const int32_t* __restrict__ slen,
                                  const int32_t* __restrict__ bboxid,
                                  const int32_t* __restrict__ box_chunk, int32_t* __restrict__ iblock,
                                  int32_t* __restrict__ is0, int32_t* __restrict__ is1) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            const int64_t nb = sizes[kNBlock];
+            const int64_t ni = ioff[nb], nr = roff[nb];
+            sizes[kNeedItem] = ni;
+            sizes[kNeedRange] = nr;
+            sizes[kNItem] = ni < cap_item ? ni : cap_item;
+            sizes[kNRange] = nr < cap_range ? nr : cap_range;
+            if (ni > cap_item) sizes[kOverflow] |= 8;
+            if (nr > cap_range) sizes[kOverflow] |= 4;
+            if (sizes[kStart] - npass > stop) sizes[kOverflow] |= 128;
+            sizes[kBad] = *bad;
+            sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
+        }
+        __threadfence_block();
+        __syncthreads();
+        if (host && threadIdx.x < kSizeSlots) host[threadIdx.x] = sizes[threadIdx.x];
+    }
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= sizes[kNBlock]) return;
     const int64_t o = ioff[b];
@@ -1071,26 +1477,11 @@ __global__ void item_fill_kernel(const int32_t* __restrict__ icount,
 }
 
 
-// Item and range totals, and the flag that makes the PP kernels return.
-__global__ void finish_sizes_kernel(int64_t* __restrict__ sizes, const int64_t* __restrict__ ioff,
-                                    const int64_t* __restrict__ roff, int64_t cap_item,
-                                    int64_t cap_range, const int* __restrict__ bad) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    const int64_t nb = sizes[kNBlock];
-    const int64_t ni = ioff[nb], nr = roff[nb];
-    sizes[kNeedItem] = ni;
-    sizes[kNeedRange] = nr;
-    sizes[kNItem] = ni < cap_item ? ni : cap_item;
-    sizes[kNRange] = nr < cap_range ? nr : cap_range;
-    if (ni > cap_item) sizes[kOverflow] |= 8;
-    if (nr > cap_range) sizes[kOverflow] |= 4;
-    sizes[kBad] = bad ? *bad : 0;
-    sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
-}
-
 // Per-pass slots of a pass that reuses the lists (the list counts stay; the
 // overflow bits of the last pass go, since the lists' own buffers fitted).
-__global__ void zero_sizes_reuse_kernel(int64_t* __restrict__ sizes, int* __restrict__ bad) {
+__global__ void zero_sizes_reuse_kernel(int64_t* __restrict__ sizes, int* __restrict__ bad,
+                                        int32_t* __restrict__ mass_flag, int nbox) {
+    for (int x = threadIdx.x; x < nbox; x += blockDim.x) mass_flag[x] = 0;
     if (threadIdx.x != 0) return;
     sizes[kOverflow] = 0;
     sizes[kCand] = 0;
@@ -1100,9 +1491,13 @@ __global__ void zero_sizes_reuse_kernel(int64_t* __restrict__ sizes, int* __rest
     *bad = 0;
 }
 
-__global__ void zero_sizes_kernel(int64_t* __restrict__ sizes, int* __restrict__ bad) {
+// ... and the per-box flags of unequal masses (mass_flag, when given).
+__global__ void zero_sizes_kernel(int64_t* __restrict__ sizes, int* __restrict__ bad,
+                                  int32_t* __restrict__ mass_flag, int nbox) {
     if (threadIdx.x < kSizeSlots) sizes[threadIdx.x] = 0;
     if (threadIdx.x == 0) *bad = 0;
+    if (mass_flag)
+        for (int x = threadIdx.x; x < nbox; x += blockDim.x) mass_flag[x] = 0;
 }
 
 }  // namespace
@@ -1120,6 +1515,18 @@ static int64_t tree_node_bound(int64_t n, int nbox) {
     return m + m / 7 + (int64_t)nbox * kTreeMaxLevels + 8;
 }
 
+// start_level on the host.
+static int host_start_level(int64_t c, int64_t most) {
+    int h = 0;
+    while (c > 1 && (h == 0 || c > most)) {
+        c = (c + 7) / 8;
+        ++h;
+    }
+    return h;
+}
+
+static int make_items(const ChunkArgs& chunks, Work& w, hipStream_t s, const uint8_t* active);
+
 // Levels of the implicit tree over at most n leaves.
 static int levels_for(int64_t n) {
     int h = 1;
@@ -1132,68 +1539,69 @@ static int levels_for(int64_t n) {
 }
 
 // Clears the count slots and the bad-input flag.
-int reset_sizes(Work& w, hipStream_t s) {
+int reset_sizes(int nbox, Work& w, hipStream_t s) {
+    PP_TRY(w.mass_flag.reserve(sizeof(int32_t) * (nbox + 1)));
     PP_TRY(w.sizes.reserve(sizeof(int64_t) * kSizeSlots));
     PP_TRY(w.bad.reserve(64));
     hipLaunchKernelGGL(zero_sizes_kernel, dim3(1), dim3(kSizeSlots), 0, s, w.sizes.as<int64_t>(),
-                       w.bad.as<int>());
+                       w.bad.as<int>(), w.mass_flag.as<int32_t>(), nbox);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
 
-int reset_sizes_reuse(Work& w, hipStream_t s) {
+int reset_sizes_reuse(int nbox, Work& w, hipStream_t s) {
     hipLaunchKernelGGL(zero_sizes_reuse_kernel, dim3(1), dim3(64), 0, s, w.sizes.as<int64_t>(),
-                       w.bad.as<int>());
+                       w.bad.as<int>(), w.mass_flag.as<int32_t>(), nbox);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
 
-int stage_leaves(const BatchDev& bd, int64_t N, const uint64_t* sorted_keys, const double* pos_s,
-                 Work& w, hipStream_t s) {
-    PP_TRY(w.sizes.reserve(sizeof(int64_t) * kSizeSlots));
-    PP_TRY(w.loff_dev.reserve(sizeof(int64_t) * (bd.nbox + 1)));
-    const int M = bd.leaf_max;
-    const int64_t len = N + M;
+// Nodes of the start level of the list expansion at most.  Small boxes start
+// as low as they can: each level skipped is three launches.  Large ones start
+// where a wave tests all nodes at once: the levels below cost less per entry
+// than testing every node for every block (2.1 M particles: 316 us from a
+// level of 540 nodes, 88 from one of 9).
+// chunks up to which the one-launch forms of the block split and of the first
+// expansion pass are taken
+constexpr int64_t kFewChunks = 4096;
+static bool small_boxes(int64_t N, int nbox) { return N / nbox <= 131072; }
+static int64_t start_nodes_for(int64_t N, int nbox) { return small_boxes(N, nbox) ? 1024 : 128; }
+
+int stage_leaves(const BatchDev& bd, int64_t N, const uint64_t* sorted_keys, Work& w, hipStream_t s) {
+    const int nbox = bd.nbox;
     const int64_t m = N > 0 ? N : 1;        // leaves: at most one per particle
-    PP_TRY(w.lam.reserve(len + 1));
-    PP_TRY(w.pmax.reserve(len + 1));
-    PP_TRY(w.smax.reserve(len + 1));
-    PP_TRY(w.level_p.reserve(N + 1));
-    PP_TRY(w.flag.reserve(sizeof(int32_t) * (N + 1)));
-    PP_TRY(w.flag_off.reserve(sizeof(int64_t) * (N + 2)));
+    PP_TRY(w.sizes.reserve(sizeof(int64_t) * kSizeSlots));
+    PP_TRY(w.loff_dev.reserve(sizeof(int64_t) * (nbox + 1)));
     PP_TRY(w.lbegin.reserve(sizeof(int64_t) * (m + 1)));
     PP_TRY(w.lcount.reserve(sizeof(int32_t) * (m + 1)));
     PP_TRY(w.llevel.reserve(sizeof(int32_t) * (m + 1)));
     PP_TRY(w.lprefix.reserve(sizeof(uint64_t) * (m + 1)));
-    // the leaf boxes are level 0 of the trees' node array (leaf a of the
-    // batch is node a): the tree levels go after them
-    PP_TRY(w.tree_boxes.reserve(sizeof(IBox) * tree_node_bound(N, bd.nbox)));
-    if (N > 0) {
-        hipLaunchKernelGGL(lam_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, bd, sorted_keys, N,
-                           w.lam.as<int8_t>());
-        const int64_t nblk = (len + M) / (M + 1);
-        hipLaunchKernelGGL(vhgw_kernel, dim3(blocks_for(nblk, 256)), dim3(256), 0, s,
-                           w.lam.as<int8_t>(), len, M + 1, w.pmax.as<int8_t>(), w.smax.as<int8_t>());
-        hipLaunchKernelGGL(level_kernel, dim3(blocks_for(N, 256)), dim3(256), 0, s, w.pmax.as<int8_t>(),
-                           w.smax.as<int8_t>(), N, M, bd.bits, w.level_p.as<int8_t>());
-        hipLaunchKernelGGL(flag_kernel, dim3(blocks_for(N, 256)), dim3(256), 0, s, bd, sorted_keys,
-                           w.level_p.as<int8_t>(), N, w.flag.as<int32_t>());
+    PP_TRY(w.tviews.reserve(sizeof(TreeView) * nbox));
+    PP_TRY(w.lvl_prefix.reserve(sizeof(int64_t) * (size_t)kTreeMaxLevels * (nbox + 1)));
+    PP_TRY(w.group_prefix.reserve(sizeof(int64_t) * (nbox + 1)));
+    if (N == 0) {
+        hipLaunchKernelGGL(no_leaves_kernel, dim3(1), dim3(64), 0, s, nbox, w.loff_dev.as<int64_t>(),
+                           w.sizes.as<int64_t>(), start_nodes_for(N, nbox), w.tviews.as<TreeView>(),
+                           w.lvl_prefix.as<int64_t>(), w.group_prefix.as<int64_t>());
         PP_HIP(hipGetLastError());
+        return PP_OK;
     }
-    PP_TRY(launch_scan_i32_to_i64(w.flag.as<int32_t>(), w.flag_off.as<int64_t>(), N, w.scan_ws, s, w.sizes.as<int64_t>()));
-    hipLaunchKernelGGL(leaf_offsets_kernel, dim3(blocks_for(bd.nbox + 1, 64)), dim3(64), 0, s, bd,
-                       w.flag_off.as<int64_t>(), w.loff_dev.as<int64_t>(), w.sizes.as<int64_t>());
+    // short tiles while there are few of them
+    constexpr int kShort = 2, kLong = 8;
+    const int ipt = N <= 131072 ? kShort : kLong;
+    const int64_t nt = (N + 256 * ipt - 1) / (256 * ipt);
+    // a small box's workspace for the whole list builder at once: it is cleared
+    // whenever it grows
+    if (N <= (1 << 20)) PP_TRY(grow_scan(w.scan_ws, 10 * N + 40960, s));
+    PP_TRY(grow_lookback(w.scan_ws, nt, s));
+    LbArgs lb;
+    PP_TRY(lookback_args(w.scan_ws, nt, &lb));
+    auto kernel = ipt == kShort ? leaves_kernel<kShort> : leaves_kernel<kLong>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nt), dim3(256), 0, s, bd, sorted_keys, N, lb, nt,
+                       w.lbegin.as<int64_t>(), w.llevel.as<int32_t>(), w.lprefix.as<uint64_t>(),
+                       w.loff_dev.as<int64_t>(), w.sizes.as<int64_t>(), start_nodes_for(N, nbox), w.tviews.as<TreeView>(),
+                       w.lvl_prefix.as<int64_t>(), w.group_prefix.as<int64_t>());
     PP_HIP(hipGetLastError());
-    if (N > 0) {
-        hipLaunchKernelGGL(leaf_fill_kernel, dim3(blocks_for(N, 256)), dim3(256), 0, s, sorted_keys,
-                           w.level_p.as<int8_t>(), w.flag.as<int32_t>(), w.flag_off.as<int64_t>(), N,
-                           bd.bits, w.lbegin.as<int64_t>(), w.llevel.as<int32_t>(),
-                           w.lprefix.as<uint64_t>());
-        hipLaunchKernelGGL(leaf_box_kernel, dim3(stride_grid(N, 128)), dim3(128), 0, s, bd, pos_s, N,
-                           w.lbegin.as<int64_t>(), w.sizes.as<int64_t>(), w.lcount.as<int32_t>(),
-                           w.tree_boxes.as<IBox>());
-        PP_HIP(hipGetLastError());
-    }
     return PP_OK;
 }
 
@@ -1206,25 +1614,25 @@ int leaves_to_host(const BatchDev& bd, Work& w, hipStream_t s) {
     return PP_OK;
 }
 
-int stage_trees(const BatchDev& bd, int64_t N, Work& w, hipStream_t s) {
+int stage_trees(const BatchDev& bd, int64_t N, const double* pos_s, Work& w, hipStream_t s) {
     const int nbox = bd.nbox;
     const int H = levels_for(N);
     w.max_levels = H;
     PP_TRY(w.tree_boxes.reserve(sizeof(IBox) * tree_node_bound(N, nbox)));
-    PP_TRY(w.tviews.reserve(sizeof(TreeView) * nbox));
-    PP_TRY(w.lvl_prefix.reserve(sizeof(int64_t) * (size_t)kTreeMaxLevels * (nbox + 1)));
-    PP_TRY(w.tree_total.reserve(sizeof(int64_t) * 2));
-    hipLaunchKernelGGL(tree_views_kernel, dim3(1), dim3(256), 0, s, w.loff_dev.as<int64_t>(), nbox,
-                       w.tviews.as<TreeView>(), w.lvl_prefix.as<int64_t>(), w.tree_total.as<int64_t>());
-    PP_HIP(hipGetLastError());
-    IBox* nodes = w.tree_boxes.as<IBox>();       // level 0: the leaf boxes (stage_leaves)
-    int64_t bound = N;
-    for (int h = 1; h < H; ++h) {
-        bound = (bound + 7) / 8 + nbox;
-        hipLaunchKernelGGL(tree_level_kernel, dim3(stride_grid(bound, 256)), dim3(256), 0, s,
-                           w.tviews.as<TreeView>(), w.lvl_prefix.as<int64_t>() + (size_t)h * (nbox + 1),
-                           nbox, h, nodes);
+    if (nbox > 1) {                              // (the leaves' kernel does it for one box)
+        hipLaunchKernelGGL(tree_views_kernel, dim3(1), dim3(256), 0, s, w.loff_dev.as<int64_t>(), nbox,
+                           w.tviews.as<TreeView>(), w.lvl_prefix.as<int64_t>(), w.group_prefix.as<int64_t>(),
+                           start_nodes_for(N, nbox), w.sizes.as<int64_t>());
+        PP_HIP(hipGetLastError());
     }
+    if (N == 0) return PP_OK;
+    IBox* nodes = w.tree_boxes.as<IBox>();
+    const int64_t groups = N / kTreeGroup + nbox;    // bound: leaves may be as many as the particles
+    hipLaunchKernelGGL(leaf_tree_kernel, dim3((unsigned)groups), dim3(kTreeGroup), 0, s, bd, pos_s, N,
+                       w.tviews.as<TreeView>(), w.group_prefix.as<int64_t>(), w.lbegin.as<int64_t>(),
+                       w.sizes.as<int64_t>(), w.lcount.as<int32_t>(), nodes);
+    if (H > 4)
+        hipLaunchKernelGGL(tree_top_kernel, dim3((unsigned)nbox), dim3(256), 0, s, w.tviews.as<TreeView>(), nodes);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
@@ -1323,8 +1731,6 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     // capacities: blocks from the chunks, the rest from the last need
     if (w.cap_block < nc + nc / 8 + 64) w.cap_block = nc + nc / 8 + 64;
     const int64_t cb = w.cap_block;
-    if (w.cap_ent[0] < 4 * cb) w.cap_ent[0] = 4 * cb;
-    PP_TRY(w.ccount.reserve(sizeof(int32_t) * (nc + 1)));
     PP_TRY(w.coff.reserve(sizeof(int64_t) * (nc + 2)));
     PP_TRY(w.bstart.reserve(sizeof(int32_t) * cb));
     PP_TRY(w.bcount.reserve(sizeof(int32_t) * cb));
@@ -1335,40 +1741,61 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     PP_TRY(w.icount.reserve(sizeof(int32_t) * (cb + 1)));
     PP_TRY(w.ioff.reserve(sizeof(int64_t) * (cb + 2)));
     PP_TRY(w.eoff.reserve(sizeof(int64_t) * (cb + 2)));
-    // expansion passes (see below) and their entry capacities: the root pass
-    // and H - 2 lowering passes, the last of which (level 2 to 1) is left
-    // out when it would need too many entries
-    const int H = w.max_levels;
-    int nlower = H > 2 ? H - 2 : 0;
-    const bool to_level1 = !w.stop_at_level2 || nlower == 0;
-    if (!to_level1) nlower -= 1;
+    // lowering passes: from the last call's start level (before the first
+    // call, that of a guess at the leaves) to level 1, or to level 2 when
+    // level 1 would need too many entries; entries that start one level
+    // higher than guessed end at level 2, and a larger miss runs the pass again
+    if (w.start_level < 0) {
+        const int64_t guess = N / nbox / (bd.leaf_max > 8 ? bd.leaf_max / 4 : 2) + 1;
+        w.start_level = host_start_level(guess, start_nodes_for(N, nbox));
+    }
+    const int stop = w.stop_at_level2 ? kDfsLevel : kDfsLevel - 1;
+    const int nlower = w.start_level > stop ? w.start_level - stop : 0;
     const int npass = 1 + nlower;
     w.npass = npass;
-    for (int p = 0; p < npass; ++p)
-        if (w.cap_ent[p] < 1024) w.cap_ent[p] = p == 0 ? 4 * cb : w.cap_ent[p - 1] * 2;
+    // entry capacities, by the level a pass ends at, for exact and for monopole
+    // lists (their first guesses fit uniform and clustered boxes at leaf_max 32)
+    w.mono_lists = mcfg.on();
+    int64_t* caps = w.cap_ent[w.mono_lists ? 1 : 0];
+    auto cap = [&](int p) -> int64_t& { return caps[stop + nlower - p]; };
+    const int64_t guess[] = {nc > kFewChunks ? 256 : 160, nc > kFewChunks ? 256 : 160, 64, 32};
+    for (int p = 0; p < npass; ++p) {
+        const int level = stop + nlower - p;
+        if (cap(p) < 1024) {
+            // monopole lists keep more, smaller nodes: 1.3 to 1.45 times the
+            // entries of exact lists of the same particles, where those are known
+            const int64_t exact = w.mono_lists ? w.cap_ent[0][level] / 2 * 3 : 0;
+            cap(p) = std::max((level < 4 ? guess[level] : 16) * cb, exact);
+        }
+    }
     int64_t capcnt = cb;
-    for (int p = 0; p < npass; ++p) capcnt = w.cap_ent[p] > capcnt ? w.cap_ent[p] : capcnt;
+    for (int p = 0; p < npass; ++p) capcnt = cap(p) > capcnt ? cap(p) : capcnt;
     // the scans' workspace for the largest scan of the pass, reserved before
     // the first one is enqueued
     PP_TRY(grow_scan(w.scan_ws, 2 * (capcnt > nc ? capcnt : nc), s));
     const double* pos_s = w.pos_s.as<double>();
-    if (nc > 0) {
-        hipLaunchKernelGGL(block_split_kernel<false>, dim3((unsigned)nc), dim3(kBlock), 0, s, bd,
-                           pos_s, N, w.choff.as<int64_t>(), nc, w.ccount.as<int32_t>(),
-                           (const int64_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr,
-                           (IBox*)nullptr, (int32_t*)nullptr, cb);
+    const BlockOut bout{w.bstart.as<int32_t>(), w.bcount.as<int32_t>(), w.bbox.as<IBox>(), w.bboxid.as<int32_t>(), cb};
+    if (nc <= kFewChunks) {
+        const int64_t nt = (nc + kSplitWaves - 1) / kSplitWaves;
+        LbArgs lb;
+        PP_TRY(grow_lookback(w.scan_ws, nt, s));
+        PP_TRY(lookback_args(w.scan_ws, nt, &lb));
+        hipLaunchKernelGGL(block_split_small_kernel, dim3((unsigned)nt), dim3(kSplitWaves * kBlock), 0, s, bd, pos_s, N,
+                           w.choff.as<int64_t>(), nc, lb, nt, w.coff.as<int64_t>(), sizes, bout);
+    } else {
+        PP_TRY(w.ccount.reserve(sizeof(int32_t) * (nc + 1)));
+        PP_TRY(w.cbox.reserve(sizeof(IBox) * nc));
+        const unsigned groups = blocks_for(nc, 256 / kBlock);
+        hipLaunchKernelGGL(block_split_kernel<false>, dim3(groups), dim3(256), 0, s, bd, pos_s, N,
+                           w.choff.as<int64_t>(), nc, w.ccount.as<int32_t>(), (const int64_t*)nullptr,
+                           w.cbox.as<IBox>(), bout);
         PP_HIP(hipGetLastError());
-    }
-    {
         const ScanNote note{(int)kNBlock, (int)kNeedBlock, cb, 1ull, -1};
-        PP_TRY(launch_scan_i32_to_i64(w.ccount.as<int32_t>(), w.coff.as<int64_t>(), nc, w.scan_ws, s, sizes,
-                                      &note));
+        PP_TRY(launch_scan_i32_to_i64(w.ccount.as<int32_t>(), w.coff.as<int64_t>(), nc, w.scan_ws, s, sizes, &note));
+        hipLaunchKernelGGL(block_split_kernel<true>, dim3(groups), dim3(256), 0, s, bd, pos_s, N,
+                           w.choff.as<int64_t>(), nc, w.ccount.as<int32_t>(), w.coff.as<int64_t>(),
+                           w.cbox.as<IBox>(), bout);
     }
-    if (nc > 0)
-        hipLaunchKernelGGL(block_split_kernel<true>, dim3((unsigned)nc), dim3(kBlock), 0, s, bd,
-                           pos_s, N, w.choff.as<int64_t>(), nc, (int32_t*)nullptr,
-                           w.coff.as<int64_t>(), w.bstart.as<int32_t>(), w.bcount.as<int32_t>(),
-                           w.bbox.as<IBox>(), w.bboxid.as<int32_t>(), cb);
     PP_HIP(hipGetLastError());
     const TreeView* tvs = w.tviews.as<TreeView>();
     const IBox* nodes = w.tree_boxes.as<IBox>();
@@ -1383,43 +1810,50 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
         PP_HIP(hipGetLastError());
         mono.amin2 = w.blk_amin2.as<double>();
     }
-    // Breadth-first expansion from every box's root: pass 0 takes the roots,
-    // every later pass lowers the entries above level 2 by one level and the
-    // last pass lowers level 2 to level 1 (when it does not exceed the entry
-    // budget), so that the depth-first walks cover at most 8 (else 64)
-    // leaves each; passes beyond a box's depth carry its entries unchanged.
-    // Entry buffers alternate between two arrays.
+    // Breadth-first expansion: pass 0 takes the nodes of the start levels,
+    // every later pass p lowers the entries above level `stop + nlower - p` by
+    // one level (entries of boxes with a lower start level wait in the early,
+    // short passes), so that the depth-first walks cover at most 8 (else 64)
+    // leaves each.  Entry buffers alternate between two arrays.
     int64_t cap_a = 0, cap_b = 0;
     for (int p = 0; p < npass; ++p) {
         int64_t& c = p % 2 == 0 ? cap_a : cap_b;
-        c = w.cap_ent[p] > c ? w.cap_ent[p] : c;
+        c = cap(p) > c ? cap(p) : c;
     }
     PP_TRY(w.fent_a.reserve(sizeof(FEntry) * (cap_a + 1)));
     PP_TRY(w.fent_b.reserve(sizeof(FEntry) * (cap_b + 1)));
     PP_TRY(w.fcnt.reserve(sizeof(int32_t) * (capcnt + 1)));
     PP_TRY(w.foff.reserve(sizeof(int64_t) * (capcnt + 2)));
     PP_TRY(w.fmask.reserve(sizeof(uint16_t) * (capcnt + 1)));
-    hipLaunchKernelGGL(bfs_root_kernel<false>, dim3(blocks_for(cb, 128)), dim3(128), 0, s, bd, tvs,
-                       nodes, bbox, bboxid, (const int64_t*)sizes, cb, w.fcnt.as<int32_t>(),
-                       (const int64_t*)nullptr, (FEntry*)nullptr, (int64_t)0, mono);
-    PP_HIP(hipGetLastError());
-    {
-        const ScanNote note{(int)kEntry0, (int)kNeedEntry0, w.cap_ent[0], 2ull, npass == 1 ? (int)kNEntry : -1};
-        PP_TRY(launch_scan_i32_to_i64(w.fcnt.as<int32_t>(), w.foff.as<int64_t>(), cb, w.scan_ws, s, sizes,
-                                      &note));
+    const int last0 = npass == 1 ? (int)kNEntry : -1;
+    if (small_boxes(N, nbox) && nc <= kFewChunks) {
+        const int64_t per = kStartWaves / kStartSplit, nt = (cb + per - 1) / per;
+        LbArgs lb;
+        PP_TRY(grow_lookback(w.scan_ws, nt, s));
+        PP_TRY(lookback_args(w.scan_ws, nt, &lb));
+        hipLaunchKernelGGL(start_small_kernel, dim3((unsigned)nt), dim3(kStartWaves * kBlock), 0, s, bd, tvs, nodes,
+                           bbox, bboxid, lb, nt, sizes, w.fent_a.as<FEntry>(), cap(0), last0, mono);
+    } else {
+        const unsigned groups = blocks_for(cb, 256 / kBlock);
+        hipLaunchKernelGGL(start_kernel<false>, dim3(groups), dim3(256), 0, s, bd, tvs, nodes, bbox, bboxid,
+                           (const int64_t*)sizes, cb, w.fcnt.as<int32_t>(), (const int64_t*)nullptr,
+                           (FEntry*)nullptr, (int64_t)0, mono);
+        PP_HIP(hipGetLastError());
+        const ScanNote note{(int)kEntry0, (int)kNeedEntry0, cap(0), 2ull, last0};
+        PP_TRY(launch_scan_i32_to_i64(w.fcnt.as<int32_t>(), w.foff.as<int64_t>(), cb, w.scan_ws, s, sizes, &note));
+        hipLaunchKernelGGL(start_kernel<true>, dim3(groups), dim3(256), 0, s, bd, tvs, nodes, bbox, bboxid,
+                           (const int64_t*)sizes, cb, (int32_t*)nullptr, w.foff.as<int64_t>(),
+                           w.fent_a.as<FEntry>(), cap(0), mono);
     }
-    hipLaunchKernelGGL(bfs_root_kernel<true>, dim3(blocks_for(cb, 128)), dim3(128), 0, s, bd, tvs,
-                       nodes, bbox, bboxid, (const int64_t*)sizes, cb, (int32_t*)nullptr,
-                       w.foff.as<int64_t>(), w.fent_a.as<FEntry>(), w.cap_ent[0], mono);
     PP_HIP(hipGetLastError());
     DevBuf* cur = &w.fent_a;
     DevBuf* nxt = &w.fent_b;
     for (int p = 1; p < npass; ++p) {
-        const int stop = (p == npass - 1 && to_level1) ? kDfsLevel - 1 : kDfsLevel;
-        const int64_t cin = w.cap_ent[p - 1], cout = w.cap_ent[p];
+        const int target = stop + nlower - p;
+        const int64_t cin = cap(p - 1), cout = cap(p);
         hipLaunchKernelGGL(bfs_level_kernel<false>, dim3(blocks_for(cin, 128)), dim3(128), 0, s, bd,
                            tvs, nodes, bbox, bboxid, cur->as<FEntry>(),
-                           (const int64_t*)(sizes + kEntry0 + p - 1), cin, stop, w.fcnt.as<int32_t>(),
+                           (const int64_t*)(sizes + kEntry0 + p - 1), cin, target, w.fcnt.as<int32_t>(),
                            (const int64_t*)nullptr, (FEntry*)nullptr, (int64_t)0, mono, w.fmask.as<uint16_t>());
         PP_HIP(hipGetLastError());
         const ScanNote note{(int)(kEntry0 + p), (int)(kNeedEntry0 + p), cout, 2ull,
@@ -1428,14 +1862,14 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
                                       &note));
         hipLaunchKernelGGL(bfs_level_kernel<true>, dim3(blocks_for(cin, 128)), dim3(128), 0, s, bd, tvs,
                            nodes, bbox, bboxid, cur->as<FEntry>(),
-                           (const int64_t*)(sizes + kEntry0 + p - 1), cin, stop, (int32_t*)nullptr,
+                           (const int64_t*)(sizes + kEntry0 + p - 1), cin, target, (int32_t*)nullptr,
                            w.foff.as<int64_t>(), nxt->as<FEntry>(), cout, mono, w.fmask.as<uint16_t>());
         PP_HIP(hipGetLastError());
         DevBuf* t = cur;
         cur = nxt;
         nxt = t;
     }
-    const int64_t F = w.cap_ent[npass - 1];    // the final entry buffer's capacity
+    const int64_t F = cap(npass - 1);          // the final entry buffer's capacity
     const FEntry* ent = cur->as<FEntry>();
     w.ent_final = ent;
     PP_TRY(w.lmask_e.reserve(sizeof(uint64_t) * (F + 1)));
@@ -1455,7 +1889,7 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     }
     w.mono0 = mono0;
     w.mono1 = mono1;
-    if (w.cap_range < 1024) w.cap_range = 16 * cb;
+    if (w.cap_range < 1024) w.cap_range = (nc > kFewChunks ? 320 : 200) * cb;
     if (w.cap_item < 1024) {
         w.cap_item = 2 * cb;
         // small boxes are cut finer: their items grow as the root of the blocks
@@ -1468,19 +1902,10 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     PP_HIP(hipGetLastError());
     PP_TRY(launch_scan2_i32_to_i64(w.rcnt_e.as<int32_t>(), w.scnt_e.as<int32_t>(), w.roff_e.as<int64_t>(),
                                    w.soff_e.as<int64_t>(), F, w.scan_ws, s, sizes));
-    hipLaunchKernelGGL(block_entry_kernel, dim3(blocks_for(cb + 1, 256)), dim3(256), 0, s, ent,
-                       (const int64_t*)sizes, cb, w.eoff.as<int64_t>());
-    hipLaunchKernelGGL(block_sum_kernel, dim3(blocks_for(cb + 1, 256)), dim3(256), 0, s,
-                       (const int64_t*)w.eoff.as<int64_t>(), (const int64_t*)w.roff_e.as<int64_t>(),
-                       (const int64_t*)w.soff_e.as<int64_t>(), sizes, cb, w.roff.as<int64_t>(),
-                       w.slen.as<int32_t>());
+    hipLaunchKernelGGL(block_sum_kernel, dim3(blocks_for(cb + 1, 256)), dim3(256), 0, s, ent,
+                       (const int64_t*)w.roff_e.as<int64_t>(), (const int64_t*)w.soff_e.as<int64_t>(), sizes, cb,
+                       w.eoff.as<int64_t>(), w.roff.as<int64_t>(), w.slen.as<int32_t>());
     PP_HIP(hipGetLastError());
-    constexpr int64_t kMaxItems = 1 << 21;
-    PP_TRY(w.box_chunk.reserve(sizeof(int32_t) * nbox));
-    hipLaunchKernelGGL(chunk_kernel, dim3(1), dim3(256), 0, s, (const int64_t*)w.soff_e.as<int64_t>(),
-                       (const int64_t*)w.eoff.as<int64_t>(), (const int64_t*)w.coff.as<int64_t>(),
-                       (const int64_t*)w.choff.as<int64_t>(), nbox, sizes, (int64_t)chunk_req, kMaxItems,
-                       adapt_chunk ? 1 : 0, w.box_chunk.as<int32_t>());
     PP_TRY(w.rbeg.reserve(sizeof(int32_t) * (w.cap_range + 1)));
     PP_TRY(w.rpre.reserve(sizeof(int32_t) * (w.cap_range + 1)));
     PP_TRY(w.rcode.reserve(sizeof(uint8_t) * (w.cap_range + 1)));
@@ -1490,10 +1915,17 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
                        (const int64_t*)w.eoff.as<int64_t>(), w.rbeg.as<int32_t>(), w.rpre.as<int32_t>(),
                        w.rcode.as<uint8_t>(), mono, (const int64_t*)sizes, w.cap_range);
     PP_HIP(hipGetLastError());
-    return stage_items(bd, w, s, active);
+    constexpr int64_t kMaxItems = 1 << 21;
+    PP_TRY(w.box_chunk.reserve(sizeof(int32_t) * nbox));
+    const ChunkArgs chunks{w.soff_e.as<int64_t>(), w.eoff.as<int64_t>(), w.coff.as<int64_t>(),
+                           w.choff.as<int64_t>(), chunk_req, kMaxItems, adapt_chunk ? 1 : 0};
+    return make_items(chunks, w, s, active);
 }
 
-int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* active) {
+int stage_items(Work& w, hipStream_t s, const uint8_t* active) { return make_items(ChunkArgs{}, w, s, active); }
+
+// The work items; chunks.soff_e null: at the chunks of the current lists.
+static int make_items(const ChunkArgs& chunks, Work& w, hipStream_t s, const uint8_t* active) {
     int64_t* sizes = w.sizes.as<int64_t>();
     const int64_t cb = w.cap_block;
     w.active = active;
@@ -1503,7 +1935,7 @@ int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* activ
                            w.perm.as<int32_t>(), w.bstart.as<int32_t>(), w.bcount.as<int32_t>(),
                            w.bact.as<uint64_t>());
     }
-    hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s, chunks,
                        w.slen.as<int32_t>(), w.bcount.as<int32_t>(), sizes, cb, w.bboxid.as<int32_t>(),
                        w.box_chunk.as<int32_t>(),
                        active ? w.bact.as<uint64_t>() : (const uint64_t*)nullptr, w.icount.as<int32_t>());
@@ -1512,12 +1944,13 @@ int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* activ
     PP_TRY(w.iblock.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.is0.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.is1.reserve(sizeof(int32_t) * (w.cap_item + 1)));
+    PP_TRY(w.sizes_h.reserve(sizeof(int64_t) * kSizeSlots));
+    int64_t* host = w.sizes_h.pinned ? w.sizes_h.as<int64_t>() : nullptr;
     hipLaunchKernelGGL(item_fill_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
-                       w.icount.as<int32_t>(), w.ioff.as<int64_t>(), (const int64_t*)sizes, w.cap_item,
+                       w.icount.as<int32_t>(), w.ioff.as<int64_t>(), sizes, w.roff.as<int64_t>(), w.cap_range,
+                       w.npass - 1, kDfsLevel, w.bad.as<int>(), host, w.cap_item,
                        w.slen.as<int32_t>(), w.bboxid.as<int32_t>(), w.box_chunk.as<int32_t>(),
                        w.iblock.as<int32_t>(), w.is0.as<int32_t>(), w.is1.as<int32_t>());
-    hipLaunchKernelGGL(finish_sizes_kernel, dim3(1), dim3(1), 0, s, sizes, w.ioff.as<int64_t>(),
-                       w.roff.as<int64_t>(), w.cap_item, w.cap_range, w.bad.as<int>());
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
@@ -1525,9 +1958,9 @@ int stage_items(const BatchDev& bd, Work& w, hipStream_t s, const uint8_t* activ
 int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
     *regrow = false;
     if (moved) *moved = false;
-    PP_TRY(w.sizes_h.reserve(sizeof(int64_t) * kSizeSlots));
     int64_t* h = w.sizes_h.as<int64_t>();
-    PP_HIP(hipMemcpyAsync(h, w.sizes.p, sizeof(int64_t) * kSizeSlots, hipMemcpyDeviceToHost, s));
+    // page-locked: the last list kernel wrote them there
+    if (!w.sizes_h.pinned) PP_HIP(hipMemcpyAsync(h, w.sizes.p, sizeof(int64_t) * kSizeSlots, hipMemcpyDeviceToHost, s));
     PP_HIP(hipStreamSynchronize(s));
     if (h[kBad]) return fail(PP_EINVAL, "non-finite position or mass");
     if (h[kMoved]) {                    // reused lists no longer cover every pair: rebuild
@@ -1539,26 +1972,46 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
     if (h[kOverflow] & 16) return fail(PP_ERANGE, "a target block lists more than 2^31 sources");
     if (h[kOverflow]) {
         w.cap_block = grow_cap(w.cap_block, h[kNeedBlock]);
+        const int stop = w.stop_at_level2 ? kDfsLevel : kDfsLevel - 1;
         int np = w.npass;
-        if (!w.stop_at_level2 && np >= 2 && h[kNeedEntry0 + np - 1] > kEntryBudget) {
+        if (!w.stop_at_level2 && h[kNeedEntry0 + np - 1] > kEntryBudget) {
             // the level-1 pass would be too large: stop at level 2 from now on
             w.stop_at_level2 = true;
             np -= 1;
         }
-        for (int p = 0; p < np; ++p) w.cap_ent[p] = grow_cap(w.cap_ent[p], h[kNeedEntry0 + p]);
-        w.cap_range = grow_cap(w.cap_range, h[kNeedRange]);
-        w.cap_item = grow_cap(w.cap_item, h[kNeedItem]);
+        // A pass whose input was cut short counted only what followed from
+        // that part: its need is scaled up by what was cut (at most 4 times),
+        // so that one more run is enough (a first call at 16M clustered
+        // particles: three runs of the lists, 36 ms, became two, 19).
+        double cut = 1.0;
+        for (int p = 0; p < np; ++p) {
+            int64_t& c = w.cap_ent[w.mono_lists ? 1 : 0][stop + w.npass - 1 - p];
+            const int64_t need = (int64_t)((double)h[kNeedEntry0 + p] * cut);
+            if (need > c) cut = std::min(4.0, std::max(cut, (double)need / (double)c));
+            c = grow_cap(c, need);
+        }
+        w.start_level = (int)h[kStart];
+        w.cap_range = grow_cap(w.cap_range, (int64_t)((double)h[kNeedRange] * cut));
+        w.cap_item = grow_cap(w.cap_item, (int64_t)((double)h[kNeedItem] * cut));
         *regrow = true;
         return PP_OK;
     }
     // capacities follow the needs (the buffers keep their size): scans and
-    // grids then span little more than the data
-    w.cap_block = settle_cap(w.cap_block, h[kNeedBlock]);
-    for (int p = 0; p < w.npass; ++p) w.cap_ent[p] = settle_cap(w.cap_ent[p], h[kNeedEntry0 + p]);
-    w.cap_range = settle_cap(w.cap_range, h[kNeedRange]);
-    // the item count follows the active flags of each call: only a call
-    // over every target brings the item capacity down
-    if (!w.active) w.cap_item = settle_cap(w.cap_item, h[kNeedItem]);
+    // grids then span little more than the data.  Not after a call that had one
+    // expansion pass too few: the next one ends at more entries.
+    if ((int)h[kStart] <= w.start_level) {
+        const int stop = w.stop_at_level2 ? kDfsLevel : kDfsLevel - 1;
+        w.cap_block = settle_cap(w.cap_block, h[kNeedBlock]);
+        for (int p = 0; p < w.npass; ++p) {
+            int64_t& c = w.cap_ent[w.mono_lists ? 1 : 0][stop + w.npass - 1 - p];
+            c = settle_cap(c, h[kNeedEntry0 + p]);
+        }
+        w.cap_range = settle_cap(w.cap_range, h[kNeedRange]);
+        // the item count follows the active flags of each call: only a call
+        // over every target brings the item capacity down
+        if (!w.active) w.cap_item = settle_cap(w.cap_item, h[kNeedItem]);
+    }
+    w.start_level = (int)h[kStart];
     w.nleaf = h[kNLeaf];
     w.nblock = h[kNBlock];
     w.nentry = h[kNEntry];
@@ -1566,7 +2019,6 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
     w.nitem = h[kNItem];
     w.candidates = h[kCand];
     w.total_src = h[kTotalSrc];
-    w.chunk = (int)h[kChunk];
     return PP_OK;
 }
 

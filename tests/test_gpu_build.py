@@ -1,0 +1,105 @@
+"""GPU tests of the list builder's forms: the leaves' tiles, the one-launch and
+the counted block split and first expansion pass, and boxes without particles."""
+import numpy as np
+import pytest
+
+import workloads as W
+from workloads import BoxParams
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1802_09824_amd as m
+    return m
+
+
+def dev(a, dtype):
+    return torch.as_tensor(np.ascontiguousarray(a)).to(device="cuda", dtype=dtype)
+
+
+# tiles of 512 particles up to 131072 of them, of 2048 beyond
+@pytest.mark.parametrize("n,leaf_max", [(1, 1), (2, 1024), (511, 1), (512, 32), (513, 7), (1025, 1024), (2049, 600),
+                                        (5000, 1023), (131072, 32), (131073, 32), (133121, 1000)])
+def test_leaf_tiles_bit_exact(pp, oracle_mod, n, leaf_max):
+    """Leaves whose runs reach over tile edges, against the oracle's tree."""
+    rng = np.random.default_rng(n + leaf_max)
+    p = W.BoxParams(L=50.0, rs=1.0, rcut=4.5, eps=0.02, leaf_max=leaf_max)
+    pos = W.mixture(rng, n, p.L, 0.6, max(1, n // 400))
+    if n > 600:
+        pos[:, 100:160] = pos[:, 100:101]            # a leaf at the finest level
+    st = oracle_mod.structure(pos, p)
+    lv = pp.pp_build_leaves(dev(st["sorted_keys"].view(np.int64), torch.int64), dev(pos[:, st["perm"]], torch.float64), p)
+    got, ref = lv.export(), st["leaves"]
+    assert got["begin"].size == ref["begin"].size
+    for k in ("begin", "count", "level", "prefix"):
+        assert np.array_equal(got[k].astype(np.int64), ref[k].astype(np.int64)), k
+    assert np.array_equal(got["lo"].astype(np.int64), st["lo"])
+    assert np.array_equal(got["hi"].astype(np.int64), st["hi"])
+
+
+@pytest.mark.parametrize("n,leaf_max,mesh", [(131072, 32, 40), (131073, 3, 40), (262144, 32, 50), (262145, 5, 50),
+                                             (300000, 2, 24)])
+def test_builder_forms_cover_every_neighbour(pp, oracle_mod, n, leaf_max, mesh):
+    """Pair counts from the lists (FP64 test of every listed source) against
+    the oracle's brute-force counts, on both sides of 4096 chunks (one launch
+    or three for the block split and the first pass) and of 131072 particles
+    (the start level), with leaves small enough that expansion passes follow,
+    in wide boxes (several blocks per chunk) and on periodic faces."""
+    rng = np.random.default_rng(n)
+    p0 = BoxParams.from_mesh(60.0, mesh)
+    p = W.BoxParams(**{**p0.__dict__, "leaf_max": leaf_max})
+    pos = W.mixture(rng, n, p.L, 0.4, n // 500)
+    mass = W.equal_masses(n)
+    plan = pp.Plan(p, n)
+    for _ in range(2):                               # guessed, then known start level and capacities
+        plan.accel(dev(pos, torch.float64), dev(mass, torch.float32))
+        _, counts = plan.count_interactions(per_target=True)
+        t = np.sort(rng.choice(n, 300, replace=False))
+        ref = oracle_mod.accel(pos, mass.astype(np.float64), p, targets=t)
+        assert np.array_equal(counts.cpu().numpy()[t], ref["n_inter"])
+
+
+@pytest.mark.parametrize("ns", [(0, 700, 0, 0, 65, 1, 0), (0, 0, 3000), (2000, 0, 0), (0, 0)])
+def test_batches_with_empty_boxes(pp, ns):
+    """Empty boxes before, between and after the others: each other box gets
+    the bits it gets alone."""
+    boxes = []
+    for b, n in enumerate(ns):
+        rng = np.random.default_rng(50 + b)
+        p = BoxParams.from_mesh(30.0 + b, 12)
+        boxes.append((rng.random((3, n)) * p.L, rng.uniform(0.5, 1.5, n).astype(np.float32), p))
+    bp = pp.BatchPlan([b[2] for b in boxes], list(ns))
+    pos = np.concatenate([b[0] for b in boxes], 1)
+    mass = np.concatenate([b[1] for b in boxes])
+    acc = bp.accel(dev(pos, torch.float64), dev(mass, torch.float32)).cpu().numpy()
+    off = 0
+    for x, m, p in boxes:
+        n = m.size
+        if n:
+            one = pp.Plan(p, n).accel(dev(x, torch.float64), dev(m, torch.float32)).cpu().numpy()
+            assert np.array_equal(acc[:, off:off + n], one)
+        off += n
+
+
+def test_resized_plan_does_not_reuse_lists(pp):
+    """A plan with a skin that is called with another particle count builds
+    new lists for it, with the cut widened again."""
+    rng = np.random.default_rng(4)
+    p = BoxParams.from_mesh(40.0, 14)
+    pos, mass = rng.random((3, 3000)) * p.L, W.equal_masses(3000)
+    plan = pp.Plan(p, 3000)
+    plan.set_skin(0.2 * p.rcut)
+    for n in (3000, 2000, 3000, 2500):
+        x, m = dev(pos[:, :n], torch.float64), dev(mass[:n], torch.float32)
+        got = plan.accel(x, m).cpu().numpy()
+        moved = dev(pos[:, :n] + 0.05 * p.rcut, torch.float64)
+        again = plan.accel(moved, m).cpu().numpy()   # every particle by the same vector: the same forces
+        ref = pp.Plan(p, n).accel(x, m).cpu().numpy()
+        scale = np.abs(ref).max()
+        assert np.allclose(got, ref, rtol=1e-5, atol=1e-5 * scale)
+        assert np.allclose(again, ref, rtol=1e-3, atol=1e-4 * scale)
