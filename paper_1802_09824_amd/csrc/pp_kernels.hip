@@ -636,6 +636,21 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
     o[2 * kBlock + tlane] = (float)(sz * (double)mu);
 }
 
+// Place of the r-th set bit of m (r below the number of set bits).
+__device__ __forceinline__ int set_bit(uint64_t m, int r) {
+    int at = 0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const int c = __popcll(m & ((1ull << d) - 1ull));
+        if (r >= c) {
+            r -= c;
+            m >>= d;
+            at += d;
+        }
+    }
+    return at;
+}
+
 // Monopoles (sec. 3.3, 1 to N): one wave per target block walks the block's
 // entries of the list expansion in order.  An entry contributes the node it
 // stands for when the breadth-first expansion accepted it, and the leaves and
@@ -645,6 +660,10 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
 // of ell), staged into an LDS ring like the particles of pp_item and swept
 // with the same pair arithmetic and the same cut.  The result is added to
 // the accelerations the PP path wrote.
+// Bound by the pair arithmetic (8.0e9 pairs on 4 M clustered particles, 3.8 ms at
+// the rate of pp_item).  One entry at a time, its few nodes in few lanes, took 9.7
+// ms, bound by the latency of the loads; full waves of nodes take 5.6, and 4.8 with
+// nodes beyond the cut dropped and the sweep unrolled.  Six waves per SIMD: 5.4.
 __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry* __restrict__ ent,
                                                       const int64_t* __restrict__ eoff,
                                                       const uint64_t* __restrict__ mono0,
@@ -654,6 +673,9 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
                                                       const double* __restrict__ pos_s, int64_t N,
                                                       int32_t* __restrict__ mcount) {
     __shared__ float4 tile[2 * kBlock];
+    __shared__ uint64_t s_m0[kBlock];
+    __shared__ int64_t s_first[kBlock];
+    __shared__ int s_from[kBlock], s_m1[kBlock], s_sc[kBlock];
     const int64_t b = blockIdx.x;
     if (ia.sizes[kSkip] || b >= ia.sizes[kNBlock]) return;
     const int lane = threadIdx.x;
@@ -663,11 +685,17 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
     const BoxDev& X = ia.box[xbox];
     const TreeView& tv = tvs[xbox];
     const double L = X.L, cell = X.cell, inv_len = X.inv_len;
-    const PolyF32 P = X.poly;
+    PolyF32 P = X.poly;
+    asm("" : "+v"(P.eps2n));                         // in VGPRs, as in pp_item
+    asm("" : "+v"(P.cut2));
+    const float keep2 = P.keep2;
     const IBox B = ia.bbox[b];
     const double ox = 0.5 * (double)(B.lo[0] + B.hi[0]) * cell;
     const double oy = 0.5 * (double)(B.lo[1] + B.hi[1]) * cell;
     const double oz = 0.5 * (double)(B.lo[2] + B.hi[2]) * cell;
+    const float hx = (float)(0.5 * (double)(B.hi[0] - B.lo[0]) * cell * inv_len) * 1.0001f + 1e-6f;
+    const float hy = (float)(0.5 * (double)(B.hi[1] - B.lo[1]) * cell * inv_len) * 1.0001f + 1e-6f;
+    const float hz = (float)(0.5 * (double)(B.hi[2] - B.lo[2]) * cell * inv_len) * 1.0001f + 1e-6f;
     const int32_t nt = ia.bcount[b];
     const int64_t t = (int64_t)ia.bstart[b] + lane;
     float xi = 0.f, yi = 0.f, zi = 0.f;
@@ -681,12 +709,12 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
     int32_t taken = 0;
     // stage this lane's node (level, index) under shift code sc if `on`
     auto stage = [&](bool on, int lev, int64_t node, int sc) {
-        bool keep = false;
+        bool some = false, keep = false;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
         if (on) {
             const double4 m = mc[tv.off[lev] + node];
             if (m.w > 0.0) {
-                keep = true;
+                some = true;
                 const double sx = (double)(sc / 9 - 1) * L;
                 const double sy = (double)((sc / 3) % 3 - 1) * L;
                 const double sz = (double)(sc % 3 - 1) * L;
@@ -694,18 +722,23 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
                 v.y = (float)((m.y / m.w + sy - oy) * inv_len);
                 v.z = (float)((m.z / m.w + sz - oz) * inv_len);
                 v.w = (float)m.w;
+                // a centre of mass beyond the cut of the block's box adds nothing
+                const float gx = fmaxf(fabsf(v.x) - hx, 0.f);
+                const float gy = fmaxf(fabsf(v.y) - hy, 0.f);
+                const float gz = fmaxf(fabsf(v.z) - hz, 0.f);
+                keep = fmaf(gx, gx, fmaf(gy, gy, gz * gz)) < keep2;
             }
         }
         const uint64_t bal = __ballot(keep);
         const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
         if (keep) tile[count + rank] = v;
-        const int got = __popcll(bal);
-        count += got;
-        taken += got;
+        count += __popcll(bal);
+        taken += __popcll(__ballot(some));
         if (count >= kBlock) {
             wave_sync();
             float tx = 0.f, ty = 0.f, tz = 0.f;
+#pragma unroll 8
             for (int q = 0; q < kBlock; ++q) pair_f32<false>(tile[q], xi, yi, zi, P, tx, ty, tz);
             kahan_add(ax, cx, tx);
             kahan_add(ay, cy, ty);
@@ -726,16 +759,47 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
         if (in) E = ent[e];
         stage(in && E.mono, E.lev, E.node, E.sc);
     }
-    // leaves and groups of 8 leaves the depth-first walk accepted
+    // leaves and groups of 8 leaves the depth-first walk accepted: 64 entries
+    // at a time, their nodes numbered by a running count and taken 64 at a time
     if (mono0) {
-        for (int64_t e = eoff[b]; e < e_end; ++e) {
-            const uint64_t m0 = mono0[e];
-            const uint32_t m1 = mono1[e];
-            if ((m0 | m1) == 0) continue;
-            const FEntry E = ent[e];
-            const int64_t first = (int64_t)E.node << (3 * E.lev);
-            if (m0) stage((m0 >> lane) & 1ull, 0, first + lane, E.sc);
-            if (m1) stage(lane < 8 && ((m1 >> lane) & 1u), 1, (first >> 3) + lane, E.sc);
+        for (int64_t e0 = eoff[b]; e0 < e_end; e0 += kBlock) {
+            const int64_t e = e0 + lane;
+            const uint64_t m0 = e < e_end ? mono0[e] : 0ull;
+            const uint32_t m1 = e < e_end ? mono1[e] : 0u;
+            const int c = __popcll(m0) + __popc(m1);
+            if (__ballot(c > 0) == 0ull) continue;
+            int upto = c;
+#pragma unroll
+            for (int d = 1; d < kBlock; d <<= 1) {
+                const int below = __shfl_up(upto, d);
+                if (lane >= d) upto += below;
+            }
+            const int total = __builtin_amdgcn_readlane(upto, kBlock - 1);
+            wave_sync();
+            s_from[lane] = upto - c;
+            s_m0[lane] = m0;
+            s_m1[lane] = m1;
+            if (c > 0) {
+                const FEntry E = ent[e];
+                s_first[lane] = (int64_t)E.node << (3 * E.lev);
+                s_sc[lane] = E.sc;
+            }
+            wave_sync();
+            for (int q0 = 0; q0 < total; q0 += kBlock) {
+                const int q = q0 + lane;
+                // the last entry that starts at or below q: the one that holds it
+                int k = 0;
+#pragma unroll
+                for (int d = kBlock / 2; d > 0; d >>= 1)
+                    if (s_from[k + d] <= q) k += d;
+                int r = q - s_from[k];
+                const uint64_t w0 = s_m0[k];
+                const int c0 = __popcll(w0);
+                const bool leaf = r < c0;
+                const int64_t first = s_first[k];
+                const int at = set_bit(leaf ? w0 : (uint64_t)s_m1[k], leaf ? r : r - c0);
+                stage(q < total, leaf ? 0 : 1, (leaf ? first : first >> 3) + at, s_sc[k]);
+            }
         }
     }
     if (count > 0) {

@@ -103,3 +103,24 @@ def test_resized_plan_does_not_reuse_lists(pp):
         scale = np.abs(ref).max()
         assert np.allclose(got, ref, rtol=1e-5, atol=1e-5 * scale)
         assert np.allclose(again, ref, rtol=1e-3, atol=1e-4 * scale)
+
+
+@pytest.mark.parametrize("n,leaf_max", [(700, 64), (3000, 1), (3000, 3), (6000, 16)])
+def test_monopole_windows_match_tree_oracle(pp, n, leaf_max):
+    """Blocks with a few and with hundreds of accepted leaves and groups, so
+    that windows of 64 nodes start, end and split inside an entry; part of the
+    nodes lies beyond the cut of its block."""
+    from tests import monopole_mirror as tree
+    rng = np.random.default_rng(n + leaf_max)
+    p0 = BoxParams.from_mesh(30.0, 16)
+    p = W.BoxParams(**{**p0.__dict__, "leaf_max": leaf_max})
+    pos = W.mixture(rng, n, p.L, 0.5, 4)
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    ref = tree.monopole_accel(pos, mass.astype(np.float64), p, 0.6)
+    plan = pp.Plan(p, n)
+    plan.set_monopole(0.6)
+    acc = plan.accel(dev(pos, torch.float64), dev(mass, torch.float32)).cpu().numpy()
+    assert plan.stats()["monopoles"] == ref["n_mono_pairs"]
+    mag = np.linalg.norm(ref["acc"], axis=0)
+    e = np.linalg.norm(acc.astype(np.float64) - ref["acc"], axis=0) / np.maximum(mag, 1e-300)
+    assert np.median(e) <= 1e-6 and np.percentile(e, 99.9) <= 1e-4, (np.median(e), np.percentile(e, 99.9))
