@@ -1,11 +1,11 @@
 // The long-range particle-mesh (PM) force of sec. 3.1, on one periodic box:
 //   1. cloud-in-cell (CIC) assignment of the masses to an N^3 mesh, without
-//      atomics: the particles are sorted by the mesh cell that holds them
-//      (a stable radix sort, so ties keep the input order); each cell's run
-//      is cut into chunks of 32 particles whose 8 corner sums are formed in
-//      order, and every mesh point adds the matching corner sums of the 8
-//      cells around it, cells and chunks in a fixed order; the result does
-//      not depend on scheduling;
+//      atomics on the mesh: the particles are sorted by the mesh cell that
+//      holds them (a stable radix sort, so ties keep the input order); each
+//      cell's run is cut at every 64th sorted particle and the 8 corner sums
+//      of each piece are formed in order, and every mesh point adds the
+//      matching corner sums of the 8 cells around it, cells and pieces in a
+//      fixed order; the result does not depend on scheduling;
 //   2. real-to-complex FFT (hipFFT, FP64);
 //   3. the 3-point difference Green function of sec. 3.1,
 //      phi_k = -pi G Delta^2 rho_k / (sin^2(pi l/N) + sin^2(pi m/N) + sin^2(pi n/N)),
@@ -21,6 +21,7 @@
 #include <cmath>
 #include <new>
 #include <string>
+#include <vector>
 
 #include <hipfft/hipfft.h>
 
@@ -33,14 +34,6 @@ __global__ void zero_f64_kernel(double* __restrict__ p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0.0;
-}
-
-__global__ void zero_i32x2_kernel(int32_t* __restrict__ a, int32_t* __restrict__ b, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        a[i] = 0;
-        b[i] = 0;
-    }
 }
 
 // Lower mesh corner and the weight of the upper corner per axis.
@@ -56,128 +49,330 @@ __device__ __forceinline__ void cic_corner(double x, double L, double inv_d, int
     i0 = i < N ? i : N - 1;
 }
 
-// Cell of every particle (the key of the sort), the identity payload, and
-// the particle's upper-corner weights and mass as one record (input order).
-__global__ void __launch_bounds__(256) cic_cell_kernel(const double* __restrict__ pos,
-                                                       const float* __restrict__ mass, int64_t n,
-                                                       double L, double inv_d, int N,
-                                                       uint64_t* __restrict__ key,
-                                                       int32_t* __restrict__ idx,
-                                                       double4* __restrict__ rec_in) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    int ix, iy, iz;
-    double fx, fy, fz;
-    cic_corner(pos[p], L, inv_d, N, ix, fx);
-    cic_corner(pos[n + p], L, inv_d, N, iy, fy);
-    cic_corner(pos[2 * n + p], L, inv_d, N, iz, fz);
-    key[p] = ((uint64_t)ix * N + iy) * N + iz;
-    idx[p] = (int32_t)p;
-    rec_in[p] = make_double4(fx, fy, fz, (double)mass[p]);
+// ------------------------------------------------------- sort by cell --
+// A stable radix sort of (cell, particle) by the cell number, lowest digit
+// first, digits of up to 11 bits: per pass a count of every tile's digits, a
+// prefix over the tiles and a scatter.  Two passes for up to 2^22 cells, where
+// a general sort of 64-bit keys takes three of 12-byte pairs and clears its
+// look-back state before each: 72 us at 2.1 M particles and 128^3 cells,
+// against 144.  Three passes of 7 bits here take 79 (longer runs of writes, one
+// more pass), tiles of 8192 particles 80.
+constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64, kSortItems = 8;
+constexpr int kSortTile = kSortThreads * kSortItems;
+constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits;
+
+struct Digit {
+    int shift, bits;
+    __device__ __forceinline__ uint32_t of(uint32_t key) const { return (key >> shift) & ((1u << bits) - 1u); }
+};
+
+// The tile's digit counts (LDS) to its row of the table.
+__device__ __forceinline__ void write_counts(const uint32_t* hist, int bits, uint32_t* __restrict__ counts) {
+    __syncthreads();
+    uint32_t* row = counts + ((int64_t)blockIdx.x << bits);
+    for (int d = threadIdx.x; d < 1 << bits; d += kSortThreads) row[d] = hist[d];
 }
 
-// Per occupied cell, its run [cbeg, cend) of the sorted particles (cells
-// that hold none keep the empty run [0, 0)); and the particle records in the
-// sorted order.
-__global__ void __launch_bounds__(256) cic_runs_kernel(const uint64_t* __restrict__ key_s,
-                                                       const int32_t* __restrict__ perm,
-                                                       const double4* __restrict__ rec_in, int64_t n,
-                                                       int32_t* __restrict__ cbeg,
-                                                       int32_t* __restrict__ cend,
-                                                       double4* __restrict__ rec) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const uint64_t c = key_s[k];
-    if (k == 0 || key_s[k - 1] != c) cbeg[c] = (int32_t)k;
-    if (k == n - 1 || key_s[k + 1] != c) cend[c] = (int32_t)(k + 1);
-    rec[k] = rec_in[perm[k]];
+// Cell of every particle (the key of the sort) and its upper-corner weights
+// and mass as one record (input order); the first pass's digit counts; and
+// every cell's run cleared.  One workgroup per tile of the sort; with few tiles
+// more of them for the clearing (two tiles alone took 60 us for 128^3 cells).
+__global__ void __launch_bounds__(kSortThreads) cic_cell_kernel(const double* __restrict__ pos,
+                                                                const float* __restrict__ mass, int64_t n,
+                                                                double L, double inv_d, int N, Digit dig,
+                                                                uint32_t* __restrict__ key,
+                                                                double4* __restrict__ rec_in,
+                                                                uint32_t* __restrict__ counts,
+                                                                int2* __restrict__ run, int64_t cells) {
+    __shared__ uint32_t hist[kDigits];
+    for (int d = threadIdx.x; d < 1 << dig.bits; d += kSortThreads) hist[d] = 0;
+    for (int64_t c = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; c < cells;
+         c += (int64_t)gridDim.x * kSortThreads)
+        run[c] = make_int2(0, 0);
+    if ((int64_t)blockIdx.x * kSortTile >= n) return;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * kSortTile + threadIdx.x;
+#pragma unroll 4
+    for (int i = 0; i < kSortItems; ++i) {
+        const int64_t p = first + (int64_t)i * kSortThreads;
+        if (p >= n) break;
+        int ix, iy, iz;
+        double fx, fy, fz;
+        cic_corner(pos[p], L, inv_d, N, ix, fx);
+        cic_corner(pos[n + p], L, inv_d, N, iy, fy);
+        cic_corner(pos[2 * n + p], L, inv_d, N, iz, fz);
+        const uint32_t c = ((uint32_t)ix * N + iy) * N + iz;
+        key[p] = c;
+        rec_in[p] = make_double4(fx, fy, fz, (double)mass[p]);
+        atomicAdd(&hist[dig.of(c)], 1u);
+    }
+    write_counts(hist, dig.bits, counts);
 }
 
-constexpr int kCicChunk = 32;         // particles per partial sum of a cell's run
-
-// Chunks of at most kCicChunk particles per cell run.
-__global__ void __launch_bounds__(256) cic_nchunk_kernel(const int32_t* __restrict__ cbeg,
-                                                         const int32_t* __restrict__ cend,
-                                                         int64_t cells, int32_t* __restrict__ nch) {
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < cells;
-         c += (int64_t)gridDim.x * blockDim.x)
-        nch[c] = (cend[c] - cbeg[c] + kCicChunk - 1) / kCicChunk;
-}
-
-// The 8 corner sums of one chunk (one thread per chunk; its cell found by
-// bisection of the chunk offsets): corner (a, b, c) of the particle's cell
-// gets m prod (a ? f : 1 - f), particles in the sorted order.
-__global__ void __launch_bounds__(256) cic_chunk_kernel(const int32_t* __restrict__ cbeg,
-                                                        const int32_t* __restrict__ cend,
-                                                        const int64_t* __restrict__ choff,
-                                                        const double4* __restrict__ rec,
-                                                        int64_t cells, int64_t max_chunks,
-                                                        double* __restrict__ part) {
-    const int64_t nchunk = choff[cells];
-    for (int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; o < nchunk && o < max_chunks;
-         o += (int64_t)gridDim.x * blockDim.x) {
-        int64_t lo = 0, hi = cells - 1;          // the last cell with choff[cell] <= o
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) >> 1;
-            if (choff[mid] <= o) lo = mid;
-            else hi = mid - 1;
-        }
-        const int32_t a0 = cbeg[lo] + (int32_t)(o - choff[lo]) * kCicChunk;
-        const int32_t a1 = a0 + kCicChunk < cend[lo] ? a0 + kCicChunk : cend[lo];
-        double w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int32_t q = a0; q < a1; ++q) {
-            const double4 r = rec[q];
-            const double x[2] = {1.0 - r.x, r.x}, y[2] = {1.0 - r.y, r.y}, z[2] = {1.0 - r.z, r.z};
+// Digit counts of a later pass's tiles.
+__global__ void __launch_bounds__(kSortThreads) digit_count_kernel(const uint2* __restrict__ in, int64_t n, Digit dig,
+                                                                   uint32_t* __restrict__ counts) {
+    __shared__ uint32_t hist[kDigits];
+    for (int d = threadIdx.x; d < 1 << dig.bits; d += kSortThreads) hist[d] = 0;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * kSortTile + threadIdx.x;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] += r.w * x[k >> 2] * y[(k >> 1) & 1] * z[k & 1];
-        }
+    for (int i = 0; i < kSortItems; ++i) {
+        const int64_t p = first + (int64_t)i * kSortThreads;
+        if (p < n) atomicAdd(&hist[dig.of(in[p].x)], 1u);
+    }
+    write_counts(hist, dig.bits, counts);
+}
+
+// Per digit (a lane each, 64 per workgroup) the counts of the tiles become
+// their exclusive prefix over the tiles, and the digit's total is kept.  The
+// 16 waves take a stretch of the tiles each.
+__global__ void __launch_bounds__(1024) digit_scan_kernel(uint32_t* __restrict__ counts, int64_t ntile, int bits,
+                                                          uint32_t* __restrict__ total) {
+    __shared__ uint32_t sum[16][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t* col = counts + blockIdx.x * 64 + lane;
+    const int64_t t0 = ntile * wv / 16, t1 = ntile * (wv + 1) / 16;
+    uint32_t mine = 0;
+#pragma unroll 8
+    for (int64_t t = t0; t < t1; ++t) mine += col[t << bits];
+    sum[wv][lane] = mine;
+    __syncthreads();
+    uint32_t at = 0;
+    for (int k = 0; k < wv; ++k) at += sum[k][lane];
+    if (wv == 15) total[blockIdx.x * 64 + lane] = at + mine;
+#pragma unroll 8
+    for (int64_t t = t0; t < t1; ++t) {
+        const uint32_t c = col[t << bits];
+        col[t << bits] = at;
+        at += c;
+    }
+}
+
+// One pass: every particle to its digit's place.  A wave takes 512
+// consecutive entries, 64 at a time; lanes with the same digit find one
+// another by a ballot per bit, and the first of them moves the wave's count
+// of that digit in LDS.  FIRST: `key` alone is read, entry p is particle p.
+template <bool FIRST>
+__global__ void __launch_bounds__(kSortThreads) digit_scatter_kernel(const uint32_t* __restrict__ key,
+                                                                     const uint2* __restrict__ in, int64_t n,
+                                                                     Digit dig, const uint32_t* __restrict__ counts,
+                                                                     const uint32_t* __restrict__ total,
+                                                                     uint2* __restrict__ out) {
+    __shared__ uint16_t cnt[kSortWaves][kDigits];
+    __shared__ uint32_t base[kDigits];
+    __shared__ uint32_t wsum[kSortWaves];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int D = 1 << dig.bits;
+    const int64_t first = (int64_t)blockIdx.x * kSortTile + wv * 64 * kSortItems + lane;
+    uint2 v[kSortItems];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) part[8 * o + k] = w[k];
+    for (int i = 0; i < kSortItems; ++i) {
+        const int64_t p = first + 64 * i;
+        v[i] = make_uint2(0u, 0u);
+        if (p < n) v[i] = FIRST ? make_uint2(key[p], (uint32_t)p) : in[p];
+    }
+    uint32_t* z = reinterpret_cast<uint32_t*>(cnt);
+    for (int d = threadIdx.x; d < kSortWaves * kDigits / 2; d += kSortThreads) z[d] = 0;
+    // the digits' first places: totals of the smaller digits, then of the
+    // earlier tiles
+    constexpr int PER = kDigits / kSortThreads;
+    uint32_t t[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = PER * threadIdx.x + k;
+        t[k] = d < D ? total[d] : 0u;
+        sum += t[k];
+    }
+    uint32_t upto = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t below = __shfl_up(upto, o);
+        if (lane >= o) upto += below;
+    }
+    if (lane == 63) wsum[wv] = upto;
+    __syncthreads();
+    uint32_t at = upto - sum;
+    for (int k = 0; k < wv; ++k) at += wsum[k];
+    const uint32_t* row = counts + ((int64_t)blockIdx.x << dig.bits);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = PER * threadIdx.x + k;
+        if (d < D) base[d] = at + row[d];
+        at += t[k];
+    }
+    uint32_t rank[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        const bool on = first + 64 * i < n;
+        const uint32_t d = dig.of(v[i].x);
+        uint64_t same = __ballot(on);
+        for (int k = 0; k < dig.bits; ++k) {
+            const bool bit = (d >> k) & 1u;
+            const uint64_t with = __ballot(bit);
+            same &= bit ? with : ~with;
+        }
+        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+        const uint32_t c = cnt[wv][d];
+        wave_sync();
+        if (on && below == 0) cnt[wv][d] = (uint16_t)(c + __popcll(same));
+        wave_sync();
+        rank[i] = c + below;
+    }
+    __syncthreads();
+    for (int d = threadIdx.x; d < D; d += kSortThreads) {
+        uint32_t sofar = 0;
+#pragma unroll
+        for (int k = 0; k < kSortWaves; ++k) {
+            const uint32_t c = cnt[k][d];
+            cnt[k][d] = (uint16_t)sofar;
+            sofar += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; ++i) {
+        if (first + 64 * i >= n) break;
+        const uint32_t d = dig.of(v[i].x);
+        out[base[d] + cnt[wv][d] + rank[i]] = v[i];
+    }
+}
+
+// --------------------------------------------------------- assignment --
+// The corner sums of a cell's particles within one 64-entry window of the
+// sorted order.  They are stored by window where the particles start with
+// the window (so that a long run has a place for each window), else by cell
+// or, when there are fewer particles than cells, by the first particle.
+struct PartAt {
+    int64_t few;         // min(n, cells): places before the windows' own
+    int by_cell;
+    __device__ __forceinline__ int64_t of(int64_t cell, int64_t k) const {
+        return (k & 63) == 0 ? few + (k >> 6) : (by_cell ? cell : k);
+    }
+};
+
+// One wave per window of 64 sorted particles: the records in sorted order,
+// every occupied cell's run of sorted particles, and the 8 corner sums of
+// the window's part of each run, in order: corner (a, b, c) of the
+// particles' cell gets m prod (a ? f : 1 - f).  8 lanes share a run, a corner
+// each, and read the window's records from LDS.  Bound by the gather of the
+// records (32 bytes each from a random line): 70 us at 2.1 M particles, where
+// the records' gather, the chunks' offsets and their sums took four kernels
+// and 159.
+__global__ void __launch_bounds__(256) cic_deposit_kernel(const uint2* __restrict__ sorted,
+                                                          const double4* __restrict__ rec_in, int64_t n, PartAt pa,
+                                                          int2* __restrict__ run, double4* __restrict__ rec,
+                                                          double* __restrict__ part) {
+    __shared__ double4 s_rec[4][64];
+    __shared__ int s_head[4][65];
+    __shared__ uint32_t s_cell[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t k0 = (int64_t)blockIdx.x * 256 + 64 * wv, k = k0 + lane;
+    if (k0 >= n) return;
+    const bool on = k < n;
+    const uint2 kv = on ? sorted[k] : make_uint2(0u, 0u);
+    uint32_t prev = __shfl_up(kv.x, 1), next = __shfl_down(kv.x, 1);
+    if (lane == 0 && k > 0) prev = sorted[k - 1].x;
+    if (lane == 63 && k + 1 < n) next = sorted[k + 1].x;
+    const bool first = on && (k == 0 || prev != kv.x), last = on && (k + 1 == n || next != kv.x);
+    if (first) run[kv.x].x = (int)k;
+    if (last) run[kv.x].y = (int)(k + 1);
+    if (on) {
+        const double4 r = rec_in[kv.y];
+        rec[k] = r;
+        s_rec[wv][lane] = r;
+        s_cell[wv][lane] = kv.x;
+    }
+    const bool head = first || (on && lane == 0);
+    const uint64_t heads = __ballot(head);
+    const int nrun = __popcll(heads);
+    if (head) s_head[wv][__builtin_amdgcn_mbcnt_hi((uint32_t)(heads >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)heads, 0u))] = lane;
+    if (lane == 0) s_head[wv][nrun] = n - k0 < 64 ? (int)(n - k0) : 64;
+    wave_sync();
+    const int corner = lane & 7;
+    for (int h = lane >> 3; h < nrun; h += 8) {
+        const int q0 = s_head[wv][h], q1 = s_head[wv][h + 1];
+        double w = 0.0;
+        for (int q = q0; q < q1; ++q) {
+            const double4 r = s_rec[wv][q];
+            w += r.w * (corner & 4 ? r.x : 1.0 - r.x) * (corner & 2 ? r.y : 1.0 - r.y) *
+                 (corner & 1 ? r.z : 1.0 - r.z);
+        }
+        part[8 * pa.of(s_cell[wv][q0], k0 + q0) + corner] = w;
     }
 }
 
 // Mesh point (i, j, k) takes corner (a, b, c) of cell (i - a, j - b, k - c)
 // (periodic): the CIC assignment seen from the mesh, with the cells and
-// their chunks in a fixed order.
-__global__ void __launch_bounds__(256) cic_gather_kernel(const int64_t* __restrict__ choff,
-                                                         const double* __restrict__ part, int N,
+// their windows in a fixed order.  A lane reads the sums of corners c = 0 and
+// 1 of the four cells (i - a, j - b, k) together, 16 bytes each; c = 1 belongs
+// to the next point of the row, so a lane takes it from the lane before it
+// (the first of a wave or a row reads its own).  Bound by the scattered loads:
+// 56 us on a 128^3 mesh with 8 loads of 8 bytes per point, 42 so.
+__global__ void __launch_bounds__(256) cic_gather_kernel(const int2* __restrict__ run,
+                                                         const double* __restrict__ part, PartAt pa, int N,
                                                          double* __restrict__ rho) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t total = (int64_t)N * N * N;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(e % N);
-        const int j = (int)((e / N) % N);
-        const int i = (int)(e / ((int64_t)N * N));
-        double sum = 0.0;
+    const int lane = threadIdx.x & 63;
+    const bool on = e < total;
+    const uint32_t p = on ? (uint32_t)e : 0u;
+    const int k = (int)(p % (uint32_t)N);
+    const int j = (int)((p / (uint32_t)N) % (uint32_t)N);
+    const int i = (int)(p / (uint32_t)(N * N));
+    uint32_t row[4];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int ci = i - a < 0 ? N - 1 : i - a;
-                    const int cj = j - b < 0 ? N - 1 : j - b;
-                    const int ck = k - c < 0 ? N - 1 : k - c;
-                    const int64_t cell = ((int64_t)ci * N + cj) * N + ck;
-                    const int corner = 4 * a + 2 * b + c;
-                    for (int64_t o = choff[cell]; o < choff[cell + 1]; ++o) sum += part[8 * o + corner];
-                }
-        rho[e] = sum;
+    for (int q = 0; q < 4; ++q) {
+        const int ci = q & 2 ? (i == 0 ? N - 1 : i - 1) : i, cj = q & 1 ? (j == 0 ? N - 1 : j - 1) : j;
+        row[q] = ((uint32_t)ci * N + cj) * N;
     }
+    // sums over the four cells at height kz of their corner pairs
+    auto pairs = [&](int kz, double& c0, double& c1) {
+        int2 r[4];
+        double2 w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r[q] = run[row[q] + kz];
+        const double2* pair = reinterpret_cast<const double2*>(part);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            w[q] = r[q].x < r[q].y ? pair[4 * pa.of(row[q] + kz, r[q].x) + q] : make_double2(0.0, 0.0);
+        c0 = 0.0;
+        c1 = 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c0 += w[q].x;
+            c1 += w[q].y;
+            for (int64_t o = ((int64_t)(r[q].x >> 6) + 1) << 6; o < r[q].y; o += 64) {
+                const double2 v = pair[4 * pa.of(row[q] + kz, o) + q];
+                c0 += v.x;
+                c1 += v.y;
+            }
+        }
+    };
+    double c0, c1, own, low;
+    pairs(k, c0, c1);
+    low = __shfl_up(c1, 1);
+    if (lane == 0 || k == 0) pairs(k == 0 ? N - 1 : k - 1, own, low);
+    if (on) rho[e] = c0 + low;
 }
 
 // phi_k = -g_k rho_k e^{-k^2 r_s^2}; scale folds in the density 1/Delta^3
 // and the 1/N^3 of the unnormalised inverse FFT.
-__global__ void __launch_bounds__(256) green_kernel(hipfftDoubleComplex* __restrict__ rk, int N,
+// sin2: sin^2(pi l / N) for l = 0 .. N - 1 (three sines per point took most
+// of the time: 19 us on a 128^3 mesh, 12 with the table).
+__global__ void __launch_bounds__(256) green_kernel(hipfftDoubleComplex* __restrict__ rk,
+                                                    const double* __restrict__ sin2, int N,
                                                     double L, double G, double rs, double scale) {
     const int nzh = N / 2 + 1;
     const int64_t total = (int64_t)N * N * nzh;
     const double pi = 3.14159265358979323846;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
-        const int kz = (int)(e % nzh);
-        const int ky = (int)((e / nzh) % N);
-        const int kx = (int)(e / ((int64_t)nzh * N));
+        const int kz = (int)((uint32_t)e % (uint32_t)nzh);
+        const int ky = (int)(((uint32_t)e / (uint32_t)nzh) % (uint32_t)N);
+        const int kx = (int)((uint32_t)e / (uint32_t)(nzh * N));
         if (kx == 0 && ky == 0 && kz == 0) {
             rk[e].x = 0.0;
             rk[e].y = 0.0;
@@ -185,8 +380,7 @@ __global__ void __launch_bounds__(256) green_kernel(hipfftDoubleComplex* __restr
         }
         const int lx = kx <= N / 2 ? kx : kx - N;
         const int ly = ky <= N / 2 ? ky : ky - N;
-        const double sx = sin(pi * lx / N), sy = sin(pi * ly / N), sz = sin(pi * kz / N);
-        const double S = sx * sx + sy * sy + sz * sz;
+        const double S = sin2[kx] + sin2[ky] + sin2[kz];
         const double d = L / N;
         const double k2 = (2.0 * pi / L) * (2.0 * pi / L) * (double)(lx * lx + ly * ly + kz * kz);
         const double f = -pi * G * d * d / S * exp(-k2 * rs * rs) * scale;
@@ -195,57 +389,73 @@ __global__ void __launch_bounds__(256) green_kernel(hipfftDoubleComplex* __restr
     }
 }
 
-// -grad phi by (8 (phi[i+1] - phi[i-1]) - (phi[i+2] - phi[i-2])) / (12 Delta).
+// -grad phi by (8 (phi[i+1] - phi[i-1]) - (phi[i+2] - phi[i-2])) / (12 Delta),
+// the three components of a point side by side.  Rows have N + 1 points, the
+// last one the first again, so that the two upper corners of a cell always
+// follow the lower ones.
 __global__ void __launch_bounds__(256) gradient_kernel(const double* __restrict__ phi, int N,
                                                        double inv_12d, double* __restrict__ g) {
-    const int64_t total = (int64_t)N * N * N;
+    const int64_t total = (int64_t)N * N * (N + 1);
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(e % N);
-        const int j = (int)((e / N) % N);
-        const int i = (int)(e / ((int64_t)N * N));
+        const uint32_t row = (uint32_t)(e / (N + 1));
+        const int kk = (int)(e - (int64_t)row * (N + 1)), k = kk == N ? 0 : kk;
+        const int j = (int)(row % (uint32_t)N);
+        const int i = (int)(row / (uint32_t)N);
         auto at = [&](int a, int b, int c) { return phi[((int64_t)a * N + b) * N + c]; };
         auto w = [&](int a) { return a >= N ? a - N : (a < 0 ? a + N : a); };
-        g[e] = -(8.0 * (at(w(i + 1), j, k) - at(w(i - 1), j, k)) - (at(w(i + 2), j, k) - at(w(i - 2), j, k))) * inv_12d;
-        g[total + e] = -(8.0 * (at(i, w(j + 1), k) - at(i, w(j - 1), k)) - (at(i, w(j + 2), k) - at(i, w(j - 2), k))) * inv_12d;
-        g[2 * total + e] = -(8.0 * (at(i, j, w(k + 1)) - at(i, j, w(k - 1))) - (at(i, j, w(k + 2)) - at(i, j, w(k - 2)))) * inv_12d;
+        g[3 * e] = -(8.0 * (at(w(i + 1), j, k) - at(w(i - 1), j, k)) - (at(w(i + 2), j, k) - at(w(i - 2), j, k))) * inv_12d;
+        g[3 * e + 1] = -(8.0 * (at(i, w(j + 1), k) - at(i, w(j - 1), k)) - (at(i, w(j + 2), k) - at(i, w(j - 2), k))) * inv_12d;
+        g[3 * e + 2] = -(8.0 * (at(i, j, w(k + 1)) - at(i, j, w(k - 1))) - (at(i, j, w(k + 2)) - at(i, j, w(k - 2)))) * inv_12d;
     }
 }
 
-__global__ void __launch_bounds__(256) cic_interp_kernel(const uint64_t* __restrict__ key_s,
-                                                         const int32_t* __restrict__ perm,
+// Linear interpolation of the mesh acceleration, in sorted order (neighbouring
+// lanes read neighbouring mesh points).  The result goes to its particle as
+// one 16-byte store, and unpack_kernel writes the three arrays: three
+// scattered stores of 4 bytes each and 24 loads of 8 bytes from three mesh
+// arrays took 165 us at 2.1 M particles, this takes 68 + 9.  Bound by the
+// scattered stores and the 192 bytes of mesh per particle through the caches.
+__global__ void __launch_bounds__(256) cic_interp_kernel(const uint2* __restrict__ sorted,
                                                          const double4* __restrict__ rec, int64_t n,
                                                          int N, const double* __restrict__ g,
-                                                         float* __restrict__ acc) {
+                                                         float4* __restrict__ acc4) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
-    const uint64_t cell = key_s[k];
-    const int iz = (int)(cell % N);
-    const int iy = (int)((cell / N) % N);
-    const int ix = (int)(cell / ((uint64_t)N * N));
+    const uint2 kv = sorted[k];
+    const int iz = (int)(kv.x % (uint32_t)N);
+    const int iy = (int)((kv.x / (uint32_t)N) % (uint32_t)N);
+    const int ix = (int)(kv.x / (uint32_t)(N * N));
     const double4 r = rec[k];
     const double fx = r.x, fy = r.y, fz = r.z;
-    const int jx = ix + 1 == N ? 0 : ix + 1, jy = iy + 1 == N ? 0 : iy + 1, jz = iz + 1 == N ? 0 : iz + 1;
-    const int xs[2] = {ix, jx}, ys[2] = {iy, jy}, zs[2] = {iz, jz};
+    const int xs[2] = {ix, ix + 1 == N ? 0 : ix + 1}, ys[2] = {iy, iy + 1 == N ? 0 : iy + 1};
     const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
-    const int64_t total = (int64_t)N * N * N;
     double ax = 0, ay = 0, az = 0;
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < 2; ++b) {
+            double q[6];                     // two points along z
+            __builtin_memcpy(q, g + 3 * (((int64_t)xs[a] * N + ys[b]) * (N + 1) + iz), sizeof(q));
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
                 const double w = wx[a] * wy[b] * wz[c];
-                const int64_t e = ((int64_t)xs[a] * N + ys[b]) * N + zs[c];
-                ax += w * g[e];
-                ay += w * g[total + e];
-                az += w * g[2 * total + e];
+                ax += w * q[3 * c];
+                ay += w * q[3 * c + 1];
+                az += w * q[3 * c + 2];
             }
-    const int64_t p = perm[k];
-    acc[p] = (float)ax;
-    acc[n + p] = (float)ay;
-    acc[2 * n + p] = (float)az;
+        }
+    acc4[kv.y] = make_float4((float)ax, (float)ay, (float)az, 0.f);
+}
+
+__global__ void __launch_bounds__(256) unpack_kernel(const float4* __restrict__ acc4, int64_t n,
+                                                     float* __restrict__ acc) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n) return;
+    const float4 a = acc4[p];
+    acc[p] = a.x;
+    acc[n + p] = a.y;
+    acc[2 * n + p] = a.z;
 }
 
 const char* fft_text(hipfftResult r) {
@@ -278,14 +488,14 @@ struct pp_pm_plan {
     hipfftHandle fwd = nullptr, inv = nullptr;
     DevBuf rho;        // FP64 [N^3]: density, then potential (in place of the real field)
     DevBuf rk;         // complex [N][N][N/2+1]
-    DevBuf g;          // FP64 [3][N^3] mesh acceleration
-    DevBuf key, key_s, idx, perm;   // particle cells and the sort by cell
+    DevBuf g;          // FP64 [N][N][N + 1][3] mesh acceleration (gradient_kernel)
+    DevBuf sin2;       // FP64 [N]: sin^2(pi l / N)
+    DevBuf key;        // uint32 [n]: cells, input order
+    DevBuf pair_a, pair_b;          // uint2 [n]: (cell, particle), sorted by turns
+    DevBuf counts, total;           // digit counts of the sort's tiles, totals
     DevBuf rec_in, rec;             // double4 [n]: upper-corner weights, mass (input, sorted order)
-    DevBuf cbeg, cend;              // int32 [N^3]: each cell's run of sorted particles
-    DevBuf sort_ws;
-    DevBuf nch, choff;              // chunks per cell run and their offsets [N^3 + 1]
-    DevBuf part;                    // FP64 [chunks][8]: corner sums per chunk
-    DevBuf scan_ws;
+    DevBuf run;                     // int2 [N^3]: each cell's run of sorted particles
+    DevBuf part;                    // FP64 [places][8]: corner sums (PartAt)
     ~pp_pm_plan() {
         if (fwd) hipfftDestroy(fwd);
         if (inv) hipfftDestroy(inv);
@@ -307,6 +517,8 @@ int pp_pm_plan_create(const pp_box_params* p, int32_t n_mesh, pp_pm_plan** out) 
     if (n_mesh < 4 || n_mesh > 2048) return fail(PP_EINVAL, "n_mesh must be in 4..2048");
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev == 0) return fail(PP_EDEVICE, "no HIP device");
+    // cell numbers are 32-bit; the mesh arrays of more cells exceed the memory
+    if ((int64_t)n_mesh * n_mesh * n_mesh > UINT32_MAX) return fail(PP_ENOMEM, "the mesh does not fit the device memory");
     pp_pm_plan* pl = new (std::nothrow) pp_pm_plan;
     if (!pl) return fail(PP_ENOMEM, "host allocation failed");
     pl->p = *p;
@@ -314,11 +526,18 @@ int pp_pm_plan_create(const pp_box_params* p, int32_t n_mesh, pp_pm_plan** out) 
     const int64_t N = n_mesh, cells = N * N * N, half = N * N * (N / 2 + 1);
     int rc = pl->rho.reserve(sizeof(double) * cells);
     if (rc == PP_OK) rc = pl->rk.reserve(sizeof(hipfftDoubleComplex) * half);
-    if (rc == PP_OK) rc = pl->g.reserve(sizeof(double) * 3 * cells);
-    if (rc == PP_OK) rc = pl->cbeg.reserve(sizeof(int32_t) * cells);
-    if (rc == PP_OK) rc = pl->cend.reserve(sizeof(int32_t) * cells);
-    if (rc == PP_OK) rc = pl->nch.reserve(sizeof(int32_t) * (cells + 1));
-    if (rc == PP_OK) rc = pl->choff.reserve(sizeof(int64_t) * (cells + 1));
+    if (rc == PP_OK) rc = pl->g.reserve(sizeof(double) * 3 * N * N * (N + 1));
+    if (rc == PP_OK) rc = pl->run.reserve(sizeof(int2) * cells);
+    if (rc == PP_OK) rc = pl->sin2.reserve(sizeof(double) * N);
+    if (rc == PP_OK) {
+        std::vector<double> t(N);
+        for (int64_t l = 0; l < N; ++l) {
+            const double v = sin(M_PI * (double)(l <= N / 2 ? l : N - l) / (double)N);
+            t[l] = v * v;
+        }
+        if (hipMemcpy(pl->sin2.p, t.data(), sizeof(double) * N, hipMemcpyHostToDevice) != hipSuccess)
+            rc = fail(PP_EDEVICE, "upload of the mesh's sines failed");
+    }
     if (rc == PP_OK) {
         hipfftResult r = hipfftPlan3d(&pl->fwd, n_mesh, n_mesh, n_mesh, HIPFFT_D2Z);
         if (r == HIPFFT_SUCCESS) r = hipfftPlan3d(&pl->inv, n_mesh, n_mesh, n_mesh, HIPFFT_Z2D);
@@ -343,41 +562,50 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
     const double L = pl->p.L, d = L / N;
     if (n > INT32_MAX) return fail(PP_EINVAL, "n must be below 2^31");
     double* rho = pl->rho.as<double>();
+    const uint2* sorted = nullptr;       // (cell, particle) by cell
     if (n > 0) {
-        int mb = 0;                      // bits per axis of the cell key
-        while ((1 << mb) < N) ++mb;
-        size_t ws = 0;
-        PP_TRY(sort_workspace(n, 1, mb, &ws));
-        PP_TRY(pl->key.reserve(sizeof(uint64_t) * n));
-        PP_TRY(pl->key_s.reserve(sizeof(uint64_t) * n));
-        PP_TRY(pl->idx.reserve(sizeof(int32_t) * n));
-        PP_TRY(pl->perm.reserve(sizeof(int32_t) * n));
+        int bits = 6;                    // of the cell number
+        while (((int64_t)1 << bits) < cells) ++bits;
+        const int npass = (bits + kDigitBits - 1) / kDigitBits;
+        const int dbits = (bits + npass - 1) / npass;
+        const int64_t ntile = (n + kSortTile - 1) / kSortTile;
+        const PartAt pa{n < cells ? n : cells, n > cells};
+        PP_TRY(pl->key.reserve(sizeof(uint32_t) * n));
+        PP_TRY(pl->pair_a.reserve(sizeof(uint2) * n));
+        PP_TRY(pl->pair_b.reserve(sizeof(uint2) * n));
+        PP_TRY(pl->counts.reserve((sizeof(uint32_t) * ntile) << dbits));
+        PP_TRY(pl->total.reserve(sizeof(uint32_t) << dbits));
         PP_TRY(pl->rec.reserve(sizeof(double4) * n));
         PP_TRY(pl->rec_in.reserve(sizeof(double4) * n));
-        PP_TRY(pl->sort_ws.reserve(ws + 1));
-        int32_t* cbeg = pl->cbeg.as<int32_t>();
-        int32_t* cend = pl->cend.as<int32_t>();
-        hipLaunchKernelGGL(zero_i32x2_kernel, dim3(2048), dim3(256), 0, s, cbeg, cend, cells);
-        hipLaunchKernelGGL(cic_cell_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, pos, mass, n, L,
-                           1.0 / d, N, pl->key.as<uint64_t>(), pl->idx.as<int32_t>(), pl->rec_in.as<double4>());
-        PP_HIP(hipGetLastError());
-        PP_TRY(launch_sort_raw(pl->key.as<uint64_t>(), pl->idx.as<int32_t>(), pl->key_s.as<uint64_t>(),
-                               pl->perm.as<int32_t>(), n, mb, pl->sort_ws.p, pl->sort_ws.bytes, s));
-        hipLaunchKernelGGL(cic_runs_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, pl->key_s.as<uint64_t>(),
-                           pl->perm.as<int32_t>(), pl->rec_in.as<double4>(), n, cbeg, cend,
-                           pl->rec.as<double4>());
-        int32_t* nch = pl->nch.as<int32_t>();
-        int64_t* choff = pl->choff.as<int64_t>();
-        hipLaunchKernelGGL(cic_nchunk_kernel, dim3(2048), dim3(256), 0, s, cbeg, cend, cells, nch);
-        PP_HIP(hipGetLastError());
-        PP_TRY(launch_scan_i32_to_i64(nch, choff, cells, pl->scan_ws, s));
-        // at most n / kCicChunk + (occupied cells) chunks
-        const int64_t max_chunks = n / kCicChunk + (n < cells ? n : cells) + 1;
-        PP_TRY(pl->part.reserve(sizeof(double) * 8 * max_chunks));
-        hipLaunchKernelGGL(cic_chunk_kernel, dim3(4096), dim3(256), 0, s, cbeg, cend, choff,
-                           pl->rec.as<double4>(), cells, max_chunks, pl->part.as<double>());
-        hipLaunchKernelGGL(cic_gather_kernel, dim3(4096), dim3(256), 0, s, choff, pl->part.as<double>(), N,
-                           rho);
+        PP_TRY(pl->part.reserve(sizeof(double) * 8 * (pa.few + n / 64 + 1)));
+        uint32_t* counts = pl->counts.as<uint32_t>();
+        uint32_t* total = pl->total.as<uint32_t>();
+        int2* run = pl->run.as<int2>();
+        const dim3 tiles((unsigned)ntile), threads(kSortThreads);
+        const int64_t clearing = (cells + 4 * kSortThreads - 1) / (4 * kSortThreads);
+        const int64_t most = clearing < 1024 ? clearing : 1024;
+        hipLaunchKernelGGL(cic_cell_kernel, dim3((unsigned)(ntile > most ? ntile : most)), threads, 0, s, pos, mass, n, L, 1.0 / d, N, Digit{0, dbits},
+                           pl->key.as<uint32_t>(), pl->rec_in.as<double4>(), counts, run, cells);
+        uint2* out = pl->pair_a.as<uint2>();
+        for (int pass = 0; pass < npass; ++pass) {
+            const Digit dig{pass * dbits, dbits};
+            const uint2* in = sorted;
+            if (pass > 0) hipLaunchKernelGGL(digit_count_kernel, tiles, threads, 0, s, in, n, dig, counts);
+            hipLaunchKernelGGL(digit_scan_kernel, dim3(1u << (dbits - 6)), dim3(1024), 0, s, counts, ntile, dbits,
+                               total);
+            if (pass == 0)
+                hipLaunchKernelGGL(digit_scatter_kernel<true>, tiles, threads, 0, s, pl->key.as<uint32_t>(), in, n,
+                                   dig, counts, total, out);
+            else
+                hipLaunchKernelGGL(digit_scatter_kernel<false>, tiles, threads, 0, s, (const uint32_t*)nullptr, in, n,
+                                   dig, counts, total, out);
+            PP_HIP(hipGetLastError());
+            sorted = out;
+            out = pass % 2 == 0 ? pl->pair_b.as<uint2>() : pl->pair_a.as<uint2>();
+        }
+        hipLaunchKernelGGL(cic_deposit_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, sorted,
+                           pl->rec_in.as<double4>(), n, pa, run, pl->rec.as<double4>(), pl->part.as<double>());
+        hipLaunchKernelGGL(cic_gather_kernel, dim3(blocks_for(cells, 256)), dim3(256), 0, s, run, pl->part.as<double>(), pa, N, rho);
     } else {
         hipLaunchKernelGGL(zero_f64_kernel, dim3(2048), dim3(256), 0, s, rho, cells);
     }
@@ -387,15 +615,17 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
     hipfftDoubleComplex* rk = pl->rk.as<hipfftDoubleComplex>();
     PM_FFT(hipfftExecD2Z(pl->fwd, rho, rk));
     const double scale = 1.0 / (d * d * d) / (double)cells;
-    hipLaunchKernelGGL(green_kernel, dim3(2048), dim3(256), 0, s, rk, N, L, pl->p.G, pl->p.rs, scale);
+    hipLaunchKernelGGL(green_kernel, dim3(2048), dim3(256), 0, s, rk, pl->sin2.as<double>(), N, L, pl->p.G, pl->p.rs, scale);
     PP_HIP(hipGetLastError());
     PM_FFT(hipfftExecZ2D(pl->inv, rk, rho));
     double* g = pl->g.as<double>();
     hipLaunchKernelGGL(gradient_kernel, dim3(2048), dim3(256), 0, s, rho, N, 1.0 / (12.0 * d), g);
-    if (n > 0)
-        hipLaunchKernelGGL(cic_interp_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s,
-                           pl->key_s.as<uint64_t>(), pl->perm.as<int32_t>(), pl->rec.as<double4>(), n, N, g,
-                           acc);
+    if (n > 0) {
+        float4* acc4 = pl->rec_in.as<float4>();          // the records in input order are no longer needed
+        hipLaunchKernelGGL(cic_interp_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, sorted,
+                           pl->rec.as<double4>(), n, N, g, acc4);
+        hipLaunchKernelGGL(unpack_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, acc4, n, acc);
+    }
     PP_HIP(hipGetLastError());
     return PP_OK;
 }
