@@ -321,7 +321,7 @@ struct Batch {
         w.pos_n = N;
         PP_TRY(reset_sizes(nbox, w, s));
         PP_TRY(stage_keys(bd, N, pos, mass_f, mass_d, w, s));
-        PP_TRY(stage_sort(bd, N, w, s));
+        PP_TRY(stage_sort(bd, N, params[0].rcut / params[0].L, w, s));
         if (mass_d) PP_TRY(w.mass_sd.reserve(8 * (N > 0 ? N : 1)));
         PP_TRY(stage_gather(N, mass_d != nullptr, w, s));
         if (mass_f && !table_ready && (tune.variant & 8)) {

@@ -26,6 +26,7 @@
 #include <hipfft/hipfft.h>
 
 #include "pp_internal.h"
+#include "radix.h"
 
 namespace pp {
 namespace {
@@ -50,28 +51,12 @@ __device__ __forceinline__ void cic_corner(double x, double L, double inv_d, int
 }
 
 // ------------------------------------------------------- sort by cell --
-// A stable radix sort of (cell, particle) by the cell number, lowest digit
-// first, digits of up to 11 bits: per pass a count of every tile's digits, a
-// prefix over the tiles and a scatter.  Two passes for up to 2^22 cells, where
-// a general sort of 64-bit keys takes three of 12-byte pairs and clears its
-// look-back state before each: 72 us at 2.1 M particles and 128^3 cells,
-// against 144.  Three passes of 7 bits here take 79 (longer runs of writes, one
-// more pass), tiles of 8192 particles 80.
-constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64, kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;
-constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits;
-
-struct Digit {
-    int shift, bits;
-    __device__ __forceinline__ uint32_t of(uint32_t key) const { return (key >> shift) & ((1u << bits) - 1u); }
-};
-
-// The tile's digit counts (LDS) to its row of the table.
-__device__ __forceinline__ void write_counts(const uint32_t* hist, int bits, uint32_t* __restrict__ counts) {
-    __syncthreads();
-    uint32_t* row = counts + ((int64_t)blockIdx.x << bits);
-    for (int d = threadIdx.x; d < 1 << bits; d += kSortThreads) row[d] = hist[d];
-}
+// Two passes of radix.h for up to 2^22 cells, where a general sort of 64-bit keys
+// takes three of 12-byte pairs and clears its look-back state before each: 72 us
+// at 2.1 M particles and 128^3 cells, against 144.  Three passes of 7 bits take 79
+// (longer runs of writes, one more pass), tiles of 8192 particles 80.
+constexpr int kCellItems = 8;
+constexpr int kCellTile = kSortThreads * kCellItems;
 
 // Cell of every particle (the key of the sort) and its upper-corner weights
 // and mass as one record (input order); the first pass's digit counts; and
@@ -89,11 +74,11 @@ __global__ void __launch_bounds__(kSortThreads) cic_cell_kernel(const double* __
     for (int64_t c = (int64_t)blockIdx.x * kSortThreads + threadIdx.x; c < cells;
          c += (int64_t)gridDim.x * kSortThreads)
         run[c] = make_int2(0, 0);
-    if ((int64_t)blockIdx.x * kSortTile >= n) return;
+    if ((int64_t)blockIdx.x * kCellTile >= n) return;
     __syncthreads();
-    const int64_t first = (int64_t)blockIdx.x * kSortTile + threadIdx.x;
+    const int64_t first = (int64_t)blockIdx.x * kCellTile + threadIdx.x;
 #pragma unroll 4
-    for (int i = 0; i < kSortItems; ++i) {
+    for (int i = 0; i < kCellItems; ++i) {
         const int64_t p = first + (int64_t)i * kSortThreads;
         if (p >= n) break;
         int ix, iy, iz;
@@ -107,136 +92,6 @@ __global__ void __launch_bounds__(kSortThreads) cic_cell_kernel(const double* __
         atomicAdd(&hist[dig.of(c)], 1u);
     }
     write_counts(hist, dig.bits, counts);
-}
-
-// Digit counts of a later pass's tiles.
-__global__ void __launch_bounds__(kSortThreads) digit_count_kernel(const uint2* __restrict__ in, int64_t n, Digit dig,
-                                                                   uint32_t* __restrict__ counts) {
-    __shared__ uint32_t hist[kDigits];
-    for (int d = threadIdx.x; d < 1 << dig.bits; d += kSortThreads) hist[d] = 0;
-    __syncthreads();
-    const int64_t first = (int64_t)blockIdx.x * kSortTile + threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const int64_t p = first + (int64_t)i * kSortThreads;
-        if (p < n) atomicAdd(&hist[dig.of(in[p].x)], 1u);
-    }
-    write_counts(hist, dig.bits, counts);
-}
-
-// Per digit (a lane each, 64 per workgroup) the counts of the tiles become
-// their exclusive prefix over the tiles, and the digit's total is kept.  The
-// 16 waves take a stretch of the tiles each.
-__global__ void __launch_bounds__(1024) digit_scan_kernel(uint32_t* __restrict__ counts, int64_t ntile, int bits,
-                                                          uint32_t* __restrict__ total) {
-    __shared__ uint32_t sum[16][64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t* col = counts + blockIdx.x * 64 + lane;
-    const int64_t t0 = ntile * wv / 16, t1 = ntile * (wv + 1) / 16;
-    uint32_t mine = 0;
-#pragma unroll 8
-    for (int64_t t = t0; t < t1; ++t) mine += col[t << bits];
-    sum[wv][lane] = mine;
-    __syncthreads();
-    uint32_t at = 0;
-    for (int k = 0; k < wv; ++k) at += sum[k][lane];
-    if (wv == 15) total[blockIdx.x * 64 + lane] = at + mine;
-#pragma unroll 8
-    for (int64_t t = t0; t < t1; ++t) {
-        const uint32_t c = col[t << bits];
-        col[t << bits] = at;
-        at += c;
-    }
-}
-
-// One pass: every particle to its digit's place.  A wave takes 512
-// consecutive entries, 64 at a time; lanes with the same digit find one
-// another by a ballot per bit, and the first of them moves the wave's count
-// of that digit in LDS.  FIRST: `key` alone is read, entry p is particle p.
-template <bool FIRST>
-__global__ void __launch_bounds__(kSortThreads) digit_scatter_kernel(const uint32_t* __restrict__ key,
-                                                                     const uint2* __restrict__ in, int64_t n,
-                                                                     Digit dig, const uint32_t* __restrict__ counts,
-                                                                     const uint32_t* __restrict__ total,
-                                                                     uint2* __restrict__ out) {
-    __shared__ uint16_t cnt[kSortWaves][kDigits];
-    __shared__ uint32_t base[kDigits];
-    __shared__ uint32_t wsum[kSortWaves];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int D = 1 << dig.bits;
-    const int64_t first = (int64_t)blockIdx.x * kSortTile + wv * 64 * kSortItems + lane;
-    uint2 v[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const int64_t p = first + 64 * i;
-        v[i] = make_uint2(0u, 0u);
-        if (p < n) v[i] = FIRST ? make_uint2(key[p], (uint32_t)p) : in[p];
-    }
-    uint32_t* z = reinterpret_cast<uint32_t*>(cnt);
-    for (int d = threadIdx.x; d < kSortWaves * kDigits / 2; d += kSortThreads) z[d] = 0;
-    // the digits' first places: totals of the smaller digits, then of the
-    // earlier tiles
-    constexpr int PER = kDigits / kSortThreads;
-    uint32_t t[PER], sum = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int d = PER * threadIdx.x + k;
-        t[k] = d < D ? total[d] : 0u;
-        sum += t[k];
-    }
-    uint32_t upto = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t below = __shfl_up(upto, o);
-        if (lane >= o) upto += below;
-    }
-    if (lane == 63) wsum[wv] = upto;
-    __syncthreads();
-    uint32_t at = upto - sum;
-    for (int k = 0; k < wv; ++k) at += wsum[k];
-    const uint32_t* row = counts + ((int64_t)blockIdx.x << dig.bits);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int d = PER * threadIdx.x + k;
-        if (d < D) base[d] = at + row[d];
-        at += t[k];
-    }
-    uint32_t rank[kSortItems];
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        const bool on = first + 64 * i < n;
-        const uint32_t d = dig.of(v[i].x);
-        uint64_t same = __ballot(on);
-        for (int k = 0; k < dig.bits; ++k) {
-            const bool bit = (d >> k) & 1u;
-            const uint64_t with = __ballot(bit);
-            same &= bit ? with : ~with;
-        }
-        const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
-                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-        const uint32_t c = cnt[wv][d];
-        wave_sync();
-        if (on && below == 0) cnt[wv][d] = (uint16_t)(c + __popcll(same));
-        wave_sync();
-        rank[i] = c + below;
-    }
-    __syncthreads();
-    for (int d = threadIdx.x; d < D; d += kSortThreads) {
-        uint32_t sofar = 0;
-#pragma unroll
-        for (int k = 0; k < kSortWaves; ++k) {
-            const uint32_t c = cnt[k][d];
-            cnt[k][d] = (uint16_t)sofar;
-            sofar += c;
-        }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kSortItems; ++i) {
-        if (first + 64 * i >= n) break;
-        const uint32_t d = dig.of(v[i].x);
-        out[base[d] + cnt[wv][d] + rank[i]] = v[i];
-    }
 }
 
 // --------------------------------------------------------- assignment --
@@ -568,7 +423,7 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
         while (((int64_t)1 << bits) < cells) ++bits;
         const int npass = (bits + kDigitBits - 1) / kDigitBits;
         const int dbits = (bits + npass - 1) / npass;
-        const int64_t ntile = (n + kSortTile - 1) / kSortTile;
+        const int64_t ntile = (n + kCellTile - 1) / kCellTile;
         const PartAt pa{n < cells ? n : cells, n > cells};
         PP_TRY(pl->key.reserve(sizeof(uint32_t) * n));
         PP_TRY(pl->pair_a.reserve(sizeof(uint2) * n));
@@ -581,24 +436,18 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
         uint32_t* counts = pl->counts.as<uint32_t>();
         uint32_t* total = pl->total.as<uint32_t>();
         int2* run = pl->run.as<int2>();
-        const dim3 tiles((unsigned)ntile), threads(kSortThreads);
-        const int64_t clearing = (cells + 4 * kSortThreads - 1) / (4 * kSortThreads);
+                const int64_t clearing = (cells + 4 * kSortThreads - 1) / (4 * kSortThreads);
         const int64_t most = clearing < 1024 ? clearing : 1024;
-        hipLaunchKernelGGL(cic_cell_kernel, dim3((unsigned)(ntile > most ? ntile : most)), threads, 0, s, pos, mass, n, L, 1.0 / d, N, Digit{0, dbits},
+        hipLaunchKernelGGL(cic_cell_kernel, dim3((unsigned)(ntile > most ? ntile : most)), dim3(kSortThreads), 0, s, pos, mass, n, L, 1.0 / d, N, Digit{0, dbits},
                            pl->key.as<uint32_t>(), pl->rec_in.as<double4>(), counts, run, cells);
         uint2* out = pl->pair_a.as<uint2>();
         for (int pass = 0; pass < npass; ++pass) {
             const Digit dig{pass * dbits, dbits};
-            const uint2* in = sorted;
-            if (pass > 0) hipLaunchKernelGGL(digit_count_kernel, tiles, threads, 0, s, in, n, dig, counts);
-            hipLaunchKernelGGL(digit_scan_kernel, dim3(1u << (dbits - 6)), dim3(1024), 0, s, counts, ntile, dbits,
-                               total);
             if (pass == 0)
-                hipLaunchKernelGGL(digit_scatter_kernel<true>, tiles, threads, 0, s, pl->key.as<uint32_t>(), in, n,
-                                   dig, counts, total, out);
+                launch_digit_pass<uint32_t, kCellItems, true>(pl->key.as<uint32_t>(), nullptr, n, dig, true, counts,
+                                                              total, out, s);
             else
-                hipLaunchKernelGGL(digit_scatter_kernel<false>, tiles, threads, 0, s, (const uint32_t*)nullptr, in, n,
-                                   dig, counts, total, out);
+                launch_digit_pass<uint32_t, kCellItems, false>(nullptr, sorted, n, dig, false, counts, total, out, s);
             PP_HIP(hipGetLastError());
             sorted = out;
             out = pass % 2 == 0 ? pl->pair_b.as<uint2>() : pl->pair_a.as<uint2>();

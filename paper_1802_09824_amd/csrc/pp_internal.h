@@ -247,6 +247,8 @@ struct Work {
     const uint8_t* mono1 = nullptr;
     const uint8_t* active = nullptr;     // the items' target flags (null: every target)
     DevBuf sort_ws, scan_ws, sort_tmp;
+    const void* sorted_rec = nullptr;   // (key, particle) by the keys' bits from sort_shift on, until the gather
+    int sort_shift = 0;
     // leaves
     DevBuf lbegin, lcount, llevel, lprefix, loff_dev;   // leaf boxes: tree_boxes[0 .. nleaf)
     int64_t nleaf = 0;                    // host copies, valid after leaves_to_host
@@ -283,7 +285,8 @@ int stage_keys(const BatchDev& bd, int64_t N, const double* pos, const float* ma
 int stage_mass_flags(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
 // out = in wrapped into [0, L) per box (the form every later stage expects)
 int stage_wrap_copy(const BatchDev& bd, int64_t N, const double* in, double* out, hipStream_t s);
-int stage_sort(const BatchDev& bd, int64_t N, Work& w, hipStream_t s);
+// reach: r_cut / L of the one box (unused in a batch)
+int stage_sort(const BatchDev& bd, int64_t N, double reach, Work& w, hipStream_t s);
 // the records in key order: FP64 positions, masses of the type given (f64)
 int stage_gather(int64_t N, bool f64, Work& w, hipStream_t s);
 int sort_workspace(int64_t n, int nbox, int bits, size_t* bytes);

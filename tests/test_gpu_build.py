@@ -124,3 +124,28 @@ def test_monopole_windows_match_tree_oracle(pp, n, leaf_max):
     mag = np.linalg.norm(ref["acc"], axis=0)
     e = np.linalg.norm(acc.astype(np.float64) - ref["acc"], axis=0) / np.maximum(mag, 1e-300)
     assert np.median(e) <= 1e-6 and np.percentile(e, 99.9) <= 1e-4, (np.median(e), np.percentile(e, 99.9))
+
+
+# 4096 particles and fewer take the library's sort, up to 131072 two passes of
+# own digits, more three; tiles of 1024, 2048 and 4096
+@pytest.mark.parametrize("n,mesh,spread", [(4096, 16, None), (4097, 16, None), (30000, 32, 0.02), (131072, 50, None),
+                                           (131073, 50, 0.3), (150000, 420, None), (1048577, 100, None)])
+def test_leading_bits_sort_orders_like_the_full_sort(pp, n, mesh, spread):
+    """A box alone (leading bits, then runs) against the same box beside a
+    second one (the library's sort of all bits): the same particle order, so
+    the same bits.  spread: half the particles in a cloud of that width, many
+    to a cell of the leading bits, some at one point."""
+    rng = np.random.default_rng(n)
+    p = BoxParams.from_mesh(50.0, mesh)
+    pos = rng.random((3, n)) * p.L
+    if spread is not None:
+        pos[:, ::2] = 20.0 + spread * rng.random((3, (n + 1) // 2))
+        pos[:, 100:140] = pos[:, 100:101]
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    other = BoxParams.from_mesh(30.0, 12)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    one = pp.Plan(p, n).accel(x, m)
+    bp = pp.BatchPlan([p, other], [n, 65])
+    y = dev(rng.random((3, 65)) * other.L, torch.float64)
+    two = bp.accel(torch.cat([x, y], 1), torch.cat([m, m[:65]]))
+    assert torch.equal(one, two[:, :n])
