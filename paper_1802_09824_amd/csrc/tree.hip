@@ -1409,79 +1409,147 @@ __global__ void __launch_bounds__(256) block_active_kernel(const int64_t* __rest
     if (lane == 0) bact[b] = m;
 }
 
-// Work items per block: its list in chunks (at least one item, so that every
+// What the item kernels read and write.
+struct ItemBuild {
+    ChunkArgs A;
+    const int32_t* slen;
+    const int32_t* bcount;
+    const int32_t* bboxid;
+    const uint64_t* bact;        // active lanes per block, or null
+    int64_t cap_block, cap_range, cap_item;
+    int npass, stop;
+    const int64_t* roff;
+    const int* bad;
+    int64_t* host;               // the host's page-locked copy of the sizes, or null
+    int64_t* sizes;
+    int32_t* box_chunk;
+    int32_t* icount;
+    int64_t* ioff;
+    int32_t* iblock;
+    int32_t* is0;
+    int32_t* is1;
+};
+
+// Work items of block b: its list in chunks (at least one item, so that every
 // target is written); none for a block without an active target when flags
-// are given.  With fresh lists (A.soff_e set) the boxes' chunks are found here too.
-__global__ void item_count_kernel(ChunkArgs A, const int32_t* __restrict__ slen,
-                                  const int32_t* __restrict__ bcount, int64_t* __restrict__ sizes,
-                                  int64_t cap_block, const int32_t* __restrict__ bboxid,
-                                  int32_t* __restrict__ box_chunk, const uint64_t* __restrict__ bact,
-                                  int32_t* __restrict__ icount) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= cap_block) return;
-    if (b >= sizes[kNBlock]) {
-        icount[b] = 0;
-        return;
+// are given.  With fresh lists (A.soff_e set) the boxes' chunks are found here
+// too.  cand: the block's (target, listed source) pairs; the kernel prunes some
+// sources further.
+__device__ __forceinline__ int32_t block_items(const ItemBuild& I, int64_t b, int64_t& chunk,
+                                               unsigned long long& cand) {
+    const int x = I.bboxid[b];
+    chunk = I.A.soff_e ? box_chunk_of(I.A, I.sizes, x) : I.box_chunk[x];
+    if (I.A.soff_e) {
+        if (b == 0) I.sizes[kTotalSrc] = I.A.soff_e[I.sizes[kNEntry]];
+        if (b == 0 || I.bboxid[b - 1] != x) I.box_chunk[x] = (int32_t)chunk;
     }
-    const int x = bboxid[b];
-    const int64_t chunk = A.soff_e ? box_chunk_of(A, sizes, x) : box_chunk[x];
-    if (A.soff_e) {
-        if (b == 0) sizes[kTotalSrc] = A.soff_e[sizes[kNEntry]];
-        if (b == 0 || bboxid[b - 1] != x) box_chunk[x] = (int32_t)chunk;
-    }
-    if (bact && bact[b] == 0) {
-        icount[b] = 0;
-        return;
-    }
-    const int32_t s = slen[b];
-    icount[b] = s <= 0 ? 1 : (int32_t)((s + chunk - 1) / chunk);
-    // (target, listed source) pairs; the kernel prunes some sources further
-    atomicAdd(reinterpret_cast<unsigned long long*>(sizes + kCand),
-              (unsigned long long)s * (unsigned long long)bcount[b]);
+    cand = 0;
+    if (I.bact && I.bact[b] == 0) return 0;
+    const int32_t s = I.slen[b];
+    cand = (unsigned long long)s * (unsigned long long)I.bcount[b];
+    return s <= 0 ? 1 : (int32_t)((s + chunk - 1) / chunk);
 }
 
-// Writes the items; the first workgroup also takes the item and range totals,
-// sets the flag that makes the PP kernels return, and copies the count slots
-// to the host's page-locked copy (host, when there is one), which saves a
-// copy operation behind the PP kernels.
-__global__ void item_fill_kernel(const int32_t* __restrict__ icount,
-                                 const int64_t* __restrict__ ioff, int64_t* __restrict__ sizes,
-                                 const int64_t* __restrict__ roff, int64_t cap_range, int npass, int stop,
-                                 const int* __restrict__ bad, int64_t* __restrict__ host, int64_t cap_item, const int32_t* __restrict__ slen,
-                                 const int32_t* __restrict__ bboxid,
-                                 const int32_t* __restrict__ box_chunk, int32_t* __restrict__ iblock,
-                                 int32_t* __restrict__ is0, int32_t* __restrict__ is1) {
+// The item and range totals, and the flag that makes the PP kernels return.
+__device__ __forceinline__ void finish_items(const ItemBuild& I, int64_t ni) {
+    int64_t* sizes = I.sizes;
+    const int64_t nr = I.roff[sizes[kNBlock]];
+    sizes[kNeedItem] = ni;
+    sizes[kNeedRange] = nr;
+    sizes[kNItem] = ni < I.cap_item ? ni : I.cap_item;
+    sizes[kNRange] = nr < I.cap_range ? nr : I.cap_range;
+    if (ni > I.cap_item) sizes[kOverflow] |= 8;
+    if (nr > I.cap_range) sizes[kOverflow] |= 4;
+    if (sizes[kStart] - I.npass > I.stop) sizes[kOverflow] |= 128;
+    sizes[kBad] = *I.bad;
+    sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
+}
+
+__device__ __forceinline__ void put_items(const ItemBuild& I, int64_t b, int64_t o, int32_t count, int64_t chunk) {
+    const int64_t len = I.slen[b];
+    for (int32_t c = 0; c < count; ++c) {
+        if (o + c >= I.cap_item) return;
+        I.iblock[o + c] = (int32_t)b;
+        I.is0[o + c] = (int32_t)(c * chunk);
+        I.is1[o + c] = (int32_t)((c + 1) * chunk < len ? (c + 1) * chunk : len);
+    }
+}
+
+__global__ void item_count_kernel(ItemBuild I) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= I.cap_block) return;
+    if (b >= I.sizes[kNBlock]) {
+        I.icount[b] = 0;
+        return;
+    }
+    int64_t chunk;
+    unsigned long long cand;
+    I.icount[b] = block_items(I, b, chunk, cand);
+    atomicAdd(reinterpret_cast<unsigned long long*>(I.sizes + kCand), cand);
+}
+
+// Writes the items; the first workgroup also finishes the sizes and copies
+// them to the host's copy, which saves a copy operation behind the PP kernels.
+__global__ void item_fill_kernel(ItemBuild I) {
+    int64_t* sizes = I.sizes;
     if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) {
-            const int64_t nb = sizes[kNBlock];
-            const int64_t ni = ioff[nb], nr = roff[nb];
-            sizes[kNeedItem] = ni;
-            sizes[kNeedRange] = nr;
-            sizes[kNItem] = ni < cap_item ? ni : cap_item;
-            sizes[kNRange] = nr < cap_range ? nr : cap_range;
-            if (ni > cap_item) sizes[kOverflow] |= 8;
-            if (nr > cap_range) sizes[kOverflow] |= 4;
-            if (sizes[kStart] - npass > stop) sizes[kOverflow] |= 128;
-            sizes[kBad] = *bad;
-            sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
-        }
+        if (threadIdx.x == 0) finish_items(I, I.ioff[sizes[kNBlock]]);
         __threadfence_block();
         __syncthreads();
-        if (host && threadIdx.x < kSizeSlots) host[threadIdx.x] = sizes[threadIdx.x];
+        if (I.host && threadIdx.x < kSizeSlots) I.host[threadIdx.x] = sizes[threadIdx.x];
     }
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= sizes[kNBlock]) return;
-    const int64_t o = ioff[b];
-    const int64_t chunk = box_chunk[bboxid[b]];
-    const int64_t len = slen[b];
-    for (int32_t c = 0; c < icount[b]; ++c) {
-        if (o + c >= cap_item) return;
-        iblock[o + c] = (int32_t)b;
-        is0[o + c] = (int32_t)(c * chunk);
-        is1[o + c] = (int32_t)((c + 1) * chunk < len ? (c + 1) * chunk : len);
-    }
+    put_items(I, b, I.ioff[b], I.icount[b], I.box_chunk[I.bboxid[b]]);
 }
 
+// Up to kFewItemBlocks blocks: one workgroup counts, scans and writes, a block per
+// thread, in the place of three launches (32 k particles: 20 us of kernels and
+// two gaps became 16; 1 k: 13 became 8).  Summing the entries here as well took
+// as long as the launch it saves: one workgroup waits for its binary searches.
+constexpr int kFewItemBlocks = 1024;
+
+__global__ void __launch_bounds__(kFewItemBlocks) item_small_kernel(ItemBuild I) {
+    __shared__ int32_t s_wave[kFewItemBlocks / 64];
+    __shared__ unsigned long long s_cand;
+    int64_t* sizes = I.sizes;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t b = threadIdx.x, nblock = sizes[kNBlock];
+    const bool any = b < nblock;
+    if (b == 0) s_cand = 0;
+    __syncthreads();
+    int64_t chunk = 1;
+    unsigned long long cand = 0;
+    const int32_t n = any ? block_items(I, b, chunk, cand) : 0;
+    int32_t upto = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t below = __shfl_up(upto, d);
+        cand += __shfl_xor(cand, d);
+        if (lane >= d) upto += below;
+    }
+    if (lane == 63) s_wave[wv] = upto;
+    if (lane == 0) atomicAdd(&s_cand, cand);
+    __syncthreads();
+    int64_t o = upto - n, total = 0;
+    for (int k = 0; k < kFewItemBlocks / 64; ++k) {
+        if (k == wv) o += total;
+        total += s_wave[k];
+    }
+    if (b < I.cap_block) {
+        I.icount[b] = n;
+        I.ioff[b] = o;
+    }
+    if (b == 0) {
+        I.ioff[I.cap_block] = total;
+        sizes[kCand] += s_cand;
+        finish_items(I, total);
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (I.host && threadIdx.x < kSizeSlots) I.host[threadIdx.x] = sizes[threadIdx.x];
+    if (any) put_items(I, b, o, n, chunk);
+}
 
 // Per-pass slots of a pass that reuses the lists (the list counts stay; the
 // overflow bits of the last pass go, since the lists' own buffers fitted).
@@ -1941,22 +2009,40 @@ static int make_items(const ChunkArgs& chunks, Work& w, hipStream_t s, const uin
                            w.perm.as<int32_t>(), w.bstart.as<int32_t>(), w.bcount.as<int32_t>(),
                            w.bact.as<uint64_t>());
     }
-    hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s, chunks,
-                       w.slen.as<int32_t>(), w.bcount.as<int32_t>(), sizes, cb, w.bboxid.as<int32_t>(),
-                       w.box_chunk.as<int32_t>(),
-                       active ? w.bact.as<uint64_t>() : (const uint64_t*)nullptr, w.icount.as<int32_t>());
-    PP_HIP(hipGetLastError());
-    PP_TRY(launch_scan_i32_to_i64(w.icount.as<int32_t>(), w.ioff.as<int64_t>(), cb, w.scan_ws, s, sizes));
     PP_TRY(w.iblock.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.is0.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.is1.reserve(sizeof(int32_t) * (w.cap_item + 1)));
     PP_TRY(w.sizes_h.reserve(sizeof(int64_t) * kSizeSlots));
-    int64_t* host = w.sizes_h.pinned ? w.sizes_h.as<int64_t>() : nullptr;
-    hipLaunchKernelGGL(item_fill_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s,
-                       w.icount.as<int32_t>(), w.ioff.as<int64_t>(), sizes, w.roff.as<int64_t>(), w.cap_range,
-                       w.npass - 1, kDfsLevel, w.bad.as<int>(), host, w.cap_item,
-                       w.slen.as<int32_t>(), w.bboxid.as<int32_t>(), w.box_chunk.as<int32_t>(),
-                       w.iblock.as<int32_t>(), w.is0.as<int32_t>(), w.is1.as<int32_t>());
+    ItemBuild I{};
+    I.A = chunks;
+    I.slen = w.slen.as<int32_t>();
+    I.bcount = w.bcount.as<int32_t>();
+    I.bboxid = w.bboxid.as<int32_t>();
+    I.bact = active ? w.bact.as<uint64_t>() : nullptr;
+    I.cap_block = cb;
+    I.cap_range = w.cap_range;
+    I.cap_item = w.cap_item;
+    I.npass = w.npass - 1;
+    I.stop = kDfsLevel;
+    I.roff = w.roff.as<int64_t>();
+    I.bad = w.bad.as<int>();
+    I.host = w.sizes_h.pinned ? w.sizes_h.as<int64_t>() : nullptr;
+    I.sizes = sizes;
+    I.box_chunk = w.box_chunk.as<int32_t>();
+    I.icount = w.icount.as<int32_t>();
+    I.ioff = w.ioff.as<int64_t>();
+    I.iblock = w.iblock.as<int32_t>();
+    I.is0 = w.is0.as<int32_t>();
+    I.is1 = w.is1.as<int32_t>();
+    if (cb <= kFewItemBlocks) {
+        hipLaunchKernelGGL(item_small_kernel, dim3(1), dim3(kFewItemBlocks), 0, s, I);
+        PP_HIP(hipGetLastError());
+        return PP_OK;
+    }
+    hipLaunchKernelGGL(item_count_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s, I);
+    PP_HIP(hipGetLastError());
+    PP_TRY(launch_scan_i32_to_i64(I.icount, I.ioff, cb, w.scan_ws, s, sizes));
+    hipLaunchKernelGGL(item_fill_kernel, dim3(blocks_for(cb, 256)), dim3(256), 0, s, I);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }

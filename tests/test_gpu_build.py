@@ -149,3 +149,25 @@ def test_leading_bits_sort_orders_like_the_full_sort(pp, n, mesh, spread):
     y = dev(rng.random((3, 65)) * other.L, torch.float64)
     two = bp.accel(torch.cat([x, y], 1), torch.cat([m, m[:65]]))
     assert torch.equal(one, two[:, :n])
+
+
+# blocks up to and beyond those of one item workgroup (1024, with the capacity's
+# margin of an eighth and 64), with and without active flags
+@pytest.mark.parametrize("n", [1, 64, 54500, 54700, 56000])
+def test_items_of_few_and_many_blocks(pp, oracle_mod, n):
+    rng = np.random.default_rng(n)
+    p = BoxParams.from_mesh(40.0, 30)
+    pos = W.mixture(rng, n, p.L, 0.4, 1 + n // 500)
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, n)
+    acc = plan.accel(x, m)
+    st = plan.stats()
+    t = np.sort(rng.choice(n, min(n, 200), replace=False))
+    ref = oracle_mod.accel(pos, mass.astype(np.float64), p, targets=t)
+    _, counts = plan.count_interactions(per_target=True)
+    assert np.array_equal(counts.cpu().numpy()[t], ref["n_inter"])
+    assert st["candidates"] >= st["evaluated"] > 0
+    active = torch.as_tensor(rng.random(n) < 0.3).cuda()
+    some = plan.accel_active(x, m, active.to(torch.uint8), torch.zeros_like(acc))
+    assert torch.equal(some[:, active], acc[:, active])
