@@ -907,18 +907,19 @@ __device__ __forceinline__ void expand2(const TreeView& tv, const IBox* nodes, i
                                         const IBox& A, const int s[3], int64_t W, int64_t T,
                                         uint32_t& pass, uint32_t& inside) {
     const int64_t c0 = 8 * i, nc = tv.cnt[h - 1];
-    const IBox* base = nodes + tv.off[h - 1];
+    const int n = nc - c0 < 8 ? (int)(nc - c0) : 8;
+    // all 8 boxes at once (past the last child: nodes of the next level, or the 8
+    // boxes that tree_node_bound adds), so that their loads overlap: child by
+    // child, 164 us in the range count on 2.1 M particles, so 136
+    IBox C[8];
+    __builtin_memcpy(C, nodes + tv.off[h - 1] + c0, sizeof(C));
     pass = 0;
     inside = 0;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        if (c0 + c < nc) {
-            const IBox C = base[c0 + c];
-            if (gap2_shift(A, C, s, W) < T) {
-                pass |= 1u << c;
-                if (maxd2_shift(A, C, s, W) < T) inside |= 1u << c;
-            }
-        }
+        const bool in = c < n && gap2_shift(A, C[c], s, W) < T;
+        pass |= in ? 1u << c : 0u;
+        inside |= in && maxd2_shift(A, C[c], s, W) < T ? 1u << c : 0u;
     }
 }
 
