@@ -49,48 +49,48 @@ TRAFFIC = {
     "sources": ["paper_1802_09824_amd/csrc/pp_kernels.hip",
                 "paper_1802_09824_amd/csrc/pp_internal.h",
                 "paper_1802_09824_amd/csrc/tree.hip"],
-    "sha1": "720ab4d49720f40a153c28a79d3c85e7edaf4e64",
+    "sha1": "8809c0f148722a3da38b071293f7e60ee9e26bf6",
     "fetch_scale": 1.99996,       # 1 GiB copy: 1048576 KiB / 524299.5 KiB of FETCH_SIZE
     "write_scale": 1.00000,       # 1 GiB copy: 1048576 KiB / 1048576.0 KiB of WRITE_SIZE
     # (chunk, waves per block, waves per CU (0: one workgroup per item), persistent):
     # (FETCH_SIZE KiB, WRITE_SIZE KiB) of the timed step's PP dispatch
     "kib": {
-        (1024, 1, 0, 0): (98508.5, 183744.5),
-        (1024, 1, 12, 1): (125898.2, 177636.7),
-        (1024, 1, 20, 1): (146260.6, 178276.7),
-        (1024, 1, 24, 1): (164353.3, 178596.7),
-        (1024, 1, 32, 1): (162324.5, 179108.7),
-        (2048, 1, 0, 0): (105528.3, 108829.9),
-        (2048, 1, 12, 1): (140234.6, 106034.8),
-        (2048, 1, 20, 1): (186092.7, 106656.2),
-        (2048, 1, 24, 1): (211390.6, 106965.2),
-        (2048, 1, 32, 1): (211354.8, 107477.7),
-        (2048, 2, 20, 1): (139695.2, 106031.5),
-        (2048, 2, 24, 1): (139916.9, 106156.1),
-        (2048, 2, 32, 1): (137368.6, 106416.7),
-        (4096, 1, 20, 1): (310858.3, 137882.4),
-        (4096, 1, 32, 1): (365708.2, 138533.8),
-        (4096, 2, 20, 1): (201871.1, 137840.6),
-        (4096, 2, 24, 1): (199949.9, 137962.2),
-        (4096, 2, 32, 1): (202702.9, 138224.7),
-        (4096, 4, 0, 0): (107140.8, 152063.1),
-        (4096, 4, 12, 1): (141256.6, 137574.5),
-        (4096, 4, 20, 1): (152858.9, 137806.2),
-        (4096, 4, 24, 1): (152999.6, 137875.5),
-        (4096, 4, 32, 1): (153520.7, 137999.6),
-        (8192, 2, 32, 1): (264249.4, 180883.7),
-        (8192, 4, 0, 0): (117253.4, 190447.5),
-        (8192, 4, 12, 1): (153192.7, 180898.8),
-        (8192, 4, 20, 1): (186151.2, 180916.6),
-        (8192, 4, 24, 1): (186111.5, 180942.6),
-        (8192, 4, 32, 1): (186622.2, 181113.0),
-        (8192, 8, 20, 1): (154129.4, 180899.1),
-        (8192, 8, 32, 1): (151935.3, 180978.5),
-        (16384, 4, 20, 1): (195679.2, 195550.9),
-        (16384, 4, 24, 1): (198638.8, 195604.2),
-        (16384, 4, 32, 1): (198745.4, 195723.9),
-        (16384, 8, 20, 1): (160202.6, 195599.1),
-        (16384, 8, 32, 1): (160010.7, 195668.2),
+        (1024, 1, 0, 0): (379328.4, 171295.8),
+        (1024, 1, 12, 1): (378858.0, 171342.9),
+        (1024, 1, 20, 1): (379418.8, 171318.0),
+        (1024, 1, 24, 1): (378953.4, 171317.2),
+        (1024, 1, 32, 1): (379112.8, 171323.4),
+        (2048, 1, 0, 0): (478970.6, 103392.7),
+        (2048, 1, 12, 1): (140064.1, 106461.6),
+        (2048, 1, 20, 1): (183324.9, 107546.4),
+        (2048, 1, 24, 1): (216059.3, 107726.2),
+        (2048, 1, 32, 1): (215654.7, 107783.7),
+        (2048, 2, 20, 1): (284069.8, 102598.2),
+        (2048, 2, 24, 1): (283978.4, 102608.1),
+        (2048, 2, 32, 1): (283977.7, 102605.4),
+        (4096, 1, 20, 1): (316657.5, 138619.1),
+        (4096, 1, 32, 1): (363614.9, 138590.1),
+        (4096, 2, 20, 1): (204178.2, 139005.4),
+        (4096, 2, 24, 1): (201290.7, 139028.0),
+        (4096, 2, 32, 1): (202091.6, 139028.4),
+        (4096, 4, 0, 0): (248165.3, 135606.8),
+        (4096, 4, 12, 1): (248262.2, 135606.8),
+        (4096, 4, 20, 1): (248241.4, 135601.8),
+        (4096, 4, 24, 1): (248258.3, 135613.6),
+        (4096, 4, 32, 1): (248235.9, 135614.3),
+        (8192, 2, 32, 1): (261078.8, 181357.8),
+        (8192, 4, 0, 0): (245807.0, 179134.0),
+        (8192, 4, 12, 1): (156491.2, 181503.6),
+        (8192, 4, 20, 1): (188352.2, 181695.2),
+        (8192, 4, 24, 1): (190085.4, 181737.5),
+        (8192, 4, 32, 1): (190562.8, 181729.5),
+        (8192, 8, 20, 1): (228260.2, 179558.1),
+        (8192, 8, 32, 1): (228457.9, 179580.2),
+        (16384, 4, 20, 1): (198864.5, 196113.4),
+        (16384, 4, 24, 1): (200864.2, 196095.9),
+        (16384, 4, 32, 1): (199792.9, 196139.0),
+        (16384, 8, 20, 1): (221006.4, 194421.7),
+        (16384, 8, 32, 1): (220644.4, 194392.8),
     },
 }
 
@@ -517,7 +517,7 @@ def bench_batched(steps, warmup, with_error=True, tune=True):
     from a hipGraph) against 64 separate pp_accel calls per step.  Both
     sides run tiles chosen by the autotuner: the batch its own, every
     per-box plan its own.  Bit identity with per-box runs is checked at equal
-    tiles (the batch's)."""
+    tiles (the batch's, 2048 positions at least)."""
     import numpy as np
     import torch
     import workloads
@@ -574,8 +574,15 @@ def bench_batched(steps, warmup, with_error=True, tune=True):
     # bit identity at equal tiles
     same = True
     offs = np.cumsum([0] + [x.n for x in boxes])
+    # (at chunks below 2048 the whole batch would pass 2^21 items and its chunk
+    # grows, which a single box's does not)
+    equal = {**batch_tuning, "use_graph": 0, "chunk": max(2048, batch_tuning["chunk"])}
+    if equal["chunk"] != batch_tuning["chunk"]:
+        bp.set_tuning(**equal)
+        bp.accel(pos, mass, out=acc)
+        acc_batched = acc.cpu().numpy()
     for (plan, pb, mb, ab), b, o in zip(per, boxes, offs):
-        plan.set_tuning(**{**batch_tuning, "use_graph": 0})
+        plan.set_tuning(**equal)
         plan.accel(pb, mb, out=ab)
         same = same and np.array_equal(ab.cpu().numpy(), acc_batched[:, o:o + b.n])
     return {
@@ -659,11 +666,16 @@ def main():
     ms_step = 1e3 * elapsed / args.steps
     value = interactions * args.steps / elapsed
     k_ms = float(np.mean(kernel_ms))
-    if tuning["persistent"]:
+    # the persistent form launches one workgroup per item where items are few
+    # (8192 waves) or short (fewer than 1000 list positions per wave on average;
+    # the positions from the candidates and the targets per block), and that
+    # launch takes its two-wave build when the items give at most two waves
+    # per SIMD
+    kw = tuning["waves_per_block"]
+    mean = st["candidates"] * st["nblock"] / max(1, box.n) / max(1, st["nitem"])
+    if tuning["persistent"] and st["nitem"] * kw > 8192 and mean >= 1000 * kw:
         kname = "pp_f32_persistent"
     else:
-        # the one-workgroup-per-item launch takes its two-wave build when the
-        # items give at most two waves per SIMD
         cus = torch.cuda.get_device_properties(0).multi_processor_count
         few = tuning["variant"] in (0, 8) and int(st["nitem"]) * tuning["waves_per_block"] <= 2 * 4 * cus
         kname = "pp_f32_kernel_few" if few else "pp_f32_kernel"
