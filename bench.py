@@ -49,48 +49,48 @@ TRAFFIC = {
     "sources": ["paper_1802_09824_amd/csrc/pp_kernels.hip",
                 "paper_1802_09824_amd/csrc/pp_internal.h",
                 "paper_1802_09824_amd/csrc/tree.hip"],
-    "sha1": "8809c0f148722a3da38b071293f7e60ee9e26bf6",
+    "sha1": "7071a7f07570a1d68d9376029ad1c2ceae0cfe75",
     "fetch_scale": 1.99996,       # 1 GiB copy: 1048576 KiB / 524299.5 KiB of FETCH_SIZE
     "write_scale": 1.00000,       # 1 GiB copy: 1048576 KiB / 1048576.0 KiB of WRITE_SIZE
     # (chunk, waves per block, waves per CU (0: one workgroup per item), persistent):
     # (FETCH_SIZE KiB, WRITE_SIZE KiB) of the timed step's PP dispatch
     "kib": {
-        (1024, 1, 0, 0): (379328.4, 171295.8),
-        (1024, 1, 12, 1): (378858.0, 171342.9),
-        (1024, 1, 20, 1): (379418.8, 171318.0),
-        (1024, 1, 24, 1): (378953.4, 171317.2),
-        (1024, 1, 32, 1): (379112.8, 171323.4),
-        (2048, 1, 0, 0): (478970.6, 103392.7),
-        (2048, 1, 12, 1): (140064.1, 106461.6),
-        (2048, 1, 20, 1): (183324.9, 107546.4),
-        (2048, 1, 24, 1): (216059.3, 107726.2),
-        (2048, 1, 32, 1): (215654.7, 107783.7),
-        (2048, 2, 20, 1): (284069.8, 102598.2),
-        (2048, 2, 24, 1): (283978.4, 102608.1),
-        (2048, 2, 32, 1): (283977.7, 102605.4),
-        (4096, 1, 20, 1): (316657.5, 138619.1),
-        (4096, 1, 32, 1): (363614.9, 138590.1),
-        (4096, 2, 20, 1): (204178.2, 139005.4),
-        (4096, 2, 24, 1): (201290.7, 139028.0),
-        (4096, 2, 32, 1): (202091.6, 139028.4),
-        (4096, 4, 0, 0): (248165.3, 135606.8),
-        (4096, 4, 12, 1): (248262.2, 135606.8),
-        (4096, 4, 20, 1): (248241.4, 135601.8),
-        (4096, 4, 24, 1): (248258.3, 135613.6),
-        (4096, 4, 32, 1): (248235.9, 135614.3),
-        (8192, 2, 32, 1): (261078.8, 181357.8),
-        (8192, 4, 0, 0): (245807.0, 179134.0),
-        (8192, 4, 12, 1): (156491.2, 181503.6),
-        (8192, 4, 20, 1): (188352.2, 181695.2),
-        (8192, 4, 24, 1): (190085.4, 181737.5),
-        (8192, 4, 32, 1): (190562.8, 181729.5),
-        (8192, 8, 20, 1): (228260.2, 179558.1),
-        (8192, 8, 32, 1): (228457.9, 179580.2),
-        (16384, 4, 20, 1): (198864.5, 196113.4),
-        (16384, 4, 24, 1): (200864.2, 196095.9),
-        (16384, 4, 32, 1): (199792.9, 196139.0),
-        (16384, 8, 20, 1): (221006.4, 194421.7),
-        (16384, 8, 32, 1): (220644.4, 194392.8),
+        (1024, 1, 0, 0): (378935.7, 171342.4),
+        (1024, 1, 12, 1): (379325.4, 171364.9),
+        (1024, 1, 20, 1): (378589.6, 171362.8),
+        (1024, 1, 24, 1): (379101.6, 171362.4),
+        (1024, 1, 32, 1): (378496.0, 171363.2),
+        (2048, 1, 0, 0): (466709.4, 94722.2),
+        (2048, 1, 12, 1): (132810.4, 97687.2),
+        (2048, 1, 20, 1): (176724.5, 98841.1),
+        (2048, 1, 24, 1): (211002.8, 98968.6),
+        (2048, 1, 32, 1): (207847.4, 99059.8),
+        (2048, 2, 20, 1): (282290.8, 93893.2),
+        (2048, 2, 24, 1): (282347.2, 93894.9),
+        (2048, 2, 32, 1): (282375.7, 93903.7),
+        (4096, 1, 20, 1): (262121.4, 74079.3),
+        (4096, 1, 32, 1): (316193.9, 74202.7),
+        (4096, 2, 20, 1): (169558.5, 74048.6),
+        (4096, 2, 24, 1): (170568.4, 74051.1),
+        (4096, 2, 32, 1): (170151.8, 74094.4),
+        (4096, 4, 0, 0): (242050.1, 70925.1),
+        (4096, 4, 12, 1): (242081.2, 70923.7),
+        (4096, 4, 20, 1): (242069.7, 70922.0),
+        (4096, 4, 24, 1): (242047.2, 70931.9),
+        (4096, 4, 32, 1): (242058.2, 70925.6),
+        (8192, 2, 32, 1): (208306.4, 69857.2),
+        (8192, 4, 0, 0): (226172.8, 67598.2),
+        (8192, 4, 12, 1): (140131.0, 69199.6),
+        (8192, 4, 20, 1): (160132.3, 69603.9),
+        (8192, 4, 24, 1): (160113.7, 69625.6),
+        (8192, 4, 32, 1): (158457.9, 69626.3),
+        (8192, 8, 20, 1): (221903.2, 68011.5),
+        (8192, 8, 32, 1): (221818.6, 68005.9),
+        (16384, 4, 20, 1): (162963.3, 68332.0),
+        (16384, 4, 24, 1): (163328.6, 68327.2),
+        (16384, 4, 32, 1): (163401.2, 68351.1),
+        (16384, 8, 20, 1): (213043.3, 66984.1),
+        (16384, 8, 32, 1): (213200.1, 66983.5),
     },
 }
 

@@ -482,12 +482,26 @@ struct Batch {
         return ((int64_t)tune.variant << 32) | ((int64_t)tune.waves_per_block << 16) | (int64_t)tune.waves_per_cu;
     }
 
+    static constexpr int64_t kWideOutput = 262144;
+
     // The PP stage: queue reset, PP kernel (or its graph), reduction and
     // monopoles; with timing on, events around the stage and the kernel.
     int run_f32(float* acc, hipStream_t s) {
         PP_TRY(partial.reserve(sizeof(float) * 3 * kBlock * (w.cap_item + 1)));
+        // Large boxes: a target's result is one 16-byte store to a random line (in
+        // the records of the sort, free by now) instead of three of 4 bytes, and
+        // a streaming kernel writes the caller's rows.  The reduction took 132 us
+        // on 2.1 M particles, bound by those stores, and now takes 58 + 10; 232 on
+        // 4 M, now 148 + 18; at 300 k 14.4, now 10.1 + 4.4: the line lies there.
+        w.acc_wide = N >= kWideOutput;
+        float* out = acc;
+        if (w.acc_wide) {
+            PP_TRY(w.rec.reserve(sizeof(double4) * N));
+            out = w.rec.as<float>();
+        }
         if (timing) PP_HIP(hipEventRecord(ev2, s));
-        PP_TRY(run_f32_stage(acc, s));
+        PP_TRY(run_f32_stage(out, s));
+        if (w.acc_wide) PP_TRY(launch_unpack_acc(w, out, acc, s));
         if (timing) PP_HIP(hipEventRecord(ev3, s));
         return PP_OK;
     }

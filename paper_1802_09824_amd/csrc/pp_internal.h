@@ -247,6 +247,7 @@ struct Work {
     const uint8_t* mono1 = nullptr;
     const uint8_t* active = nullptr;     // the items' target flags (null: every target)
     DevBuf sort_ws, scan_ws, sort_tmp;
+    int acc_wide = 0;        // the FP32 kernels write a 16-byte record per particle, unpacked afterwards
     const void* sorted_rec = nullptr;   // (key, particle) by the keys' bits from sort_shift on, until the gather
     int sort_shift = 0;
     // leaves
@@ -396,6 +397,8 @@ int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, co
 // Workgroups of the one-workgroup-per-item launch that launch_pp_f32 would
 // make (0: the persistent one).
 int f32_grid_groups(const Work& w, int waves_per_block, Mode mode, int64_t* groups);
+// the results' records (Work::acc_wide) to the caller's three rows
+int launch_unpack_acc(const Work& w, const float* rec, float* acc, hipStream_t s);
 int launch_reduce_f32(const BatchDev& bd, const Work& w, const float* partial, float* acc,
                       hipStream_t s);
 int launch_pp_f64(const BatchDev& bd, const Work& w, double* partial, hipStream_t s);

@@ -50,9 +50,22 @@ struct ItemArgs {
     const int32_t* mass_flag;  // per box: 1 where the masses are not all equal
     const float4* split_tab;   // the interpolated split table (variant bit 8)
     float* acc;                // FP32 output (single-item blocks write it directly)
+    int wide;                  // acc: a 16-byte record per particle (Work::acc_wide), else three rows
     const uint8_t* active;     // per input particle: outputs written only where set (null: all)
     const uint64_t* bact;      // per block: the lanes whose targets are active (set with active)
 };
+
+// Particle i's result.
+__device__ __forceinline__ void put_acc(float* __restrict__ acc, int wide, int64_t N, int64_t i, float x, float y,
+                                        float z) {
+    if (wide) {
+        reinterpret_cast<float4*>(acc)[i] = make_float4(x, y, z, 0.f);
+    } else {
+        acc[i] = x;
+        acc[N + i] = y;
+        acc[2 * N + i] = z;
+    }
+}
 
 __device__ __forceinline__ bool target_on(const ItemArgs& ia, int64_t i) {
     return !ia.active || ia.active[i] != 0;
@@ -78,6 +91,7 @@ ItemArgs item_args(const BatchDev& bd, const Work& w) {
     ia.mass_flag = w.mass_flag.as<int32_t>();
     ia.split_tab = w.split_tab.as<float4>();
     ia.acc = nullptr;
+    ia.wide = w.acc_wide;
     ia.active = w.active;
     ia.bact = w.active ? w.bact.as<uint64_t>() : nullptr;
     return ia;
@@ -622,9 +636,7 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
         if (PACK ? mine : lane < nt && target_on(ia, ia.perm[t])) {
             const int64_t i = ia.perm[to];
             const double sc = X.scale * (double)mu;
-            ia.acc[i] = (float)(sx * sc);
-            ia.acc[N + i] = (float)(sy * sc);
-            ia.acc[2 * N + i] = (float)(sz * sc);
+            put_acc(ia.acc, ia.wide, N, i, (float)(sx * sc), (float)(sy * sc), (float)(sz * sc));
         }
         return;
     }
@@ -813,9 +825,10 @@ __global__ void __launch_bounds__(64) monopole_kernel(ItemArgs ia, const FEntry*
     if (taken == 0) return;
     if (lane < nt && target_on(ia, ia.perm[t])) {
         const int64_t i = ia.perm[t];
-        ia.acc[i] += (float)(((double)ax - (double)cx) * X.scale);
-        ia.acc[N + i] += (float)(((double)ay - (double)cy) * X.scale);
-        ia.acc[2 * N + i] += (float)(((double)az - (double)cz) * X.scale);
+        const int64_t at = ia.wide ? 4 * i : i, row = ia.wide ? 1 : N;
+        const float x = ia.acc[at], y = ia.acc[at + row], z = ia.acc[at + 2 * row];
+        put_acc(ia.acc, ia.wide, N, i, x + (float)(((double)ax - (double)cx) * X.scale),
+                y + (float)(((double)ay - (double)cy) * X.scale), z + (float)(((double)az - (double)cz) * X.scale));
     }
     if (mcount && lane == 0) mcount[b] = taken;
 }
@@ -1025,10 +1038,21 @@ __global__ void __launch_bounds__(256) reduce_f32_kernel(ItemArgs ia,
         const double scale = ia.box[ia.bboxid[b]].scale;
         const int64_t i = perm[(int64_t)ia.bstart[b] + l];
         if (!target_on(ia, i)) continue;
-        acc[i] = (float)(sx * scale);
-        acc[N + i] = (float)(sy * scale);
-        acc[2 * N + i] = (float)(sz * scale);
+        put_acc(acc, ia.wide, N, i, (float)(sx * scale), (float)(sy * scale), (float)(sz * scale));
     }
+}
+
+// The records of put_acc to the caller's rows, active particles only.
+__global__ void __launch_bounds__(256) unpack_acc_kernel(const float4* __restrict__ rec, int64_t N,
+                                                         const int64_t* __restrict__ sizes,
+                                                         const uint8_t* __restrict__ active,
+                                                         float* __restrict__ acc) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (sizes[kSkip] || i >= N || (active && !active[i])) return;
+    const float4 a = rec[i];
+    acc[i] = a.x;
+    acc[N + i] = a.y;
+    acc[2 * N + i] = a.z;
 }
 
 // ------------------------------------------------------------------ FP64 --
@@ -1488,6 +1512,13 @@ int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, co
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, out, 3);
     hipLaunchKernelGGL(sum_staged_kernel, dim3(256), dim3(256), 0, s, item_args(bd, w), icount, waves_per_block,
                        mcount, out);
+    PP_HIP(hipGetLastError());
+    return PP_OK;
+}
+
+int launch_unpack_acc(const Work& w, const float* rec, float* acc, hipStream_t s) {
+    hipLaunchKernelGGL(unpack_acc_kernel, dim3(blocks_for(w.pos_n, 256)), dim3(256), 0, s,
+                       reinterpret_cast<const float4*>(rec), w.pos_n, w.sizes.as<int64_t>(), w.active, acc);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }

@@ -1206,7 +1206,7 @@ __device__ void entry_ranges(const BatchDev& bd, const TreeView* __restrict__ tv
     const bool walk_inside = mono.theta2 > 0.0 || mono.alpha > 0.0;   // inside nodes are opened too
     if (E.mono || (E.lev > kDfsLevel && (!E.inside || walk_inside))) {
         // a monopole: no source ranges; a node above the walk's reach: the
-        // pass runs again with more expansion passes (finish_sizes)
+        // pass runs again with more expansion passes (finish_items)
     } else if (E.lev == 0 || (E.inside && !walk_inside)) {
         emit(first, last);
     } else {

@@ -122,3 +122,29 @@ def test_f64_pair_arithmetic(pp, oracle_mod, n, eps):
     tol = (64 + 2 * ref["n_inter"]) * 2.0 ** -53 * ref["pair_abs"]
     err = np.linalg.norm(acc - ref["acc"], axis=0)
     assert np.all(err <= tol), (float((err / np.maximum(tol, 1e-300)).max()), int(np.argmax(err - tol)))
+
+
+# results leave as one 16-byte record per particle from 262144 particles on
+@pytest.mark.parametrize("n", [262143, 262144, 262145])
+def test_results_by_record_and_by_row(pp, oracle_mod, n):
+    """Sampled targets against the oracle on both sides of the line, the columns
+    of inactive particles left alone, and one plan serving both sizes."""
+    rng = np.random.default_rng(n)
+    p = BoxParams.from_mesh(60.0, 52)
+    pos = W.mixture(rng, n, p.L, 0.3, 300)
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, n)
+    acc = plan.accel(x, m)
+    t = np.sort(rng.choice(n, 200, replace=False))
+    ref = oracle_mod.accel(pos, mass.astype(np.float64), p, targets=t)["acc"]
+    got = acc.cpu().numpy()[:, t].astype(np.float64)
+    e = np.linalg.norm(got - ref, axis=0) / np.maximum(np.linalg.norm(ref, axis=0), 1e-300)
+    assert np.median(e) <= 1e-6 and np.percentile(e, 99) <= 1e-4
+    on = torch.as_tensor(rng.random(n) < 0.1).cuda()
+    out = torch.full_like(acc, 7.0)
+    plan.accel_active(x, m, on.to(torch.uint8), out)
+    assert torch.equal(out[:, on], acc[:, on]) and bool((out[:, ~on] == 7.0).all())
+    small = plan.accel(x[:, :9000].contiguous(), m[:9000].contiguous())
+    assert torch.equal(small, pp.Plan(p, 9000).accel(x[:, :9000].contiguous(), m[:9000].contiguous()))
+    assert torch.equal(plan.accel(x, m), acc)
