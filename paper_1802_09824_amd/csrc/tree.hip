@@ -968,8 +968,13 @@ __device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& 
             const int64_t node = (int64_t)i * kBlock + lane;
             FEntry E{};
             bool emit = false;
-            // the 64 nodes' common ancestor first (its box holds theirs)
-            if ((fill && kept) || start + 2 > top || gap2_shift(A, nodes[tv.off[start + 2] + i], s, W) < T)
+            // the 64 nodes' common ancestor first (its box holds theirs).  With
+            // monopoles the first unit of every higher node is walked in any
+            // case: such a node may lie within the cut, and be accepted, where
+            // its first 64 nodes do not, and the entry is theirs to write
+            const bool first_of_higher = mono_on && start + 3 <= top && (i & 7) == 0;
+            if ((fill && kept) || start + 2 > top || first_of_higher ||
+                gap2_shift(A, nodes[tv.off[start + 2] + i], s, W) < T)
                 for (int h = mono_on ? top : start; h >= start && node < n0 && (known >> lane & 1ull); --h) {
                     const int64_t up = node >> (3 * (h - start));
                     const IBox R = nodes[tv.off[h] + up];

@@ -188,3 +188,28 @@ def test_monopole_error_within_the_dtt_error(pp, dtt_box, theta, alpha):
     for k in ("median", "p999", "max"):
         assert g[k] <= DTT_FACTOR * o[k] + BARS[k], (k, g, o)
 
+
+@pytest.mark.parametrize("seed,mesh,theta,alpha", [(3, 28, 0.9, 0.0), (13, 28, 0.9, 0.0), (3, 28, 0.0, 50.0)])
+def test_nodes_far_above_the_start_level(pp, seed, mesh, theta, alpha):
+    """Two clumps in trees of six levels whose expansion starts at level 1:
+    nodes of 4096 leaves are accepted whose first 512 leaves lie beyond the cut
+    while the node itself does not.  Every accepted node acts."""
+    from tests import monopole_mirror as tree
+    rng = np.random.default_rng(seed)
+    ca = 12.0 + rng.random(3) * 30
+    d = rng.normal(size=3)
+    cb = ca + d / np.linalg.norm(d) * (10 + 4 * rng.random())
+    pos = np.concatenate([ca[:, None] + rng.random((3, 4096)), cb[:, None] + (6 * rng.random((3, 4000)) - 3)], 1)
+    n = pos.shape[1]
+    p = BoxParams.from_mesh(60.0, mesh, leaf_max=1)
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    acc_ref = np.full((3, n), 1000.0, dtype=np.float32)
+    ref = tree.monopole_accel(pos, mass.astype(np.float64), p, theta, alpha=alpha, acc_ref=acc_ref)
+    plan = pp.Plan(p, n)
+    plan.set_monopole(theta)
+    if alpha > 0:
+        plan.set_monopole_relative(alpha, dev(acc_ref, torch.float32))
+    acc = plan.accel(dev(pos, torch.float64), dev(mass, torch.float32)).cpu().numpy()
+    assert plan.stats()["monopoles"] == ref["n_mono_pairs"] > 0
+    e = rel(acc, ref["acc"])
+    assert np.median(e) <= 1e-6 and np.percentile(e, 99.9) <= 1e-4, (np.median(e), np.percentile(e, 99.9))
