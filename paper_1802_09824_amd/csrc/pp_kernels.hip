@@ -1137,7 +1137,7 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
     const int32_t nt = ia.bcount[b];
     const BoxDev& X = ia.box[ia.bboxid[b]];
     const double L = X.L, cell = X.cell, inv_len = X.inv_len, G = X.G;
-    const float keep2 = X.poly.keep2;
+    const float keep2 = fmaxf(X.poly.keep2, 1e-30f);     // a split scale far above the cut underflows its square
     F64Const C;
     C.eps2 = X.eps * X.eps;
     C.rcut2 = X.rcut * X.rcut;
@@ -1151,7 +1151,11 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
     const double xi = pos_s[t], yi = pos_s[N + t], zi = pos_s[2 * N + t];
     {
         // boxes around the runs of 16 targets (lanes past the last target
-        // repeat the first one), relative to the block centre in units of ell
+        // repeat the first one), relative to the block centre in units of ell.
+        // A half side is widened by the FP32 rounding of what the test
+        // subtracts, too: at most 5 roundings of 2^-24 of the targets' offsets
+        // (those of the cut itself are in keep2).  Offsets are large against
+        // the cut where a grid cell is (few key bits)
         const float fx = (float)((xi - ox) * inv_len), fy = (float)((yi - oy) * inv_len),
                     fz = (float)((zi - oz) * inv_len);
         float ax_ = fx, bx_ = fx, ay_ = fy, by_ = fy, az_ = fz, bz_ = fz;
@@ -1166,10 +1170,11 @@ __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* _
         }
         if (lane % GW == 0) {
             const int g = lane / GW;
-            qb[2 * g] = make_float4(0.5f * (ax_ + bx_), 0.5f * (ay_ + by_), 0.5f * (az_ + bz_),
-                                    0.5f * (bx_ - ax_) * 1.0001f + 1e-6f);
-            qb[2 * g + 1] = make_float4(0.5f * (by_ - ay_) * 1.0001f + 1e-6f,
-                                        0.5f * (bz_ - az_) * 1.0001f + 1e-6f, 0.f, 0.f);
+            auto half = [](float a, float b) {
+                return 0.5f * (b - a) * 1.0001f + 1e-6f + 5e-7f * fmaxf(fabsf(a), fabsf(b));
+            };
+            qb[2 * g] = make_float4(0.5f * (ax_ + bx_), 0.5f * (ay_ + by_), 0.5f * (az_ + bz_), half(ax_, bx_));
+            qb[2 * g + 1] = make_float4(half(ay_, by_), half(az_, bz_), 0.f, 0.f);
         }
         wave_sync();
     }

@@ -148,3 +148,28 @@ def test_results_by_record_and_by_row(pp, oracle_mod, n):
     small = plan.accel(x[:, :9000].contiguous(), m[:9000].contiguous())
     assert torch.equal(small, pp.Plan(p, 9000).accel(x[:, :9000].contiguous(), m[:9000].contiguous()))
     assert torch.equal(plan.accel(x, m), acc)
+
+
+@pytest.mark.parametrize("key_bits,rcut,rs", [(1, 1e-4, None), (1, 1e-5, None), (4, 1e-7, None), (10, 1e-7, None),
+                                              (21, 1e-11, None), (21, 1e-3, None), (21, 0.05, 1e30)])
+def test_f64_pairs_at_the_cut_in_wide_cells(pp, oracle_mod, key_bits, rcut, rs):
+    """Pairs just inside the cut whose offsets from the block centre are up to
+    4e4 times the cut (grid cells far wider than it), and a split scale whose
+    square underflows FP32: no pair is dropped, in the sums or in the counts."""
+    rng = np.random.default_rng(key_bits)
+    n = 1000
+    p = BoxParams(L=1.0, rs=rcut / 4.5 if rs is None else rs, rcut=rcut, eps=0.01 * rcut, key_bits=key_bits)
+    a, d = rng.random((3, n)), rng.normal(size=(3, n))
+    pos = np.concatenate([a, a + d / np.linalg.norm(d, axis=0) * rcut * (1 - 1e-4)], 1)
+    mass = rng.uniform(0.5, 1.5, 2 * n)
+    plan = pp.Plan(p, 2 * n)
+    acc = plan.accel_f64(dev(pos, torch.float64), dev(mass, torch.float64)).cpu().numpy()
+    _, counts = plan.count_interactions(per_target=True)
+    ref = oracle_mod.accel(pos, mass, p, pair_abs=True)
+    assert ref["n_inter"].min() >= 1
+    assert np.array_equal(counts.cpu().numpy(), ref["n_inter"])
+    tol = (64 + 2 * ref["n_inter"]) * 2.0 ** -53 * ref["pair_abs"]
+    # the separations of positions of size 1 hold 2^-52 / rcut, equal on both sides but for the wrap's rounding
+    tol = tol + 16 * 2.0 ** -52 / rcut * ref["pair_abs"]
+    err = np.linalg.norm(acc - ref["acc"], axis=0)
+    assert np.all(err <= tol), float((err / tol).max())
