@@ -1011,24 +1011,9 @@ int pp_accel_active(pp_plan* pl, const double* pos, const float* mass, int64_t n
     return pl->b.accel_f32(pos, mass, acc, S(stream), active);
 }
 
-int pp_accel_scratch(const pp_box_params* p, const double* pos, const float* mass, int64_t n,
-                     float* acc, void* stream) {
-    PP_TRY(validate_params(p, true));
-    if (n < 0 || n > kScratchMaxN)
-        return fail(PP_EINVAL, "pp_accel_scratch takes at most 65536 particles (the static scratch)");
-    PP_TRY(check_ptr(pos, n, "pos"));
-    PP_TRY(check_ptr(mass, n, "mass"));
-    PP_TRY(check_ptr(acc, n, "acc"));
-    if (n == 0) return PP_OK;
-    int dev = 0;
-    PP_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= kScratchDevices) return fail(PP_EDEVICE, "device index out of range");
-    std::lock_guard<std::mutex> lock(g_scratch_mu[dev]);
-    char* base = nullptr;
-    PP_TRY(scratch_address(dev, &base));
-    Arena arena{base, kScratchBytes, 0};
-    ScratchScope scope(&arena);
-    hipStream_t s = S(stream);
+// One call's passes, every buffer carved from the arena.
+static int accel_scratch(const pp_box_params* p, const double* pos, const float* mass, int64_t n, float* acc,
+                         Arena& arena, hipStream_t s) {
     // the list capacities of the last attempt (a pass that overflowed runs
     // again, every buffer carved afresh from the start of the array)
     int64_t cap_block = 0, cap_range = 0, cap_item = 0;
@@ -1058,6 +1043,30 @@ int pp_accel_scratch(const pp_box_params* p, const double* pos, const float* mas
         start_level = b.w.start_level;
     }
     return fail(PP_ENOMEM, "the list buffers kept growing");
+}
+
+int pp_accel_scratch(const pp_box_params* p, const double* pos, const float* mass, int64_t n,
+                     float* acc, void* stream) {
+    PP_TRY(validate_params(p, true));
+    if (n < 0 || n > kScratchMaxN)
+        return fail(PP_EINVAL, "pp_accel_scratch takes at most 65536 particles (the static scratch)");
+    PP_TRY(check_ptr(pos, n, "pos"));
+    PP_TRY(check_ptr(mass, n, "mass"));
+    PP_TRY(check_ptr(acc, n, "acc"));
+    if (n == 0) return PP_OK;
+    int dev = 0;
+    PP_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= kScratchDevices) return fail(PP_EDEVICE, "device index out of range");
+    std::lock_guard<std::mutex> lock(g_scratch_mu[dev]);
+    char* base = nullptr;
+    PP_TRY(scratch_address(dev, &base));
+    Arena arena{base, kScratchBytes, 0};
+    ScratchScope scope(&arena);
+    const int rc = accel_scratch(p, pos, mass, n, acc, arena, S(stream));
+    // a pass that failed part of the way has left kernels on the stream: the
+    // next call, on any stream, must find the array at rest
+    if (rc != PP_OK) (void)hipStreamSynchronize(S(stream));
+    return rc;
 }
 
 int pp_accel_f64(pp_plan* pl, const double* pos, const double* mass, int64_t n, double* acc,

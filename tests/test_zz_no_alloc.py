@@ -64,3 +64,27 @@ def test_no_alloc_rejects_too_many_particles(pp):
     with pytest.raises(pp.PPError) as e:
         pp.pp_accel_scratch(p, pos, mass)
     assert e.value.code == pp.PP_EINVAL
+
+
+def test_no_alloc_after_a_failed_call_on_another_stream(pp):
+    """A call whose lists do not fit fails with its first kernels enqueued; the
+    next call, on another stream, gets the array to itself."""
+    rng = np.random.default_rng(5)
+    n = 65536
+    wide = BoxParams.from_mesh(50.0, 12, leaf_max=1)          # every particle near every other
+    big, big_m = dev(rng.random((3, n)) * wide.L, torch.float64), dev(W.equal_masses(n), torch.float32)
+    p = BoxParams.from_mesh(40.0, 20)
+    pos = dev(W.mixture(rng, 9001, p.L, 0.6, 5), torch.float64)
+    mass = dev(rng.uniform(0.5, 1.5, 9001), torch.float32)
+    want = pp.Plan(p, 9001).accel(pos, mass)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(10):
+        with torch.cuda.stream(one):
+            with pytest.raises(pp.PPError) as e:
+                pp.pp_accel_scratch(wide, big, big_m)
+            assert e.value.code == pp.PP_ENOMEM
+        with torch.cuda.stream(two):
+            got = pp.pp_accel_scratch(p, pos, mass)
+        two.synchronize()
+        assert torch.equal(got, want)
