@@ -43,16 +43,25 @@ static thread_local Arena* t_arena = nullptr;
 ScratchScope::ScratchScope(Arena* a) : prev(t_arena) { t_arena = a; }
 ScratchScope::~ScratchScope() { t_arena = prev; }
 
+void reuse_list_scratch() {
+    if (t_arena) t_arena->used = 0;
+}
+
 int DevBuf::reserve(size_t need) {
     if (need <= bytes) return PP_OK;
     release();
     if (t_arena) {
         const size_t want = (need + 255) & ~(size_t)255;
-        if (t_arena->used + want > t_arena->cap)
+        if (t_arena->used + t_arena->kept + want > t_arena->cap)
             return fail(PP_ENOMEM, "the input needs more than the static device scratch of the "
                                    "allocation-free entry point holds");
-        p = t_arena->base + t_arena->used;
-        t_arena->used += want;
+        if (keep) {
+            t_arena->kept += want;
+            p = t_arena->base + (t_arena->cap - t_arena->kept);
+        } else {
+            p = t_arena->base + t_arena->used;
+            t_arena->used += want;
+        }
         bytes = want;
         carved = true;
         tag = 0;
@@ -238,6 +247,11 @@ struct Batch {
             (void)hipGetLastError();
             return fail(PP_EDEVICE, "no HIP device available");
         }
+        // what launch_pp_f32 and launch_reduce_f32 read
+        for (DevBuf* b : {&box_dev, &poff_dev, &queues, &w.pos_s, &w.mass_s, &w.mass_flag, &w.perm, &w.bad, &w.sizes,
+                          &w.bstart, &w.bcount, &w.bbox, &w.bboxid, &w.roff, &w.rbeg, &w.rpre, &w.rcode, &w.ioff,
+                          &w.iblock, &w.is0, &w.is1, &w.split_tab})
+            b->keep = true;
         nbox = nb;
         params.assign(p, p + nb);
         poff.assign(nb + 1, 0);
@@ -487,6 +501,7 @@ struct Batch {
     // The PP stage: queue reset, PP kernel (or its graph), reduction and
     // monopoles; with timing on, events around the stage and the kernel.
     int run_f32(float* acc, hipStream_t s) {
+        reuse_list_scratch();
         PP_TRY(partial.reserve(sizeof(float) * 3 * kBlock * (w.cap_item + 1)));
         // Large boxes: a target's result is one 16-byte store to a random line (in
         // the records of the sort, free by now) instead of three of 4 bytes, and
@@ -1011,17 +1026,19 @@ int pp_accel_active(pp_plan* pl, const double* pos, const float* mass, int64_t n
     return pl->b.accel_f32(pos, mass, acc, S(stream), active);
 }
 
-// One call's passes, every buffer carved from the arena.
+// One call's passes, every buffer carved from the arena.  A pass whose lists
+// outgrew their buffers runs again, every buffer carved afresh.  When the
+// capacities, grown with their margins, do not fit the array, the passes start
+// over with capacities that grow to the measured needs alone.
 static int accel_scratch(const pp_box_params* p, const double* pos, const float* mass, int64_t n, float* acc,
                          Arena& arena, hipStream_t s) {
-    // the list capacities of the last attempt (a pass that overflowed runs
-    // again, every buffer carved afresh from the start of the array)
+    // the list capacities of the last attempt
     int64_t cap_block = 0, cap_range = 0, cap_item = 0;
     int64_t cap_ent[kMaxPasses] = {};
-    bool stop2 = false;
+    bool stop2 = false, tight = false;
     int start_level = -1;
     for (int attempt = 0; attempt < 32; ++attempt) {
-        arena.used = 0;
+        arena.used = arena.kept = 0;
         Batch b;
         PP_TRY(b.init(1, p, &n, true, s, false));
         b.w.cap_block = cap_block;
@@ -1030,8 +1047,16 @@ static int accel_scratch(const pp_box_params* p, const double* pos, const float*
         for (int k = 0; k < kMaxPasses; ++k) b.w.cap_ent[0][k] = cap_ent[k];
         b.w.stop_at_level2 = stop2;
         b.w.start_level = start_level;
-        PP_TRY(b.prepare(pos, mass, nullptr, s));
-        PP_TRY(b.run_f32(acc, s));
+        b.w.tight = tight;
+        int rc = b.prepare(pos, mass, nullptr, s);
+        if (rc == PP_OK) rc = b.run_f32(acc, s);
+        if (rc == PP_ENOMEM && attempt > 0 && !tight) {
+            tight = true;
+            cap_block = cap_range = cap_item = 0;
+            for (int k = 0; k < kMaxPasses; ++k) cap_ent[k] = 0;
+            continue;
+        }
+        PP_TRY(rc);
         bool again = false;
         PP_TRY(b.finish(s, &again));
         if (!again) return PP_OK;

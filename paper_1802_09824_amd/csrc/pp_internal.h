@@ -39,10 +39,12 @@ int hip_fail(hipError_t e, const char* what, const char* file, int line);
 // growth bumps a global generation so cached graphs can notice.
 // Bump region of device memory that DevBuf::reserve carves buffers from
 // instead of calling hipMalloc while a ScratchScope is active on the thread
-// (the allocation-free entry point); such buffers are never freed.
+// (the allocation-free entry point); such buffers are never freed.  What the
+// PP stage reads (DevBuf::keep) comes from the region's end, everything else
+// from its start: the PP stage takes that part again for its partial sums.
 struct Arena {
     char* base = nullptr;
-    size_t cap = 0, used = 0;
+    size_t cap = 0, used = 0, kept = 0;
 };
 struct ScratchScope {
     explicit ScratchScope(Arena* a);
@@ -54,6 +56,7 @@ struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
     bool carved = false;     // carved from an Arena (not hipMalloc'ed)
+    bool keep = false;       // read by the PP stage (see Arena)
     uint32_t tag = 0;        // free for the owner's bookkeeping; 0 after every reallocation
     int reserve(size_t need);
     void release();
@@ -64,6 +67,8 @@ struct DevBuf {
     DevBuf& operator=(const DevBuf&) = delete;
 };
 uint64_t alloc_generation();
+// Under a ScratchScope: the list builder's buffers are dead from here on.
+void reuse_list_scratch();
 
 inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
@@ -230,6 +235,7 @@ struct Work {
     // would need more than kEntryBudget entries; then the depth-first walks
     // start at level 2 (64 leaves each) for the rest of the plan's life
     bool stop_at_level2 = false;
+    bool tight = false;      // capacities grow to what was needed and no further (scratch calls short of memory)
     HostBuf sizes_h;                      // host copy of sizes after a pass
     // particles
     DevBuf keys, keys_s, iota, perm, pos_s, mass_s, mass_sd, bad;

@@ -1777,9 +1777,10 @@ int build_canonical_pairs(const BatchDev& bd, const Work& w, int64_t W, int64_t 
 
 // Capacities start from estimates and grow to 5/4 of what a pass needed
 // whenever a buffer was too small (lists_to_host); the pass then runs again.
-static int64_t grow_cap(int64_t cap, int64_t need) {
+// (tight: to the need itself.)
+static int64_t grow_cap(int64_t cap, int64_t need, bool tight) {
     if (need <= cap) return cap;
-    return need + need / 4 + 1024;
+    return tight ? need : need + need / 4 + 1024;
 }
 
 // After a pass that fitted: a capacity well above the need comes down to it
@@ -2069,7 +2070,7 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
     if (h[kOverflow] & 64) return fail(PP_EDEVICE, "the list builder's single-pass scan did not complete");
     if (h[kOverflow] & 16) return fail(PP_ERANGE, "a target block lists more than 2^31 sources");
     if (h[kOverflow]) {
-        w.cap_block = grow_cap(w.cap_block, h[kNeedBlock]);
+        w.cap_block = grow_cap(w.cap_block, h[kNeedBlock], w.tight);
         const int stop = w.stop_at_level2 ? kDfsLevel : kDfsLevel - 1;
         int np = w.npass;
         if (!w.stop_at_level2 && h[kNeedEntry0 + np - 1] > kEntryBudget) {
@@ -2085,12 +2086,12 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
         for (int p = 0; p < np; ++p) {
             int64_t& c = w.cap_ent[w.mono_lists ? 1 : 0][stop + w.npass - 1 - p];
             const int64_t need = (int64_t)((double)h[kNeedEntry0 + p] * cut);
-            if (need > c) cut = std::min(4.0, std::max(cut, (double)need / (double)c));
-            c = grow_cap(c, need);
+            if (need > c && !w.tight) cut = std::min(4.0, std::max(cut, (double)need / (double)c));
+            c = grow_cap(c, need, w.tight);
         }
         w.start_level = (int)h[kStart];
-        w.cap_range = grow_cap(w.cap_range, (int64_t)((double)h[kNeedRange] * cut));
-        w.cap_item = grow_cap(w.cap_item, (int64_t)((double)h[kNeedItem] * cut));
+        w.cap_range = grow_cap(w.cap_range, (int64_t)((double)h[kNeedRange] * cut), w.tight);
+        w.cap_item = grow_cap(w.cap_item, (int64_t)((double)h[kNeedItem] * cut), w.tight);
         *regrow = true;
         return PP_OK;
     }

@@ -88,3 +88,19 @@ def test_no_alloc_after_a_failed_call_on_another_stream(pp):
             got = pp.pp_accel_scratch(p, pos, mass)
         two.synchronize()
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("mesh,leaf_max,frac", [(30, 32, 0), (30, 8, 0), (30, 8, 0.5), (30, 4, 0), (30, 4, 0.8), (24, 16, 0),
+                                                (20, 16, 0.5), (20, 16, 0.8), (40, 4, 0), (40, 4, 0.8), (40, 1, 0),
+                                                (40, 1, 0.8), (16, 32, 0), (16, 32, 0.8), (20, 32, 0), (20, 32, 0.5)])
+def test_no_alloc_takes_long_lists_at_the_particle_limit(pp, mesh, leaf_max, frac):
+    """65536 particles whose lists and partial sums fill most of the 64 MiB
+    (many small leaves, wide cuts): a plan's bits, twice."""
+    rng = np.random.default_rng(mesh + leaf_max)
+    n = 65536
+    p = BoxParams.from_mesh(100.0, mesh, leaf_max=leaf_max)
+    pos = dev(W.mixture(rng, n, p.L, frac, 128) if frac else rng.random((3, n)) * p.L, torch.float64)
+    mass = dev(rng.uniform(0.5, 1.5, n), torch.float32)
+    want = pp.Plan(p, n).accel(pos, mass)
+    for _ in range(2):
+        assert torch.equal(pp.pp_accel_scratch(p, pos, mass), want)
