@@ -574,13 +574,14 @@ def bench_batched(steps, warmup, with_error=True, tune=True):
     # bit identity at equal tiles
     same = True
     offs = np.cumsum([0] + [x.n for x in boxes])
-    # (at chunks below 2048 the whole batch would pass 2^21 items and its chunk
-    # grows, which a single box's does not)
-    equal = {**batch_tuning, "use_graph": 0, "chunk": max(2048, batch_tuning["chunk"])}
-    if equal["chunk"] != batch_tuning["chunk"]:
-        bp.set_tuning(**equal)
-        bp.accel(pos, mass, out=acc)
-        acc_batched = acc.cpu().numpy()
+    # (one workgroup per item: that form takes the chunk as given, where the
+    # persistent one cuts a box alone finer than the batch; at chunks below 2048
+    # the whole batch would pass 2^21 items and its chunk grows, which a single
+    # box's does not)
+    equal = {**batch_tuning, "use_graph": 0, "persistent": 0, "chunk": max(2048, batch_tuning["chunk"])}
+    bp.set_tuning(**equal)
+    bp.accel(pos, mass, out=acc)
+    acc_batched = acc.cpu().numpy()
     for (plan, pb, mb, ab), b, o in zip(per, boxes, offs):
         plan.set_tuning(**equal)
         plan.accel(pb, mb, out=ab)

@@ -258,7 +258,8 @@ int pp_plan_set_timing(pp_plan* plan, int on);
  *               persistent = 1 and waves_per_block = 1 an upper bound: a box
  *               whose target blocks list fewer than 2^27 sources in all is
  *               cut into chunks of about listed^(2/3) / 93 positions
- *               (at least 256, or 128 below 2^17 listed)
+ *               (at least 256, or 128 below 2^17 listed, and at least 1/65536
+ *               of what all boxes of a batch list)
  *  persistent   0: one workgroup per work item (when the previous call's
  *               items give at most two waves per SIMD, a build of the
  *               kernel for two resident waves; same results); 1: a fixed

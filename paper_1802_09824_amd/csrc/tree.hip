@@ -886,14 +886,18 @@ constexpr int kDfsLevel = 2;
 // particles (49 k listed) 64, 28 us against 189 at 2048; 20 k (1.3 M) 128, 65
 // against 142; 32 k (2 M) 128, 85 against 155; 150 k (10 M) 256, 246 against
 // 350; 300 k (20 M) 256 to 512, 454 against 535; 1 M (70 M) 1024, 1.44 ms
-// against 1.50.  The rule stays at or above them: it sees one box, and in a
-// batch, which has no last items to wait for, shorter chunks only add items
-// (17 boxes of 6 k particles ran 9 % slower at 64 positions than at 2048).
-// The floors cost a lone box 1 to 5 us.
+// against 1.50.  The rule stays at or above them; its floors cost a lone box 1
+// to 5 us.  A batch waits for its last items once, however many boxes it has, so
+// all of it together is cut into no more than kEnoughItems by this rule: with
+// each box cut as if it were alone 20000 boxes of 1000 particles took 35.2 ms
+// against 30.6 at 2048 positions, 4000 of them 7.36 against 6.48, 1000 boxes of
+// 32 k 66.6 against 62.0, 64 of 100 k 15.3 against 14.8.  A lone box is never
+// bounded by it (2^27 positions in 65536 items are 2048 each).
 constexpr int64_t kSmallBox = (int64_t)1 << 27;
 constexpr double kChunkScale = 0.01075;
 constexpr int64_t kTinyBox = (int64_t)1 << 17;
 constexpr int64_t kTinyChunk = 128, kSmallChunk = 256;
+constexpr int64_t kEnoughItems = 65536;
 // target blocks per box up to which the first guess of the items follows that rule
 constexpr int64_t kSmallBlocks = 65536;
 // Monopoles may be taken at every level: by the breadth-first expansion for
@@ -1369,8 +1373,7 @@ __global__ void ranges_fill_kernel(BatchDev bd, const TreeView* __restrict__ tvs
 
 // The chunk of a box: the requested one, or larger when the item partial sums (3 x 64
 // floats per item) would pass max_items items.  With `adapt` a small box gets
-// a smaller one of its own (see kSmallBox); it depends on that box alone, so a
-// box is cut the same way in a batch and by itself.
+// a smaller one of its own (see kSmallBox), bounded by what the whole batch lists.
 struct ChunkArgs {
     const int64_t* soff_e;
     const int64_t* eoff;
@@ -1394,6 +1397,8 @@ __device__ int64_t box_chunk_of(const ChunkArgs& A, const int64_t* __restrict__ 
             int64_t few = (int64_t)(kChunkScale * root * root / kBlock + 0.5) * kBlock;
             const int64_t floor_ = own < kTinyBox ? kTinyChunk : kSmallChunk;
             if (few < floor_) few = floor_;
+            const int64_t least = (total + kEnoughItems * kBlock - 1) / (kEnoughItems * kBlock) * kBlock;
+            if (few < least) few = least;
             chunk = few < chunk ? few : chunk;
         }
     }

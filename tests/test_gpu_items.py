@@ -173,3 +173,28 @@ def test_f64_pairs_at_the_cut_in_wide_cells(pp, oracle_mod, key_bits, rcut, rs):
     tol = tol + 16 * 2.0 ** -52 / rcut * ref["pair_abs"]
     err = np.linalg.norm(acc - ref["acc"], axis=0)
     assert np.all(err <= tol), float((err / tol).max())
+
+
+@pytest.mark.parametrize("nbox,n", [(3, 1000), (400, 1000), (2000, 700)])
+def test_many_small_boxes_share_the_item_bound(pp, oracle_mod, nbox, n):
+    """By the finer cut of small boxes a batch as a whole makes at most 65536
+    items more than it has blocks; few boxes keep the cut, and the bits, they
+    have alone."""
+    rng = np.random.default_rng(nbox)
+    p = BoxParams.from_mesh(50.0, 12)
+    pos = rng.random((3, nbox * n)) * p.L
+    mass = rng.uniform(0.5, 1.5, nbox * n).astype(np.float32)
+    bp = pp.BatchPlan([p] * nbox, [n] * nbox)
+    acc = bp.accel(dev(pos, torch.float64), dev(mass, torch.float32))
+    st = bp.stats()
+    assert st["nitem"] <= st["nblock"] + 65536
+    for b in (0, nbox - 1):
+        a = slice(b * n, b * n + n)
+        one = pp.Plan(p, n)
+        alone = one.accel(dev(pos[:, a], torch.float64), dev(mass[a], torch.float32))
+        if nbox == 3:
+            assert st["nitem"] > 2 * st["nblock"]
+            assert torch.equal(acc[:, a], alone)
+        ref = oracle_mod.accel(pos[:, a], mass[a].astype(np.float64), p)
+        s = parity.summary(acc[:, a].cpu().numpy(), ref)
+        assert s["zero_ok"] and s["median"] <= 1e-6 and s["p999"] <= 1e-4, s
