@@ -1978,8 +1978,11 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
     if (w.cap_range < 1024) w.cap_range = (nc > kFewChunks ? 320 : 200) * cb;
     if (w.cap_item < 1024) {
         w.cap_item = 2 * cb;
-        // small boxes are cut finer: their items grow as the root of the blocks
-        const int64_t fine = (int64_t)(1000.0 * sqrt((double)cb * nbox));
+        // small boxes are cut finer: their items grow as the root of the blocks,
+        // those of a batch as far as kEnoughItems (twice that here) and else
+        // as the blocks (2 to 4 of 2048 positions each)
+        int64_t fine = (int64_t)(1000.0 * sqrt((double)cb * nbox));
+        if (nbox > 1) fine = std::min(fine, 5 * cb + 2 * kEnoughItems);
         if (adapt_chunk && fine > w.cap_item && cb < nbox * kSmallBlocks) w.cap_item = fine;
     }
     hipLaunchKernelGGL(ranges_count_kernel, dim3(blocks_for(F, 128)), dim3(128), 0, s, bd, tvs, nodes, ent,

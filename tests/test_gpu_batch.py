@@ -314,3 +314,22 @@ def test_full_64_box_batch_sampled(pp, oracle_mod):
         s = parity.summary(acc[:, off[k] + t], ref)
         assert s["zero_ok"] and s["median"] <= 1e-6 and s["p999"] <= 1e-4, (b.name, s)
         assert s["robust_max"] <= parity.ROBUST_MAX, (b.name, s)
+
+
+def test_many_small_boxes_hold_little_memory(pp):
+    """4000 boxes of 1000 particles: after its first call the plan holds what
+    its items need (130 k of 768 B) beside the lists, not room for the items
+    of 4000 boxes cut as if each were alone (3 GB against 18)."""
+    nbox, n = 4000, 1000
+    p = BoxParams.from_mesh(50.0, 12)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(8)
+    pos = torch.rand(3, nbox * n, dtype=torch.float64, device="cuda", generator=gen) * p.L
+    mass = torch.full((nbox * n,), 1.0 / n, dtype=torch.float32, device="cuda")
+    out = torch.empty(3, nbox * n, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    bp = pp.BatchPlan([p] * nbox, [n] * nbox)
+    bp.accel(pos, mass, out)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 5e9
