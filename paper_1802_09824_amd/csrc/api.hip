@@ -1035,7 +1035,7 @@ static int accel_scratch(const pp_box_params* p, const double* pos, const float*
     // the list capacities of the last attempt
     int64_t cap_block = 0, cap_range = 0, cap_item = 0;
     int64_t cap_ent[kMaxPasses] = {};
-    bool stop2 = false, tight = false;
+    bool stop2 = false, tight = false, full_sort = false;
     int start_level = -1;
     for (int attempt = 0; attempt < 32; ++attempt) {
         arena.used = arena.kept = 0;
@@ -1048,6 +1048,7 @@ static int accel_scratch(const pp_box_params* p, const double* pos, const float*
         b.w.stop_at_level2 = stop2;
         b.w.start_level = start_level;
         b.w.tight = tight;
+        b.w.full_sort = full_sort;
         int rc = b.prepare(pos, mass, nullptr, s);
         if (rc == PP_OK) rc = b.run_f32(acc, s);
         if (rc == PP_ENOMEM && attempt > 0 && !tight) {
@@ -1066,6 +1067,7 @@ static int accel_scratch(const pp_box_params* p, const double* pos, const float*
         for (int k = 0; k < kMaxPasses; ++k) cap_ent[k] = b.w.cap_ent[0][k];
         stop2 = b.w.stop_at_level2;
         start_level = b.w.start_level;
+        full_sort = b.w.full_sort;
     }
     return fail(PP_ENOMEM, "the list buffers kept growing");
 }

@@ -8,6 +8,7 @@
 // significant bit of every 3-bit digit.  The sort makes every octree node a
 // contiguous run of particles (sec. 3.2); in a batch each box is sorted as
 // its own segment.
+#include <algorithm>
 #include <cstring>
 
 #include <rocprim/device/device_radix_sort.hpp>
@@ -132,12 +133,23 @@ __global__ void __launch_bounds__(256) keys_raw_kernel(const double* __restrict_
     keys[k] = key_of(pos[k], pos[n + k], pos[2 * n + k], L, scale, b);
 }
 
+// Longest run of particles alike in the leading key bits that is put in order
+// in the gather: a run of m costs each of its particles m dependent loads of
+// 0.12 us, so this one 30 us, where the own sort saves 14 us at 32 k particles,
+// 64 at 300 k and 160 at 2.1 M.
+constexpr int kLongRun = 256;
+
+// keys_s, shift (0: unused): notes whether the sort by leading bits would have
+// met a longer run (sizes[kRun] = 1).
 template <class M>
 __global__ void __launch_bounds__(256) gather_kernel(const double4* __restrict__ rec,
-                                                     const int32_t* __restrict__ perm, int64_t N,
-                                                     double* __restrict__ pos_s, M* __restrict__ mass_s) {
+                                                     const int32_t* __restrict__ perm,
+                                                     const uint64_t* __restrict__ keys_s, int shift, int64_t N,
+                                                     double* __restrict__ pos_s, M* __restrict__ mass_s,
+                                                     int64_t* __restrict__ sizes) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= N) return;
+    if (shift > 0 && k + kLongRun < N && keys_s[k] >> shift == keys_s[k + kLongRun] >> shift) sizes[kRun] = 1;
     const double4 r = rec[perm[k]];
     pos_s[k] = r.x;
     pos_s[N + k] = r.y;
@@ -148,13 +160,16 @@ __global__ void __launch_bounds__(256) gather_kernel(const double4* __restrict__
 // The gather into key order, from records sorted by the keys' bits from
 // `shift` on (ties in input order): the few that agree in those bits come into
 // the order of the remaining ones here, each by counting the records of its
-// run that belong before it.
+// run that belong before it.  The particles of a run longer than kLongRun stay
+// where they are, and sizes[kRun] = 2 has the pass run again with a sort by all
+// bits (every particle of such a run finds it too long).
 template <class M>
 __global__ void __launch_bounds__(256) sorted_gather_kernel(const ulonglong2* __restrict__ sorted, int shift,
                                                             const double4* __restrict__ rec, int64_t N,
                                                             uint64_t* __restrict__ keys_s,
                                                             int32_t* __restrict__ perm,
-                                                            double* __restrict__ pos_s, M* __restrict__ mass_s) {
+                                                            double* __restrict__ pos_s, M* __restrict__ mass_s,
+                                                            int64_t* __restrict__ sizes) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= N) return;
     const ulonglong2 e = sorted[k];
@@ -162,15 +177,21 @@ __global__ void __launch_bounds__(256) sorted_gather_kernel(const ulonglong2* __
     int64_t at = k;
     if (shift > 0) {
         const uint64_t run = e.x >> shift;
-        for (int64_t j = k - 1; j >= 0; --j) {
-            const uint64_t o = sorted[j].x;
+        const int64_t lo = k > kLongRun ? k - kLongRun : 0, hi = k + kLongRun < N ? k + kLongRun : N - 1;
+        int64_t a = k - 1, b = k + 1;
+        for (; a >= lo; --a) {
+            const uint64_t o = sorted[a].x;
             if (o >> shift != run) break;
             at -= o > e.x;
         }
-        for (int64_t j = k + 1; j < N; ++j) {
-            const uint64_t o = sorted[j].x;
+        for (; b <= hi; ++b) {
+            const uint64_t o = sorted[b].x;
             if (o >> shift != run) break;
             at += o < e.x;
+        }
+        if (b - a - 1 > kLongRun) {
+            at = k;
+            sizes[kRun] = 2;
         }
     }
     keys_s[at] = e.x;
@@ -334,15 +355,19 @@ int launch_sort_raw(const uint64_t* keys, const int32_t* idx_in, uint64_t* keys_
 }
 
 // Passes of radix.h for the leading bits of the keys of one box of N particles
-// (0: the library's sort of all bits).  Particles that agree in those bits are
-// put in order by sorted_gather_kernel, at a cost of the square of their
-// number; they lie in one tree cell of level 7 (two passes) or 11 (three), so
-// with a cut of at least the cell's diagonal each of these comparisons stands
-// beside a pair that the call evaluates anyway, at twice the cost.  A smaller
-// cut takes the library's sort.  So do up to kSmallSort particles: one
-// workgroup sorts them there in one launch (15 us).  Sort and gather, the
-// library's and these: 46 and 32 us at 32 k particles, 144 and 80 at 300 k, 360
-// and 198 at 2.1 M.
+// (0: the library's sort of all bits).  Particles that agree in those bits lie
+// in one tree cell of level 7 (two passes) or 11 (three) and are put in order
+// by sorted_gather_kernel.  A cut below the cell's diagonal takes the library's
+// sort: cells may hold many particles there as a rule.  So does a box whose
+// last call met a run longer than kLongRun, whatever the call evaluates (few
+// active targets, monopoles): lists_to_host has the pass that meets one run
+// again, and returns to the leading bits once no run is that long.  With up
+// to kSmallSort particles one workgroup of the library's sort takes one launch
+// (15 us).  Sort and gather, the library's and these: 46 and 32 us at 32 k
+// particles, 144 and 80 at 300 k, 360 and 198 at 2.1 M.  With runs of any
+// length ordered in the gather, 16384 particles in one cell took a call with 5
+// active targets of 32 k from 0.57 to 2.33 ms, 65536 of 2.1 M a whole one from
+// 6.3 to 15.9.
 constexpr int64_t kSmallSort = 4096;
 static int key_passes(int64_t N, int nbox, double reach) {
     if (nbox != 1 || N <= kSmallSort) return 0;
@@ -360,8 +385,6 @@ static int sort_leading(int64_t N, int bits, int npass, Work& w, hipStream_t s) 
     ulonglong2* tmp = w.pos_s.as<ulonglong2>();
     uint32_t* total = reinterpret_cast<uint32_t*>(ws + N);
     uint32_t* counts = total + kDigits;
-    const int top = 3 * bits - kDigitBits * npass;
-    w.sort_shift = top > 0 ? top : 0;
     const ulonglong2* in = nullptr;
     for (int p = 0; p < npass; ++p) {
         ulonglong2* out = (npass - p) % 2 == 1 ? ws : tmp;
@@ -381,7 +404,8 @@ int stage_sort(const BatchDev& bd, int64_t N, double reach, Work& w, hipStream_t
     w.sorted_rec = nullptr;
     if (N == 0) return PP_OK;
     const int npass = key_passes(N, bd.nbox, reach);
-    if (npass > 0) {
+    w.sort_shift = npass > 0 ? std::max(0, 3 * bd.bits - kDigitBits * npass) : 0;
+    if (npass > 0 && !w.full_sort) {
         if (N <= 131072) return sort_leading<2>(N, bd.bits, npass, w, s);
         if (N <= 1048576) return sort_leading<4>(N, bd.bits, npass, w, s);
         return sort_leading<8>(N, bd.bits, npass, w, s);
@@ -435,21 +459,22 @@ int stage_gather(int64_t N, bool f64, Work& w, hipStream_t s) {
         if (f64)
             hipLaunchKernelGGL(sorted_gather_kernel<double>, grid, group, 0, s, sorted, w.sort_shift, rec, N,
                                w.keys_s.as<uint64_t>(), w.perm.as<int32_t>(), w.pos_s.as<double>(),
-                               w.mass_sd.as<double>());
+                               w.mass_sd.as<double>(), w.sizes.as<int64_t>());
         else
             hipLaunchKernelGGL(sorted_gather_kernel<float>, grid, group, 0, s, sorted, w.sort_shift, rec, N,
                                w.keys_s.as<uint64_t>(), w.perm.as<int32_t>(), w.pos_s.as<double>(),
-                               w.mass_s.as<float>());
+                               w.mass_s.as<float>(), w.sizes.as<int64_t>());
         PP_HIP(hipGetLastError());
         return PP_OK;
     }
     const int32_t* perm = w.perm.as<int32_t>();
+    const uint64_t* keys_s = w.keys_s.as<uint64_t>();
     if (f64)
-        hipLaunchKernelGGL(gather_kernel<double>, grid, group, 0, s, rec, perm, N, w.pos_s.as<double>(),
-                           w.mass_sd.as<double>());
+        hipLaunchKernelGGL(gather_kernel<double>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, N,
+                           w.pos_s.as<double>(), w.mass_sd.as<double>(), w.sizes.as<int64_t>());
     else
-        hipLaunchKernelGGL(gather_kernel<float>, grid, group, 0, s, rec, perm, N, w.pos_s.as<double>(),
-                           w.mass_s.as<float>());
+        hipLaunchKernelGGL(gather_kernel<float>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, N,
+                           w.pos_s.as<double>(), w.mass_s.as<float>(), w.sizes.as<int64_t>());
     PP_HIP(hipGetLastError());
     return PP_OK;
 }

@@ -195,12 +195,14 @@ enum SizeSlot : int {
     kSkip = 7,          // nonzero: a buffer was too small or an input not finite; the PP kernels return
     kCand = 8,          // (target, listed source) pairs
     kOverflow = 9,      // bit 0: blocks, 1: entries, 2: ranges, 3: items, 4: a list longer than int32,
-                        // 6: a single-pass scan gave up waiting, 7: too few expansion passes
+                        // 6: a single-pass scan gave up waiting, 7: too few expansion passes,
+                        // 8: the leading bits of the keys left a run too long to order
     kBad = 10,          // a non-finite position or mass
     kNeedBlock = 11,
     kNeedRange = 12,
     kNeedItem = 13,
     kMoved = 14,        // a call reusing the lists met a particle that moved half the skin or more
+    kRun = 15,          // a long run of keys alike in their leading bits: 2 after a sort by those, 1 after one by all
     kEntry0 = 16,       // kEntry0 + p: entries after expansion pass p (clamped)
     kNeedEntry0 = 40,   // kNeedEntry0 + p: the same, unclamped
     kSizeSlots = 64
@@ -255,7 +257,8 @@ struct Work {
     DevBuf sort_ws, scan_ws, sort_tmp;
     int acc_wide = 0;        // the FP32 kernels write a 16-byte record per particle, unpacked afterwards
     const void* sorted_rec = nullptr;   // (key, particle) by the keys' bits from sort_shift on, until the gather
-    int sort_shift = 0;
+    int sort_shift = 0;      // (0: no sort by leading bits for this box)
+    bool full_sort = false;  // the last call's keys held a long run: sort by all bits
     // leaves
     DevBuf lbegin, lcount, llevel, lprefix, loff_dev;   // leaf boxes: tree_boxes[0 .. nleaf)
     int64_t nleaf = 0;                    // host copies, valid after leaves_to_host
@@ -374,7 +377,8 @@ int stage_regather(const BatchDev& bd, int64_t N, const double* pos, const float
 // *regrow and grows the capacities when a buffer was too small (the pass must
 // then run again); sets *regrow and *moved when a pass that reused the lists
 // met a particle that moved too far (the lists must be rebuilt); PP_EINVAL
-// when an input was not finite.  Otherwise fills the host copies (nleaf,
+// when an input was not finite.  A run of keys too long for the sort by
+// leading bits sets *regrow too.  Otherwise fills the host copies (nleaf,
 // nblock, nentry, nrange, nitem, candidates).
 int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved = nullptr);
 // Mass and mass-weighted position sums of every tree node (after stage_trees;

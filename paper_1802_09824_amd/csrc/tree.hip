@@ -1472,6 +1472,7 @@ __device__ __forceinline__ void finish_items(const ItemBuild& I, int64_t ni) {
     if (ni > I.cap_item) sizes[kOverflow] |= 8;
     if (nr > I.cap_range) sizes[kOverflow] |= 4;
     if (sizes[kStart] - I.npass > I.stop) sizes[kOverflow] |= 128;
+    if (sizes[kRun] == 2) sizes[kOverflow] |= 256;
     sizes[kBad] = *I.bad;
     sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
 }
@@ -2076,6 +2077,11 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
         return PP_OK;
     }
     if (h[kOverflow] & 64) return fail(PP_EDEVICE, "the list builder's single-pass scan did not complete");
+    if (h[kOverflow] & 256) {           // lists of particles out of order: again, sorted by all key bits
+        w.full_sort = true;
+        *regrow = true;
+        return PP_OK;
+    }
     if (h[kOverflow] & 16) return fail(PP_ERANGE, "a target block lists more than 2^31 sources");
     if (h[kOverflow]) {
         w.cap_block = grow_cap(w.cap_block, h[kNeedBlock], w.tight);
@@ -2119,6 +2125,7 @@ int lists_to_host(Work& w, hipStream_t s, bool* regrow, bool* moved) {
         if (!w.active) w.cap_item = settle_cap(w.cap_item, h[kNeedItem]);
     }
     w.start_level = (int)h[kStart];
+    w.full_sort = h[kRun] != 0;
     w.nleaf = h[kNLeaf];
     w.nblock = h[kNBlock];
     w.nentry = h[kNEntry];

@@ -171,3 +171,81 @@ def test_items_of_few_and_many_blocks(pp, oracle_mod, n):
     active = torch.as_tensor(rng.random(n) < 0.3).cuda()
     some = plan.accel_active(x, m, active.to(torch.uint8), torch.zeros_like(acc))
     assert torch.equal(some[:, active], acc[:, active])
+
+
+def dense_cell(n, m, seed=2):
+    """n particles of which m share one cell of the leading key bits (level 7
+    up to 131072 particles, 11 beyond), with distinct keys, out of order."""
+    rng = np.random.default_rng(seed)
+    p = BoxParams.from_mesh(100.0, max(12, int(round(n ** (1 / 3)))))
+    w = p.L / (128 if n <= 131072 else 2048)
+    pos = rng.random((3, n)) * p.L
+    pos[:, rng.permutation(n)[:m]] = 50.0 + w * (0.02 + 0.9 * rng.random((3, m)))
+    return pos, rng.uniform(0.5, 1.5, n).astype(np.float32), p
+
+
+# runs of up to 256 particles are ordered in the gather, longer ones by a sort
+# of all bits
+@pytest.mark.parametrize("n,m", [(30000, 255), (30000, 256), (30000, 257), (30000, 258), (30000, 9000),
+                                 (140000, 256), (140000, 257), (140000, 20000)])
+def test_dense_cells_order_like_the_full_sort(pp, n, m):
+    """The first call (which meets the run), the ones after it and those after
+    a change to other particles and back, by every entry point: the particle
+    order, and so the bits, of the library's sort in a batch of two boxes."""
+    pos, mass, p = dense_cell(n, m)
+    spread = np.random.default_rng(3).random((3, n)) * p.L
+    other = BoxParams.from_mesh(30.0, 12)
+    y = dev(np.random.default_rng(1).random((3, 65)) * other.L, torch.float64)
+    mm = dev(mass, torch.float32)
+    bp = pp.BatchPlan([p, other], [n, 65])
+
+    def full(x):
+        return bp.accel(torch.cat([x, y], 1), torch.cat([mm, mm[:65]]))[:, :n].clone()
+
+    x, z = dev(pos, torch.float64), dev(spread, torch.float64)
+    want, want_z = full(x), full(z)
+    plan = pp.Plan(p, n)
+    for _ in range(3):
+        assert torch.equal(plan.accel(x, mm), want)
+    on = torch.as_tensor(np.random.default_rng(4).random(n) < 0.1).cuda()
+    fresh = pp.Plan(p, n)
+    got = fresh.accel_active(x, mm, on.to(torch.uint8), torch.zeros_like(want))
+    assert torch.equal(got[:, on], want[:, on])
+    for _ in range(2):
+        assert torch.equal(plan.accel(z, mm), want_z)
+    assert torch.equal(plan.accel(x, mm), want)
+    if n <= 65536:
+        for _ in range(2):
+            assert torch.equal(pp.pp_accel_scratch(p, x, mm), want)
+    m64 = mm.to(torch.float64)
+    a, b = pp.Plan(p, n), pp.Plan(p, n)
+    b.accel(x, mm)                                   # has met the run
+    assert torch.equal(a.accel_f64(x, m64), b.accel_f64(x, m64))
+
+
+def test_a_dense_cell_does_not_hold_up_few_targets(pp):
+    """Half of 131072 particles in one cell of the leading key bits, 5 active
+    targets elsewhere: the call takes about as long as on spread particles (1.0
+    times with a sort by all bits, 30 times with the square of the cell's
+    particles in the gather)."""
+    n = 131072
+    pos, mass, p = dense_cell(n, n // 2)
+    pos[:, :5] = np.random.default_rng(6).random((3, 5)) * 20.0
+    spread = np.random.default_rng(3).random((3, n)) * p.L
+    on = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    on[:5] = 1
+    out, mm = torch.zeros(3, n, device="cuda"), dev(mass, torch.float32)
+
+    def best(x):
+        plan = pp.Plan(p, n)
+        t = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            plan.accel_active(x, mm, on, out)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b))
+        return min(t)
+
+    assert best(dev(pos, torch.float64)) < 6 * best(dev(spread, torch.float64))
