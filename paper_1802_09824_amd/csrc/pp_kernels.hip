@@ -963,10 +963,12 @@ __global__ void reset_queues_kernel(unsigned* q) {
 
 // Sums of the items' staged sources: out[0] times the block's targets,
 // out[1] times the lanes; with mcount, out[2]: the blocks' monopoles times
-// their targets.  (out is cleared by the caller.)
+// their targets.  (out is cleared by the caller, and stays so after a pass whose
+// kernels returned at once: they counted nothing.)
 __global__ void __launch_bounds__(256) sum_staged_kernel(ItemArgs ia, const int32_t* __restrict__ icount,
                                                          int K, const int32_t* __restrict__ mcount,
                                                          unsigned long long* __restrict__ out) {
+    if (ia.sizes[kSkip]) return;
     unsigned long long ev = 0, ln = 0, mo = 0;
     if (mcount)
         for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < ia.sizes[kNBlock];

@@ -198,3 +198,25 @@ def test_many_small_boxes_share_the_item_bound(pp, oracle_mod, nbox, n):
         ref = oracle_mod.accel(pos[:, a], mass[a].astype(np.float64), p)
         s = parity.summary(acc[:, a].cpu().numpy(), ref)
         assert s["zero_ok"] and s["median"] <= 1e-6 and s["p999"] <= 1e-4, s
+
+
+@pytest.mark.parametrize("theta", [0.0, 0.5])
+def test_statistics_after_a_rejected_call(pp, theta):
+    """A call rejected for its input swept nothing, whatever the call before it
+    counted; the next good call counts again."""
+    pos, mass, p = box(6001)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, 6001)
+    plan.set_monopole(theta)
+    plan.accel(x, m)
+    good = plan.stats()
+    bad = x.clone()
+    bad[1, 77] = float("nan")
+    with pytest.raises(pp.PPError):
+        plan.accel(bad, m)
+    st = plan.stats()
+    assert good["evaluated"] > 0
+    assert (st["evaluated"], st["lane_pairs"], st["monopoles"]) == (0, 0, 0)
+    plan.accel(x, m)
+    st = plan.stats()
+    assert [st[k] for k in ("evaluated", "lane_pairs", "monopoles")] == [good[k] for k in ("evaluated", "lane_pairs", "monopoles")]
