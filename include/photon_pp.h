@@ -192,7 +192,9 @@ typedef struct pp_stats {
                                its bounding-box test, incl. pairs masked by the cut); -1 if
                                the last call was not pp_accel */
     int64_t lane_pairs;     /* lane-pair slots the FP32 kernel swept (64 per staged source,
-                               idle lanes of partly filled blocks included); -1 likewise */
+                               idle lanes of partly filled blocks included; 32 or 16 where a
+                               block's few active targets sweep two or four tiles at once);
+                               -1 likewise */
     int64_t interactions;   /* pairs with s < rcut, j != i (set by pp_count_interactions), else -1 */
     double pp_kernel_ms;    /* duration of the last PP kernel launch (HIP events on the
                                caller's stream) when timing is on, else -1 */

@@ -208,7 +208,7 @@ struct Batch {
     hipEvent_t ev2 = nullptr, ev3 = nullptr;   // around the whole PP stage
     DevBuf partial, pcount, counters, queues;
     DevBuf staged, staged_mono;    // sources swept per item and wave, monopoles per block (direct launches)
-    int staged_waves = 1;
+    int staged_waves = 1, staged_variant = 0;
     // captured PP graph (persistent kernel + reduction)
     hipGraphExec_t gexec = nullptr;
     hipGraph_t graph = nullptr;
@@ -457,6 +457,7 @@ struct Batch {
         PP_TRY(launch_reduce_f32(bd, w, partial.as<float>(), acc, s));
         if (lists_mono) PP_TRY(launch_monopole(bd, w, acc, staged_mono.as<int32_t>(), s));
         staged_waves = tune.waves_per_block;
+        staged_variant = tune.variant;
         evaluated_valid = true;
         return PP_OK;
     }
@@ -558,7 +559,7 @@ struct Batch {
         st.list_reuses = list_reuses;
         if (evaluated_valid) {
             unsigned long long h[3] = {0, 0, 0};
-            PP_TRY(launch_sum_staged(bd, w, staged_waves, staged.as<int32_t>(),
+            PP_TRY(launch_sum_staged(bd, w, staged_waves, staged_variant, staged.as<int32_t>(),
                                      lists_mono ? staged_mono.as<int32_t>() : nullptr,
                                      counters.as<unsigned long long>(), (hipStream_t)0));
             PP_HIP(hipMemcpy(h, counters.p, sizeof(h), hipMemcpyDeviceToHost));

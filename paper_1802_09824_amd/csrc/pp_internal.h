@@ -402,7 +402,7 @@ int launch_pp_f32(const BatchDev& bd, const Work& w, int groups, Mode mode, int 
                   int variant, float* partial, float* acc, int32_t* icount, unsigned* queues,
                   hipStream_t s);
 // What the last FP32 launch swept (see sum_staged_kernel), into out[0 .. 2].
-int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, const int32_t* icount,
+int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, int variant, const int32_t* icount,
                       const int32_t* mcount, unsigned long long* out, hipStream_t s);
 // Workgroups of the one-workgroup-per-item launch that launch_pp_f32 would
 // make (0: the persistent one).

@@ -341,6 +341,10 @@ constexpr int kPackMax = 4;            // copies at most
 template <int VAR>
 constexpr int tile_entries() { return (VAR & 16) ? (kPackMax + 1) * (kBlock + 1) : 2 * kBlock; }
 
+// Copies (a power of two) of a block's active targets that one wave holds when
+// na of them are active (pp_item, PACK).
+__device__ __forceinline__ int pack_copies(int na) { return na <= kBlock / 4 ? 2 : na <= kBlock / 2 ? 1 : 0; }
+
 template <int VAR, int K>
 __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
                                         const double* __restrict__ pos_s,
@@ -442,7 +446,7 @@ __device__ __forceinline__ void pp_item(const ItemArgs& ia, int64_t item,
     if (PACK) {
         const uint64_t on = ia.bact[b];
         const int na = __popcll(on);
-        lcopies = na <= kBlock / 4 ? 2 : na <= kBlock / 2 ? 1 : 0;
+        lcopies = pack_copies(na);
         mine = (on >> lane) & 1ull;
         if (lcopies > 0) {
             const int slot = lane & ((kBlock >> lcopies) - 1);
@@ -961,12 +965,15 @@ __global__ void reset_queues_kernel(unsigned* q) {
     if (threadIdx.x < 8) q[threadIdx.x * kQueueStride] = 0u;
 }
 
-// Sums of the items' staged sources: out[0] times the block's targets,
-// out[1] times the lanes; with mcount, out[2]: the blocks' monopoles times
+// Sums of the items' staged sources: out[0] times the block's targets (the
+// active ones where only they are swept), out[1] the lane slots of the sweeps
+// (64 per staged source; with packed copies, of as many tiles at once, and of
+// the fullest of the last tiles); with mcount, out[2]: the blocks' monopoles times
 // their targets.  (out is cleared by the caller, and stays so after a pass whose
 // kernels returned at once: they counted nothing.)
 __global__ void __launch_bounds__(256) sum_staged_kernel(ItemArgs ia, const int32_t* __restrict__ icount,
-                                                         int K, const int32_t* __restrict__ mcount,
+                                                         int K, int packed,
+                                                         const int32_t* __restrict__ mcount,
                                                          unsigned long long* __restrict__ out) {
     if (ia.sizes[kSkip]) return;
     unsigned long long ev = 0, ln = 0, mo = 0;
@@ -976,10 +983,19 @@ __global__ void __launch_bounds__(256) sum_staged_kernel(ItemArgs ia, const int3
             mo += (unsigned long long)mcount[b] * (unsigned long long)ia.bcount[b];
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < ia.sizes[kNItem];
          it += (int64_t)gridDim.x * blockDim.x) {
-        unsigned long long c = 0;
-        for (int k = 0; k < K; ++k) c += (unsigned long long)icount[it * K + k];
-        ev += c * (unsigned long long)ia.bcount[ia.iblock[it]];
-        ln += c * (unsigned long long)kBlock;
+        const int32_t b = ia.iblock[it];
+        int targets = ia.bcount[b], lcopies = 0;
+        if (packed) {
+            const int na = __popcll(ia.bact[b]);
+            lcopies = pack_copies(na);
+            if (lcopies > 0) targets = na;
+        }
+        const unsigned full = (unsigned)kBlock << lcopies;
+        for (int k = 0; k < K; ++k) {
+            const unsigned c = (unsigned)icount[it * K + k], rest = c % full;
+            ev += (unsigned long long)c * (unsigned long long)targets;
+            ln += (unsigned long long)(c / full * kBlock + (rest < kBlock ? rest : kBlock)) * (unsigned long long)kBlock;
+        }
     }
     for (int d = 32; d >= 1; d >>= 1) {
         ev += __shfl_xor(ev, d);
@@ -1468,13 +1484,16 @@ static int launch_pp_f32_k(const ItemArgs& ia, const Work& w, Mode mode, int wav
     }
 }
 
+// Whether a launch over active targets packs them (pp_item, PACK).
+static bool packs_active(const Work& w, int variant) { return w.active && (variant & 7) == 0; }
+
 int launch_pp_f32(const BatchDev& bd, const Work& w, int waves_per_block, Mode mode, int waves_per_cu,
                   int variant, float* partial, float* acc, int32_t* icount,
                   unsigned* queues, hipStream_t s) {
     ItemArgs ia = item_args(bd, w);
     ia.acc = acc;
     variant &= 15;
-    if (w.active && (variant & 7) == 0) variant |= 16;
+    if (packs_active(w, variant)) variant |= 16;
     if (waves_per_block == 2)
         return launch_pp_f32_k<2>(ia, w, mode, waves_per_cu, variant, partial, icount, queues, s);
     if (waves_per_block == 4)
@@ -1514,11 +1533,11 @@ int launch_monopole(const BatchDev& bd, const Work& w, float* acc, int32_t* mcou
     return PP_OK;
 }
 
-int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, const int32_t* icount,
+int launch_sum_staged(const BatchDev& bd, const Work& w, int waves_per_block, int variant, const int32_t* icount,
                       const int32_t* mcount, unsigned long long* out, hipStream_t s) {
     hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, s, out, 3);
     hipLaunchKernelGGL(sum_staged_kernel, dim3(256), dim3(256), 0, s, item_args(bd, w), icount, waves_per_block,
-                       mcount, out);
+                       packs_active(w, variant) ? 1 : 0, mcount, out);
     PP_HIP(hipGetLastError());
     return PP_OK;
 }

@@ -220,3 +220,34 @@ def test_statistics_after_a_rejected_call(pp, theta):
     plan.accel(x, m)
     st = plan.stats()
     assert [st[k] for k in ("evaluated", "lane_pairs", "monopoles")] == [good[k] for k in ("evaluated", "lane_pairs", "monopoles")]
+
+
+@pytest.mark.parametrize("k", [1, 4])
+def test_statistics_of_packed_blocks(pp, k):
+    """With 1, 20, 40 and all targets of every block active, the evaluated
+    pairs are those of the active targets where only they are swept (up to 32
+    of a block), and the lane slots fall to a quarter or a half plus at most one
+    partial sweep per wave and item."""
+    pos, mass, p = box(20011)
+    n = pos.shape[1]
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, n)
+    plan.set_tuning(chunk=1024 * k, waves_per_block=k)
+    plan.accel(x, m)
+    full, lists = plan.stats(), plan.export_lists()
+    c = full["lane_pairs"] // 64                          # staged sources of all waves
+    for want, copies in ((1, 4), (20, 2), (40, 1), (64, 1)):
+        on = np.zeros(n, np.uint8)
+        for a, cnt in zip(lists["bstart"], lists["bcount"]):
+            on[lists["perm"][a:a + min(int(cnt), want)]] = 1
+        plan.accel_active(x, m, dev(on, torch.uint8), torch.zeros(3, n, device="cuda"))
+        st = plan.stats()
+        assert st["nitem"] == full["nitem"]
+        if want == 1:
+            assert st["evaluated"] == c
+        elif copies == 1:
+            assert (st["evaluated"], st["lane_pairs"]) == (full["evaluated"], full["lane_pairs"])
+        assert st["evaluated"] <= full["evaluated"]
+        assert copies * st["lane_pairs"] >= full["lane_pairs"]
+        if copies > 1 and lists["bcount"].min() > 20:
+            assert st["lane_pairs"] <= full["lane_pairs"] // copies + 64 * 64 * k * st["nitem"]
