@@ -296,6 +296,8 @@ int pp_plan_set_timing(pp_plan* plan, int on);
 typedef struct pp_tuning {
     int32_t chunk, persistent, waves_per_cu, use_graph, variant, waves_per_block;
 } pp_tuning;
+/* The tuning as set: chunk is the bound asked for where the cut is finer
+ * (pp_stats.nitem counts the items that ran).                               */
 int pp_plan_get_tuning(const pp_plan* plan, pp_tuning* t);
 int pp_plan_set_tuning(pp_plan* plan, const pp_tuning* t);
 
@@ -306,8 +308,9 @@ int pp_plan_set_tuning(pp_plan* plan, const pp_tuning* t);
  * waves per target block (chunk = positions x waves_per_block), persistent
  * at 20 waves per CU, and 256 or 512 positions too when the lists hold
  * fewer than 2^24 positions in all (small boxes); then, at the best tiles, the launch shape: persistent
- * with 12, 24 or 32 waves per CU, or one workgroup per item.  The variant is
- * kept.  With cache_path (may be NULL) the choice is looked up first and
+ * with 12, 24 or 32 waves per CU, or one workgroup per item.  Chunks that the
+ * finer cut of small boxes makes alike are timed once, and the tuning kept
+ * names the (coarsest) chunk that ran.  The variant is kept.  With cache_path (may be NULL) the choice is looked up first and
  * stored afterwards, one line "arch/nbox<k>/n2^<j>/leaf<m> chunk persistent
  * waves graph waves_per_block" per shape class.  The caller's inputs are not
  * modified.  Synchronises the stream.  */

@@ -637,6 +637,7 @@ struct Batch {
                     check_tuning_ok(t)) {
                     tune = t;
                     lists_valid = false;
+                    reuse_ready = false;
                     return PP_OK;
                 }
             }
@@ -646,10 +647,25 @@ struct Batch {
         const bool multi = variant == 0 || variant == 8;      // K > 1 is built for these
         pp_tuning best = tune;
         float best_ms = 1e30f;
-        auto trial = [&](const pp_tuning& t) -> int {
+        // With one wave per block the persistent form takes the chunk as an upper
+        // bound.  `cut`: the coarsest cut of a box by that rule, once a trial
+        // has met it below its chunk; chunks from there on are the same cut.
+        int32_t cut = INT32_MAX;
+        auto trial = [&](pp_tuning t) -> int {
+            const bool bound = t.persistent && t.waves_per_block == 1;
+            if (bound && t.chunk > cut) return PP_OK;          // timed before, at `cut`
             tune = t;
+            reuse_ready = false;                               // lists at another chunk
             float ms = 0.f;
             PP_TRY(time_pp(pos, mass, acc, 3, s, &ms));
+            if (bound) {
+                std::vector<int32_t> c(nbox);
+                PP_HIP(hipMemcpy(c.data(), w.box_chunk.p, sizeof(int32_t) * nbox, hipMemcpyDeviceToHost));
+                int32_t most = 0;
+                for (int x = 0; x < nbox; ++x)
+                    if (poff[x + 1] > poff[x]) most = std::max(most, c[x]);
+                if (most < t.chunk) t.chunk = cut = most;      // what ran, and what is kept
+            }
             if (ms < best_ms) {
                 best_ms = ms;
                 best = t;
@@ -681,6 +697,7 @@ struct Batch {
         PP_TRY(trial(pp_tuning{tiled.chunk, 0, 20, 0, variant, tiled.waves_per_block}));
         tune = best;
         lists_valid = false;
+        reuse_ready = false;
         if (cache_path) {
             std::vector<std::string> keep;
             {

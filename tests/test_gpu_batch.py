@@ -333,3 +333,20 @@ def test_many_small_boxes_hold_little_memory(pp):
     bp.accel(pos, mass, out)
     torch.cuda.synchronize()
     assert free - torch.cuda.mem_get_info()[0] < 5e9
+
+
+@pytest.mark.parametrize("n", [700, 6001, 20011, 32768, 60000])
+def test_autotuned_chunk_is_the_cut_that_runs(pp, n):
+    """The tuning kept for a small box, which the persistent form cuts finer
+    than the chunk asked for (variant 1: one wave per block only), names the
+    chunk of its work items."""
+    rng = np.random.default_rng(n)
+    p = BoxParams.from_mesh(60.0, max(12, int(round(n ** (1 / 3)))))
+    x = dev(W.mixture(rng, n, p.L, 0.4, max(1, n // 500)), torch.float64)
+    m = dev(rng.uniform(0.5, 1.5, n), torch.float32)
+    plan = pp.Plan(p, n)
+    plan.set_tuning(variant=1)
+    t = plan.autotune(x, m)
+    plan.accel(x, m)
+    slen = plan.export_lists()["slen"].astype(np.int64)
+    assert plan.stats()["nitem"] == int(np.maximum(1, -(-slen // t["chunk"])).sum()), t
