@@ -1435,6 +1435,8 @@ int f32_grid_groups(const Work& w, int waves_per_block, Mode mode, int64_t* grou
     const bool grid = mode == Mode::kGrid || room <= kGridFew ||
                       (w.nitem > 0 ? w.total_src / w.nitem < kGridLength * waves_per_block : room <= kGridFirst);
     *groups = grid ? xcd_groups(w.cap_item) : 0;
+    // a launch takes fewer than 2^32 threads; the queues take any number of items
+    if (mode != Mode::kGrid && *groups * waves_per_block * kBlock > (int64_t)UINT32_MAX) *groups = 0;
     return PP_OK;
 }
 

@@ -251,3 +251,26 @@ def test_statistics_of_packed_blocks(pp, k):
         assert copies * st["lane_pairs"] >= full["lane_pairs"]
         if copies > 1 and lists["bcount"].min() > 20:
             assert st["lane_pairs"] <= full["lane_pairs"] // copies + 64 * 64 * k * st["nitem"]
+
+
+def test_more_items_than_one_launch_takes(pp, oracle_mod):
+    """7.2 M target blocks of one particle each (a cut below half a grid cell),
+    their short items shared by 8 waves: one workgroup per item would be more
+    than 2^32 threads, so the queues serve the later calls too."""
+    n = 7200000
+    p = BoxParams(L=1.0, rs=2e-7 / 4.5, rcut=2e-7, eps=1e-9)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    a = torch.rand(3, n // 2, dtype=torch.float64, device="cuda", generator=gen) * 0.99
+    pos = torch.cat([a, a + 1e-7 * torch.rand(3, n // 2, dtype=torch.float64, device="cuda", generator=gen)], 1)
+    mass = torch.full((n,), 1.0 / n, dtype=torch.float32, device="cuda")
+    plan = pp.Plan(p, n)
+    plan.set_tuning(chunk=4096, waves_per_block=8)
+    first = plan.accel(pos, mass).clone()
+    for _ in range(2):
+        assert torch.equal(plan.accel(pos, mass), first)
+    assert plan.stats()["nitem"] * 8 * 64 > 0.8 * 2 ** 32          # its capacity has a margin of a quarter
+    t = np.arange(0, n, n // 20)
+    ref = oracle_mod.accel(pos.cpu().numpy(), mass.cpu().numpy().astype(np.float64), p, targets=t)["acc"]
+    e = np.linalg.norm(first.cpu().numpy()[:, t] - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.median(e) <= 1e-5 and e.max() <= 1e-2
