@@ -935,6 +935,44 @@ __device__ __forceinline__ void expand2(const TreeView& tv, const IBox* nodes, i
 // entries are those of a walk from the root, which took two kernels and a scan
 // per level.
 //
+// The entry, if any, of one node of the start level under one shift.
+__device__ __forceinline__ bool start_entry(const TreeView& tv, const BoxDev& X, const IBox* __restrict__ nodes,
+                                            const IBox& A, int64_t b, const int s[3], int sc, int64_t node,
+                                            bool fill, const MonoDev& mono, FEntry& E) {
+    const int64_t W = X.W, T = X.T;
+    const int start = tv.start;
+    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
+    for (int h = mono_on ? tv.nlev - 1 : start; h >= start; --h) {
+        const int64_t up = node >> (3 * (h - start));
+        const IBox R = nodes[tv.off[h] + up];
+        if (!(gap2_shift(A, R, s, W) < T)) return false;
+        const bool taken = mono_on && h >= kMonoMinLevel &&
+                           accept_monopole(A, R, s, W, mono, tv.off[h] + up, b, X.G, X.cell);
+        if (h > start && !taken) continue;
+        E.blk = (int32_t)b;
+        E.node = (int32_t)up;
+        E.sc = (uint8_t)sc;
+        E.lev = (uint8_t)h;
+        E.inside = fill && maxd2_shift(A, R, s, W) < T;
+        E.mono = taken;
+        return up << (3 * (h - start)) == node;
+    }
+    return false;
+}
+
+// Whether any of the 64 nodes of the start level from 64 i on can give an
+// entry: their common ancestor first (its box holds theirs).  With monopoles
+// the first unit of every higher node is walked in any case: such a node may
+// lie within the cut, and be accepted, where its first 64 nodes do not, and
+// the entry is theirs to write.
+__device__ __forceinline__ bool start_unit(const TreeView& tv, const BoxDev& X, const IBox* __restrict__ nodes,
+                                           const IBox& A, const int s[3], int i, const MonoDev& mono) {
+    const int top = tv.nlev - 1, start = tv.start;
+    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
+    return start + 2 > top || (mono_on && start + 3 <= top && (i & 7) == 0) ||
+           gap2_shift(A, nodes[tv.off[start + 2] + i], s, X.W) < X.T;
+}
+
 // One wave walks the units (allowed shift, 64 nodes) from u0 to u1 - 1 of
 // block b and returns the number of entries, which it writes from number o on
 // when `fill`.  With KEEP, the first KEEP units' ballots of the counting walk
@@ -946,11 +984,8 @@ __device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& 
                                               bool fill, int64_t o, FEntry* __restrict__ out, int64_t cap_out,
                                               const MonoDev& mono, uint64_t* keep) {
     const int lane = threadIdx.x & (kBlock - 1);
-    const int64_t W = X.W, T = X.T;
-    const int top = tv.nlev - 1, start = tv.start;
-    const int64_t n0 = tv.cnt[start];
+    const int64_t n0 = tv.cnt[tv.start];
     const int per = (int)((n0 + kBlock - 1) / kBlock);               // units per shift
-    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
     int32_t c = 0;
     int u = 0;
     for (int sc = 0; sc < 27 && u < u1; ++sc) {
@@ -972,29 +1007,8 @@ __device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& 
             const int64_t node = (int64_t)i * kBlock + lane;
             FEntry E{};
             bool emit = false;
-            // the 64 nodes' common ancestor first (its box holds theirs).  With
-            // monopoles the first unit of every higher node is walked in any
-            // case: such a node may lie within the cut, and be accepted, where
-            // its first 64 nodes do not, and the entry is theirs to write
-            const bool first_of_higher = mono_on && start + 3 <= top && (i & 7) == 0;
-            if ((fill && kept) || start + 2 > top || first_of_higher ||
-                gap2_shift(A, nodes[tv.off[start + 2] + i], s, W) < T)
-                for (int h = mono_on ? top : start; h >= start && node < n0 && (known >> lane & 1ull); --h) {
-                    const int64_t up = node >> (3 * (h - start));
-                    const IBox R = nodes[tv.off[h] + up];
-                    if (!(gap2_shift(A, R, s, W) < T)) break;
-                    const bool taken = mono_on && h >= kMonoMinLevel &&
-                                       accept_monopole(A, R, s, W, mono, tv.off[h] + up, b, X.G, X.cell);
-                    if (h > start && !taken) continue;
-                    E.blk = (int32_t)b;
-                    E.node = (int32_t)up;
-                    E.sc = (uint8_t)sc;
-                    E.lev = (uint8_t)h;
-                    E.inside = fill && maxd2_shift(A, R, s, W) < T;
-                    E.mono = taken;
-                    emit = up << (3 * (h - start)) == node;
-                    break;
-                }
+            if ((fill && kept) || start_unit(tv, X, nodes, A, s, i, mono))
+                if (node < n0 && (known >> lane & 1ull)) emit = start_entry(tv, X, nodes, A, b, s, sc, node, fill, mono, E);
             const uint64_t bal = __ballot(emit);
             if (KEEP > 0 && !fill && kept && lane == 0) keep[u - u0] = bal;
             if (fill) {
@@ -1021,8 +1035,8 @@ __device__ __forceinline__ int start_units(const TreeView& tv, const int mask[3]
     return __popc(mask[0]) * __popc(mask[1]) * __popc(mask[2]) * (int)((tv.cnt[tv.start] + kBlock - 1) / kBlock);
 }
 
-// Large boxes: one wave per block, a counting and a writing launch around a
-// scan.
+// Large boxes, up to kManyBlocks blocks: one wave per block, a counting and a
+// writing launch around a scan.
 template <bool FILL>
 __global__ void __launch_bounds__(256) start_kernel(BatchDev bd, const TreeView* __restrict__ tvs,
                                                     const IBox* __restrict__ nodes,
@@ -1045,6 +1059,80 @@ __global__ void __launch_bounds__(256) start_kernel(BatchDev bd, const TreeView*
     const int32_t c = start_walk<0>(tvs[x], bd.box[x], nodes, A, b, mask, 0, start_units(tvs[x], mask), FILL,
                                     FILL ? off[b] : 0, out, cap_out, mono, nullptr);
     if (!FILL && first) cnt[b] = c;
+}
+
+// The same with one lane per block, for more than kManyBlocks of them: each
+// lane walks its box's tree from the root down to the start level, in order.
+// Neighbouring blocks take nearly the same way.  A wave per block tests every
+// node of the start level, most lanes of it idle, and costs about 1 us of a
+// wave's time for each block: 4 M particles whose cut splits them into 1.6 M
+// blocks took 1122 us in both launches, so 182; 16.8 M clustered ones 575, so
+// 152; 64 boxes of a batch (500 k blocks) 1198, so 454; 63 k blocks with
+// monopoles 269, so 199.  Fewer blocks leave lanes without enough waves in
+// flight: 37 k of them 94, so 162.
+template <bool FILL>
+__global__ void __launch_bounds__(256) start_many_kernel(BatchDev bd, const TreeView* __restrict__ tvs,
+                                                         const IBox* __restrict__ nodes,
+                                                         const IBox* __restrict__ bbox,
+                                                         const int32_t* __restrict__ bboxid,
+                                                         const int64_t* __restrict__ sizes, int64_t cap_in,
+                                                         int32_t* __restrict__ cnt, const int64_t* __restrict__ off,
+                                                         FEntry* __restrict__ out, int64_t cap_out, MonoDev mono) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= cap_in) return;
+    if (b >= sizes[kNBlock]) {
+        if (!FILL) cnt[b] = 0;
+        return;
+    }
+    const int x = bboxid[b];
+    const TreeView& tv = tvs[x];
+    const BoxDev& X = bd.box[x];
+    const IBox A = bbox[b];
+    const int64_t W = X.W, T = X.T;
+    const int top = tv.nlev - 1, start = tv.start;
+    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
+    int mask[3];
+    allowed_shifts(A, W, T, mask);
+    int64_t o = FILL ? off[b] : 0;
+    int32_t c = 0;
+    for (int sc = 0; sc < 27; ++sc) {
+        int s[3];
+        decode_shift(sc, s);
+        if (!shift_allowed(mask, s)) continue;
+        int h = top;
+        int64_t i = 0;
+        for (;;) {
+            const int64_t g = tv.off[h] + i;
+            const IBox R = nodes[g];
+            if (gap2_shift(A, R, s, W) < T) {
+                const bool taken = mono_on && h >= kMonoMinLevel && accept_monopole(A, R, s, W, mono, g, b, X.G, X.cell);
+                if (!taken && h > start) {
+                    h -= 1;
+                    i *= 8;
+                    continue;
+                }
+                if (FILL && o < cap_out) {
+                    FEntry E;
+                    E.blk = (int32_t)b;
+                    E.node = (int32_t)i;
+                    E.sc = (uint8_t)sc;
+                    E.lev = (uint8_t)h;
+                    E.inside = maxd2_shift(A, R, s, W) < T;
+                    E.mono = taken;
+                    out[o] = E;
+                }
+                ++o;
+                ++c;
+            }
+            while (h < top && (((i + 1) & 7) == 0 || i + 1 >= tv.cnt[h])) {
+                i >>= 3;
+                h += 1;
+            }
+            if (h == top) break;
+            ++i;
+        }
+    }
+    if (!FILL) cnt[b] = c;
 }
 
 // Small boxes: kStartSplit waves share a block, each a stretch of its units (a
@@ -1648,8 +1736,10 @@ int reset_sizes_reuse(int nbox, Work& w, hipStream_t s) {
 // than testing every node for every block (2.1 M particles: 316 us from a
 // level of 540 nodes, 88 from one of 9).
 // chunks up to which the one-launch forms of the block split and of the first
-// expansion pass are taken
+// expansion pass are taken, and room for blocks beyond which that pass takes a
+// lane for each
 constexpr int64_t kFewChunks = 4096;
+constexpr int64_t kManyBlocks = 65536;
 static bool small_boxes(int64_t N, int nbox) { return N / nbox <= 131072; }
 static int64_t start_nodes_for(int64_t N, int nbox) { return small_boxes(N, nbox) ? 1024 : 128; }
 
@@ -1921,15 +2011,16 @@ int stage_lists(const BatchDev& bd, const std::vector<int64_t>& poff, int chunk_
         hipLaunchKernelGGL(start_small_kernel, dim3((unsigned)nt), dim3(kStartWaves * kBlock), 0, s, bd, tvs, nodes,
                            bbox, bboxid, lb, nt, sizes, w.fent_a.as<FEntry>(), cap(0), last0, mono);
     } else {
-        const unsigned groups = blocks_for(cb, 256 / kBlock);
-        hipLaunchKernelGGL(start_kernel<false>, dim3(groups), dim3(256), 0, s, bd, tvs, nodes, bbox, bboxid,
-                           (const int64_t*)sizes, cb, w.fcnt.as<int32_t>(), (const int64_t*)nullptr,
-                           (FEntry*)nullptr, (int64_t)0, mono);
+        const bool many = cb > kManyBlocks;
+        const unsigned groups = blocks_for(cb, many ? 256 : 256 / kBlock);
+        hipLaunchKernelGGL(many ? start_many_kernel<false> : start_kernel<false>, dim3(groups), dim3(256), 0, s, bd,
+                           tvs, nodes, bbox, bboxid, (const int64_t*)sizes, cb, w.fcnt.as<int32_t>(),
+                           (const int64_t*)nullptr, (FEntry*)nullptr, (int64_t)0, mono);
         PP_HIP(hipGetLastError());
         const ScanNote note{(int)kEntry0, (int)kNeedEntry0, cap(0), 2ull, last0};
         PP_TRY(launch_scan_i32_to_i64(w.fcnt.as<int32_t>(), w.foff.as<int64_t>(), cb, w.scan_ws, s, sizes, &note));
-        hipLaunchKernelGGL(start_kernel<true>, dim3(groups), dim3(256), 0, s, bd, tvs, nodes, bbox, bboxid,
-                           (const int64_t*)sizes, cb, (int32_t*)nullptr, w.foff.as<int64_t>(),
+        hipLaunchKernelGGL(many ? start_many_kernel<true> : start_kernel<true>, dim3(groups), dim3(256), 0, s, bd, tvs,
+                           nodes, bbox, bboxid, (const int64_t*)sizes, cb, (int32_t*)nullptr, w.foff.as<int64_t>(),
                            w.fent_a.as<FEntry>(), cap(0), mono);
     }
     PP_HIP(hipGetLastError());

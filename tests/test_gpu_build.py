@@ -249,3 +249,54 @@ def test_a_dense_cell_does_not_hold_up_few_targets(pp):
         return min(t)
 
     assert best(dev(pos, torch.float64)) < 6 * best(dev(spread, torch.float64))
+
+
+@pytest.mark.parametrize("theta", [0.0, 0.95])
+def test_many_blocks_with_short_cuts(pp, oracle_mod, theta, monkeypatch):
+    """Clumps of 16 particles in cubes 4 cuts wide, far from one another: some
+    hundred thousand blocks of a few targets each, whose first entries a lane
+    per block finds.  Neighbour counts against the oracle, and with monopoles
+    the forces of sampled blocks against the library's acceptance restated."""
+    from tests import monopole_mirror as tree
+    rng = np.random.default_rng(12)
+    n, rcut = 320000, 1e-4
+    p = W.BoxParams(L=1.0, rs=rcut / 4.5, rcut=rcut, eps=0.01 * rcut, leaf_max=1 if theta else 8)
+    centre = np.repeat(rng.random((3, n // 16)), 16, axis=1)
+    centre[:, :1600] = rng.random((3, 1600)) * 2e-3                  # part of them across the faces
+    pos = centre + (rng.random((3, n)) - 0.5) * 4 * rcut
+    mass = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    x, m = dev(pos, torch.float64), dev(mass, torch.float32)
+    plan = pp.Plan(p, n)
+    t = np.concatenate([np.arange(0, 1600, 20), np.sort(rng.choice(n, 200, replace=False))])
+    if theta == 0:
+        for _ in range(2):
+            acc = plan.accel(x, m)
+            _, counts = plan.count_interactions(per_target=True)
+            ref = oracle_mod.accel(pos, mass.astype(np.float64), p, targets=t)
+            assert np.array_equal(counts.cpu().numpy()[t], ref["n_inter"])
+        assert plan.stats()["nblock"] > 65536
+        return
+    plan.set_monopole(theta)
+    for _ in range(2):
+        acc = plan.accel(x, m)
+    st = plan.stats()
+    assert st["nblock"] > 65536 and st["monopoles"] > 0
+    keep = []
+    blocks = tree._blocks
+
+    def sample(q, n_, emax):
+        all_ = blocks(q, n_, emax)
+        assert len(all_) == st["nblock"]
+        keep.extend(all_[k] for k in range(0, len(all_), len(all_) // 400))
+        return keep
+
+    monkeypatch.setattr(tree, "_blocks", sample)
+    ref = tree.monopole_accel(pos, mass.astype(np.float64), p, theta)
+    assert ref["n_mono_pairs"] > 0
+    perm = plan.export_lists()["perm"]
+    at = np.concatenate([perm[s:s + c] for s, c, _, _ in keep])
+    got, want = acc.cpu().numpy()[:, at].astype(np.float64), ref["acc"][:, at]
+    mag = np.linalg.norm(want, axis=0)
+    e = np.linalg.norm(got - want, axis=0)[mag > 0] / mag[mag > 0]
+    assert np.all(got[:, mag == 0] == 0)
+    assert np.median(e) <= 1e-6 and np.percentile(e, 99) <= 1e-4, (np.median(e), np.percentile(e, 99))
