@@ -307,12 +307,13 @@ int pp_plan_set_tuning(pp_plan* plan, const pp_tuning* t);
  * tiles: 1024, 2048 or 4096 source-list positions per wave with 1, 2, 4 or 8
  * waves per target block (chunk = positions x waves_per_block), persistent
  * at 20 waves per CU, and 256 or 512 positions too when the lists hold
- * fewer than 2^24 positions in all (small boxes); then, at the best tiles, the launch shape: persistent
- * with 12, 24 or 32 waves per CU, or one workgroup per item.  Chunks that the
- * finer cut of small boxes makes alike are timed once, and the tuning kept
- * names the (coarsest) chunk that ran.  The variant is kept.  With cache_path (may be NULL) the choice is looked up first and
- * stored afterwards, one line "arch/nbox<k>/n2^<j>/leaf<m> chunk persistent
- * waves graph waves_per_block" per shape class.  The caller's inputs are not
+ * fewer than 2^24 positions in all (small boxes); then, at the best tiles,
+ * the launch shape: persistent with 12, 24 or 32 waves per CU, or one
+ * workgroup per item.  Chunks that the finer cut of small boxes makes alike
+ * are timed once, and the tuning kept names the (coarsest) chunk that ran.
+ * The variant is kept.  With cache_path (may be NULL) the choice is looked up
+ * first and stored afterwards, one line "arch/nbox<k>/n2^<j>/leaf<m> chunk
+ * persistent waves graph waves_per_block" per shape class.  The caller's inputs are not
  * modified.  Synchronises the stream.  */
 int pp_autotune(pp_plan* plan, const double* pos, const float* mass, int64_t n,
                 const char* cache_path, void* stream);

@@ -436,10 +436,11 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
         uint32_t* counts = pl->counts.as<uint32_t>();
         uint32_t* total = pl->total.as<uint32_t>();
         int2* run = pl->run.as<int2>();
-                const int64_t clearing = (cells + 4 * kSortThreads - 1) / (4 * kSortThreads);
+        const int64_t clearing = (cells + 4 * kSortThreads - 1) / (4 * kSortThreads);
         const int64_t most = clearing < 1024 ? clearing : 1024;
-        hipLaunchKernelGGL(cic_cell_kernel, dim3((unsigned)(ntile > most ? ntile : most)), dim3(kSortThreads), 0, s, pos, mass, n, L, 1.0 / d, N, Digit{0, dbits},
-                           pl->key.as<uint32_t>(), pl->rec_in.as<double4>(), counts, run, cells);
+        hipLaunchKernelGGL(cic_cell_kernel, dim3((unsigned)(ntile > most ? ntile : most)), dim3(kSortThreads), 0, s,
+                           pos, mass, n, L, 1.0 / d, N, Digit{0, dbits}, pl->key.as<uint32_t>(),
+                           pl->rec_in.as<double4>(), counts, run, cells);
         uint2* out = pl->pair_a.as<uint2>();
         for (int pass = 0; pass < npass; ++pass) {
             const Digit dig{pass * dbits, dbits};
@@ -454,7 +455,8 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
         }
         hipLaunchKernelGGL(cic_deposit_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, sorted,
                            pl->rec_in.as<double4>(), n, pa, run, pl->rec.as<double4>(), pl->part.as<double>());
-        hipLaunchKernelGGL(cic_gather_kernel, dim3(blocks_for(cells, 256)), dim3(256), 0, s, run, pl->part.as<double>(), pa, N, rho);
+        hipLaunchKernelGGL(cic_gather_kernel, dim3(blocks_for(cells, 256)), dim3(256), 0, s, run,
+                           pl->part.as<double>(), pa, N, rho);
     } else {
         hipLaunchKernelGGL(zero_f64_kernel, dim3(2048), dim3(256), 0, s, rho, cells);
     }
@@ -464,7 +466,8 @@ int pp_pm_accel(pp_pm_plan* pl, const double* pos, const float* mass, int64_t n,
     hipfftDoubleComplex* rk = pl->rk.as<hipfftDoubleComplex>();
     PM_FFT(hipfftExecD2Z(pl->fwd, rho, rk));
     const double scale = 1.0 / (d * d * d) / (double)cells;
-    hipLaunchKernelGGL(green_kernel, dim3(2048), dim3(256), 0, s, rk, pl->sin2.as<double>(), N, L, pl->p.G, pl->p.rs, scale);
+    hipLaunchKernelGGL(green_kernel, dim3(2048), dim3(256), 0, s, rk, pl->sin2.as<double>(), N, L, pl->p.G, pl->p.rs,
+                       scale);
     PP_HIP(hipGetLastError());
     PM_FFT(hipfftExecZ2D(pl->inv, rk, rho));
     double* g = pl->g.as<double>();
