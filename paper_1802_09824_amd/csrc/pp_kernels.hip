@@ -1095,8 +1095,8 @@ __device__ __forceinline__ double fma_const(double a, double b, double c) {
 // so the cut decides as its own test does.  With y = 1 / s_eps from the
 // hardware estimate and one third-order step, x = s_eps / 2 r_s and the split
 // factor g = 2^-n 2^-f P(x) (split_poly64.h), the pair factor G m g y^3 holds
-// about 3e-16 (relative, rms over the cut sphere), against 5e-16 with the
-// library's erfc, exp, square root and quotients.
+// about 4.7e-16 (relative, rms over the cut sphere, against 40 digits), and
+// 5.5e-16 with the library's erfc, exp, square root and quotients.
 __device__ __forceinline__ void pair_f64(double dx, double dy, double dz, double gm, const F64Const& C,
                                          double& tx, double& ty, double& tz) {
 #pragma clang fp contract(off)
@@ -1131,7 +1131,7 @@ __device__ __forceinline__ void pair_f64(double dx, double dy, double dz, double
 // by all lanes.  The bound is FP64 issue: about 75 instructions per lane-pair
 // at 4 clocks each.  The earlier form, library functions on every listed
 // source with a branch per pair, held all of them (both branches of erfc
-// among them) for one lane inside the cut: 262 k particles took 8.2 ms per
+// among them) for one lane inside the cut: 262 k particles took 10.9 ms per
 // call, now 3.4.
 template <bool COUNT>
 __global__ void __launch_bounds__(64) pp_f64_kernel(ItemArgs ia, const double* __restrict__ pos_s,
