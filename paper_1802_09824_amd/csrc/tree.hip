@@ -935,44 +935,6 @@ __device__ __forceinline__ void expand2(const TreeView& tv, const IBox* nodes, i
 // entries are those of a walk from the root, which took two kernels and a scan
 // per level.
 //
-// The entry, if any, of one node of the start level under one shift.
-__device__ __forceinline__ bool start_entry(const TreeView& tv, const BoxDev& X, const IBox* __restrict__ nodes,
-                                            const IBox& A, int64_t b, const int s[3], int sc, int64_t node,
-                                            bool fill, const MonoDev& mono, FEntry& E) {
-    const int64_t W = X.W, T = X.T;
-    const int start = tv.start;
-    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
-    for (int h = mono_on ? tv.nlev - 1 : start; h >= start; --h) {
-        const int64_t up = node >> (3 * (h - start));
-        const IBox R = nodes[tv.off[h] + up];
-        if (!(gap2_shift(A, R, s, W) < T)) return false;
-        const bool taken = mono_on && h >= kMonoMinLevel &&
-                           accept_monopole(A, R, s, W, mono, tv.off[h] + up, b, X.G, X.cell);
-        if (h > start && !taken) continue;
-        E.blk = (int32_t)b;
-        E.node = (int32_t)up;
-        E.sc = (uint8_t)sc;
-        E.lev = (uint8_t)h;
-        E.inside = fill && maxd2_shift(A, R, s, W) < T;
-        E.mono = taken;
-        return up << (3 * (h - start)) == node;
-    }
-    return false;
-}
-
-// Whether any of the 64 nodes of the start level from 64 i on can give an
-// entry: their common ancestor first (its box holds theirs).  With monopoles
-// the first unit of every higher node is walked in any case: such a node may
-// lie within the cut, and be accepted, where its first 64 nodes do not, and
-// the entry is theirs to write.
-__device__ __forceinline__ bool start_unit(const TreeView& tv, const BoxDev& X, const IBox* __restrict__ nodes,
-                                           const IBox& A, const int s[3], int i, const MonoDev& mono) {
-    const int top = tv.nlev - 1, start = tv.start;
-    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
-    return start + 2 > top || (mono_on && start + 3 <= top && (i & 7) == 0) ||
-           gap2_shift(A, nodes[tv.off[start + 2] + i], s, X.W) < X.T;
-}
-
 // One wave walks the units (allowed shift, 64 nodes) from u0 to u1 - 1 of
 // block b and returns the number of entries, which it writes from number o on
 // when `fill`.  With KEEP, the first KEEP units' ballots of the counting walk
@@ -984,8 +946,15 @@ __device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& 
                                               bool fill, int64_t o, FEntry* __restrict__ out, int64_t cap_out,
                                               const MonoDev& mono, uint64_t* keep) {
     const int lane = threadIdx.x & (kBlock - 1);
-    const int64_t n0 = tv.cnt[tv.start];
+    const int64_t W = X.W, T = X.T;
+    const int top = tv.nlev - 1, start = tv.start;
+    const int64_t n0 = tv.cnt[start];
     const int per = (int)((n0 + kBlock - 1) / kBlock);               // units per shift
+    const bool mono_on = mono.theta2 > 0.0 || mono.alpha > 0.0;
+    // with monopoles the first unit of every higher node is walked in any case:
+    // such a node may lie within the cut, and be accepted, where its first 64
+    // nodes do not, and the entry is theirs to write
+    const bool higher = mono_on && start + 3 <= top;
     int32_t c = 0;
     int u = 0;
     for (int sc = 0; sc < 27 && u < u1; ++sc) {
@@ -1007,8 +976,25 @@ __device__ __forceinline__ int32_t start_walk(const TreeView& tv, const BoxDev& 
             const int64_t node = (int64_t)i * kBlock + lane;
             FEntry E{};
             bool emit = false;
-            if ((fill && kept) || start_unit(tv, X, nodes, A, s, i, mono))
-                if (node < n0 && (known >> lane & 1ull)) emit = start_entry(tv, X, nodes, A, b, s, sc, node, fill, mono, E);
+            // the 64 nodes' common ancestor first (its box holds theirs)
+            if ((fill && kept) || start + 2 > top || gap2_shift(A, nodes[tv.off[start + 2] + i], s, W) < T ||
+                (higher && (i & 7) == 0))
+                for (int h = mono_on ? top : start; h >= start && node < n0 && (known >> lane & 1ull); --h) {
+                    const int64_t up = node >> (3 * (h - start));
+                    const IBox R = nodes[tv.off[h] + up];
+                    if (!(gap2_shift(A, R, s, W) < T)) break;
+                    const bool taken = mono_on && h >= kMonoMinLevel &&
+                                       accept_monopole(A, R, s, W, mono, tv.off[h] + up, b, X.G, X.cell);
+                    if (h > start && !taken) continue;
+                    E.blk = (int32_t)b;
+                    E.node = (int32_t)up;
+                    E.sc = (uint8_t)sc;
+                    E.lev = (uint8_t)h;
+                    E.inside = fill && maxd2_shift(A, R, s, W) < T;
+                    E.mono = taken;
+                    emit = up << (3 * (h - start)) == node;
+                    break;
+                }
             const uint64_t bal = __ballot(emit);
             if (KEEP > 0 && !fill && kept && lane == 0) keep[u - u0] = bal;
             if (fill) {
