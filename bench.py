@@ -49,48 +49,48 @@ TRAFFIC = {
     "sources": ["paper_1802_09824_amd/csrc/pp_kernels.hip",
                 "paper_1802_09824_amd/csrc/pp_internal.h",
                 "paper_1802_09824_amd/csrc/tree.hip"],
-    "sha1": "7071a7f07570a1d68d9376029ad1c2ceae0cfe75",
+    "sha1": "e6d56562e8a0533cec5c43ee1b60475fdc55445d",
     "fetch_scale": 1.99996,       # 1 GiB copy: 1048576 KiB / 524299.5 KiB of FETCH_SIZE
     "write_scale": 1.00000,       # 1 GiB copy: 1048576 KiB / 1048576.0 KiB of WRITE_SIZE
     # (chunk, waves per block, waves per CU (0: one workgroup per item), persistent):
     # (FETCH_SIZE KiB, WRITE_SIZE KiB) of the timed step's PP dispatch
     "kib": {
-        (1024, 1, 0, 0): (378935.7, 171342.4),
-        (1024, 1, 12, 1): (379325.4, 171364.9),
-        (1024, 1, 20, 1): (378589.6, 171362.8),
-        (1024, 1, 24, 1): (379101.6, 171362.4),
-        (1024, 1, 32, 1): (378496.0, 171363.2),
-        (2048, 1, 0, 0): (466709.4, 94722.2),
-        (2048, 1, 12, 1): (132810.4, 97687.2),
-        (2048, 1, 20, 1): (176724.5, 98841.1),
-        (2048, 1, 24, 1): (211002.8, 98968.6),
-        (2048, 1, 32, 1): (207847.4, 99059.8),
-        (2048, 2, 20, 1): (282290.8, 93893.2),
-        (2048, 2, 24, 1): (282347.2, 93894.9),
-        (2048, 2, 32, 1): (282375.7, 93903.7),
-        (4096, 1, 20, 1): (262121.4, 74079.3),
-        (4096, 1, 32, 1): (316193.9, 74202.7),
-        (4096, 2, 20, 1): (169558.5, 74048.6),
-        (4096, 2, 24, 1): (170568.4, 74051.1),
-        (4096, 2, 32, 1): (170151.8, 74094.4),
-        (4096, 4, 0, 0): (242050.1, 70925.1),
-        (4096, 4, 12, 1): (242081.2, 70923.7),
-        (4096, 4, 20, 1): (242069.7, 70922.0),
-        (4096, 4, 24, 1): (242047.2, 70931.9),
-        (4096, 4, 32, 1): (242058.2, 70925.6),
-        (8192, 2, 32, 1): (208306.4, 69857.2),
-        (8192, 4, 0, 0): (226172.8, 67598.2),
-        (8192, 4, 12, 1): (140131.0, 69199.6),
-        (8192, 4, 20, 1): (160132.3, 69603.9),
-        (8192, 4, 24, 1): (160113.7, 69625.6),
-        (8192, 4, 32, 1): (158457.9, 69626.3),
-        (8192, 8, 20, 1): (221903.2, 68011.5),
-        (8192, 8, 32, 1): (221818.6, 68005.9),
-        (16384, 4, 20, 1): (162963.3, 68332.0),
-        (16384, 4, 24, 1): (163328.6, 68327.2),
-        (16384, 4, 32, 1): (163401.2, 68351.1),
-        (16384, 8, 20, 1): (213043.3, 66984.1),
-        (16384, 8, 32, 1): (213200.1, 66983.5),
+        (1024, 1, 0, 0): (377368.1, 171271.3),
+        (1024, 1, 12, 1): (377571.8, 171283.6),
+        (1024, 1, 20, 1): (376813.8, 171272.0),
+        (1024, 1, 24, 1): (377027.6, 171286.8),
+        (1024, 1, 32, 1): (377111.6, 171290.0),
+        (2048, 1, 0, 0): (465898.5, 94729.2),
+        (2048, 1, 12, 1): (139882.0, 97665.6),
+        (2048, 1, 20, 1): (180353.6, 98782.4),
+        (2048, 1, 24, 1): (207207.3, 98981.4),
+        (2048, 1, 32, 1): (202521.6, 99049.7),
+        (2048, 2, 20, 1): (281872.4, 93887.4),
+        (2048, 2, 24, 1): (281807.2, 93897.0),
+        (2048, 2, 32, 1): (281813.0, 93891.2),
+        (4096, 1, 20, 1): (264510.1, 74071.3),
+        (4096, 1, 32, 1): (313993.8, 74218.3),
+        (4096, 2, 20, 1): (171973.0, 73968.6),
+        (4096, 2, 24, 1): (168917.0, 73976.8),
+        (4096, 2, 32, 1): (170742.1, 74039.4),
+        (4096, 4, 0, 0): (241855.8, 70926.2),
+        (4096, 4, 12, 1): (241905.9, 70929.6),
+        (4096, 4, 20, 1): (241971.0, 70924.2),
+        (4096, 4, 24, 1): (241861.2, 70931.2),
+        (4096, 4, 32, 1): (241955.5, 70930.2),
+        (8192, 2, 32, 1): (208910.0, 69822.0),
+        (8192, 4, 0, 0): (225717.8, 67597.1),
+        (8192, 4, 12, 1): (142078.6, 69206.2),
+        (8192, 4, 20, 1): (158493.4, 69620.8),
+        (8192, 4, 24, 1): (157835.1, 69653.7),
+        (8192, 4, 32, 1): (157055.4, 69635.4),
+        (8192, 8, 20, 1): (221885.6, 68009.0),
+        (8192, 8, 32, 1): (221895.4, 68005.0),
+        (16384, 4, 20, 1): (164993.7, 68340.9),
+        (16384, 4, 24, 1): (165348.4, 68359.1),
+        (16384, 4, 32, 1): (164478.2, 68379.0),
+        (16384, 8, 20, 1): (213055.3, 66982.7),
+        (16384, 8, 32, 1): (213173.1, 66978.4),
     },
 }
 
