@@ -133,23 +133,26 @@ __global__ void __launch_bounds__(256) keys_raw_kernel(const double* __restrict_
     keys[k] = key_of(pos[k], pos[n + k], pos[2 * n + k], L, scale, b);
 }
 
-// Longest run of particles alike in the leading key bits that is put in order
-// in the gather: a run of m costs each of its particles m dependent loads of
-// 0.12 us, so this one 30 us, where the own sort saves 14 us at 32 k particles,
-// 64 at 300 k and 160 at 2.1 M.
-constexpr int kLongRun = 256;
+// Runs of particles alike in the leading key bits.  A run of m costs each of its
+// particles m loads, four in flight: 0.06 us a step in the gather.  Up to
+// kLongestRun it is put in order there (0.12 ms, where running the pass again
+// costs a box of 20 k particles 0.25).  Beyond long_run the plan's next call takes
+// the sort of all bits: the own sort saves 14 us at 32 k particles, 64 at 300 k
+// and 160 at 2.1 M, the steps of 256, 1024 and 2048 particles cost 15, 61 and 123.
+constexpr int kLongestRun = 2048;
+int long_run(int64_t N) { return N <= 131072 ? 256 : N <= 1048576 ? 1024 : kLongestRun; }
 
 // keys_s, shift (0: unused): notes whether the sort by leading bits would have
-// met a longer run (sizes[kRun] = 1).
+// met a run longer than `many`.
 template <class M>
 __global__ void __launch_bounds__(256) gather_kernel(const double4* __restrict__ rec,
                                                      const int32_t* __restrict__ perm,
-                                                     const uint64_t* __restrict__ keys_s, int shift, int64_t N,
-                                                     double* __restrict__ pos_s, M* __restrict__ mass_s,
-                                                     int64_t* __restrict__ sizes) {
+                                                     const uint64_t* __restrict__ keys_s, int shift, int many,
+                                                     int64_t N, double* __restrict__ pos_s,
+                                                     M* __restrict__ mass_s, int64_t* __restrict__ sizes) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= N) return;
-    if (shift > 0 && k + kLongRun < N && keys_s[k] >> shift == keys_s[k + kLongRun] >> shift) sizes[kRun] = 1;
+    if (shift > 0 && k + many < N && keys_s[k] >> shift == keys_s[k + many] >> shift) sizes[kRun] = 1;
     const double4 r = rec[perm[k]];
     pos_s[k] = r.x;
     pos_s[N + k] = r.y;
@@ -160,12 +163,13 @@ __global__ void __launch_bounds__(256) gather_kernel(const double4* __restrict__
 // The gather into key order, from records sorted by the keys' bits from
 // `shift` on (ties in input order): the few that agree in those bits come into
 // the order of the remaining ones here, each by counting the records of its
-// run that belong before it.  The particles of a run longer than kLongRun stay
-// where they are, and sizes[kRun] = 2 has the pass run again with a sort by all
-// bits (every particle of such a run finds it too long).
+// run that belong before it.  Runs longer than `many` are noted.  The
+// particles of a run longer than kLongestRun stay where they are, and
+// sizes[kRerun] has the pass run again with a sort by all bits (every particle
+// of such a run finds it too long, after kLongestRun + 1 steps).
 template <class M>
 __global__ void __launch_bounds__(256) sorted_gather_kernel(const ulonglong2* __restrict__ sorted, int shift,
-                                                            const double4* __restrict__ rec, int64_t N,
+                                                            int many, const double4* __restrict__ rec, int64_t N,
                                                             uint64_t* __restrict__ keys_s,
                                                             int32_t* __restrict__ perm,
                                                             double* __restrict__ pos_s, M* __restrict__ mass_s,
@@ -177,21 +181,37 @@ __global__ void __launch_bounds__(256) sorted_gather_kernel(const ulonglong2* __
     int64_t at = k;
     if (shift > 0) {
         const uint64_t run = e.x >> shift;
-        const int64_t lo = k > kLongRun ? k - kLongRun : 0, hi = k + kLongRun < N ? k + kLongRun : N - 1;
+        // the neighbours first (most runs are of one), then four loads in flight
+        const int64_t lo = k > kLongestRun ? k - kLongestRun : 0;
         int64_t a = k - 1, b = k + 1;
-        for (; a >= lo; --a) {
-            const uint64_t o = sorted[a].x;
-            if (o >> shift != run) break;
-            at -= o > e.x;
+        for (bool go = a >= lo && sorted[a].x >> shift == run; go;) {
+            uint64_t o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = sorted[a - u > lo ? a - u : lo].x;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                go = go && a >= lo && o[u] >> shift == run;
+                at -= go && o[u] > e.x;
+                a -= go;
+            }
         }
-        for (; b <= hi; ++b) {
-            const uint64_t o = sorted[b].x;
-            if (o >> shift != run) break;
-            at += o < e.x;
+        const int64_t hi = a + 1 + kLongestRun < N ? a + 1 + kLongestRun : N - 1;
+        for (bool go = b <= hi && sorted[b].x >> shift == run; go;) {
+            uint64_t o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = sorted[b + u < hi ? b + u : hi].x;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                go = go && b <= hi && o[u] >> shift == run;
+                at += go && o[u] < e.x;
+                b += go;
+            }
         }
-        if (b - a - 1 > kLongRun) {
+        const int64_t len = b - a - 1;
+        if (len > many) sizes[kRun] = 1;
+        if (len > kLongestRun) {
             at = k;
-            sizes[kRun] = 2;
+            sizes[kRerun] = 1;
         }
     }
     keys_s[at] = e.x;
@@ -359,9 +379,9 @@ int launch_sort_raw(const uint64_t* keys, const int32_t* idx_in, uint64_t* keys_
 // in one tree cell of level 7 (two passes) or 11 (three) and are put in order
 // by sorted_gather_kernel.  A cut below the cell's diagonal takes the library's
 // sort: cells may hold many particles there as a rule.  So does a box whose
-// last call met a run longer than kLongRun, whatever the call evaluates (few
-// active targets, monopoles): lists_to_host has the pass that meets one run
-// again, and returns to the leading bits once no run is that long.  With up
+// last call met a run longer than long_run, whatever the call evaluates (few
+// active targets, monopoles), until no run is that long; a call that meets one
+// longer than kLongestRun runs its pass again (lists_to_host).  With up
 // to kSmallSort particles one workgroup of the library's sort takes one launch
 // (15 us).  Sort and gather, the library's and these: 46 and 32 us at 32 k
 // particles, 144 and 80 at 300 k, 360 and 198 at 2.1 M.  With runs of any
@@ -457,11 +477,11 @@ int stage_gather(int64_t N, bool f64, Work& w, hipStream_t s) {
     if (w.sorted_rec) {
         const ulonglong2* sorted = static_cast<const ulonglong2*>(w.sorted_rec);
         if (f64)
-            hipLaunchKernelGGL(sorted_gather_kernel<double>, grid, group, 0, s, sorted, w.sort_shift, rec, N,
+            hipLaunchKernelGGL(sorted_gather_kernel<double>, grid, group, 0, s, sorted, w.sort_shift, long_run(N), rec, N,
                                w.keys_s.as<uint64_t>(), w.perm.as<int32_t>(), w.pos_s.as<double>(),
                                w.mass_sd.as<double>(), w.sizes.as<int64_t>());
         else
-            hipLaunchKernelGGL(sorted_gather_kernel<float>, grid, group, 0, s, sorted, w.sort_shift, rec, N,
+            hipLaunchKernelGGL(sorted_gather_kernel<float>, grid, group, 0, s, sorted, w.sort_shift, long_run(N), rec, N,
                                w.keys_s.as<uint64_t>(), w.perm.as<int32_t>(), w.pos_s.as<double>(),
                                w.mass_s.as<float>(), w.sizes.as<int64_t>());
         PP_HIP(hipGetLastError());
@@ -470,10 +490,10 @@ int stage_gather(int64_t N, bool f64, Work& w, hipStream_t s) {
     const int32_t* perm = w.perm.as<int32_t>();
     const uint64_t* keys_s = w.keys_s.as<uint64_t>();
     if (f64)
-        hipLaunchKernelGGL(gather_kernel<double>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, N,
+        hipLaunchKernelGGL(gather_kernel<double>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, long_run(N), N,
                            w.pos_s.as<double>(), w.mass_sd.as<double>(), w.sizes.as<int64_t>());
     else
-        hipLaunchKernelGGL(gather_kernel<float>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, N,
+        hipLaunchKernelGGL(gather_kernel<float>, grid, group, 0, s, rec, perm, keys_s, w.sort_shift, long_run(N), N,
                            w.pos_s.as<double>(), w.mass_s.as<float>(), w.sizes.as<int64_t>());
     PP_HIP(hipGetLastError());
     return PP_OK;

@@ -202,8 +202,9 @@ enum SizeSlot : int {
     kNeedRange = 12,
     kNeedItem = 13,
     kMoved = 14,        // a call reusing the lists met a particle that moved half the skin or more
-    kRun = 15,          // a long run of keys alike in their leading bits: 2 after a sort by those, 1 after one by all
+    kRun = 15,          // nonzero: a long run of keys alike in their leading bits (sort by all bits next time)
     kEntry0 = 16,       // kEntry0 + p: entries after expansion pass p (clamped)
+    kRerun = 39,        // nonzero: one too long to order after a sort by those bits
     kNeedEntry0 = 40,   // kNeedEntry0 + p: the same, unclamped
     kSizeSlots = 64
 };

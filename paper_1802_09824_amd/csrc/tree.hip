@@ -1546,7 +1546,7 @@ __device__ __forceinline__ void finish_items(const ItemBuild& I, int64_t ni) {
     if (ni > I.cap_item) sizes[kOverflow] |= 8;
     if (nr > I.cap_range) sizes[kOverflow] |= 4;
     if (sizes[kStart] - I.npass > I.stop) sizes[kOverflow] |= 128;
-    if (sizes[kRun] == 2) sizes[kOverflow] |= 256;
+    if (sizes[kRerun]) sizes[kOverflow] |= 256;
     sizes[kBad] = *I.bad;
     sizes[kSkip] = (sizes[kOverflow] != 0 || sizes[kBad] != 0 || sizes[kMoved] != 0) ? 1 : 0;
 }

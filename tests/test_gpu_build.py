@@ -184,10 +184,12 @@ def dense_cell(n, m, seed=2):
     return pos, rng.uniform(0.5, 1.5, n).astype(np.float32), p
 
 
-# runs of up to 256 particles are ordered in the gather, longer ones by a sort
-# of all bits
-@pytest.mark.parametrize("n,m", [(30000, 255), (30000, 256), (30000, 257), (30000, 258), (30000, 9000),
-                                 (140000, 256), (140000, 257), (140000, 20000)])
+# runs of up to 2048 particles are ordered in the gather, longer ones by a second
+# pass with a sort of all bits; after one of more than 256 (1024 beyond 131072
+# particles, 2048 beyond 2^20) the next call takes that
+@pytest.mark.parametrize("n,m", [(30000, 255), (30000, 256), (30000, 257), (30000, 258), (30000, 2047), (30000, 2048),
+                                 (30000, 2049), (30000, 2050), (30000, 9000), (140000, 1024), (140000, 1025),
+                                 (140000, 2048), (140000, 2049), (140000, 20000)])
 def test_dense_cells_order_like_the_full_sort(pp, n, m):
     """The first call (which meets the run), the ones after it and those after
     a change to other particles and back, by every entry point: the particle
