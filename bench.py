@@ -49,48 +49,48 @@ TRAFFIC = {
     "sources": ["paper_1802_09824_amd/csrc/pp_kernels.hip",
                 "paper_1802_09824_amd/csrc/pp_internal.h",
                 "paper_1802_09824_amd/csrc/tree.hip"],
-    "sha1": "e6d56562e8a0533cec5c43ee1b60475fdc55445d",
+    "sha1": "0f5b6113e213f53d72aec9b7d69275017b92131a",
     "fetch_scale": 1.99996,       # 1 GiB copy: 1048576 KiB / 524299.5 KiB of FETCH_SIZE
     "write_scale": 1.00000,       # 1 GiB copy: 1048576 KiB / 1048576.0 KiB of WRITE_SIZE
     # (chunk, waves per block, waves per CU (0: one workgroup per item), persistent):
     # (FETCH_SIZE KiB, WRITE_SIZE KiB) of the timed step's PP dispatch
     "kib": {
-        (1024, 1, 0, 0): (377368.1, 171271.3),
-        (1024, 1, 12, 1): (377571.8, 171283.6),
-        (1024, 1, 20, 1): (376813.8, 171272.0),
-        (1024, 1, 24, 1): (377027.6, 171286.8),
-        (1024, 1, 32, 1): (377111.6, 171290.0),
-        (2048, 1, 0, 0): (465898.5, 94729.2),
-        (2048, 1, 12, 1): (139882.0, 97665.6),
-        (2048, 1, 20, 1): (180353.6, 98782.4),
-        (2048, 1, 24, 1): (207207.3, 98981.4),
-        (2048, 1, 32, 1): (202521.6, 99049.7),
-        (2048, 2, 20, 1): (281872.4, 93887.4),
-        (2048, 2, 24, 1): (281807.2, 93897.0),
-        (2048, 2, 32, 1): (281813.0, 93891.2),
-        (4096, 1, 20, 1): (264510.1, 74071.3),
-        (4096, 1, 32, 1): (313993.8, 74218.3),
-        (4096, 2, 20, 1): (171973.0, 73968.6),
-        (4096, 2, 24, 1): (168917.0, 73976.8),
-        (4096, 2, 32, 1): (170742.1, 74039.4),
-        (4096, 4, 0, 0): (241855.8, 70926.2),
-        (4096, 4, 12, 1): (241905.9, 70929.6),
-        (4096, 4, 20, 1): (241971.0, 70924.2),
-        (4096, 4, 24, 1): (241861.2, 70931.2),
-        (4096, 4, 32, 1): (241955.5, 70930.2),
-        (8192, 2, 32, 1): (208910.0, 69822.0),
-        (8192, 4, 0, 0): (225717.8, 67597.1),
-        (8192, 4, 12, 1): (142078.6, 69206.2),
-        (8192, 4, 20, 1): (158493.4, 69620.8),
-        (8192, 4, 24, 1): (157835.1, 69653.7),
-        (8192, 4, 32, 1): (157055.4, 69635.4),
-        (8192, 8, 20, 1): (221885.6, 68009.0),
-        (8192, 8, 32, 1): (221895.4, 68005.0),
-        (16384, 4, 20, 1): (164993.7, 68340.9),
-        (16384, 4, 24, 1): (165348.4, 68359.1),
-        (16384, 4, 32, 1): (164478.2, 68379.0),
-        (16384, 8, 20, 1): (213055.3, 66982.7),
-        (16384, 8, 32, 1): (213173.1, 66978.4),
+        (1024, 1, 0, 0): (379142.8, 171317.4),
+        (1024, 1, 12, 1): (378923.1, 171335.1),
+        (1024, 1, 20, 1): (378878.2, 171326.4),
+        (1024, 1, 24, 1): (379075.6, 171322.1),
+        (1024, 1, 32, 1): (378740.4, 171314.4),
+        (2048, 1, 0, 0): (467248.4, 94774.4),
+        (2048, 1, 12, 1): (137356.8, 97688.4),
+        (2048, 1, 20, 1): (184094.8, 98785.6),
+        (2048, 1, 24, 1): (209932.4, 98969.9),
+        (2048, 1, 32, 1): (211380.9, 99080.7),
+        (2048, 2, 20, 1): (282389.1, 93910.2),
+        (2048, 2, 24, 1): (282242.8, 93909.3),
+        (2048, 2, 32, 1): (282375.4, 93910.5),
+        (4096, 1, 20, 1): (270823.8, 74086.3),
+        (4096, 1, 32, 1): (318488.3, 74246.8),
+        (4096, 2, 20, 1): (174261.4, 74028.7),
+        (4096, 2, 24, 1): (176090.4, 74074.7),
+        (4096, 2, 32, 1): (174244.9, 74081.8),
+        (4096, 4, 0, 0): (242101.4, 70928.4),
+        (4096, 4, 12, 1): (242085.0, 70929.5),
+        (4096, 4, 20, 1): (242068.6, 70928.7),
+        (4096, 4, 24, 1): (242041.4, 70927.4),
+        (4096, 4, 32, 1): (242125.2, 70934.2),
+        (8192, 2, 32, 1): (214659.8, 69864.7),
+        (8192, 4, 0, 0): (226212.8, 67615.5),
+        (8192, 4, 12, 1): (142838.9, 69198.1),
+        (8192, 4, 20, 1): (159990.9, 69581.2),
+        (8192, 4, 24, 1): (162112.0, 69579.2),
+        (8192, 4, 32, 1): (160507.0, 69612.3),
+        (8192, 8, 20, 1): (221940.8, 68007.5),
+        (8192, 8, 32, 1): (221908.1, 68010.9),
+        (16384, 4, 20, 1): (166488.3, 68353.9),
+        (16384, 4, 24, 1): (168931.9, 68355.7),
+        (16384, 4, 32, 1): (167088.4, 68387.7),
+        (16384, 8, 20, 1): (213262.3, 66977.9),
+        (16384, 8, 32, 1): (213015.4, 66981.4),
     },
 }
 
